@@ -98,6 +98,7 @@ struct GemmDesc {
   uint64_t seed = 0; uint32_t refill_stream = 0; double refill_scale = 1.0; int64_t refill_ld = 0;
   void *partial = nullptr; size_t partial_bytes = 0;   // split-K scratch
   int force_splits = 0;                                 // 0 = heuristic
+  void *packed = nullptr; size_t packed_bytes = 0;      // fp32 only: room for the split operand B (gemm_packed_bytes), or NULL
   int prof_kind = PK_SMALL;                             // class of the main kernel; the split-K reduction is +1
   // skip_reduce: leave split-K partials ([splits][M][N], accumulator type) unreduced in
   // `partial` for the consumer to add up; *splits_out receives their number (1 = C was written).
@@ -120,6 +121,10 @@ enum GemmKind { GEMM_F32 = 0, GEMM_F64 = 1, GEMM_F32_ACC64 = 2 };  // last: fp32
 // Bytes of split-K scratch the heuristic would use for this shape.
 size_t gemm_partial_bytes(const rsvd_ctx *ctx, GemmKind kind, int trans_a, int64_t M, int64_t N, int64_t K);
 hipError_t gemm_launch(rsvd_ctx *ctx, hipStream_t s, GemmKind kind, const GemmDesc &d);
+// Bytes in which an fp32 product with a K x N operand B keeps that operand split once and for all tiles (0: not used).
+// Without them the product gives the same result, bit for bit, in more time.
+size_t gemm_packed_bytes(int64_t K, int64_t N);
+hipError_t gemm_split_init_device(rsvd_ctx *ctx);
 
 // ---------------------------------------------------------------- sketch
 // batch > 1: problem b (blockIdx.y) writes to out + b * stride_out bytes with seed + b.

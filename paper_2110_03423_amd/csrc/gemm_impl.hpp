@@ -154,6 +154,23 @@ struct TileStage {
   }
 };
 
+// The tile of C and the part of the k range that this workgroup works on.
+// Workgroups are handed to the 8 XCDs round-robin by launch index, and each XCD has
+// its own L2.  Renumber so that one XCD receives a contiguous run of tile indices:
+// the column tiles of one row tile (which all read the same rows of A) then share an L2.
+__device__ __forceinline__ void tile_of_workgroup(const GemmParams &P, int &tile_m, int &tile_n, int &split) {
+  const int total = (int)gridDim.x;
+  const int pid = (int)blockIdx.x;
+  const int per_xcd = (total + 7) >> 3;
+  const int tall = (total & 7) ? (total & 7) : 8;        // XCDs that receive per_xcd workgroups
+  const int xcd = pid & 7, local = pid >> 3;
+  const int tile = (xcd < tall) ? xcd * per_xcd + local
+                                : tall * per_xcd + (xcd - tall) * (per_xcd - 1) + local;
+  tile_n = tile % P.tiles_n;
+  tile_m = (tile / P.tiles_n) % P.tiles_m;
+  split = tile / (P.tiles_n * P.tiles_m);
+}
+
 // Epilogues (EPI):
 //   0  the kernel can only store its tile as it is (or as a split-K partial);
 //   1  the full epilogue (scaling, accumulation, transposed store, replacement columns);
@@ -165,6 +182,108 @@ struct TileStage {
 //      the fact as it would with a rank-one correction of the product).
 // Separate instantiations: the full epilogue carries the Philox and Box-Muller code and more registers,
 // which the products with A never need.
+// Stores a wavefront's TM x TN blocks of 16 x 16, the first of which has its origin at (row0, col0).
+template <typename TIn, typename TAcc, typename TOut, int TM, int TN, int EPI>
+__device__ __forceinline__ void gemm_epilogue(const GemmParams &P, typename Mfma<TAcc>::vec (&acc)[TM][TN], int split,
+                                              int64_t row0, int64_t col0, int lane) {
+  const int r16 = lane & 15;
+  if (EPI == 0 || EPI == 3 || P.splits > 1) {
+    TOut *Cp = (TOut *)P.C;
+    TAcc *Pp = (TAcc *)P.partial + (int64_t)split * P.M * P.N;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int64_t row = row0 + i * 16 + Mfma<TAcc>::row(lane, v);
+          const int64_t col = col0 + j * 16 + r16;
+          if (row < P.M && col < P.N) {
+            if (P.splits > 1) Pp[row * P.N + col] = acc[i][j][v];
+            else Cp[row * P.ldc + col] = (TOut)acc[i][j][v];
+          }
+        }
+    return;
+  }
+  if (EPI == 1) {
+    // Replacement columns are rare and do not depend on the accumulators: the flags of this lane's TN
+    // columns are read once, the ordinary elements are stored on a short path, and the replacement
+    // values follow in a rolled loop, so that the generator is in the code once (inlined per element
+    // it made the kernel half again as slow, replacement or not).
+    unsigned dead_cols = 0u;
+    if (P.dead != nullptr) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int64_t col = col0 + j * 16 + r16;
+        if (col < P.N && P.dead[col] != 0) dead_cols |= 1u << j;
+      }
+    }
+    TOut *Cp = (TOut *)P.C;
+    const TAcc alpha = (TAcc)P.alpha, beta = (TAcc)P.beta;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int64_t row = row0 + i * 16 + Mfma<TAcc>::row(lane, v);
+          const int64_t col = col0 + j * 16 + r16;
+          if (row < P.M && col < P.N && !((dead_cols >> j) & 1u)) {
+            if (P.trans_c) {
+              Cp[col * P.ldc + row] = (TOut)(alpha * acc[i][j][v]);
+            } else {
+              TOut *dst = Cp + row * P.ldc + col;
+              TAcc val = alpha * acc[i][j][v];
+              if (beta != (TAcc)0) val += beta * (TAcc)(*dst);
+              *dst = (TOut)val;
+            }
+          }
+        }
+    if (dead_cols != 0u) {
+#pragma unroll 1
+      for (int e = 0; e < TM * TN * 4; ++e) {
+        const int v = e & 3, j = (e >> 2) % TN, i = (e >> 2) / TN;
+        if (!((dead_cols >> j) & 1u)) continue;
+        const int64_t row = row0 + i * 16 + Mfma<TAcc>::row(lane, v);
+        const int64_t col = col0 + j * 16 + r16;
+        if (row < P.M && col < P.N) store_result<TOut, TAcc, sizeof(TIn) == 4>(P, row, col, (TAcc)0);
+      }
+    }
+  }
+  if (EPI == 2) {
+    TOut *Cp = (TOut *)P.C;
+    const TAcc alpha = (TAcc)P.alpha, beta = (TAcc)P.beta;
+    if (beta != (TAcc)0) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int64_t row = row0 + i * 16 + Mfma<TAcc>::row(lane, v);
+            const int64_t col = col0 + j * 16 + r16;
+            const TAcc old = (row < P.M && col < P.N) ? (TAcc)Cp[row * P.ldc + col] : (TAcc)0;
+            acc[i][j][v] = alpha * acc[i][j][v] + beta * old;
+          }
+    } else {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] *= alpha;
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int64_t row = row0 + i * 16 + Mfma<TAcc>::row(lane, v);
+          const int64_t col = col0 + j * 16 + r16;
+          if (row < P.M && col < P.N) Cp[row * P.ldc + col] = (TOut)acc[i][j][v];
+        }
+  }
+}
+
 template <typename TIn, typename TAcc, typename TOut, bool TA, int BM, int BN, int WGM, int WGN, int VEC, int EPI,
           int BK = 32>
 __global__ __launch_bounds__(256) void gemm_kernel(const GemmParams P0) {
@@ -186,19 +305,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(const GemmParams P0) {
   const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
   const int r16 = lane & 15, kq = lane >> 4;
 
-  // Workgroups are handed to the 8 XCDs round-robin by launch index, and each XCD has
-  // its own L2.  Renumber so that one XCD receives a contiguous run of tile indices:
-  // the column tiles of one row tile (which all read the same rows of A) then share an L2.
-  const int total = (int)gridDim.x;
-  const int pid = (int)blockIdx.x;
-  const int per_xcd = (total + 7) >> 3;
-  const int tall = (total & 7) ? (total & 7) : 8;        // XCDs that receive per_xcd workgroups
-  const int xcd = pid & 7, local = pid >> 3;
-  const int tile = (xcd < tall) ? xcd * per_xcd + local
-                                : tall * per_xcd + (xcd - tall) * (per_xcd - 1) + local;
-  const int tile_n = tile % P.tiles_n;
-  const int tile_m = (tile / P.tiles_n) % P.tiles_m;
-  const int split = tile / (P.tiles_n * P.tiles_m);
+  int tile_m, tile_n, split;
+  tile_of_workgroup(P, tile_m, tile_n, split);
   const int64_t m0 = (int64_t)tile_m * BM;
   const int64_t n0 = (int64_t)tile_n * BN;
   if (P.upper_bm > 0 && n0 + BN <= m0) return;       // symmetric result: this tile mirrors one that is computed
@@ -252,102 +360,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(const GemmParams P0) {
     __syncthreads();
   }
 
-  // epilogue
-  if (EPI == 0 || EPI == 3 || P.splits > 1) {
-    TOut *Cp = (TOut *)P.C;
-    TAcc *Pp = (TAcc *)P.partial + (int64_t)split * P.M * P.N;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int64_t row = m0 + wm0 + i * 16 + Mfma<TAcc>::row(lane, v);
-          const int64_t col = n0 + wn0 + j * 16 + r16;
-          if (row < P.M && col < P.N) {
-            if (P.splits > 1) Pp[row * P.N + col] = acc[i][j][v];
-            else Cp[row * P.ldc + col] = (TOut)acc[i][j][v];
-          }
-        }
-    return;
-  }
-  if (EPI == 1) {
-    // Replacement columns are rare and do not depend on the accumulators: the flags of this lane's TN
-    // columns are read once, the ordinary elements are stored on a short path, and the replacement
-    // values follow in a rolled loop, so that the generator is in the code once (inlined per element
-    // it made the kernel half again as slow, replacement or not).
-    unsigned dead_cols = 0u;
-    if (P.dead != nullptr) {
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int64_t col = n0 + wn0 + j * 16 + r16;
-        if (col < P.N && P.dead[col] != 0) dead_cols |= 1u << j;
-      }
-    }
-    TOut *Cp = (TOut *)P.C;
-    const TAcc alpha = (TAcc)P.alpha, beta = (TAcc)P.beta;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int64_t row = m0 + wm0 + i * 16 + Mfma<TAcc>::row(lane, v);
-          const int64_t col = n0 + wn0 + j * 16 + r16;
-          if (row < P.M && col < P.N && !((dead_cols >> j) & 1u)) {
-            if (P.trans_c) {
-              Cp[col * P.ldc + row] = (TOut)(alpha * acc[i][j][v]);
-            } else {
-              TOut *dst = Cp + row * P.ldc + col;
-              TAcc val = alpha * acc[i][j][v];
-              if (beta != (TAcc)0) val += beta * (TAcc)(*dst);
-              *dst = (TOut)val;
-            }
-          }
-        }
-    if (dead_cols != 0u) {
-#pragma unroll 1
-      for (int e = 0; e < TM * TN * 4; ++e) {
-        const int v = e & 3, j = (e >> 2) % TN, i = (e >> 2) / TN;
-        if (!((dead_cols >> j) & 1u)) continue;
-        const int64_t row = m0 + wm0 + i * 16 + Mfma<TAcc>::row(lane, v);
-        const int64_t col = n0 + wn0 + j * 16 + r16;
-        if (row < P.M && col < P.N) store_result<TOut, TAcc, sizeof(TIn) == 4>(P, row, col, (TAcc)0);
-      }
-    }
-  }
-  if (EPI == 2) {
-    TOut *Cp = (TOut *)P.C;
-    const TAcc alpha = (TAcc)P.alpha, beta = (TAcc)P.beta;
-    if (beta != (TAcc)0) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int64_t row = m0 + wm0 + i * 16 + Mfma<TAcc>::row(lane, v);
-            const int64_t col = n0 + wn0 + j * 16 + r16;
-            const TAcc old = (row < P.M && col < P.N) ? (TAcc)Cp[row * P.ldc + col] : (TAcc)0;
-            acc[i][j][v] = alpha * acc[i][j][v] + beta * old;
-          }
-    } else {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] *= alpha;
-    }
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int64_t row = m0 + wm0 + i * 16 + Mfma<TAcc>::row(lane, v);
-          const int64_t col = n0 + wn0 + j * 16 + r16;
-          if (row < P.M && col < P.N) Cp[row * P.ldc + col] = (TOut)acc[i][j][v];
-        }
-  }
+  gemm_epilogue<TIn, TAcc, TOut, TM, TN, EPI>(P, acc, split, m0 + wm0, n0 + wn0, lane);
 }
 
 // Sum of the split-K partials.  SG (1, 2, 4 or 8, P.reduce_groups) threads share one element: thread
@@ -520,6 +533,57 @@ inline void launch_plain_reduce(hipStream_t s, const GemmParams &P, unsigned blo
   }
 }
 
+inline GemmParams make_params(const GemmDesc &d, const SplitChoice &c, int upper_bm = 0, int upper_bn = 0) {
+  GemmParams P;
+  P.M = d.M; P.N = d.N; P.K = d.K;
+  P.A = d.A; P.lda = d.lda; P.B = d.B; P.ldb = d.ldb; P.C = d.C; P.ldc = d.ldc;
+  P.partial = d.partial; P.k_per_split = c.k_per_split; P.splits = c.splits;
+  P.trans_c = d.trans_c; P.alpha = d.alpha; P.beta = d.beta;
+  P.upper_bm = upper_bm; P.upper_bn = upper_bn;
+  P.b_upper = d.b_upper;
+  P.a_shift = d.a_shift;
+  P.dead = d.dead; P.seed = d.seed; P.refill_stream = d.refill_stream;
+  P.refill_scale = d.refill_scale; P.refill_ld = d.refill_ld;
+  P.stride_a = d.stride_a; P.stride_b = d.stride_b; P.stride_c = d.stride_c; P.stride_partial = d.stride_partial;
+  P.stride_dead = d.stride_dead; P.seed_step = d.seed_step;
+  P.skip_flag = d.skip_flag; P.alt_flag = d.alt_flag; P.B_alt = d.B_alt; P.stride_flag = d.stride_flag; P.skip_now = 0;
+  P.reduce_groups = 1;
+  P.tiles_n = P.tiles_m = 0;
+  return P;
+}
+
+// Behind the product kernel: the split-K partials are added (or left to the consumer).
+template <typename TIn, typename TAcc, typename TOut>
+inline hipError_t finish_splits(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, GemmParams P) {
+  hipError_t e = hipSuccess;
+  if (d.splits_out != nullptr) *d.splits_out = P.splits;
+  if (P.splits > 1 && !(d.skip_reduce && P.splits <= d.skip_reduce_max)) {
+    ProfScope ps(ctx, s, d.prof_kind + 1);
+    constexpr int V16 = 16 / sizeof(TAcc);
+    const bool plain = sizeof(TAcc) == sizeof(TOut) && d.alpha == 1.0 && d.beta == 0.0 && d.dead == nullptr &&
+                       !d.trans_c && !d.upper_only && d.N % V16 == 0 && d.ldc % V16 == 0 &&
+                       (uintptr_t)d.C % 16 == 0 && (uintptr_t)d.partial % 16 == 0 &&
+                       (d.batch == 1 || (d.stride_c % 16 == 0 && d.stride_partial % 16 == 0)) &&
+                       d.M * d.N >= 262144;       // (smaller outputs do better with one element per thread)
+    if (plain) {
+      int64_t blocks = ceil_div(d.M * d.N / V16, 256);
+      if (blocks > 8192) blocks = 8192;
+      launch_plain_reduce<TAcc, TOut>(s, P, (unsigned)blocks, (unsigned)d.batch);
+      return hipGetLastError();
+    }
+    // threads per element: enough of them to put ~64k loads in flight, at least eight partials each
+    int sg = 1;
+    while (sg < 8 && d.M * d.N * d.batch * sg < 65536 && P.splits >= 16 * sg) sg *= 2;
+    P.reduce_groups = sg;
+    int64_t blocks = ceil_div(d.M * d.N, 256 / sg);
+    if (blocks > 8192) blocks = 8192;
+    hipLaunchKernelGGL((splitk_reduce_kernel<TIn, TAcc, TOut>), dim3((unsigned)blocks, (unsigned)d.batch), dim3(256),
+                       0, s, P);
+    e = hipGetLastError();
+  }
+  return e;
+}
+
 template <typename TIn, typename TAcc, typename TOut>
 struct GemmDispatch {
   template <bool TA, int BM, int BN, int WGM, int WGN, int BK = 32>
@@ -592,20 +656,7 @@ struct GemmDispatch {
     // the centred product has the lean epilogue only
     if (d.a_shift != nullptr && (d.dead != nullptr || d.trans_c || d.alpha != 1.0 || d.beta != 0.0 || d.batch != 1))
       return hipErrorInvalidValue;
-    GemmParams P;
-    P.M = d.M; P.N = d.N; P.K = d.K;
-    P.A = d.A; P.lda = d.lda; P.B = d.B; P.ldb = d.ldb; P.C = d.C; P.ldc = d.ldc;
-    P.partial = d.partial; P.k_per_split = c.k_per_split; P.splits = c.splits;
-    P.trans_c = d.trans_c; P.alpha = d.alpha; P.beta = d.beta;
-    P.upper_bm = d.upper_only ? t.bm : 0; P.upper_bn = d.upper_only ? t.bn : 0;
-    P.b_upper = d.b_upper;
-    P.a_shift = d.a_shift;
-    P.dead = d.dead; P.seed = d.seed; P.refill_stream = d.refill_stream;
-    P.refill_scale = d.refill_scale; P.refill_ld = d.refill_ld;
-    P.stride_a = d.stride_a; P.stride_b = d.stride_b; P.stride_c = d.stride_c; P.stride_partial = d.stride_partial;
-    P.stride_dead = d.stride_dead; P.seed_step = d.seed_step;
-    P.skip_flag = d.skip_flag; P.alt_flag = d.alt_flag; P.B_alt = d.B_alt; P.stride_flag = d.stride_flag; P.skip_now = 0;
-    P.reduce_groups = 1;
+    const GemmParams P = make_params(d, c, d.upper_only ? t.bm : 0, d.upper_only ? t.bn : 0);
     // 16-byte vector loads need aligned bases, leading dimensions and extents.
     constexpr int V = 16 / sizeof(TIn);
     const int64_t a_contig = d.trans_a ? d.M : d.K;
@@ -619,32 +670,7 @@ struct GemmDispatch {
       e = d.trans_a ? by_tile<true>(s, P, t, vec, d.batch) : by_tile<false>(s, P, t, vec, d.batch);
     }
     if (e != hipSuccess) return e;
-    if (d.splits_out != nullptr) *d.splits_out = c.splits;
-    if (c.splits > 1 && !(d.skip_reduce && c.splits <= d.skip_reduce_max)) {
-      ProfScope ps(ctx, s, d.prof_kind + 1);
-      constexpr int V16 = 16 / sizeof(TAcc);
-      const bool plain = sizeof(TAcc) == sizeof(TOut) && d.alpha == 1.0 && d.beta == 0.0 && d.dead == nullptr &&
-                         !d.trans_c && !d.upper_only && d.N % V16 == 0 && d.ldc % V16 == 0 &&
-                         (uintptr_t)d.C % 16 == 0 && (uintptr_t)d.partial % 16 == 0 &&
-                         (d.batch == 1 || (d.stride_c % 16 == 0 && d.stride_partial % 16 == 0)) &&
-                         d.M * d.N >= 262144;       // (smaller outputs do better with one element per thread)
-      if (plain) {
-        int64_t blocks = ceil_div(d.M * d.N / V16, 256);
-        if (blocks > 8192) blocks = 8192;
-        launch_plain_reduce<TAcc, TOut>(s, P, (unsigned)blocks, (unsigned)d.batch);
-        return hipGetLastError();
-      }
-      // threads per element: enough of them to put ~64k loads in flight, at least eight partials each
-      int sg = 1;
-      while (sg < 8 && d.M * d.N * d.batch * sg < 65536 && c.splits >= 16 * sg) sg *= 2;
-      P.reduce_groups = sg;
-      int64_t blocks = ceil_div(d.M * d.N, 256 / sg);
-      if (blocks > 8192) blocks = 8192;
-      hipLaunchKernelGGL((splitk_reduce_kernel<TIn, TAcc, TOut>), dim3((unsigned)blocks, (unsigned)d.batch), dim3(256),
-                         0, s, P);
-      e = hipGetLastError();
-    }
-    return e;
+    return finish_splits<TIn, TAcc, TOut>(ctx, s, d, P);
   }
 };
 

@@ -1,0 +1,512 @@
+// fp32 products on the bf16 matrix cores, without giving up a bit of the inputs.
+//
+// An fp32 number is the exact sum of three bf16 numbers (x = h + m + t: 8 + 8 + 8 significand bits, each the
+// rounded rest of the ones before), so  a b = sum of nine bf16 products, of which the six of order 2^-16 and above are
+// taken (hh, hm, mh, mm, ht, th); what is left out, mt + tm + tt, is below 2^-25 |a b|, half a unit of the last place
+// of an fp32 product.  The products are exact in the matrix instruction and summed in fp32, one accumulator per
+// element of C as in the fp32 instruction, but with an eighth of the accumulation steps.  A 16x16x32 bf16
+// instruction takes 16 cycles where eight 16x16x4 fp32 ones take 256: six of them leave a factor 2.7.
+//
+// The split is exact for |x| < 2^127 as long as t stays above the smallest bf16 number.  A k-tile that holds a larger,
+// infinite or undefined value, or nothing but values below 2^-106, is therefore multiplied by the fp32 instruction,
+// straight from global memory (slow_tile).
+//
+// Both operands are staged as [row][k] bf16 planes, the eight k of a matrix operand in one 16-byte chunk, so that
+// matrices whose rows run along the other index are transposed by the loads of the staging (eight dwords a
+// thread, one per k) and not by LDS.  The chunks of a row are XOR-swizzled with the row number, which spreads the eight
+// rows a quarter-wavefront touches over all banks without padding.  Loads are unaligned-safe (a vector load of
+// gfx950 needs the alignment of its element only): odd leading dimensions and odd N take the same path.
+//
+// Both operands are double-buffered in LDS.  What bounds the kernel is the matrix pipe as far as the chip's power lets it
+// run (65536 x 16384, l = 576: pipe busy 61 % of the cycles at 2.0 GHz), so everything else is put in its shadow: the vector
+// instructions that split the next tile of A are issued among the matrix instructions of the current one, the loads of
+// the tile after it stay in flight across the barrier, and a wide B is split once (split_pack_kernel) and copied to LDS
+// without registers.  Measured against the fp32 instruction: 65536 x 16384, l = 576: A X 9.20 -> 5.78 ms (214 TFLOP/s),
+// A^T X 9.99 -> 5.82 ms; l = 210: 6.14 -> 2.52 and 5.12 -> 2.56 ms; 30011 x 2999, l = 61 (odd strides): 0.187 -> 0.146 and
+// 0.197 -> 0.119 ms.  Relative error against 64 bits at K = 16384: 2.3e-6 -> 0.8e-6.
+#pragma once
+
+#include "gemm_impl.hpp"
+#include <type_traits>
+
+namespace rsvd {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+#define RSVD_INLINE __attribute__((always_inline))
+
+constexpr int kSplitBK = 32;                       // k-tile: one 16x16x32 instruction deep
+constexpr unsigned kSplitHuge = 0x7f000000u;       // 2^127
+constexpr unsigned kSplitTiny = 0x0a800000u;       // 2^-106
+
+// Operand of s_waitcnt: at most n vector memory operations outstanding, no LDS operation.
+constexpr int wait_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; }
+
+// Flags of a k-tile, collected in LDS
+enum { SPLIT_BAD = 1, SPLIT_A_USUAL = 2, SPLIT_A_ANY = 4, SPLIT_B_USUAL = 8, SPLIT_B_ANY = 16 };
+__device__ __forceinline__ bool split_unfit(int f) {
+  return (f & SPLIT_BAD) || (f & (SPLIT_A_USUAL | SPLIT_A_ANY)) == SPLIT_A_ANY ||
+         (f & (SPLIT_B_USUAL | SPLIT_B_ANY)) == SPLIT_B_ANY;
+}
+
+// Byte offset of chunk c (eight k) of row r inside a plane of 64-byte rows.
+__device__ __forceinline__ int split_chunk(int r, int c) { return r * 64 + ((c ^ ((r >> 1) & 3)) << 4); }
+
+// Stages ROWS x 32 elements.  KROWS = false: consecutive k are consecutive in memory; true: they are `ld` apart and
+// consecutive rows are consecutive.  SHIFT: an fp64 offset per column of the stored matrix (per k when KROWS is false,
+// per row when it is true) is taken away, rounded once, on the way to LDS.
+template <int NT, int ROWS, bool KROWS, bool SHIFT = false>
+struct SplitStage {
+  static constexpr int TASKS = ROWS * 4, ITERS = (TASKS + NT - 1) / NT;
+  static constexpr bool WHOLE = TASKS % NT == 0;
+  float x[ITERS][8];
+  double sh[SHIFT ? (KROWS ? 1 : 8) : 1];
+
+  // Row and chunk of thread `tid` in iteration `it`; threads left over in the last one repeat the first tasks (same bytes
+  // to the same place) rather than branch.
+  static __device__ __forceinline__ void place(int tid, int it, int &row, int &c) {
+    int idx = tid + NT * it;
+    if (!WHOLE && idx >= TASKS) idx = TASKS >= NT ? idx - TASKS : idx % TASKS;
+    if (KROWS) { c = idx / ROWS; row = idx - c * ROWS; }
+    else { row = idx >> 2; c = idx & 3; }
+  }
+  // The offsets of the columns this thread stages (SHIFT): of the rows once per workgroup, of the k with every tile.
+  __device__ __forceinline__ void load_shift(const double *__restrict__ shift, int64_t rows_left, int64_t k_left, int tid) {
+    int row, c;
+    place(tid, 0, row, c);            // (the same row, or the same k, in every iteration)
+    if (KROWS) sh[0] = row < rows_left ? shift[row] : 0.0;
+    else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sh[e] = 8 * c + e < k_left ? shift[8 * c + e] : 0.0;
+    }
+  }
+  // Loads of iteration `it`.  Addresses are a wave-uniform base and a 32-bit byte offset per lane that does not change
+  // from tile to tile (split_fits: it does not overflow).  Rows beyond the last read that one again (what comes of
+  // them is not stored), k beyond the last are zero; WHOLE_K: there are none.
+  template <bool WHOLE_K>
+  __device__ __forceinline__ void load(int it, const float *__restrict__ origin, int64_t ld, int64_t rows_left, int64_t k_left,
+                                       int tid) {
+    const char *base = reinterpret_cast<const char *>(origin);
+    const int last = (int)(rows_left < ROWS ? rows_left : ROWS) - 1;
+    int row, c;
+    place(tid, it, row, c);
+    row = row < last ? row : last;
+    const unsigned off = KROWS ? ((unsigned)(8 * c) * (unsigned)ld + (unsigned)row) * 4u
+                               : ((unsigned)row * (unsigned)ld + (unsigned)(8 * c)) * 4u;
+    if (!WHOLE_K) {
+      const int kl = (int)(k_left < kSplitBK ? k_left : kSplitBK) - 1;      // (at least one k is left)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int k = 8 * c + e, kc = k < kl ? k : kl;
+        const unsigned o = KROWS ? ((unsigned)kc * (unsigned)ld + (unsigned)row) * 4u
+                                 : ((unsigned)row * (unsigned)ld + (unsigned)kc) * 4u;
+        const float v = *reinterpret_cast<const float *>(base + o);
+        x[it][e] = k <= kl ? v : 0.f;
+      }
+    } else if (KROWS) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[it][e] = *reinterpret_cast<const float *>(base + (int64_t)e * ld * 4 + off);
+    } else {
+      const f32x4_any lo = *reinterpret_cast<const f32x4_any *>(base + off);
+      const f32x4_any hi = *reinterpret_cast<const f32x4_any *>(base + 16 + off);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { x[it][e] = lo[e]; x[it][4 + e] = hi[e]; }
+    }
+  }
+  // Zeros in the place of rows beyond the last.
+  __device__ __forceinline__ void clear_beyond(int it, int64_t rows_left, int tid) {
+    int row, c;
+    place(tid, it, row, c);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[it][e] = row < rows_left ? x[it][e] : 0.f;
+  }
+  // Splits iteration `it` and writes its three planes; pos, neg follow the largest magnitudes seen (see mag()).
+  __device__ __forceinline__ void store(int it, char *planes, int tid, int &pos, unsigned &neg) const {
+    int row, c;
+    place(tid, it, row, c);
+    u32x4 h, m, t;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      float a = x[it][2 * p], b = x[it][2 * p + 1];
+      if (SHIFT) {
+        a = (float)((double)a - sh[KROWS ? 0 : 2 * p]);
+        b = (float)((double)b - sh[KROWS ? 0 : 2 * p + 1]);
+      }
+      const unsigned ua = __float_as_uint(a), ub = __float_as_uint(b);
+      neg = max(max(neg, ua), ub);                  // unsigned order: the largest negative magnitude, if any
+      pos = max(max(pos, (int)ua), (int)ub);        // signed order: the largest positive one
+      h[p] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
+      const float a1 = a - __uint_as_float(h[p] << 16), b1 = b - __uint_as_float(h[p] & 0xffff0000u);
+      m[p] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a1, b1}, bf16x2));
+      const float a2 = a1 - __uint_as_float(m[p] << 16), b2 = b1 - __uint_as_float(m[p] & 0xffff0000u);
+      t[p] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a2, b2}, bf16x2));
+    }
+    char *dst = planes + split_chunk(row, c);
+    *reinterpret_cast<u32x4 *>(dst) = h;
+    *reinterpret_cast<u32x4 *>(dst + ROWS * 64) = m;
+    *reinterpret_cast<u32x4 *>(dst + 2 * ROWS * 64) = t;
+  }
+};
+// largest magnitude (bit pattern) behind the two running maxima
+__device__ __forceinline__ unsigned split_mag(int pos, unsigned neg) { return max(neg & 0x7fffffffu, (unsigned)pos); }
+
+// Wide outputs: the column tiles of a row tile all need the same planes of B, and every row tile needs them again.
+// This kernel splits B once, into the bytes a k-tile of it occupies in LDS (planes of 64-byte rows, chunks swizzled,
+// zeros beyond N and K), tile after tile with the column tiles of a k-tile next to each other; the product kernel then
+// copies them without touching a register.  One flag word per tile.
+template <int BN>
+__global__ __launch_bounds__(256) void split_pack_kernel(const GemmParams P0, char *__restrict__ packed, int *__restrict__ flags) {
+  const GemmParams P = select_problem(P0);
+  if (P.skip_now) return;
+  const int tile_n = (int)blockIdx.x % P.tiles_n, kt = (int)blockIdx.x / P.tiles_n;
+  const int64_t k0 = (int64_t)kt * kSplitBK, n0 = (int64_t)tile_n * BN;
+  const int tid = threadIdx.x;
+  __shared__ int fl;
+  if (tid == 0) fl = 0;
+  __syncthreads();
+  SplitStage<256, BN, true> sb;
+  char *dst = packed + (int64_t)blockIdx.x * (3 * BN * 64);
+  int pos = 0;
+  unsigned neg = 0u;
+#pragma unroll
+  for (int it = 0; it < sb.ITERS; ++it) {
+    sb.template load<false>(it, (const float *)P.B + k0 * P.ldb + n0, P.ldb, P.N - n0, P.K - k0, tid);
+    sb.clear_beyond(it, P.N - n0, tid);
+    sb.store(it, dst, tid, pos, neg);
+  }
+  const unsigned mb = split_mag(pos, neg);
+  const int f = (mb >= kSplitHuge ? SPLIT_BAD : 0) | (mb >= kSplitTiny ? SPLIT_B_USUAL : 0) | (mb != 0u ? SPLIT_B_ANY : 0);
+  if (f) atomicOr(&fl, f);
+  __syncthreads();
+  if (tid == 0) flags[blockIdx.x] = fl;
+}
+
+// Epilogues as in gemm_kernel: 0 plain, 1 full, 3 plain with the column offsets of A taken away while staging.
+// PACKED: B comes as split_pack_kernel left it.
+template <bool TA, int BM, int BN, int WGM, int WGN, int EPI, bool PACKED>
+__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const GemmParams P0, const char *__restrict__ packed,
+                                                                       const int *__restrict__ packed_flags) {
+  const GemmParams P = select_problem(P0);
+  if (P.skip_now) return;
+  constexpr int BK = kSplitBK, NT = 64 * WGM * WGN;
+  constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
+  static_assert(WM % 16 == 0 && WN % 16 == 0, "wave tile must be made of 16x16 blocks");
+  constexpr bool CENTER = (EPI == 3);
+  constexpr int PA = BM * 64, PB = BN * 64, BUF = 3 * (PA + PB);      // bytes of a plane, of both operands of a k-tile
+  extern __shared__ __attribute__((aligned(16))) char split_lds[];
+  // behind the two buffers, one int per wavefront: flags of the tile in hand and of the next
+  constexpr int WAVES = NT / 64;
+  int *flags = reinterpret_cast<int *>(split_lds + 2 * BUF);
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
+  const int r16 = lane & 15, kq = lane >> 4;
+  int tile_m, tile_n, split;
+  tile_of_workgroup(P, tile_m, tile_n, split);
+  const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
+  const int64_t k_begin = (int64_t)split * P.k_per_split;
+  int64_t k_end = (k_begin + P.k_per_split < P.K) ? (k_begin + P.k_per_split) : P.K;
+  if (P.b_upper != 0 && n0 + BN < k_end) k_end = n0 + BN;      // rows of B from n0 + BN on are zero in these columns
+
+  const float *A = (const float *)P.A;
+  const float *B = (const float *)P.B;
+  // The products of the leading planes and the five terms below them are summed apart: one rounding at the size of the
+  // result per k-tile instead of six, and a long k range ends four to five times closer than with the fp32 instruction.
+  f32x4 acc[TM][TN], low[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = low[i][j] = (f32x4)0.f;
+
+  SplitStage<NT, BM, TA, CENTER> sa;
+  SplitStage<NT, PACKED ? 16 : BN, true> sb;
+  constexpr int NA = decltype(sa)::ITERS, NB = PACKED ? 0 : decltype(sb)::ITERS;
+  if (CENTER && TA) sa.load_shift(P.a_shift + m0, P.M - m0, 0, tid);
+  // k-tiles of this workgroup, counted from its first; all but the last are whole
+  const int kt0 = (int)(k_begin / BK), nkt = k_begin < k_end ? (int)((k_end - k_begin + BK - 1) / BK) : 0;
+  const int last_k = (int)(k_end - k_begin) - (nkt - 1) * BK;
+  const int whole_tiles = last_k == BK ? nkt : nkt - 1;
+  const float *a_tile = TA ? A + k_begin * P.lda + m0 : A + m0 * P.lda + k_begin;      // the next tile to be loaded
+  const float *b_tile = B + k_begin * P.ldb + n0;
+  const double *s_tile = CENTER && !TA ? P.a_shift + k_begin : nullptr;
+  const int64_t a_step = TA ? BK * P.lda : BK, b_step = BK * P.ldb;
+  const int m_left = (int)(P.M - m0 < BM ? P.M - m0 : BM), n_left = (int)(P.N - n0 < BN ? P.N - n0 : BN);
+  // iteration w of the staging through registers: those of A, then those of B
+  auto load_part = [&](auto whole, int w, int k_left) RSVD_INLINE {
+    constexpr bool W = decltype(whole)::value;
+    if (w < NA) sa.template load<W>(w, a_tile, P.lda, m_left, k_left, tid);
+    else sb.template load<W>(w - NA, b_tile, P.ldb, n_left, k_left, tid);
+    if (CENTER && !TA && w == NA - 1) sa.load_shift(s_tile, 0, k_left, tid);     // (behind the last use of the old ones)
+    if (w == NA + NB - 1) {
+      a_tile += a_step;
+      if (!PACKED) b_tile += b_step;
+      if (CENTER && !TA) s_tile += BK;
+    }
+  };
+  int pa = 0, pb = 0;
+  unsigned na = 0u, nb = 0u;
+  auto store_part = [&](int w, int buf) RSVD_INLINE {
+    if (w < NA) sa.store(w, split_lds + buf * BUF, tid, pa, na);
+    else sb.store(w - NA, split_lds + buf * BUF + 3 * PA, tid, pb, nb);
+  };
+  // raises the flags of a staged tile from the maxima of its parts
+  auto put_flags = [&](int fl) RSVD_INLINE {
+    const unsigned ma = split_mag(pa, na), mb = split_mag(pb, nb);
+    pa = pb = 0;
+    na = nb = 0u;
+    int f = 0;
+    if (__ballot(ma >= kSplitHuge || mb >= kSplitHuge)) f |= SPLIT_BAD;
+    if (__ballot(ma >= kSplitTiny)) f |= SPLIT_A_USUAL;
+    if (__ballot(ma != 0u)) f |= SPLIT_A_ANY;
+    if (!PACKED) {
+      if (__ballot(mb >= kSplitTiny)) f |= SPLIT_B_USUAL;
+      if (__ballot(mb != 0u)) f |= SPLIT_B_ANY;
+    }
+    if (lane == 0) flags[fl * WAVES + wave] = f;
+  };
+  // PACKED: the next tile of B straight into buffer `buf`, 1024 bytes a wavefront and instruction (a wavefront without a
+  // piece of its own copies the last one again: no branches)
+  constexpr int PIECES = 3 * PB / 1024, ROUNDS = (PIECES + NT / 64 - 1) / (NT / 64);
+  const char *b_packed = nullptr;
+  int64_t b_packed_step = 0;
+  if (PACKED) {
+    b_packed = packed + ((int64_t)kt0 * P.tiles_n + tile_n) * (3 * PB) + lane * 16;
+    b_packed_step = (int64_t)P.tiles_n * (3 * PB);
+  }
+  auto copy_b = [&](int buf) RSVD_INLINE {
+    if constexpr (PACKED) {
+      char *dst = split_lds + buf * BUF + 3 * PA;
+#pragma unroll
+      for (int t = 0; t < ROUNDS; ++t) {
+        int piece = wave + t * (NT / 64);
+        if ((t + 1) * (NT / 64) > PIECES) piece = piece < PIECES ? piece : PIECES - 1;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(b_packed + piece * 1024),
+                                         (__attribute__((address_space(3))) void *)(dst + piece * 1024), 16, 0, 0);
+      }
+      b_packed += b_packed_step;
+    }
+  };
+  auto load_all = [&](int k_left) RSVD_INLINE {
+#pragma unroll
+    for (int w = 0; w < NA + NB; ++w) load_part(std::false_type(), w, k_left);
+  };
+  auto store_all = [&](int buf) RSVD_INLINE {
+#pragma unroll
+    for (int w = 0; w < NA + NB; ++w) store_part(w, buf);
+  };
+  // A k-tile that the split does not represent: the fp32 instruction on operands fetched one by one.
+  auto slow_tile = [&](int64_t k0) RSVD_INLINE {
+#pragma unroll 1
+    for (int kk = 0; kk < BK; kk += 4) {
+      const int64_t k = k0 + kk + kq;
+      float af[TM], bf[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int64_t row = m0 + wm0 + i * 16 + r16;
+        const bool ok = row < P.M && k < k_end;
+        af[i] = ok ? A[TA ? k * P.lda + row : row * P.lda + k] : 0.f;
+        if (CENTER && ok) af[i] = (float)((double)af[i] - P.a_shift[TA ? row : k]);
+      }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int64_t col = n0 + wn0 + j * 16 + r16;
+        bf[j] = (col < P.N && k < k_end) ? B[k * P.ldb + col] : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<float>::run(af[i], bf[j], acc[i][j]);
+    }
+  };
+  const char *ap0 = split_lds + split_chunk(wm0 + r16, kq);
+  const char *bp0 = split_lds + 3 * PA + split_chunk(wn0 + r16, kq);
+  // the matrix instructions of a tile; between(j) is issued among those of column block j
+  auto multiply = [&](int buf, auto between) RSVD_INLINE {
+    const char *ap = ap0 + buf * BUF, *bp = bp0 + buf * BUF;
+    bf16x8 af[3][TM], bf[2][3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+      for (int i = 0; i < TM; ++i) af[s][i] = *reinterpret_cast<const bf16x8 *>(ap + s * PA + i * 1024);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) bf[0][s] = *reinterpret_cast<const bf16x8 *>(bp + s * PB);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      if (j + 1 < TN) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) bf[(j + 1) & 1][s] = *reinterpret_cast<const bf16x8 *>(bp + s * PB + (j + 1) * 1024);
+      }
+      between(j);
+      constexpr int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};      // (plane of A, plane of B)
+#pragma unroll
+      for (int o = 0; o < 6; ++o)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          f32x4 &c = o < 5 ? low[i][j] : acc[i][j];
+          c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[order[o][0]][i], bf[j & 1][order[o][1]], c, 0, 0, 0);
+        }
+      __builtin_amdgcn_sched_barrier(0);       // (one column block of operands ahead, not all of them: registers)
+    }
+  };
+
+  // flags of the tile in buffer `buf`; f_b: what the packed tile of B holds
+  int buf = 1, kt = -1, f_b = 0;
+  auto tile_flags = [&]() RSVD_INLINE {
+    int f = f_b;
+    if (kt >= 0) {
+      const int seen = flags[buf * WAVES + (lane & (WAVES - 1))];
+#pragma unroll
+      for (int b = 1; b <= SPLIT_B_ANY; b <<= 1) f |= __ballot((seen & b) != 0) ? b : 0;
+    }
+    if (PACKED && kt + 1 < nkt) f_b = packed_flags[(int64_t)(kt0 + kt + 1) * P.tiles_n + tile_n];
+    return f;
+  };
+  if (nkt > 0) load_all(nkt > 1 ? BK : last_k);
+  // On entry of an iteration tile kt lies in buffer `buf` (none before the first), the next one (if any) in the registers
+  // of the stages.
+  while (kt < nkt) {
+    int f = tile_flags();
+    // the rule: the next tile is split and the loads of the one after it are issued among the matrix instructions
+    while (kt >= 0 && kt + 2 < whole_tiles && !split_unfit(f)) {
+      // (split first, then load: a wait for an older load while a copy to LDS is outstanding would wait for everything)
+      multiply(buf, [&](int j) RSVD_INLINE {
+        constexpr int LAST = NA + NB < TN ? NA + NB : TN - 1;
+#pragma unroll
+        for (int w = 0; w < NA + NB; ++w)
+          if ((w < LAST ? w : LAST - 1) == j) store_part(w, buf ^ 1);
+        if (j == LAST) {
+          copy_b(buf ^ 1);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int w = 0; w < NA + NB; ++w) load_part(std::true_type(), w, BK);
+        }
+      });
+      put_flags(buf ^ 1);
+      // The packed tile has landed once at most the loads of A issued behind it (8 or 2 a part) are outstanding; those
+      // stay in flight across the barrier, which __syncthreads() would not let them.
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(wait_imm(PACKED ? (TA ? 8 : 2) * NA : 63));
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      ++kt;
+      buf ^= 1;
+      f = tile_flags();
+    }
+    if (kt + 1 < nkt) {
+      copy_b(buf ^ 1);
+      store_all(buf ^ 1);
+      put_flags(buf ^ 1);
+      if (kt + 2 < nkt) load_all(kt + 2 < whole_tiles ? BK : last_k);
+    }
+    if (kt >= 0) {
+      if (split_unfit(f)) slow_tile(k_begin + (int64_t)kt * BK);
+      else multiply(buf, [](int) RSVD_INLINE {});
+    }
+    if (PACKED) __builtin_amdgcn_s_waitcnt(wait_imm(0));
+    __syncthreads();
+    ++kt;
+    buf ^= 1;
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j];
+  gemm_epilogue<float, float, float, TM, TN, EPI>(P, acc, split, m0 + wm0, n0 + wn0, lane);
+}
+
+// ---------------------------------------------------------------- host side
+
+// Byte offsets inside a tile are 32-bit (SplitStage::load): 128 rows of A, 32 of B or of A^T.
+inline bool split_fits(int64_t lda, int64_t ldb) { return lda < (1 << 22) && ldb < (1 << 24); }
+
+// Column tile: the fewest tiles of at most 144 columns (128 where B is not packed), evenly filled.
+inline int split_tile_n(int64_t N, bool packed) {
+  const int64_t tiles = ceil_div(N, packed ? 144 : 128);
+  return (int)(ceil_div(ceil_div(N, tiles), 16) * 16);
+}
+// Bytes that split_pack_kernel leaves for a K x N operand, and the flags behind them.
+inline size_t split_packed_bytes(int64_t K, int64_t N) {
+  const int64_t bn = split_tile_n(N, true), tiles = ceil_div(N, bn) * ceil_div(K, kSplitBK);
+  return (size_t)tiles * (size_t)(3 * bn * 64) + align_up((size_t)tiles * sizeof(int), 256);
+}
+// 32 rows a wavefront, all columns of the tile.  Up to 80 columns two workgroups of four wavefronts fit in a CU beside each other
+// (20000 x 5000, l = 48: 134 -> 121 us against one of eight), beyond that one of eight.
+constexpr int split_tile_m(int bn) { return bn <= 80 ? 128 : 256; }
+constexpr int split_wgs_per_cu(int bn) { return bn <= 80 ? 2 : 1; }
+template <int BN> struct SplitTile {
+  static constexpr int BM = split_tile_m(BN), WAVES = BM / 32, WGN = 1, WGM = WAVES;
+  static constexpr size_t lds = (size_t)2 * 3 * 64 * (BM + BN) + 2 * WAVES * sizeof(int);      // planes, flags
+};
+
+template <bool TA, int BN, bool PACKED>
+hipError_t split_run(hipStream_t s, const GemmParams &P, int batch, char *packed) {
+  typedef SplitTile<BN> T;
+  GemmParams Q = P;
+  Q.tiles_n = (int)ceil_div(P.N, BN);
+  Q.tiles_m = (int)ceil_div(P.M, T::BM);
+  const dim3 grid((unsigned)((int64_t)Q.tiles_n * Q.tiles_m * P.splits), (unsigned)batch);
+  int *flags = nullptr;
+  if (PACKED) {
+    const int64_t tiles = Q.tiles_n * ceil_div(P.K, kSplitBK);
+    flags = reinterpret_cast<int *>(packed + tiles * (3 * BN * 64));
+    hipLaunchKernelGGL((split_pack_kernel<BN>), dim3((unsigned)tiles), dim3(256), 0, s, Q, packed, flags);
+  }
+  const bool general = P.splits == 1 && (P.dead != nullptr || P.trans_c != 0);
+  if (P.a_shift != nullptr)
+    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 3, PACKED>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed, flags);
+  else if (general)
+    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 1, PACKED>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed, flags);
+  else
+    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 0, PACKED>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed, flags);
+  return hipGetLastError();
+}
+
+#define RSVD_SPLIT_TILES(X) X(48) X(64) X(80) X(96) X(112) X(128)
+#define RSVD_SPLIT_TILES_PACKED(X) X(80) X(96) X(112) X(128) X(144)
+
+template <bool TA>
+hipError_t split_by_tile(hipStream_t s, const GemmParams &P, int batch, char *packed) {
+  if (packed != nullptr) {
+    switch (split_tile_n(P.N, true)) {
+#define RSVD_SPLIT_CASE(BN) case BN: return split_run<TA, BN, true>(s, P, batch, packed);
+      RSVD_SPLIT_TILES_PACKED(RSVD_SPLIT_CASE)
+#undef RSVD_SPLIT_CASE
+    }
+    return hipErrorInvalidValue;
+  }
+  switch (split_tile_n(P.N, false)) {
+#define RSVD_SPLIT_CASE(BN) case BN: return split_run<TA, BN, false>(s, P, batch, nullptr);
+    RSVD_SPLIT_TILES(RSVD_SPLIT_CASE)
+#undef RSVD_SPLIT_CASE
+  }
+  return hipErrorInvalidValue;
+}
+template <bool TA, int BN, int EPI, bool PACKED>
+void split_raise_lds(hipError_t &e) {
+  typedef SplitTile<BN> T;
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, EPI, PACKED>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::lds);
+}
+template <bool TA>
+hipError_t split_init() {
+  hipError_t e = hipSuccess;
+#define RSVD_SPLIT_CASE(BN) split_raise_lds<TA, BN, 0, false>(e); split_raise_lds<TA, BN, 1, false>(e); split_raise_lds<TA, BN, 3, false>(e);
+  RSVD_SPLIT_TILES(RSVD_SPLIT_CASE)
+#undef RSVD_SPLIT_CASE
+#define RSVD_SPLIT_CASE(BN) split_raise_lds<TA, BN, 0, true>(e); split_raise_lds<TA, BN, 1, true>(e); split_raise_lds<TA, BN, 3, true>(e);
+  RSVD_SPLIT_TILES_PACKED(RSVD_SPLIT_CASE)
+#undef RSVD_SPLIT_CASE
+  return e;
+}
+hipError_t split_init_n();
+hipError_t split_init_t();
+hipError_t split_by_tile_n(hipStream_t s, const GemmParams &P, int batch, char *packed);      // op(A) = A
+hipError_t split_by_tile_t(hipStream_t s, const GemmParams &P, int batch, char *packed);      // op(A) = A^T
+
+}  // namespace rsvd

@@ -181,7 +181,8 @@ struct Layout {
   size_t sigma, Wj, Xj;             // all l triplets of step 5: sigma, Ub (= W), X
   size_t jac_scratch, jac_scratch_bytes;
   size_t mean;                      // centred variant: column means (n, fp64)
-  size_t total;
+  size_t total;                     // what a call cannot do without
+  size_t packed, packed_bytes;      // behind it, used where the workspace holds it: the split operand of fp32 products
 };
 
 static Layout make_layout(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t m, int64_t n, int64_t l) {
@@ -221,6 +222,12 @@ static Layout make_layout(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t m, int6
   L.jac_scratch = take(L.jac_scratch_bytes);
   L.mean = take((size_t)n * 8);
   L.total = off;
+  L.packed = off;
+  L.packed_bytes = 0;
+  if (dtype == RSVD_F32) {
+    const size_t pn = gemm_packed_bytes(n, l), pm = gemm_packed_bytes(m, l);
+    L.packed_bytes = align_up(pn > pm ? pn : pm, 256);
+  }
   return L;
 }
 
@@ -229,6 +236,7 @@ struct Ws {
   Layout L;
   int batch = 1;           // equal-shaped problems handled by every launch
   int64_t stride = 0;      // bytes between the workspaces of consecutive problems (every buffer of L)
+  bool has_packed = false; // the caller's workspace also holds L.packed
   template <typename P> P *at(size_t off) const { return reinterpret_cast<P *>(base + off); }
 };
 
@@ -409,6 +417,7 @@ static int product(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, const Ws &w, 
   d.A = A; d.lda = lda; d.B = B; d.ldb = ldb; d.C = C; d.ldc = ldc;
   if (allow_split) { d.partial = w.at<void>(w.L.partial); d.partial_bytes = w.L.partial_bytes; }
   else d.force_splits = 1;
+  if (w.has_packed) { d.packed = w.at<void>(w.L.packed); d.packed_bytes = w.L.packed_bytes; }
   RSVD_TRY(gemm_launch(ctx, s, dtype == RSVD_F32 ? GEMM_F32 : GEMM_F64, d), "gemm");
   return 0;
 }
@@ -500,6 +509,7 @@ int rsvd_create(rsvd_ctx **out, int device) {
       if (e2 == hipSuccess) e2 = jacobi_init_device(c);
       if (e2 == hipSuccess) e2 = apply_init_device(c);
       if (e2 == hipSuccess) e2 = gram_init_device(c);
+      if (e2 == hipSuccess) e2 = gemm_split_init_device(c);
       if (cur >= 0 && cur != device) (void)hipSetDevice(cur);
       if (e2 != hipSuccess) {
         (void)hipGetLastError();
@@ -576,7 +586,8 @@ int rsvd_workspace_bytes(rsvd_ctx *ctx, rsvd_dtype dtype, int64_t m, int64_t n, 
   if (q < 0) return -7;
   if (job < RSVD_JOB_S || job > RSVD_JOB_SUV) return -8;
   if (bytes == nullptr) return -9;
-  *bytes = make_layout(ctx, dtype, m, n, (int64_t)k + p).total;
+  const Layout L = make_layout(ctx, dtype, m, n, (int64_t)k + p);
+  *bytes = L.total + L.packed_bytes;
   return 0;
 }
 
@@ -616,6 +627,7 @@ static int run_impl(rsvd_ctx *ctx, void *stream, rsvd_dtype dtype, rsvd_job job,
   w.stride = (int64_t)w.L.total;             // a multiple of 256
   if (workspace == nullptr || ((uintptr_t)workspace & 255) != 0) return -18;
   if (workspace_bytes < w.L.total * (size_t)batch) return -19;
+  w.has_packed = batch == 1 && w.L.packed_bytes > 0 && workspace_bytes >= w.L.total + w.L.packed_bytes;
   if (l > jacobi_max_lds_order(ctx, dtype) && jacobi_scratch_bytes(ctx, dtype, l) == 0) return RSVD_ERR_UNSUPPORTED;
   if (batch > 1 && (l > jacobi_max_batched_order(ctx, dtype) || l > chol_max_block(ctx) || center))
     return RSVD_ERR_UNSUPPORTED;
@@ -775,7 +787,7 @@ int rsvd_workspace_bytes_batched(rsvd_ctx *ctx, rsvd_dtype dtype, int batch, int
   const int rc = rsvd_workspace_bytes(ctx, dtype, m, n, k, p, q, job, &one);
   if (rc != 0) return rc < -2 ? rc - 1 : rc;          // arguments after `batch` sit one place later here
   if (bytes == nullptr) return -10;
-  *bytes = one * (size_t)batch;
+  *bytes = batch == 1 ? one : make_layout(ctx, dtype, m, n, (int64_t)k + p).total * (size_t)batch;
   return 0;
 }
 
@@ -841,6 +853,7 @@ static int stage_gemm(rsvd_ctx *ctx, void *stream, rsvd_dtype dtype, int trans_a
   w.base = (char *)workspace;
   if (workspace == nullptr || ((uintptr_t)workspace & 255) != 0) return -13;
   if (workspace_bytes < w.L.total) return -14;
+  w.has_packed = w.L.packed_bytes > 0 && workspace_bytes >= w.L.total + w.L.packed_bytes;
   if (ctx->device < 0) return RSVD_ERR_NO_DEVICE;
   if (trans_a) return product(ctx, (hipStream_t)stream, dtype, w, 1, n, l, m, A, lda, X, ldx, Y, ldy, 0, true, PK_GEMM_ATX);
   return product(ctx, (hipStream_t)stream, dtype, w, 0, m, l, n, A, lda, X, ldx, Y, ldy, 0, true, PK_GEMM_AX);
