@@ -17,7 +17,11 @@ hipError_t gemm_split_init_device(rsvd_ctx *ctx) {
 // 16384, l = 16: 5.7 TB/s).  Below 2^29 multiply-adds (2000 x 500, l = 33: 19 us split, 14 us not) the longer prologue of the
 // large tiles costs more than the faster instruction brings; above, split products win from 10000 x 2000, l = 80 (48 -> 41 us)
 // to 65536 x 16384, l = 576 (9.2 -> 5.8 ms).
+// A triangular B (the applies of R^-1) leaves only part of a short k range per column tile, and the fp32 kernel's narrower tiles
+// waste less of it (65536 x 576: 176 us, split 224 us) unless it is down to scalar loads (50021 x 210: 86 us, split 72 us).
 static bool takes_split(const GemmDesc &d) {
+  const bool aligned = ((uintptr_t)d.A | (uintptr_t)d.B) % 16 == 0 && (d.lda | d.ldb | d.K | d.N) % 4 == 0;
+  if (d.b_upper != 0 && aligned) return false;
   return d.N > 32 && (double)d.M * (double)d.N * (double)d.K * (double)d.batch >= 536870912.0 && !d.upper_only &&
          d.alpha == 1.0 && d.beta == 0.0 && split_fits(d.lda, d.ldb);
 }

@@ -187,7 +187,11 @@ __global__ __launch_bounds__(256) void split_pack_kernel(const GemmParams P0, ch
 
 // Epilogues as in gemm_kernel: 0 plain, 1 full, 3 plain with the column offsets of A taken away while staging.
 // PACKED: B comes as split_pack_kernel left it.
-template <bool TA, int BM, int BN, int WGM, int WGN, int EPI, bool PACKED>
+// CHAIN: no second set of accumulators; the six terms of a k-tile are summed from zero and added to the one set there is.
+// That is more vector instructions (9 % at 65536 x 16384, l = 576) but 16 registers instead of one set of accumulators, and
+// outputs of one column tile of 112 or 128 columns, which split B in place and wait for A from HBM besides, are faster
+// with it (100000 x 1000, l = 120: A X 262 -> 230 us, A^T X 191 -> 180 us; at 96 columns and below it is the other way round).
+template <bool TA, int BM, int BN, int WGM, int WGN, int EPI, bool PACKED, bool CHAIN>
 __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const GemmParams P0, const char *__restrict__ packed,
                                                                        const int *__restrict__ packed_flags) {
   const GemmParams P = select_problem(P0);
@@ -216,11 +220,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const Gem
   const float *B = (const float *)P.B;
   // The products of the leading planes and the five terms below them are summed apart: one rounding at the size of the
   // result per k-tile instead of six, and a long k range ends four to five times closer than with the fp32 instruction.
-  f32x4 acc[TM][TN], low[TM][TN];
+  constexpr int LN = CHAIN ? 1 : TN;
+  f32x4 acc[TM][TN], low[TM][LN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = low[i][j] = (f32x4)0.f;
+    for (int j = 0; j < TN; ++j) acc[i][j] = low[i][j % LN] = (f32x4)0.f;
 
   SplitStage<NT, BM, TA, CENTER> sa;
   SplitStage<NT, PACKED ? 16 : BN, true> sb;
@@ -328,6 +333,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const Gem
   auto multiply = [&](int buf, auto between) RSVD_INLINE {
     const char *ap = ap0 + buf * BUF, *bp = bp0 + buf * BUF;
     bf16x8 af[3][TM], bf[2][3];
+    f32x4 sum[2][TM];
 #pragma unroll
     for (int s = 0; s < 3; ++s)
 #pragma unroll
@@ -346,10 +352,23 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const Gem
       for (int o = 0; o < 6; ++o)
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-          f32x4 &c = o < 5 ? low[i][j] : acc[i][j];
-          c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[order[o][0]][i], bf[j & 1][order[o][1]], c, 0, 0, 0);
+          const bf16x8 x = af[order[o][0]][i], y = bf[j & 1][order[o][1]];
+          if (CHAIN) {
+            sum[j & 1][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, o == 0 ? (f32x4)0.f : sum[j & 1][i], 0, 0, 0);
+          } else {
+            f32x4 &c = o < 5 ? low[i][j % LN] : acc[i][j];
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, c, 0, 0, 0);
+          }
         }
+      if (CHAIN && j > 0) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[i][j - 1] += sum[(j - 1) & 1][i];
+      }
       __builtin_amdgcn_sched_barrier(0);       // (one column block of operands ahead, not all of them: registers)
+    }
+    if (CHAIN) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) acc[i][TN - 1] += sum[(TN - 1) & 1][i];
     }
   };
 
@@ -412,10 +431,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const Gem
     ++kt;
     buf ^= 1;
   }
+  if (!CHAIN) {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j];
+      for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j % LN];
+  }
   gemm_epilogue<float, float, float, TM, TN, EPI>(P, acc, split, m0 + wm0, n0 + wn0, lane);
 }
 
@@ -443,7 +464,7 @@ template <int BN> struct SplitTile {
   static constexpr size_t lds = (size_t)2 * 3 * 64 * (BM + BN) + 2 * WAVES * sizeof(int);      // planes, flags
 };
 
-template <bool TA, int BN, bool PACKED>
+template <bool TA, int BN, bool PACKED, bool CHAIN>
 hipError_t split_run(hipStream_t s, const GemmParams &P, int batch, char *packed) {
   typedef SplitTile<BN> T;
   GemmParams Q = P;
@@ -458,50 +479,63 @@ hipError_t split_run(hipStream_t s, const GemmParams &P, int batch, char *packed
   }
   const bool general = P.splits == 1 && (P.dead != nullptr || P.trans_c != 0);
   if (P.a_shift != nullptr)
-    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 3, PACKED>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed, flags);
+    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 3, PACKED, CHAIN>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed, flags);
   else if (general)
-    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 1, PACKED>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed, flags);
+    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 1, PACKED, CHAIN>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed, flags);
   else
-    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 0, PACKED>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed, flags);
+    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 0, PACKED, CHAIN>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed, flags);
   return hipGetLastError();
 }
 
-#define RSVD_SPLIT_TILES(X) X(48) X(64) X(80) X(96) X(112) X(128)
+#define RSVD_SPLIT_TILES_ONE(X) X(48) X(64) X(80) X(96) X(112) X(128)
+#define RSVD_SPLIT_TILES(X) X(80) X(96) X(112) X(128)
 #define RSVD_SPLIT_TILES_PACKED(X) X(80) X(96) X(112) X(128) X(144)
 
 template <bool TA>
 hipError_t split_by_tile(hipStream_t s, const GemmParams &P, int batch, char *packed) {
-  if (packed != nullptr) {
+  if (P.N <= 128) {                    // one column tile
+    switch (split_tile_n(P.N, false)) {
+#define RSVD_SPLIT_CASE(BN) case BN: return split_run<TA, BN, false, (BN >= 112)>(s, P, batch, nullptr);
+      RSVD_SPLIT_TILES_ONE(RSVD_SPLIT_CASE)
+#undef RSVD_SPLIT_CASE
+    }
+  } else if (packed != nullptr) {
     switch (split_tile_n(P.N, true)) {
-#define RSVD_SPLIT_CASE(BN) case BN: return split_run<TA, BN, true>(s, P, batch, packed);
+#define RSVD_SPLIT_CASE(BN) case BN: return split_run<TA, BN, true, false>(s, P, batch, packed);
       RSVD_SPLIT_TILES_PACKED(RSVD_SPLIT_CASE)
 #undef RSVD_SPLIT_CASE
     }
-    return hipErrorInvalidValue;
-  }
-  switch (split_tile_n(P.N, false)) {
-#define RSVD_SPLIT_CASE(BN) case BN: return split_run<TA, BN, false>(s, P, batch, nullptr);
-    RSVD_SPLIT_TILES(RSVD_SPLIT_CASE)
+  } else {                             // the same sums without the packed operand
+    switch (split_tile_n(P.N, false)) {
+#define RSVD_SPLIT_CASE(BN) case BN: return split_run<TA, BN, false, false>(s, P, batch, nullptr);
+      RSVD_SPLIT_TILES(RSVD_SPLIT_CASE)
 #undef RSVD_SPLIT_CASE
+    }
   }
   return hipErrorInvalidValue;
 }
-template <bool TA, int BN, int EPI, bool PACKED>
+template <bool TA, int BN, int EPI, bool PACKED, bool CHAIN>
 void split_raise_lds(hipError_t &e) {
   typedef SplitTile<BN> T;
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, EPI, PACKED>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, EPI, PACKED, CHAIN>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::lds);
 }
 template <bool TA>
 hipError_t split_init() {
   hipError_t e = hipSuccess;
-#define RSVD_SPLIT_CASE(BN) split_raise_lds<TA, BN, 0, false>(e); split_raise_lds<TA, BN, 1, false>(e); split_raise_lds<TA, BN, 3, false>(e);
+#define RSVD_SPLIT_RAISE(BN, PACKED, CHAIN) \
+  split_raise_lds<TA, BN, 0, PACKED, CHAIN>(e); split_raise_lds<TA, BN, 1, PACKED, CHAIN>(e); split_raise_lds<TA, BN, 3, PACKED, CHAIN>(e);
+#define RSVD_SPLIT_CASE(BN) RSVD_SPLIT_RAISE(BN, false, (BN >= 112))
+  RSVD_SPLIT_TILES_ONE(RSVD_SPLIT_CASE)
+#undef RSVD_SPLIT_CASE
+#define RSVD_SPLIT_CASE(BN) RSVD_SPLIT_RAISE(BN, false, false)
   RSVD_SPLIT_TILES(RSVD_SPLIT_CASE)
 #undef RSVD_SPLIT_CASE
-#define RSVD_SPLIT_CASE(BN) split_raise_lds<TA, BN, 0, true>(e); split_raise_lds<TA, BN, 1, true>(e); split_raise_lds<TA, BN, 3, true>(e);
+#define RSVD_SPLIT_CASE(BN) RSVD_SPLIT_RAISE(BN, true, false)
   RSVD_SPLIT_TILES_PACKED(RSVD_SPLIT_CASE)
 #undef RSVD_SPLIT_CASE
+#undef RSVD_SPLIT_RAISE
   return e;
 }
 hipError_t split_init_n();

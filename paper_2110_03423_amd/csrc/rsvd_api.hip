@@ -225,7 +225,7 @@ static Layout make_layout(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t m, int6
   L.packed = off;
   L.packed_bytes = 0;
   if (dtype == RSVD_F32) {
-    const size_t pn = gemm_packed_bytes(n, l), pm = gemm_packed_bytes(m, l);
+    const size_t pn = gemm_packed_bytes(n, l), pm = gemm_packed_bytes(m, l);      // l <= min(m, n): R^-1 fits as well
     L.packed_bytes = align_up(pn > pm ? pn : pm, 256);
   }
   return L;
@@ -338,6 +338,7 @@ static int orthonormalize(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, const 
     a.batch = w.batch; a.stride_a = a.stride_b = a.stride_c = a.stride_dead = w.stride; a.seed_step = 1;
     a.skip_flag = gate; a.stride_flag = w.stride;
     a.prof_kind = PK_APPLY;
+    if (w.has_packed) { a.packed = w.at<void>(L.packed); a.packed_bytes = L.packed_bytes; }
     RSVD_TRY(gemm_launch(ctx, s, kind, a), "apply R^-1");
     return 0;
   };
