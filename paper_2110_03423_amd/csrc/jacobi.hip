@@ -387,19 +387,16 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
 //
 // Block one-sided Jacobi.  M^T and J^T live in global memory (column c of M is
 // row c of Mt, contiguous).  The columns are cut into blocks of b; an outer
-// sweep is a round-robin tournament over the blocks, one kernel launch per
-// round, one workgroup per block pair.  The workgroup pulls its two blocks
-// (2b columns of length l) into LDS, runs the same pairwise rotations as above
-// over those columns while accumulating them in a small 2b x 2b matrix T,
-// writes the columns back and leaves T for the matching columns of J.  In the
-// launch that rotates the pairs inside one block every rotation is a plane
-// rotation of actual columns; the launches over block pairs take the rotations
-// from the Gram matrix of the panel and apply T once (jb_cross_kernel), or
-// rotate column by column where that panel does not fit in LDS (jb_panel_kernel).
+// sweep is a round-robin tournament over the blocks, one workgroup per block pair.
+// Orders whose panel of 2b columns fits in LDS take one launch for all sweeps
+// (jb_flow_kernel, rotations from the Gram matrix of the panel).  Longer columns
+// take one launch per round (jb_panel_kernel): the workgroup rotates its columns pair
+// by pair, accumulates the rotations in a small 2b x 2b matrix T, writes the columns
+// back and leaves T for the matching columns of J.
 // counters[s] collects the largest relative inner product that outer sweep s
-// rotated away; a launch that finds the sweeps before it sufficient
-// (jacobi_done_before) returns at once, which keeps the whole sequence free of
-// host synchronisation.
+// rotated away; sweeps that the ones before make unnecessary (jacobi_done) are left
+// out by the kernels themselves, which keeps the whole sequence free of host
+// synchronisation.
 
 // Sum over the 32 lanes of a pair group: the 16-lane row by DPP (neighbours, pairs,
 // half-row mirror, row mirror), then one exchange with the partner row.
@@ -512,6 +509,10 @@ struct JbHeader {
   double unscale;         // the singular values of M are those of the scaled matrix times this
   int counters[64];       // per outer sweep: bit pattern of the largest relative inner product rotated away
   double partial[kJbFroParts];   // sums of squares, one per workgroup of jb_fro_kernel
+  // jb_flow_kernel
+  int ticket;             // next task
+  int stop;               // != 0: converged
+  int finished[32];       // per outer sweep: block pairs whose columns of M are done
 };
 
 // ||M||_F^2 in kJbFroParts partial sums (fixed assignment of elements and fixed order: reproducible).
@@ -535,7 +536,8 @@ __global__ __launch_bounds__(256) void jb_fro_kernel(const double *__restrict__ 
 // the type whatever the scale of the input.  Grid of workgroups, each taking a slab of elements.
 template <typename T>
 __global__ __launch_bounds__(256) void jb_init_kernel(const double *__restrict__ M, int l, T *__restrict__ Mt,
-                                                      T *__restrict__ Jt, JbHeader *hdr, int rows) {
+                                                      T *__restrict__ Jt, JbHeader *hdr, int rows,
+                                                      int *__restrict__ ver, int nver) {
   double fro2 = 0;
   for (int i = 0; i < kJbFroParts; ++i) fro2 += hdr->partial[i];
   double sc = 1.0, unscale = 1.0;
@@ -553,7 +555,11 @@ __global__ __launch_bounds__(256) void jb_init_kernel(const double *__restrict__
   }
   if (blockIdx.x == 0) {
     if (threadIdx.x < 64) hdr->counters[threadIdx.x] = 0;
+    if (threadIdx.x < 32) hdr->finished[threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < nver; i += blockDim.x) ver[i] = 0;
     if (threadIdx.x == 0) {
+      hdr->ticket = 0;
+      hdr->stop = 0;
       hdr->fro2 = fro2 * sc * sc;
       hdr->unscale = unscale;
     }
@@ -823,292 +829,439 @@ __global__ __launch_bounds__(1024) void jb_panel_kernel(T *__restrict__ Mt, T *_
   }
 }
 
-// ---- cross phase through the Gram matrix of the block pair ----
+// ---- all sweeps in one launch, rotations from the Gram matrix of a block pair ----
 //
-// The b rounds of a cross launch rotate 2b columns of length l; done column by column (jb_panel_kernel) a round
-// costs ~1 us of plain vector instructions whatever l is.  The rotations only need inner products, and those
-// follow from the 2b x 2b Gram matrix G of the panel: G is formed once on the matrix cores, the b rounds rotate G
-// on both sides (G <- J^T G J, a 2 x 2 block per thread) and accumulate T <- T J, and the panel is multiplied by T
-// once, again on the matrix cores.  Pair order, rotation formulas, thresholds and the stopping rule are those of
-// the column-by-column kernel; the first round sees exact inner products, later rounds the tracked ones (their
-// error is of second order in the rotation angles and is wiped out by the next launch, which forms G afresh).
+// Rotating 2b columns of length l column by column (jb_panel_kernel) costs ~1 us of plain vector instructions a round
+// whatever l is.  The rotations only need inner products, and those follow from the 2b x 2b Gram matrix G of the panel:
+// G is formed once on the matrix cores, the rounds rotate G on both sides (G <- J^T G J, a 2 x 2 block per thread) and
+// accumulate T <- T J, and the panel is multiplied by T once, again on the matrix cores.  Rotation formulas, thresholds
+// and the stopping rule are those of the column-by-column kernel; the first round sees exact inner products, later
+// rounds the tracked ones (their error is of second order in the rotation angles and is wiped out by the next visit,
+// which forms G afresh).
+//
+// A sweep is a tournament over the column blocks: nblk2 - 1 steps of nblk2 / 2 block pairs.  A pair's task rotates the
+// b x b pairs of columns across its two blocks (b rounds: pair i of round r is (i, b + (i + r) mod b)), in the first step
+// of a sweep also the pairs inside either block before them (b - 1 rounds of the circle method, both blocks side by
+// side); then it applies T to the matching columns of J.
+//
+// Tasks are numbered in the order sweep, step, pair and handed out by a counter; a task waits until its blocks have
+// been through the step before (ver: M, ver + nblk: J), the tasks of the first step of a sweep until the sweep before is
+// complete, whose record says whether there is anything left to do.  Every wait is for tasks with lower numbers, whose
+// workgroups are running already, so the lowest unfinished task never waits for anything unfinished: no number of
+// resident workgroups is assumed, and no other kernel on the chip can stop the progress.  M and J are read and
+// written with device-wide scope (the L2 caches of the XCDs do not see each other's lines).  J is off the critical
+// path: the columns of M are published before it is touched, and with two workgroups per block pair the next step
+// runs meanwhile.
+//
+// What bounds a step is its chain: panel in 2.1 us, G 3.0, 16 rounds of ~0.4 (fp64; 0.3 in fp32), panel out 1.9, the
+// stores' arrival 1.3, the wait for them elsewhere ~1 (fp64, l = 288).  Against one launch per step with the rotations of
+// J a step behind (the launches of sweeps that are not needed come to a quarter of the time): whole decomposition
+// with a spectrum over three decades 1009 -> 685 us (fp64, l = 120), 2751 -> 1717 (fp64, 288), 1516 -> 897 (fp32, 210),
+// 5157 -> 3289 (fp32, 576).
 constexpr int kJgB = 16;                    // block width this kernel is written for
 constexpr int kJgN = 2 * kJgB;              // columns of a panel
 constexpr int kJgLd = kJgN + 1;             // row stride of G and T in LDS
 constexpr int kJgMat = kJgN * kJgLd;        // elements of one such matrix
 constexpr int kJgPart = 3 * 256;            // elements of one partial sum of G (three 16 x 16 blocks)
+template <bool V> struct JbKind { static constexpr bool value = V; };
 
-// Column stride of the panel in LDS: l padded to whole 16-row blocks, plus what spreads 16 columns over the banks.
+// Column stride of the panel in LDS: l padded to whole 16-row blocks, plus what spreads sixteen 16-byte pieces of 16
+// columns over the banks.
 template <typename T> __host__ __device__ constexpr int jg_ldp(int l) {
-  return (l + 15) / 16 * 16 + (sizeof(T) == 4 ? 2 : 1);
+  return (l + 15) / 16 * 16 + 16 / (int)sizeof(T);
 }
 template <typename T> __host__ __device__ constexpr size_t jg_lds_bytes(int l) {
   return ((size_t)kJgN * jg_ldp<T>(l) + 5 * (size_t)kJgMat) * sizeof(T);
 }
 
-// Rotation of pair `a` in round r (columns p = a and q = b + (a + r) mod b of the panel), from the tracked Gram
-// matrix: (c, s) = (1, 0) when the pair is left alone; returns the relative inner product that is rotated away
-// (0 if none).  Without branches: the chain of dependent instructions of a round starts here.
+// Longest columns (a wavefront stages a column through this many / 64 registers); LDS ends at about the same order.
+template <typename T> __host__ __device__ constexpr int jg_max_order() { return sizeof(T) == 4 ? 1088 : 512; }
+
+// Pair i of a round is always the columns in slots p and q of G and T; behind the round the contents of these slots move to
+// slots mp and mq, so that the next round finds its pairs in the same places: no address depends on the round.  INTRA,
+// pairs inside the blocks: circle method over the 16 slots of a block (slot 15 stays, the others move up by one), pairs 0-7 in
+// the first block and 8-15 in the second.  Else pairs across the blocks: the second block moves down by one.  After the
+// b - 1 and the b rounds every column is back in its own slot.
+template <bool INTRA> __device__ __forceinline__ void jg_pair(int i, int &p, int &q, int &mp, int &mq) {
+  if (INTRA) {
+    const int h = i & 7, base = (i >> 3) * kJgB;
+    p = base + h;
+    q = base + kJgB - 1 - h;
+    mp = p + 1;
+    mq = h == 0 ? q : (h == 1 ? base : q + 1);
+  } else {
+    p = mp = i;
+    q = kJgB + i;
+    mq = kJgB + ((i - 1) & (kJgB - 1));
+  }
+}
+
+// Rotation of columns p and q of the panel from the tracked Gram matrix: (c, s) = (1, 0) when the pair is left alone
+// (columns that are padding have norm zero); returns the relative inner product that is rotated away (0 if none).
+// Without branches: the chain of dependent instructions of a round starts here.
 template <typename T>
-__device__ __forceinline__ float jg_pair_params(const T *G, int a, int r, int cols_i, int cols_j, T tol, T floor2,
-                                                int &q, T &c, T &s) {
-  const int qi = (a + r) & (kJgB - 1);
-  q = kJgB + qi;
-  const T alpha = G[a * kJgLd + a], beta = G[q * kJgLd + q], gamma = G[a * kJgLd + q];
-  const T rel = fabs(gamma) * fast_rsq(alpha * beta);
-  const bool rot = (a < cols_i) & (qi < cols_j) & (alpha > floor2) & (beta > floor2) & (rel > tol);
-  const T g = rot ? gamma : (T)1;
-  const T zeta = (beta - alpha) * fast_rcp((T)2 * g);
-  const T az = fabs(zeta);
-  T cc, ss;
+__device__ __forceinline__ float jg_pair_params(const T *G, int p, int q, T tol, T floor2, T &c, T &s) {
+  const T alpha = G[p * kJgLd + p], beta = G[q * kJgLd + q], gamma = G[p * kJgLd + q];
+  T rel, cc, ss;
+  bool rot = (alpha > floor2) & (beta > floor2);
   if constexpr (sizeof(T) == 4) {
-    // t = 1 / (|zeta| + sqrt(1 + zeta^2)), c = 1 / sqrt(1 + t^2), s = c t: s tied to c, so that c^2 + s^2 - 1 stays
-    // at the 1e-9 level in fp32 (the columns of T and J keep their length over thousands of rotations)
-    const T t_small = (T)0.5 * fast_rcp(az);                     // |zeta| > 1e7: zeta^2 would overflow
-    const T t_usual = fast_rcp(az + fast_sqrt((T)1 + zeta * zeta));
-    const T t = az > (T)1e7 ? t_small : t_usual;
+    rel = fabsf(gamma) * fast_rsq(alpha * beta);
+    rot = rot & (rel > tol);
+    // t = 2 gamma / (|delta| + sqrt(delta^2 + 4 gamma^2)) with delta = beta - alpha, c = 1 / sqrt(1 + t^2), s = c t.
+    // M is scaled to norm ~1 and columns below eps of that are not rotated: with the factor 2^32 the squares neither
+    // overflow nor underflow.
+    const T delta = (beta - alpha) * (T)4294967296.0, g2 = gamma * (T)8589934592.0;
+    const T x = delta * delta + g2 * g2;
+    const T t = g2 * fast_rcp(fabsf(delta) + x * fast_rsq(x));
     cc = fast_rsq((T)1 + t * t);
     ss = cc * t;
   } else {
-    // the same rotation with one reciprocal square root less on the chain of dependent instructions (each costs
-    // two Newton steps in fp64): with w = sqrt(1 + zeta^2), c^2 = (|zeta| + w) / (2 w), s^2 = 1 / (2 w (|zeta| + w))
-    const T q2 = (T)1 + zeta * zeta;
-    const T u = fast_rsq(q2);
-    const T w = q2 * u;
-    const T c_usual = fast_sqrt((T)0.5 + (T)0.5 * az * u);
-    const T s_usual = fast_rsq((T)2 * w * (az + w));
-    const bool huge = az > (T)1e100;                             // zeta^2 would overflow; t = 1 / (2 |zeta|)
-    cc = huge ? (T)1 : c_usual;
-    ss = huge ? (T)0.5 * fast_rcp(az) : s_usual;
+    // From the double angle, one division less on the chain of dependent instructions: with delta = beta - alpha and
+    // u = 1 / sqrt(delta^2 + 4 gamma^2), c^2 = (1 + |delta| u) / 2 and s = gamma u / c.  M is scaled to norm ~1 and
+    // columns below eps of that are not rotated, so the squares neither overflow nor underflow.  (rel only meets the
+    // threshold and the rate of convergence: the hardware's estimate will do.)
+    rel = fabs(gamma) * __builtin_amdgcn_rsq(alpha * beta);
+    rot = rot & (rel > tol);
+    const T delta = beta - alpha, ad = fabs(delta), g2 = (T)2 * gamma;
+    const T u = fast_rsq(delta * delta + g2 * g2);
+    const T y = (T)0.5 + (T)0.5 * ad * u;
+    const T ri = fast_rsq(y);
+    cc = y * ri;
+    ss = gamma * u * ri;
   }
-  ss = zeta < (T)0 ? -ss : ss;
+  // The estimates err to one side: c^2 + s^2 is brought to 1 within a rounding, or every column drifts the same way over the
+  // thousands of rotations it goes through (|J^T J - I| at l = 130 ... 450: 1.4e-13 with this line, 1.8e-12 without).
+  const T off = (T)0.5 * fma(ss, ss, fma(cc, cc, (T)-1));
+  cc -= cc * off;
+  ss -= ss * off;
+  ss = beta < alpha ? -ss : ss;
   c = rot ? cc : (T)1;
   s = rot ? ss : (T)0;
   return rot ? (float)rel : 0.f;
 }
 
-template <typename T> __device__ __forceinline__ T lane_read(T v, int src_lane);
-template <> __device__ __forceinline__ float lane_read<float>(float v, int src_lane) {
-  return __int_as_float(__builtin_amdgcn_ds_bpermute(src_lane << 2, __float_as_int(v)));
+// Loads and stores that every XCD sees.
+template <typename V> __device__ __forceinline__ V device_load(const V *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-template <> __device__ __forceinline__ double lane_read<double>(double v, int src_lane) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_ds_bpermute(src_lane << 2, (int)b);
-  const int hi = __builtin_amdgcn_ds_bpermute(src_lane << 2, (int)(b >> 32));
-  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned int)lo);
+template <typename V> __device__ __forceinline__ void device_store(V *p, V v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The device-wide stores of this wavefront have arrived where every XCD sees them (no write-back of the L2 is needed
+// for those, which a release fence would ask for in every wavefront: 8 us a step more in fp64).
+__device__ __forceinline__ void device_stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Waits until *p and *p2 reached `want`, or until *stop is set (if there is one); returns false in that case.
+__device__ __forceinline__ bool jb_wait(const int *p, const int *p2, int want, const int *stop) {
+  for (;;) {
+    const int a = device_load(p), b = device_load(p2), st = stop != nullptr ? device_load(stop) : 0;
+    if (a >= want && b >= want) return true;
+    if (st != 0) return false;
+    __builtin_amdgcn_s_sleep(1);
+  }
 }
 
 template <typename T>
-__global__ __launch_bounds__(1024) void jb_cross_kernel(T *__restrict__ Mt, T *__restrict__ Jt, int l, int nblk,
-                                                        int round, int sweep, int rot_wgs, int prev_phase,
-                                                        int prev_round, int prev_sweep, T *__restrict__ Tring,
-                                                        int *__restrict__ chg, int slot, JbHeader *hdr) {
+__global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__restrict__ Jt, int l, int nblk,
+                                                       int max_sweeps, int *__restrict__ ver, JbHeader *hdr) {
   constexpr int b = kJgB;
+  typedef typename Mfma<T>::vec acc_t;
   const T tol = Eps<T>::value * sqrt((T)l);
-  extern __shared__ __attribute__((aligned(16))) double lds_raw[];
-  if ((int)blockIdx.x >= rot_wgs) {
-    jb_j_role<T>(Jt, l, b, nblk, rot_wgs, prev_phase, prev_round, prev_sweep, Tring, chg, slot, hdr, (float)tol,
-                 reinterpret_cast<T *>(lds_raw));
-    return;
-  }
-  if (jacobi_done_before(hdr->counters, sweep, (float)tol)) return;        // the sweeps before finished the job
-  const JbPair pr = jb_pair(1, round, (int)blockIdx.x, l, b, nblk);
-  if (!pr.valid) return;                                       // bye
-  const int cols_i = pr.cols_i, cols_j = pr.cols_j, ncols = cols_i + cols_j;
+  const T floor2 = (T)(Eps<T>::value * Eps<T>::value * hdr->fro2);
+  const int nblk2 = nblk + (nblk & 1), pairs = nblk2 / 2, steps_per_sweep = nblk2 - 1;
   const int ldp = jg_ldp<T>(l), lp = (l + 15) / 16 * 16;
+  extern __shared__ __attribute__((aligned(16))) double lds_raw[];
   T *Pc = reinterpret_cast<T *>(lds_raw);                      // [2b][ldp]: column c of the panel, zero padded
   T *G0 = Pc + (size_t)kJgN * ldp;                             // G, even rounds
   T *R4 = G0 + kJgMat;                                         // four matrices: the five partial sums of G, then T0, T1, G1 and the (c, s) of every round
-  __shared__ int rotations;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r16 = lane & 15, kq = lane >> 4;
-  auto gcol = [&](int c) { return c < b ? pr.bi * b + c : pr.bj * b + (c - b); };      // global column of panel column c
-  auto live = [&](int c) { return c < b ? c < cols_i : c - b < cols_j; };
+  T *CS = R4 + 3 * kJgMat;                                     // [rounds][16 pairs][c, s]
+  __shared__ int rotations, task;
+  int ticket = 0;
+  if (threadIdx.x == 0) ticket = atomicAdd(&hdr->ticket, 1);
 
-  // panel in: wavefront w takes columns w and w + 16, every load in flight before the first LDS store
-  {
-    constexpr int MAXJ = sizeof(T) == 4 ? 17 : 8;              // 64 * MAXJ rows at most (the LDS limit is lower)
-    T v[2][MAXJ];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int c = wave + 16 * u;
-      const T *src = Mt + (int64_t)gcol(live(c) ? c : 0) * l;
-#pragma unroll
-      for (int j = 0; j < MAXJ; ++j) {
-        const int rr = lane + 64 * j;
-        v[u][j] = (live(c) && rr < l) ? src[rr] : (T)0;
+  for (;;) {
+    // (worked out anew for every task: the addresses that follow from them were kept across tasks otherwise, in
+    // scratch memory)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, kq = lane >> 4;
+    if (tid == 0) {
+      bool go = ticket < max_sweeps * steps_per_sweep * pairs;
+      if (go) {
+        const int n = ticket / pairs, g = ticket - n * pairs;                  // step, pair
+        const int sweep = n / steps_per_sweep, round = n - sweep * steps_per_sweep;
+        if (round == 0) {
+          if (sweep > 0) {
+            const int *f = &hdr->finished[sweep - 1];
+            go = jb_wait(f, f, steps_per_sweep * pairs, &hdr->stop);
+            if (go) {
+              const float rho = __int_as_float(device_load(&hdr->counters[sweep - 1]));
+              const float before = sweep > 1 ? __int_as_float(device_load(&hdr->counters[sweep - 2])) : -1.f;
+              if (jacobi_done(rho, before, (float)tol)) {
+                device_store(&hdr->stop, 1);
+                go = false;
+              }
+            }
+          }
+        } else {
+          const JbPair pr = jb_pair(1, round, g, l, b, nblk);
+          go = jb_wait(ver + pr.bi, ver + (pr.valid ? pr.bj : pr.bi), n, &hdr->stop);
+        }
       }
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int c = wave + 16 * u;
-#pragma unroll
-      for (int j = 0; j < MAXJ; ++j) {
-        const int rr = lane + 64 * j;
-        if (rr < lp) Pc[c * ldp + rr] = v[u][j];
-      }
-    }
-  }
-  if (tid == 0) rotations = 0;
-  __syncthreads();
-
-  // G = P^T P: wavefront w takes 16 x 16 block (ti, tj) over the quarter sl of the rows, eight k-steps of
-  // operands at a time ahead of their matrix instructions, two accumulators
-  typedef typename Mfma<T>::vec acc_t;
-  {
-    // (G is symmetric: blocks (0,0), (0,1) and (1,1) only, five row slices each, fifteen wavefronts)
-    const int sl = wave / 3, tile = wave - 3 * sl;
-    const int ti = tile >> 1, tj = (tile + 1) >> 1;
-    const int steps = lp / 4, per = (steps + 4) / 5;
-    const int s0 = sl * per, s1 = (wave == 15) ? 0 : ((s0 + per < steps) ? s0 + per : steps);
-    acc_t acc0 = (acc_t)(T)0, acc1 = (acc_t)(T)0;
-    const T *ap = Pc + (ti * 16 + r16) * ldp + kq;
-    const T *bp = Pc + (tj * 16 + r16) * ldp + kq;
-    for (int st = s0; st < s1; st += 8) {
-      T av[8], bv[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const bool ok = st + u < s1;
-        av[u] = ok ? ap[4 * (st + u)] : (T)0;
-        bv[u] = ok ? bp[4 * (st + u)] : (T)0;
-      }
-#pragma unroll
-      for (int u = 0; u < 8; u += 2) {
-        acc0 = Mfma<T>::run(av[u], bv[u], acc0);
-        acc1 = Mfma<T>::run(av[u + 1], bv[u + 1], acc1);
-      }
-    }
-    if (wave < 15) {
-      T *dst = R4 + sl * kJgPart + tile * 256;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) dst[Mfma<T>::row(lane, v) * 16 + r16] = acc0[v] + acc1[v];
-    }
-  }
-  __syncthreads();
-  {
-    // entry (i, j) of G from the five partial sums of its block (the block above the diagonal read transposed below it)
-    const int i = tid >> 5, j = tid & 31;
-    const int bi2 = i >> 4, bj2 = j >> 4;
-    const bool lower = bi2 > bj2;
-    const int tile = lower ? 1 : bi2 + bj2;
-    const int e = tile * 256 + (lower ? (j & 15) * 16 + (i & 15) : (i & 15) * 16 + (j & 15));
-    G0[i * kJgLd + j] = ((R4[e] + R4[kJgPart + e]) + (R4[2 * kJgPart + e] + R4[3 * kJgPart + e])) + R4[4 * kJgPart + e];
-  }
-  __syncthreads();
-  T *Tb[2] = {R4, R4 + kJgMat};
-  T *Gb[2] = {G0, R4 + 2 * kJgMat};
-  {
-    const int i = tid >> 5, j = tid & 31;
-    Tb[0][i * kJgLd + j] = (i == j) ? (T)1 : (T)0;
-  }
-  __syncthreads();
-
-  // b rounds.  Wavefronts 0-3 (one per SIMD: the chain of dependent instructions of a round is theirs alone):
-  // G <- J^T G J, thread (a, bb) the rows of pair a and the columns of pair bb; every lane works out the rotation of
-  // pair bb = lane mod 16, fetches that of pair a from lane a, and the first sixteen leave (c, s) of the round in
-  // LDS.  Wavefronts 4-11: T <- T J one round behind, thread (rr, bb) row rr and the columns of pair bb.  One barrier
-  // per round (G and T alternate between two copies).
-  const T floor2 = (T)(Eps<T>::value * Eps<T>::value * hdr->fro2);
-  T *CS = R4 + 3 * kJgMat;                                     // [b rounds][16 pairs][c, s], in the fourth matrix
-  float rho = 0.f;
-  const int bb = tid & 15;
-  auto rotate_t = [&](int r) {                                 // T <- T J_r
-    const T *Ts = Tb[r & 1];
-    T *Td = Tb[(r & 1) ^ 1];
-    const int rr = (tid - 256) >> 4;
-    const int qb = kJgB + ((bb + r) & (kJgB - 1));
-    const T cb = CS[(r * 16 + bb) * 2], sb = CS[(r * 16 + bb) * 2 + 1];
-    const T tp = Ts[rr * kJgLd + bb], tq = Ts[rr * kJgLd + qb];
-    Td[rr * kJgLd + bb] = cb * tp - sb * tq;
-    Td[rr * kJgLd + qb] = sb * tp + cb * tq;
-  };
-  for (int r = 0; r < b; ++r) {
-    if (tid < 256) {
-      const T *Gs = Gb[r & 1];
-      T *Gd = Gb[(r & 1) ^ 1];
-      int qb;
-      T cb, sb;
-      const float rel = jg_pair_params<T>(Gs, bb, r, cols_i, cols_j, tol, floor2, qb, cb, sb);
-      const int a = tid >> 4;
-      const int qa = kJgB + ((a + r) & (kJgB - 1));
-      const T g00 = Gs[a * kJgLd + bb], g01 = Gs[a * kJgLd + qb];
-      const T g10 = Gs[qa * kJgLd + bb], g11 = Gs[qa * kJgLd + qb];
-      const T ca = lane_read<T>(cb, a), sa = lane_read<T>(sb, a);
-      const T h00 = ca * g00 - sa * g10, h01 = ca * g01 - sa * g11;
-      const T h10 = sa * g00 + ca * g10, h11 = sa * g01 + ca * g11;
-      T n00 = cb * h00 - sb * h01, n01 = sb * h00 + cb * h01;
-      T n10 = cb * h10 - sb * h11, n11 = sb * h10 + cb * h11;
-      if (a == bb && rel > 0.f) {
-        n01 = (T)0;
-        n10 = (T)0;
-        rho = fmaxf(rho, rel);
-      }
-      Gd[a * kJgLd + bb] = n00; Gd[a * kJgLd + qb] = n01;
-      Gd[qa * kJgLd + bb] = n10; Gd[qa * kJgLd + qb] = n11;
-      if (a == 0) {
-        CS[(r * 16 + bb) * 2] = cb;
-        CS[(r * 16 + bb) * 2 + 1] = sb;
-      }
-    } else if (tid < 768 && r > 0) {
-      rotate_t(r - 1);
+      task = go ? ticket : -1;
+      rotations = 0;
     }
     __syncthreads();
-  }
-  if (tid >= 256 && tid < 768) rotate_t(b - 1);
-  if (rho > 0.f) atomicMax(&rotations, __float_as_int(rho));
-  __syncthreads();
-  const int rho_bits = rotations;
-  if (rho_bits == 0) {                                        // nothing changed: leave M alone, no T to apply
-    if (tid == 0) chg[slot * nblk + blockIdx.x] = 0;
-    return;
-  }
-  const T *Tf = Tb[b & 1];                                    // T[k][j]
-  // panel out: (P T)^T = T^T P^T in 16 x 16 blocks; wavefront w takes the output columns jb * 16 ... and the row
-  // blocks rb, rb + 8, ..., two of them at a time
-  {
-    const int jb = wave & 1;
-    T ta[kJgN / 4];
+    if (task < 0) return;
+    const int n = task / pairs, g = task - n * pairs;
+    const int sweep = n / steps_per_sweep, round = n - sweep * steps_per_sweep;
+    const JbPair pr = jb_pair(1, round, g, l, b, nblk);
+    const int cols_i = pr.cols_i, cols_j = pr.cols_j;
+    const int intra = (round == 0) ? b - 1 : 0;
+    const int rounds = intra + (pr.valid ? b : 0);
+    auto gcol = [&](int c) { return c < b ? pr.bi * b + c : pr.bj * b + (c - b); };      // global column of panel column c
+    auto live = [&](int c) { return c < b ? c < cols_i : c - b < cols_j; };
+    int rho_bits = 0;
+    if (rounds > 0) {                                            // (a bye only passes its block on)
+      // panel in: wavefront w takes columns w and w + 16, every load in flight before the first LDS store
+      {
+        constexpr int MAXJ = jg_max_order<T>() / 64;
+        T v[2][MAXJ];
 #pragma unroll
-    for (int ks = 0; ks < kJgN / 4; ++ks) ta[ks] = Tf[(4 * ks + kq) * kJgLd + jb * 16 + r16];     // A[i = column][k] = T[k][column]
-    const int nrb = lp / 16;
-    for (int rb = wave >> 1; rb < nrb; rb += 16) {
-      const int rb2 = rb + 8;
-      const bool two = rb2 < nrb;
-      const T *bp0 = Pc + kq * ldp + rb * 16 + r16;                                              // B[k][n = row] = P[row][k]
-      const T *bp1 = Pc + kq * ldp + (two ? rb2 : rb) * 16 + r16;
-      T b0[kJgN / 4], b1[kJgN / 4];
+        for (int u = 0; u < 2; ++u) {
+          const int c = wave + 16 * u;
+          const T *src = Mt + (int64_t)gcol(live(c) ? c : 0) * l;
 #pragma unroll
-      for (int ks = 0; ks < kJgN / 4; ++ks) { b0[ks] = bp0[(4 * ks) * ldp]; b1[ks] = bp1[(4 * ks) * ldp]; }
-      acc_t acc0 = (acc_t)(T)0, acc1 = (acc_t)(T)0;
+          for (int j = 0; j < MAXJ; ++j) {
+            const int rr = lane + 64 * j;
+            v[u][j] = (T)0;
+            if (live(c) && rr < l) v[u][j] = device_load(src + rr);
+          }
+        }
 #pragma unroll
-      for (int ks = 0; ks < kJgN / 4; ++ks) {
-        acc0 = Mfma<T>::run(ta[ks], b0[ks], acc0);
-        acc1 = Mfma<T>::run(ta[ks], b1[ks], acc1);
+        for (int u = 0; u < 2; ++u) {
+          const int c = wave + 16 * u;
+#pragma unroll
+          for (int j = 0; j < MAXJ; ++j) {
+            const int rr = lane + 64 * j;
+            if (rr < lp) Pc[c * ldp + rr] = v[u][j];
+          }
+        }
       }
+      __syncthreads();
+
+      // G = P^T P (symmetric: blocks (0,0), (0,1) and (1,1) only, five row slices each, fifteen wavefronts): a lane reads
+      // 16 bytes down a column, which are the operands of two (fp64) or four matrix instructions, four such pieces ahead;
+      // two accumulators
+      {
+        typedef T piece __attribute__((ext_vector_type(16 / sizeof(T))));
+        constexpr int V = 16 / (int)sizeof(T);
+        const int sl = wave / 3, tile = wave - 3 * sl;
+        const int ti = tile >> 1, tj = (tile + 1) >> 1;
+        const int steps = lp / (4 * V), per = (steps + 4) / 5;
+        const int s0 = sl * per, s1 = (wave == 15) ? 0 : ((s0 + per < steps) ? s0 + per : steps);
+        acc_t acc0 = (acc_t)(T)0, acc1 = (acc_t)(T)0;
+        const piece *ap = reinterpret_cast<const piece *>(Pc + (ti * 16 + r16) * ldp + kq * V);
+        const piece *bp = reinterpret_cast<const piece *>(Pc + (tj * 16 + r16) * ldp + kq * V);
+        for (int st = s0; st < s1; st += 4) {
+          piece av[4], bv[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int c = jb * 16 + Mfma<T>::row(lane, v);
-        if (live(c)) {
-          T *dst = Mt + (int64_t)gcol(c) * l;
-          if (rb * 16 + r16 < l) dst[rb * 16 + r16] = acc0[v];
-          if (two && rb2 * 16 + r16 < l) dst[rb2 * 16 + r16] = acc1[v];
+          for (int u = 0; u < 4; ++u) {
+            av[u] = (piece)(T)0;
+            bv[u] = (piece)(T)0;
+            if (st + u < s1) {
+              av[u] = ap[4 * (st + u)];
+              bv[u] = bp[4 * (st + u)];
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (st + u < s1) {
+#pragma unroll
+              for (int x = 0; x < V; x += 2) {
+                acc0 = Mfma<T>::run(av[u][x], bv[u][x], acc0);
+                acc1 = Mfma<T>::run(av[u][x + 1], bv[u][x + 1], acc1);
+              }
+            }
+        }
+        if (wave < 15) {
+          T *dst = R4 + sl * kJgPart + tile * 256;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) dst[Mfma<T>::row(lane, v) * 16 + r16] = acc0[v] + acc1[v];
+        }
+      }
+      __syncthreads();
+      {
+        // entry (i, j) of G from the five partial sums of its block (the block above the diagonal read transposed below it)
+        const int i = tid >> 5, j = tid & 31;
+        const int bi2 = i >> 4, bj2 = j >> 4;
+        const bool lower = bi2 > bj2;
+        const int tile = lower ? 1 : bi2 + bj2;
+        const int e = tile * 256 + (lower ? (j & 15) * 16 + (i & 15) : (i & 15) * 16 + (j & 15));
+        G0[i * kJgLd + j] =
+            ((R4[e] + R4[kJgPart + e]) + (R4[2 * kJgPart + e] + R4[3 * kJgPart + e])) + R4[4 * kJgPart + e];
+      }
+      __syncthreads();
+      // The rounds.  Wavefronts 0-3 (one per SIMD; what bounds a round is the number of instructions they issue, one every
+      // four cycles): G <- J^T G J, thread (a, bb) the rows of pair a and the columns of pair bb; every lane works out the
+      // rotation of pair bb, and the first sixteen leave (c, s) of the round in LDS.  Wavefronts 4-11: T <- T J one round
+      // behind, thread (rr, bb) row rr and the columns of pair bb.  One barrier per round (G and T alternate between two
+      // copies).
+      float rho = 0.f;
+      auto run_rounds = [&](auto kind, int r0, int count) {        // rounds r0, ... of the task
+        constexpr bool INTRA = decltype(kind)::value;
+        if (wave < 4) {
+          // lane 0 of a row of 16 lanes holds pair bb = a, whose rotation it hands to the others
+          const int a = tid >> 4, bb = (tid + a) & 15;
+          int pa, qa, mpa, mqa, pb, qb, mpb, mqb;
+          jg_pair<INTRA>(a, pa, qa, mpa, mqa);
+          jg_pair<INTRA>(bb, pb, qb, mpb, mqb);
+          T *cs = CS + bb * 2;
+          for (int r = 0; r < count; ++r) {
+            const int odd = (r0 + r) & 1;                          // (offsets: a choice between pointers into LDS makes flat accesses)
+            const T *Gs = G0 + odd * (3 * kJgMat);
+            T *Gd = G0 + (odd ^ 1) * (3 * kJgMat);
+            T cb, sb;
+            const T g00 = Gs[pa * kJgLd + pb], g01 = Gs[pa * kJgLd + qb];
+            const T g10 = Gs[qa * kJgLd + pb], g11 = Gs[qa * kJgLd + qb];
+            const float rel = jg_pair_params<T>(Gs, pb, qb, tol, floor2, cb, sb);
+            const T ca = dpp_mov<0x150>(cb), sa = dpp_mov<0x150>(sb);          // row_newbcast:0
+            const T h00 = ca * g00 - sa * g10, h01 = ca * g01 - sa * g11;
+            const T h10 = sa * g00 + ca * g10, h11 = sa * g01 + ca * g11;
+            T n00 = cb * h00 - sb * h01, n01 = sb * h00 + cb * h01;
+            T n10 = cb * h10 - sb * h11, n11 = sb * h10 + cb * h11;
+            if (a == bb && rel > 0.f) {
+              n01 = (T)0;
+              n10 = (T)0;
+              rho = fmaxf(rho, rel);
+            }
+            Gd[mpa * kJgLd + mpb] = n00; Gd[mpa * kJgLd + mqb] = n01;
+            Gd[mqa * kJgLd + mpb] = n10; Gd[mqa * kJgLd + mqb] = n11;
+            if (a == 0) {
+              cs[r * 32] = cb;
+              cs[r * 32 + 1] = sb;
+            }
+            __syncthreads();
+          }
+          __syncthreads();
+        } else {
+          const int rr = (tid - 256) >> 4, bb = tid & 15;
+          int pb, qb, mpb, mqb;
+          jg_pair<INTRA>(bb, pb, qb, mpb, mqb);
+          const T *cs = CS + bb * 2;
+          for (int r = -1; r < count; ++r) {                       // T <- T J_r, one round behind
+            if (r >= 0 && wave < 12) {
+              const int odd = (r0 + r) & 1;
+              const T *Ts = R4 + odd * kJgMat + rr * kJgLd;
+              T *Td = R4 + (odd ^ 1) * kJgMat + rr * kJgLd;
+              const T cb = cs[r * 32], sb = cs[r * 32 + 1];
+              T tp = Ts[pb], tq = Ts[qb];
+              if (r0 + r == 0) {                                   // (T is the identity)
+                tp = rr == pb ? (T)1 : (T)0;
+                tq = rr == qb ? (T)1 : (T)0;
+              }
+              Td[mpb] = cb * tp - sb * tq;
+              Td[mqb] = sb * tp + cb * tq;
+            }
+            __syncthreads();
+          }
+        }
+      };
+      if (round == 0) run_rounds(JbKind<true>(), 0, intra);
+      if (pr.valid) run_rounds(JbKind<false>(), intra, b);
+      if (rho > 0.f) atomicMax(&rotations, __float_as_int(rho));
+      __syncthreads();
+      rho_bits = rotations;
+    }
+
+    const T *Tf = R4 + (rounds & 1) * kJgMat;                              // T[k][j]
+    if (rho_bits != 0) {
+      // panel out: (P T)^T = T^T P^T in 16 x 16 blocks; wavefront w takes the output columns jb * 16 ... and the row
+      // blocks rb, rb + 8, ..., two of them at a time
+      const int jb = wave & 1;
+      T ta[kJgN / 4];
+#pragma unroll
+      for (int ks = 0; ks < kJgN / 4; ++ks) ta[ks] = Tf[(4 * ks + kq) * kJgLd + jb * 16 + r16];     // A[i = column][k] = T[k][column]
+      const int nrb = lp / 16;
+      for (int rb = wave >> 1; rb < nrb; rb += 16) {
+        const int rb2 = rb + 8;
+        const bool two = rb2 < nrb;
+        const T *bp0 = Pc + kq * ldp + rb * 16 + r16;                                              // B[k][n = row] = P[row][k]
+        const T *bp1 = Pc + kq * ldp + (two ? rb2 : rb) * 16 + r16;
+        T b0[kJgN / 4], b1[kJgN / 4];
+#pragma unroll
+        for (int ks = 0; ks < kJgN / 4; ++ks) { b0[ks] = bp0[(4 * ks) * ldp]; b1[ks] = bp1[(4 * ks) * ldp]; }
+        acc_t acc0 = (acc_t)(T)0, acc1 = (acc_t)(T)0;
+#pragma unroll
+        for (int ks = 0; ks < kJgN / 4; ++ks) {
+          acc0 = Mfma<T>::run(ta[ks], b0[ks], acc0);
+          acc1 = Mfma<T>::run(ta[ks], b1[ks], acc1);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int c = jb * 16 + Mfma<T>::row(lane, v);
+          if (live(c)) {
+            T *dst = Mt + (int64_t)gcol(c) * l;
+            if (rb * 16 + r16 < l) device_store(dst + rb * 16 + r16, acc0[v]);
+            if (two && rb2 * 16 + r16 < l) device_store(dst + rb2 * 16 + r16, acc1[v]);
+          }
         }
       }
     }
-  }
-  T *Tg = Tring + ((size_t)slot * nblk + blockIdx.x) * (size_t)(4 * b * b);
-  {
-    // ring format: Tg[c * 2b + k] = T[k][c] over the live columns, packed (those of the first block, then the second)
-    const int c = tid >> 5, k = tid & 31;
-    auto unpack = [&](int x) { return x < cols_i ? x : b + (x - cols_i); };
-    T val = (T)0;
-    if (c < ncols && k < ncols) val = Tf[unpack(k) * kJgLd + unpack(c)];
-    else if (c == k) val = (T)1;
-    Tg[c * (2 * b) + k] = val;
-  }
-  if (tid == 0) {
-    chg[slot * nblk + blockIdx.x] = 1;
-    atomicMax(&hdr->counters[sweep], rho_bits);
+    device_stores_done();
+    __syncthreads();
+    if (tid == 0) {
+      device_store(ver + pr.bi, n + 1);
+      if (pr.valid) device_store(ver + pr.bj, n + 1);
+      if (rho_bits != 0) atomicMax(&hdr->counters[sweep], rho_bits);
+      device_stores_done();                                      // (counters before finished)
+      atomicAdd(&hdr->finished[sweep], 1);
+      ticket = atomicAdd(&hdr->ticket, 1);
+      // J: the same two blocks of columns, after the step before
+      int *verj = ver + nblk;
+      (void)jb_wait(verj + pr.bi, verj + (pr.valid ? pr.bj : pr.bi), n, nullptr);
+    }
+    __syncthreads();
+    if (rho_bits != 0) {
+      // wavefront w takes the row blocks w, w + 16, ...: it reads both blocks of columns before it writes either
+      T ta[2][kJgN / 4];
+#pragma unroll
+      for (int ks = 0; ks < kJgN / 4; ++ks) {
+        ta[0][ks] = Tf[(4 * ks + kq) * kJgLd + r16];
+        ta[1][ks] = Tf[(4 * ks + kq) * kJgLd + 16 + r16];
+      }
+      for (int rb = wave; rb < lp / 16; rb += 16) {
+        const int row = rb * 16 + r16;
+        T bv[kJgN / 4];
+#pragma unroll
+        for (int ks = 0; ks < kJgN / 4; ++ks) {
+          const int c = 4 * ks + kq;
+          bv[ks] = (T)0;
+          if (live(c) && row < l) bv[ks] = device_load(Jt + (int64_t)gcol(c) * l + row);
+        }
+        acc_t acc[2] = {(acc_t)(T)0, (acc_t)(T)0};
+#pragma unroll
+        for (int ks = 0; ks < kJgN / 4; ++ks) {
+          acc[0] = Mfma<T>::run(ta[0][ks], bv[ks], acc[0]);
+          acc[1] = Mfma<T>::run(ta[1][ks], bv[ks], acc[1]);
+        }
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int c = jb * 16 + Mfma<T>::row(lane, v);
+            if (live(c) && row < l) device_store(Jt + (int64_t)gcol(c) * l + row, acc[jb][v]);
+          }
+      }
+    }
+    device_stores_done();
+    __syncthreads();
+    if (tid == 0) {
+      device_store(ver + nblk + pr.bi, n + 1);
+      if (pr.valid) device_store(ver + nblk + pr.bj, n + 1);
+    }
   }
 }
 
@@ -1240,6 +1393,13 @@ size_t jacobi_scratch_bytes(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t l) {
          align_up(2 * nblk * sizeof(int), 256);
 }
 
+// The flow kernel is written for 16 columns to a block and holds the panel of a block pair in LDS; longer columns
+// are rotated in place by the panel kernel.
+template <typename T>
+static bool jb_takes_flow(const rsvd_ctx *ctx, int b, int l) {
+  return b == kJgB && l <= jg_max_order<T>() && jg_lds_bytes<T>(l) + 1024 <= ctx->lds_per_block;
+}
+
 template <typename T>
 static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int l, const double *M,
                                       T *sigma, T *X, T *W, DevInfo *info, char *scratch, int rows) {
@@ -1262,26 +1422,24 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
   const size_t lds_j = ((size_t)(2 * b) * (kJbRowChunk + 8) + (size_t)(2 * b) * (2 * b + 2)) * es;   // jb_apply_t
   const size_t lds = lds_rot > lds_j ? lds_rot : lds_j;
   const int chunks = (l + kJbRowChunk - 1) / kJbRowChunk;
-  // cross launches go through the Gram matrix of the block pair when its panel of 2b columns fits in LDS
-  const bool gram_cross = b == kJgB && jg_lds_bytes<T>(l) + 1024 <= ctx->lds_per_block;
-  const size_t lds_gram = jg_lds_bytes<T>(l) > lds_j ? jg_lds_bytes<T>(l) : lds_j;
   ProfScope ps(ctx, s, PK_JACOBI);
   hipLaunchKernelGGL(jb_fro_kernel, dim3(kJbFroParts), dim3(256), 0, s, M, l, hdr);
   {
     int64_t blocks = ((int64_t)l * l + 255) / 256;
     if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL((jb_init_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, s, M, l, Mt, Jt, hdr, rows);
+    hipLaunchKernelGGL((jb_init_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, s, M, l, Mt, Jt, hdr, rows, chg,
+                       2 * nblk);
   }
+  if (jb_takes_flow<T>(ctx, b, l)) {
+    hipLaunchKernelGGL((jb_flow_kernel<T>), dim3(nblk2), dim3(1024), jg_lds_bytes<T>(l), s, Mt, Jt, l, nblk,
+                       kJbMaxSweeps, chg, hdr);
+  } else {
 #define RSVD_JB_CASE(NVV)                                                                                        \
   case NVV: {                                                                                                    \
     int slot = 0, pp = -1, pr = 0, psw = 0, pwgs = 0;          /* the launch before: phase, round, sweep, pairs */ \
     auto go = [&](int phase, int round, int sweep, int wgs) {                                                    \
-      if (phase == 1 && wgs > 0 && gram_cross)                                                                   \
-        hipLaunchKernelGGL((jb_cross_kernel<T>), dim3(wgs + pwgs * chunks), dim3(1024), lds_gram, s, Mt, Jt, l,  \
-                           nblk, round, sweep, wgs, pp, pr, psw, Tring, chg, slot, hdr);                         \
-      else                                                                                                       \
-        hipLaunchKernelGGL((jb_panel_kernel<T, NVV>), dim3(wgs + pwgs * chunks), dim3(1024), lds, s, Mt, Jt, l,  \
-                           b, nblk, phase, round, sweep, wgs, pp, pr, psw, Tring, chg, slot, hdr);               \
+      hipLaunchKernelGGL((jb_panel_kernel<T, NVV>), dim3(wgs + pwgs * chunks), dim3(1024), lds, s, Mt, Jt, l,    \
+                         b, nblk, phase, round, sweep, wgs, pp, pr, psw, Tring, chg, slot, hdr);                 \
       pp = phase; pr = round; psw = sweep; pwgs = wgs; slot ^= 1;                                                \
     };                                                                                                           \
     for (int sweep = 0; sweep < kJbMaxSweeps; ++sweep) {                                                         \
@@ -1290,13 +1448,12 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
     }                                                                                                            \
     go(0, 0, kJbMaxSweeps, 0);                                 /* applies the T of the last round */            \
   } break
-  switch (nv) {
-    RSVD_JB_CASE(2); RSVD_JB_CASE(3); RSVD_JB_CASE(4); RSVD_JB_CASE(5); RSVD_JB_CASE(6); RSVD_JB_CASE(7);
-    RSVD_JB_CASE(8); RSVD_JB_CASE(9); RSVD_JB_CASE(10); RSVD_JB_CASE(12); RSVD_JB_CASE(14); RSVD_JB_CASE(16);
-    RSVD_JB_CASE(18); RSVD_JB_CASE(20); RSVD_JB_CASE(24);
-    default: return hipErrorNotSupported;
-  }
+    switch (nv) {                                              // (smaller orders take the flow kernel)
+      RSVD_JB_CASE(14); RSVD_JB_CASE(16); RSVD_JB_CASE(18); RSVD_JB_CASE(20); RSVD_JB_CASE(24);
+      default: return hipErrorNotSupported;
+    }
 #undef RSVD_JB_CASE
+  }
   hipLaunchKernelGGL((jb_norms_kernel<T>), dim3((l + 3) / 4), dim3(256), 0, s, Mt, l, nrm);
   hipLaunchKernelGGL((jb_rank_kernel<T>), dim3((l + 255) / 256), dim3(256), 0, s, nrm, l, rnk, sigma, hdr,
                      kJbMaxSweeps, info);
@@ -1368,10 +1525,7 @@ static void raise_lds_limit_panel(hipError_t &e) {
 }
 template <typename T>
 static void raise_lds_limit_panels(hipError_t &e) {
-  raise_lds_limit_panel<T, 2>(e); raise_lds_limit_panel<T, 3>(e); raise_lds_limit_panel<T, 4>(e);
-  raise_lds_limit_panel<T, 5>(e); raise_lds_limit_panel<T, 6>(e); raise_lds_limit_panel<T, 7>(e);
-  raise_lds_limit_panel<T, 8>(e); raise_lds_limit_panel<T, 9>(e); raise_lds_limit_panel<T, 10>(e);
-  raise_lds_limit_panel<T, 12>(e); raise_lds_limit_panel<T, 14>(e); raise_lds_limit_panel<T, 16>(e);
+  raise_lds_limit_panel<T, 14>(e); raise_lds_limit_panel<T, 16>(e);
   raise_lds_limit_panel<T, 18>(e); raise_lds_limit_panel<T, 20>(e); raise_lds_limit_panel<T, 24>(e);
 }
 
@@ -1391,10 +1545,10 @@ hipError_t jacobi_init_device(rsvd_ctx *ctx) {
   raise_lds_limit_panels<float>(e);
   raise_lds_limit_panels<double>(e);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&jb_cross_kernel<float>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&jb_flow_kernel<float>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&jb_cross_kernel<double>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&jb_flow_kernel<double>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
   return e;
 }

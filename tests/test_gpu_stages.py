@@ -232,6 +232,50 @@ def test_jacobi_matches_oracle(dt, l):
         assert np.abs(np.abs(np.sum(W * Wo, axis=0)) - 1).max() <= min(0.1, tol)
 
 
+# One task per block pair of 16-column blocks: the smallest orders, an odd number of blocks (one sits out every step), a last block of
+# one and of fifteen columns, the longest columns that the panel in LDS holds and the first order beyond it (column by column).
+@pytest.mark.parametrize("dt,l", [("f64", 97), ("f64", 113), ("f64", 127), ("f64", 464), ("f64", 465), ("f32", 129), ("f32", 145),
+                                  ("f32", 255), ("f32", 1088), ("f32", 1089)])
+def test_block_jacobi_edges(dt, l):
+    say("block jacobi", dt, l)
+    M = workloads.graded_matrix(l, l, 1e3, seed=l, dtype=NPDT[dt])
+    M[:, 3] = 0                                   # a column that is never rotated
+    c = ctx()
+    sig, X, W, info = c.rsvd_stage_jacobi(to_dev(M))
+    assert info.status == 0 and info.jacobi_sweeps <= 20
+    again = c.rsvd_stage_jacobi(to_dev(M))        # whichever workgroup took which task
+    for a, b in zip((sig, X, W), again[:3]):
+        assert np.array_equal(to_np(a), to_np(b))
+    sig, X, W = (to_np(t).astype(np.float64) for t in (sig, X, W))
+    _svd_check(sig, X, W, M.astype(np.float64), dt, "graded")
+    # each of the l columns of W has length 1 up to a random walk of ~20 l roundings
+    eps = np.finfo(NPDT[dt]).eps
+    assert np.abs(np.linalg.norm(W, axis=0) - 1).max() <= 4 * eps * np.sqrt(20 * l)
+
+
+def test_block_jacobi_on_two_streams():
+    """Two decompositions share the chip: neither waits for workgroups of its own that are not running yet."""
+    import torch
+    say("block jacobi on two streams")
+    M = [to_dev(workloads.gaussian_matrix(288, 288, 70 + i)) for i in range(2)]
+    c = [ctx(), type(ctx())()]
+    want = [c[0].rsvd_stage_jacobi(m.clone())[:3] for m in M]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    got = [[], []]
+    args = [[m.clone() for _ in range(3)] for m in M]
+    torch.cuda.synchronize()
+    for rep in range(3):
+        for i in range(2):
+            with torch.cuda.stream(streams[i]):
+                got[i].append(c[i].rsvd_stage_jacobi(args[i][rep])[:3])
+    torch.cuda.synchronize()
+    for i in range(2):
+        for g in got[i]:
+            for a, b in zip(g, want[i]):
+                assert np.array_equal(to_np(a), to_np(b))
+
+
 @pytest.mark.parametrize("dt", ["f32", "f64"])
 def test_jacobi_special_matrices(dt):
     say("jacobi special", dt)
