@@ -10,6 +10,7 @@
 // orthonormal basis that contains range(Y).
 #include "common.hpp"
 #include "mfma.hpp"
+#include "philox_dev.hpp"
 
 namespace rsvd {
 
@@ -77,6 +78,9 @@ template <int NB> struct CholLds {
 //   thr  : lane c holds tau * (reference squared norm of column c); pos: bit c set when that norm is > 0
 //          (and not below the caller's absolute floor)
 //   piv  : 16 doubles of LDS scratch
+//   cols : pivots from here on are padding, which is the identity, and are left out four at a time (0.2 us each; asked for
+//          one by one, the branches cost the chain 0.1 us a pivot).  16 in the kernel for larger orders: no gain was
+//          seen there.
 //   raise: a pivot at or below its threshold (with a usable reference norm) does not drop its column but SETS IT
 //          ASIDE: the pivot takes the value of the threshold, the row is not used to eliminate anything (its
 //          part of R is the diagonal element alone), so the column comes out of Q = Y R^-1 as what is left of it
@@ -86,17 +90,20 @@ template <int NB> struct CholLds {
 //          inverse overflowed on a sketch with ~100 such rows)
 //   returns the 16-bit mask of dropped (dependent) columns, and in bits 16..31 that of the columns set aside
 __device__ __forceinline__ unsigned diag_factor(f64x4 &dblk, f64x4 &z, double thr, unsigned pos, int lane,
-                                                double *piv, bool raise) {
+                                                double *piv, bool raise, int cols) {
   const int lr = lane >> 4, lc = lane & 15;
   double mrow[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) mrow[q] = (lr == q) ? 1.0 : 0.0;
 #pragma unroll
   for (int v = 0; v < 4; ++v) z[v] = (4 * v + lr == lc) ? 1.0 : 0.0;
-  f64x4 sd = {0.0, 0.0, 0.0, 0.0}, sz = {0.0, 0.0, 0.0, 0.0};
+  f64x4 sd, sz;                             // (rows of the padding: those of the identity, as they come in)
+#pragma unroll
+  for (int v = 0; v < 4; ++v) sd[v] = sz[v] = (4 * v + lr == lc && 4 * v >= cols) ? 1.0 : 0.0;
   unsigned dmask = 0, wmask = 0;
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
+    if (j % 4 == 0 && j >= cols) break;
     const int q = j & 3, v4 = j >> 2;
     double rowv = dblk[v4];
     const double d = readlane_f64(rowv, 16 * q + j);            // pivot S[j][j]
@@ -237,7 +244,7 @@ __global__ __launch_bounds__(NB * 64) void chol_mfma_kernel(const double *__rest
     const unsigned pos = (unsigned)__ballot(d0c > 0.0 && d0c >= floor_abs) & 0xffffu;
     // pivot threshold: tau times the column's reference norm, or the same for every column (abs_thr > 0:
     // rounds that work on a panel whose resolved columns have unit length)
-    const unsigned masks = diag_factor(dblk, z, abs_thr > 0.0 ? abs_thr : tau * d0c, pos, lane, piv, raise != 0);
+    const unsigned masks = diag_factor(dblk, z, abs_thr > 0.0 ? abs_thr : tau * d0c, pos, lane, piv, raise != 0, 16);
     const unsigned dmask = masks & 0xffffu, wmask = masks >> 16;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -375,6 +382,196 @@ __global__ __launch_bounds__(NB * 64) void chol_mfma_kernel(const double *__rest
       else if (n_weak > 0) *redo_skip = 0;
     }
   }
+}
+
+// ---------------------------------------------------------------- small fp32 panels: every round in one workgroup
+//
+// A panel of up to 16 columns that fits in LDS: all CholeskyQR rounds of a call (Gram matrix, factor and inverse, apply, the
+// product of the triangular factors) in one workgroup, the panel in LDS from the first to the last.  As separate
+// kernels a round is three or four launches of 3 to 8 us that wait for each other.  What bounds it is the chain of pivots in
+// one wavefront (diag_factor).  Arithmetic and rules are those of the separate kernels: Gram matrix and factor in fp64, R^-1
+// rounded to fp32, the apply in fp32.  Singular values of a 300 x 200 matrix, l = 16, one power iteration: 148 -> 117 us.
+// (Tried for 17 to 32 columns, where the second pivot block doubles the chain: 700 x 500, l = 32, 293 -> 347 us; for fp64
+// panels, whose matrix instructions and replacement columns are too much for one CU: 512 x 256, l = 20, 506 -> 535 us.)
+struct PanelParams {
+  int rows, l, ldy;
+  const float *src; int64_t ld_src;
+  float *dst; int64_t ld_dst;
+  int rounds;
+  double tau;
+  uint64_t seed; uint32_t refill_stream; double refill_scale;
+  float *Rinv; double *R1;                // R^-1 of the last round, R of the first (NULL: not wanted), ld l
+  double *Rout;                           // product of all factors, ld l, or NULL
+  DevInfo *info;
+  const int *skip_flag;
+};
+constexpr int kPanelThreads = 512;        // (1024: the factoring wavefront has half the registers and its chain spills, 2x slower)
+constexpr int kPanelMat = 16 * 17;
+constexpr size_t kPanelFixed = (8 * 256 + 256 + 16 + 3 * kPanelMat) * sizeof(double);
+
+__global__ __launch_bounds__(kPanelThreads) void panel_qr_kernel(const PanelParams P) {
+  constexpr int LD = 17, NT = kPanelThreads;
+  if (P.skip_flag != nullptr && *P.skip_flag != 0) return;
+  extern __shared__ double smem[];
+  double *part = smem;                           // [wavefront][256]
+  double *Gt = part + 8 * 256;                   // the Gram matrix
+  double *piv = Gt + 256;
+  double *Rl = piv + 16, *Ra = Rl + kPanelMat;   // the factor of this round, the product so far
+  float *Xl = reinterpret_cast<float *>(Ra + kPanelMat);                        // R^-1
+  float *Y = reinterpret_cast<float *>(smem + kPanelFixed / sizeof(double));    // [rows16][ldy]
+  __shared__ unsigned dead_sh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane >> 4, lc = lane & 15;
+  const int rows = P.rows, l = P.l, ldy = P.ldy, rows16 = (rows + 15) & ~15;
+
+  for (int e0 = tid; e0 < rows16 * l; e0 += 8 * NT) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int e = e0 + NT * u, r = e / l, c = e - r * l;
+      v[u] = r < rows ? P.src[(int64_t)r * P.ld_src + c] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int e = e0 + NT * u, r = e / l, c = e - r * l;
+      if (r < rows16) Y[r * ldy + c] = v[u];
+    }
+  }
+  int refilled = 0, bad = 0;
+  for (int round = 0; round < P.rounds; ++round) {
+    __syncthreads();
+    // ---- Gram matrix: the wavefronts share the rows
+    {
+      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      const float *y = Y + lr * ldy + (lc < l ? lc : 0);
+      for (int s0 = wave; s0 < rows16 / 4; s0 += 4 * 8) {
+        double a[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int s = s0 + u * 8;
+          a[u] = (s < rows16 / 4 && lc < l) ? (double)y[4 * s * ldy] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc = Mfma<double>::run(a[u], a[u], acc);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) part[wave * 256 + (4 * v + lr) * 16 + lc] = acc[v];
+    }
+    __syncthreads();
+    if (tid < 256) {
+      double sum = part[tid];
+#pragma unroll
+      for (int w = 1; w < 8; ++w) sum += part[w * 256 + tid];
+      Gt[tid] = sum;
+    }
+    __syncthreads();
+    // ---- factor and inverse (wavefront 0); the padding of the Gram matrix is the identity
+    if (wave == 0) {
+      f64x4 d, z;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        d[v] = Gt[(4 * v + lr) * 16 + lc];
+        if (4 * v + lr == lc && lc >= l) d[v] = 1.0;
+      }
+      const double d0 = lc < l ? Gt[lc * 17] : 1.0;
+      if (__ballot(!(fabs(d0) <= 1.79e308))) bad = 1;
+      const unsigned pos = (unsigned)__ballot(d0 > 0.0) & 0xffffu;
+      const unsigned dead = diag_factor(d, z, P.tau * d0, pos, lane, piv, false, l) & ((1u << l) - 1u);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = 4 * v + lr;
+        Rl[row * LD + lc] = lc >= row ? d[v] : 0.0;
+        Xl[lc * LD + row] = lc <= row ? (float)z[v] : 0.f;       // R^-1 = Z^T
+      }
+      refilled += __popc(dead);
+      if (lane == 0) dead_sh = dead;
+    }
+    __syncthreads();
+    const unsigned dead = dead_sh;
+    // ---- the factors that the caller wants
+    if (tid < l * l) {
+      const int i = tid / l, j = tid - i * l;
+      if (P.Rinv != nullptr) P.Rinv[tid] = Xl[i * LD + j];
+      if (P.R1 != nullptr && round == 0) P.R1[tid] = Rl[i * LD + j];
+    }
+    if (P.Rout != nullptr) {
+      // Ra <- Rl Ra, row sums in ascending order
+      const int i = tid >> 4, j = tid & 15;
+      double acc = 0.0;
+      if (tid < 256) {
+        if (round == 0) acc = Rl[i * LD + j];
+        else
+          for (int t = i; t <= j; ++t) acc = fma(Rl[i * LD + t], Ra[t * LD + j], acc);
+      }
+      __syncthreads();
+      if (tid < 256) Ra[i * LD + j] = acc;
+    }
+    // ---- apply: a wavefront takes 16 rows at a time; they are its own, so the result replaces them
+    float b[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) b[s] = Xl[(4 * s + lr) * LD + lc];
+    for (int t = wave; t < rows16 / 16; t += NT / 64) {
+      const float *row = Y + (16 * t + lc) * ldy;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      float a[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) a[s] = (4 * s + lr < l) ? row[4 * s + lr] : 0.f;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc = Mfma<float>::run(a[s], b[s], acc);
+      if (lc < l) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Y[(16 * t + Mfma<float>::row(lane, v)) * ldy + lc] = acc[v];
+      }
+    }
+    // ---- replacement columns: their elements shared out evenly over all threads
+    if (dead != 0u) {
+      __syncthreads();
+      const int nf = __popc(dead);
+      for (int e = tid; e < rows * nf; e += NT) {
+        const int r = e / nf;
+        unsigned left = dead;
+        for (int i = e - r * nf; i > 0; --i) left &= left - 1u;
+        const int c = __ffs(left) - 1;
+        Y[r * ldy + c] = (float)(P.refill_scale * philox_normal_at<true>((uint64_t)((int64_t)r * l + c),
+                                                                      P.refill_stream + (uint32_t)round, P.seed));
+      }
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < rows * l; e += NT) {
+    const int r = e / l, c = e - r * l;
+    P.dst[(int64_t)r * P.ld_dst + c] = Y[r * ldy + c];
+  }
+  if (P.Rout != nullptr && tid < l * l) P.Rout[tid] = Ra[(tid / l) * LD + tid % l];
+  if (tid == 0 && P.info != nullptr) {
+    if (refilled > 0) atomicAdd(&P.info->refilled, refilled);
+    if (bad) atomicMax(&P.info->status, (int)RSVD_ERR_NONFINITE);
+  }
+}
+
+// Columns of a panel row in LDS, and what the whole takes.
+static int panel_ld(int64_t l) { return (int)align_up((size_t)l, 2) + 4; }
+static size_t panel_lds_bytes(int64_t rows, int64_t l) {
+  return kPanelFixed + align_up((size_t)rows, 16) * panel_ld(l) * sizeof(float);
+}
+
+// One fp32 problem (the workgroups of a batch fill the chip as separate kernels) of up to 16 columns and 1024 rows: a
+// 600 x 600 call with l = 8 takes 208 -> 178 us; with the panel of 1500 rows here as well, a 1500 x 300 one with l = 16 is no
+// faster than without (237, 218 us).
+bool panel_qr_takes(rsvd_dtype dtype, int64_t rows, int64_t l, int batch) {
+  return dtype == RSVD_F32 && batch == 1 && l <= 16 && rows <= 1024;
+}
+
+hipError_t panel_qr_launch(rsvd_ctx *ctx, hipStream_t s, const PanelQr &q) {
+  PanelParams P;
+  P.rows = (int)q.rows; P.l = (int)q.l; P.ldy = panel_ld(q.l);
+  P.src = q.src; P.ld_src = q.ld_src; P.dst = q.dst; P.ld_dst = q.ld_dst;
+  P.rounds = q.rounds; P.tau = q.tau;
+  P.seed = q.seed; P.refill_stream = q.refill_stream; P.refill_scale = 1.0 / sqrt((double)q.rows);
+  P.Rinv = q.Rinv; P.R1 = q.R1; P.Rout = q.Rout; P.info = q.info; P.skip_flag = q.skip_flag;
+  ProfScope ps(ctx, s, PK_CHOL);
+  hipLaunchKernelGGL(panel_qr_kernel, dim3(1), dim3(kPanelThreads), panel_lds_bytes(q.rows, q.l), s, P);
+  return hipGetLastError();
 }
 
 // First launch of a blocked factorisation: keeps the original diagonal for the pivot tests and arms the switch
@@ -599,6 +796,9 @@ hipError_t chol_init_device(rsvd_ctx *ctx) {
   (void)ctx;
   hipError_t e = chol_raise_lds_limits<float>();
   if (e == hipSuccess) e = chol_raise_lds_limits<double>();
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&panel_qr_kernel),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)panel_lds_bytes(1024, 16));
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tri_inverse_strip_kernel<6>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);

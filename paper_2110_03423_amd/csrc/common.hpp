@@ -177,6 +177,20 @@ hipError_t jacobi_init_device(rsvd_ctx *ctx);
 // l x l factor is at most `limit` and finite, else 0.  R fp64, Rinv in `dtype`, both l x l with ld l.
 // info (may be NULL): skipped_reorth is raised to the flag.
 // redo_skip (may be NULL; strided like the rest): when it reads 0 - the factorisation raised a pivot - the flag is 0.
+// All CholeskyQR rounds of one small fp32 panel in one launch (chol.hip).
+struct PanelQr {
+  int64_t rows = 0, l = 0;
+  const float *src = nullptr; int64_t ld_src = 0;
+  float *dst = nullptr; int64_t ld_dst = 0;
+  int rounds = 1;
+  double tau = 0.0;
+  uint64_t seed = 0; uint32_t refill_stream = 0;
+  float *Rinv = nullptr; double *R1 = nullptr, *Rout = nullptr;
+  DevInfo *info = nullptr; const int *skip_flag = nullptr;
+};
+bool panel_qr_takes(rsvd_dtype dtype, int64_t rows, int64_t l, int batch);
+hipError_t panel_qr_launch(rsvd_ctx *ctx, hipStream_t s, const PanelQr &q);
+
 hipError_t cond_flag_launch(hipStream_t s, rsvd_dtype dtype, int64_t l, const double *R, const void *Rinv,
                             double limit, int *flag, DevInfo *info, int batch = 1, int64_t stride = 0,
                             const int *redo_skip = nullptr);

@@ -289,6 +289,17 @@ static int orthonormalize(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, const 
     const double rel = 32.0 * 1.1920929e-07;           // 3.8e-6 of the column norm
     if (rel * rel > tau) tau = rel * rel;
   }
+  if (panel_qr_takes(dtype, rows, l, w.batch)) {
+    PanelQr pq;
+    pq.rows = rows; pq.l = l; pq.rounds = rounds; pq.tau = tau;
+    pq.src = (const float *)Y; pq.ld_src = ldy;
+    pq.dst = (float *)(rounds == 1 ? tmp : Y); pq.ld_dst = rounds == 1 ? l : ldy;
+    pq.seed = seed; pq.refill_stream = refill_stream;
+    if (keep_r) { pq.Rinv = w.at<float>(L.Rinv); pq.R1 = w.at<double>(L.R1); }
+    pq.Rout = Rout; pq.info = w.at<DevInfo>(L.info); pq.skip_flag = skip_flag;
+    RSVD_TRY(panel_qr_launch(ctx, s, pq), "panel");
+    return 0;
+  }
   const bool rescue = dtype == RSVD_F64;
   int *redo_skip = rescue ? w.at<int>(L.flags) + 1 : nullptr;      // 0 = the first round raised a pivot
   void *src = Y; int64_t lds_ = ldy;

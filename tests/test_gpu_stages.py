@@ -232,6 +232,29 @@ def test_jacobi_matches_oracle(dt, l):
         assert np.abs(np.abs(np.sum(W * Wo, axis=0)) - 1).max() <= min(0.1, tol)
 
 
+# Small fp32 panels are orthonormalised in one workgroup up to 16 columns and 1024 rows: one column, rows that are no multiple of
+# 16, the largest panel, the first ones beyond, and columns that depend on others (replaced, the same either way).
+@pytest.mark.parametrize("rows,l,rank", [(1, 1, 1), (17, 1, 1), (40, 16, 16), (333, 7, 7), (1024, 16, 16), (1025, 16, 16), (1024, 17, 17),
+                                         (500, 13, 9), (64, 16, 15)])
+def test_orthonormalize_small_panels(rows, l, rank):
+    say("small panel", rows, l, rank)
+    c = ctx()
+    Y = workloads.gaussian_matrix(rows, l, 3, np.float32)
+    Y[:, rank:] = Y[:, :l - rank]
+    D = to_dev(np.concatenate([Y, np.ones((rows, 3), np.float32)], axis=1))[:, :l]          # a leading dimension of l + 3
+    Q, R, info = c.rsvd_stage_orth(D, want_r=True)
+    Q, R = to_np(Q).astype(np.float64), to_np(R)
+    eps = np.finfo(np.float32).eps
+    assert info.status == 0 and info.refilled_columns >= l - rank
+    # Q^T Q: sums of `rows` products of entries rounded to eps, the rounding errors adding up like a random walk
+    assert np.abs(Q.T @ Q - np.eye(l)).max() <= 16 * eps * np.sqrt(l)
+    assert np.abs(np.tril(R, -1)).max(initial=0) == 0
+    # Y = Q R: a round is a product with R^-1 rounded to eps, l terms (condition below 10 here); what a dependent column leaves
+    # behind lies below the pivot threshold, 32 eps of its norm
+    norms = np.linalg.norm(Y, axis=0)
+    assert (np.linalg.norm(Q @ R - Y, axis=0) <= (64 * np.sqrt(l) * eps) * norms.max()).all()
+
+
 # One task per block pair of 16-column blocks: the smallest orders, an odd number of blocks (one sits out every step), a last block of
 # one and of fifteen columns, the longest columns that the panel in LDS holds and the first order beyond it (column by column).
 @pytest.mark.parametrize("dt,l", [("f64", 97), ("f64", 113), ("f64", 127), ("f64", 464), ("f64", 465), ("f32", 129), ("f32", 145),
