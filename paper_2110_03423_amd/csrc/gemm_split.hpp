@@ -3,8 +3,9 @@
 // An fp32 number is the exact sum of three bf16 numbers (x = h + m + t: 8 + 8 + 8 significand bits, each the
 // rounded rest of the ones before), so  a b = sum of nine bf16 products, of which the six of order 2^-16 and above are
 // taken (hh, hm, mh, mm, ht, th); what is left out, mt + tm + tt, is below 2^-25 |a b|, half a unit of the last place
-// of an fp32 product.  The products are exact in the matrix instruction and summed in fp32, one accumulator per
-// element of C as in the fp32 instruction, but with an eighth of the accumulation steps.  A 16x16x32 bf16
+// of an fp32 product.  The products are exact in the matrix instruction and summed in fp32, with an eighth of the
+// accumulation steps of the fp32 instruction: the leading products in one accumulator per element of C and the other five
+// in a second, or, where the registers don't hold two (CHAIN), the six of a k-tile from zero and one addition.  A 16x16x32 bf16
 // instruction takes 16 cycles where eight 16x16x4 fp32 ones take 256: six of them leave a factor 2.7.
 //
 // The split is exact for |x| < 2^127 as long as t stays above the smallest bf16 number.  A k-tile that holds a larger,
@@ -442,7 +443,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const Gem
 
 // ---------------------------------------------------------------- host side
 
-// Byte offsets inside a tile are 32-bit (SplitStage::load): 128 rows of A, 32 of B or of A^T.
+// Byte offsets inside a tile are 32-bit (SplitStage::load): up to 256 rows of A, 32 of B or of A^T.
 inline bool split_fits(int64_t lda, int64_t ldb) { return lda < (1 << 22) && ldb < (1 << 24); }
 
 // Column tile: the fewest tiles of at most 144 columns (128 where B is not packed), evenly filled.
