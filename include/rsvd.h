@@ -107,8 +107,12 @@ int rsvd_profile_enable(rsvd_ctx *ctx, int on);
 int rsvd_profile_read(rsvd_ctx *ctx, int n_kinds, double *total_ms, int *launches);
 const char *rsvd_profile_kind_name(int kind);
 
-/* Bytes of device workspace that rsvd_run and every stage call need for a
- * problem of this size (one figure covers all of them). */
+/* Bytes of device workspace for rsvd_run and every stage call on a problem of
+ * this size (one figure covers all of them).  For fp32 problems with
+ * k + p > 128 the figure includes room for the split operand of the products
+ * with A (6 bytes per element of the larger panel); a call whose workspace
+ * lacks some or all of that room is accepted as well, gives the same results
+ * bit for bit and takes longer. */
 int rsvd_workspace_bytes(rsvd_ctx *ctx, rsvd_dtype dtype, int64_t m, int64_t n,
                          int k, int p, int q, rsvd_job job, size_t *bytes);
 
@@ -151,9 +155,10 @@ int rsvd_run(rsvd_ctx *ctx, void *stream, rsvd_dtype dtype, rsvd_job job,
  * RSVD_STATIC_SCRATCH_BYTES (32 MiB) that lives inside the loaded library, one
  * copy per GPU, held until the process ends.  The call allocates nothing and
  * frees nothing (with per-kernel profiling off, its default).
- *   - A problem whose rsvd_workspace_bytes() exceeds the buffer is turned away
- *     with RSVD_ERR_SCRATCH_LIMIT before anything is launched (the paper's
- *     10000 x 2000, k + p = 80 benchmark shape needs 29 MiB and fits).
+ *   - A problem that does not fit in the buffer is turned away with
+ *     RSVD_ERR_SCRATCH_LIMIT before anything is launched (the paper's
+ *     10000 x 2000, k + p = 80 benchmark shape needs 29 MiB and fits).  What
+ *     rsvd_workspace_bytes() adds for the split operand is not needed.
  *   - Every call on one GPU uses the same buffer, whatever the context or the
  *     stream: calls that overlap in time on one GPU race.  The buffer keeps the
  *     contents of the call before; the kernels clear what they need cleared.

@@ -57,7 +57,7 @@ hipError_t gemm_launch_f32(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d) {
   // the k ranges of the fp32 kernel bound those taken here: the workspace is sized for their partial sums
   const TileChoice t = choose_tile(d.M, d.N, d.K, sizeof(float), d.trans_a != 0);
   SplitChoice c = choose_split(ctx, t, d.M, d.N, d.K, d.force_splits, false, d.batch);
-  if (d.force_splits <= 0) c = split_ranges(ctx, d, split_tile_n(d.N, packed != nullptr), c.splits);
+  if (d.force_splits <= 0) c = split_ranges(ctx, d, split_tile_n(d.N), c.splits);
   if (c.splits > 1) {
     const size_t need = (size_t)c.splits * (size_t)d.M * (size_t)d.N * sizeof(float);
     if (d.partial == nullptr || d.partial_bytes < need) return hipErrorInvalidValue;

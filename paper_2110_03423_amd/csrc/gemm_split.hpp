@@ -446,14 +446,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const Gem
 // Byte offsets inside a tile are 32-bit (SplitStage::load): up to 256 rows of A, 32 of B or of A^T.
 inline bool split_fits(int64_t lda, int64_t ldb) { return lda < (1 << 22) && ldb < (1 << 24); }
 
-// Column tile: the fewest tiles of at most 144 columns (128 where B is not packed), evenly filled.
-inline int split_tile_n(int64_t N, bool packed) {
-  const int64_t tiles = ceil_div(N, packed ? 144 : 128);
+// Column tile: one of up to 128 columns, else the fewest of at most 144, evenly filled; the same whether B is packed or not, so
+// that the workgroups, their k ranges and with them every bit of the result do not depend on it.
+inline int split_tile_n(int64_t N) {
+  const int64_t tiles = N <= 128 ? 1 : ceil_div(N, 144);
   return (int)(ceil_div(ceil_div(N, tiles), 16) * 16);
 }
 // Bytes that split_pack_kernel leaves for a K x N operand, and the flags behind them.
 inline size_t split_packed_bytes(int64_t K, int64_t N) {
-  const int64_t bn = split_tile_n(N, true), tiles = ceil_div(N, bn) * ceil_div(K, kSplitBK);
+  const int64_t bn = split_tile_n(N), tiles = ceil_div(N, bn) * ceil_div(K, kSplitBK);
   return (size_t)tiles * (size_t)(3 * bn * 64) + align_up((size_t)tiles * sizeof(int), 256);
 }
 // 32 rows a wavefront, all columns of the tile.  Up to 80 columns two workgroups of four wavefronts fit in a CU beside each other
@@ -489,25 +490,25 @@ hipError_t split_run(hipStream_t s, const GemmParams &P, int batch, char *packed
 }
 
 #define RSVD_SPLIT_TILES_ONE(X) X(48) X(64) X(80) X(96) X(112) X(128)
-#define RSVD_SPLIT_TILES(X) X(80) X(96) X(112) X(128)
-#define RSVD_SPLIT_TILES_PACKED(X) X(80) X(96) X(112) X(128) X(144)
+#define RSVD_SPLIT_TILES(X) X(80) X(96) X(112) X(128) X(144)
 
 template <bool TA>
 hipError_t split_by_tile(hipStream_t s, const GemmParams &P, int batch, char *packed) {
+  const int bn = split_tile_n(P.N);
   if (P.N <= 128) {                    // one column tile
-    switch (split_tile_n(P.N, false)) {
+    switch (bn) {
 #define RSVD_SPLIT_CASE(BN) case BN: return split_run<TA, BN, false, (BN >= 112)>(s, P, batch, nullptr);
       RSVD_SPLIT_TILES_ONE(RSVD_SPLIT_CASE)
 #undef RSVD_SPLIT_CASE
     }
   } else if (packed != nullptr) {
-    switch (split_tile_n(P.N, true)) {
+    switch (bn) {
 #define RSVD_SPLIT_CASE(BN) case BN: return split_run<TA, BN, true, false>(s, P, batch, packed);
-      RSVD_SPLIT_TILES_PACKED(RSVD_SPLIT_CASE)
+      RSVD_SPLIT_TILES(RSVD_SPLIT_CASE)
 #undef RSVD_SPLIT_CASE
     }
   } else {                             // the same sums without the packed operand
-    switch (split_tile_n(P.N, false)) {
+    switch (bn) {
 #define RSVD_SPLIT_CASE(BN) case BN: return split_run<TA, BN, false, false>(s, P, batch, nullptr);
       RSVD_SPLIT_TILES(RSVD_SPLIT_CASE)
 #undef RSVD_SPLIT_CASE
@@ -534,7 +535,7 @@ hipError_t split_init() {
   RSVD_SPLIT_TILES(RSVD_SPLIT_CASE)
 #undef RSVD_SPLIT_CASE
 #define RSVD_SPLIT_CASE(BN) RSVD_SPLIT_RAISE(BN, true, false)
-  RSVD_SPLIT_TILES_PACKED(RSVD_SPLIT_CASE)
+  RSVD_SPLIT_TILES(RSVD_SPLIT_CASE)
 #undef RSVD_SPLIT_CASE
 #undef RSVD_SPLIT_RAISE
   return e;

@@ -77,7 +77,10 @@ def test_values_outside_the_split(l):
     assert float(rel) <= 2 * np.sqrt(n) * EPS
 
 
-@pytest.mark.parametrize("m,n,k,p,q", [(6000, 1500, 150, 20, 1), (2000, 9001, 190, 11, 2)])
+# column tiles of 80 to 144, two and three of them; at 6000 x 1500, l = 280 and 20000 x 5000, l = 140 tiles of up to 128 columns, which
+# would do without the packed operand, would lead to other k ranges
+@pytest.mark.parametrize("m,n,k,p,q", [(6000, 1500, 150, 20, 1), (2000, 9001, 190, 11, 2), (6000, 1500, 256, 24, 1),
+                                       (20000, 5000, 130, 10, 1), (9001, 2203, 129, 0, 1), (12000, 3000, 400, 30, 0)])
 def test_without_room_for_the_packed_operand(m, n, k, p, q):
     """A workspace that lacks it is still accepted and gives the same bits."""
     import torch
