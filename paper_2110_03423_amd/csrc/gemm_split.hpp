@@ -2,15 +2,18 @@
 //
 // An fp32 number is the exact sum of three bf16 numbers (x = h + m + t: 8 + 8 + 8 significand bits, each the
 // rounded rest of the ones before), so  a b = sum of nine bf16 products, of which the six of order 2^-16 and above are
-// taken (hh, hm, mh, mm, ht, th); what is left out, mt + tm + tt, is below 2^-25 |a b|, half a unit of the last place
-// of an fp32 product.  The products are exact in the matrix instruction and summed in fp32, with an eighth of the
-// accumulation steps of the fp32 instruction: the leading products in one accumulator per element of C and the other five
-// in a second, or, where the registers don't hold two (CHAIN), the six of a k-tile from zero and one addition.  A 16x16x32 bf16
-// instruction takes 16 cycles where eight 16x16x4 fp32 ones take 256: six of them leave a factor 2.7.
+// taken (hh, hm, mh, mm, ht, th); what is left out, mt + tm + tt, is below 2^-24 |a b|, half a unit of the last place
+// of an fp32 product (at most 1.98 2^-25 over all significands, root mean square 2^-27.5).  The products are exact in the
+// matrix instruction and summed in fp32, with an eighth of the accumulation steps of the fp32 instruction: the leading
+// products in one accumulator per element of C and the other five in a second, or, where the registers don't hold two (CHAIN),
+// the six of a k-tile from zero and one addition.  A 16x16x32 bf16 instruction takes 16 cycles where eight 16x16x4 fp32 ones
+// take 256: six of them leave a factor 2.7.  (The split of a product into bf16 parts: Henry, Tang, Heinecke, "Leveraging the
+// bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", ARITH 2019.)
 //
-// The split is exact for |x| < 2^127 as long as t stays above the smallest bf16 number.  A k-tile that holds a larger,
-// infinite or undefined value, or nothing but values below 2^-106, is therefore multiplied by the fp32 instruction,
-// straight from global memory (slow_tile).
+// Both operands are multiplied by 2^16 on the way in and the result by 2^-32 on the way out: the last of the three parts
+// of the smallest fp32 number is then still a bf16 number (2^-149 2^16 = 2^-133), so the split is exact for every fp32 value.
+// What overflows by that (results from 2^96 on, infinities, NaN) is seen in the accumulators, which stay infinite or
+// undefined: a workgroup that ends so, or has got there after its first k-tile, computes its tile again with the fp32 instruction.
 //
 // Both operands are staged as [row][k] bf16 planes, the eight k of a matrix operand in one 16-byte chunk, so that
 // matrices whose rows run along the other index are transposed by the loads of the staging (eight dwords a
@@ -22,9 +25,9 @@
 // run (65536 x 16384, l = 576: pipe busy 61 % of the cycles at 2.0 GHz), so everything else is put in its shadow: the vector
 // instructions that split the next tile of A are issued among the matrix instructions of the current one, the loads of
 // the tile after it stay in flight across the barrier, and a wide B is split once (split_pack_kernel) and copied to LDS
-// without registers.  Measured against the fp32 instruction: 65536 x 16384, l = 576: A X 9.20 -> 5.78 ms (214 TFLOP/s),
-// A^T X 9.99 -> 5.82 ms; l = 210: 6.14 -> 2.52 and 5.12 -> 2.56 ms; 30011 x 2999, l = 61 (odd strides): 0.187 -> 0.146 and
-// 0.197 -> 0.119 ms.  Relative error against 64 bits at K = 16384: 2.3e-6 -> 0.8e-6.
+// without registers.  Measured against the fp32 instruction: 65536 x 16384, l = 576: A X 9.21 -> 5.81 ms, A^T X 10.04 -> 5.96 ms;
+// 4001 x 50021, l = 210: 1.26 -> 0.54 and 1.27 -> 0.56 ms; 30011 x 2999, l = 61 (odd strides): 0.178 -> 0.122 and 0.206 -> 0.104 ms.
+// Relative error against 64 bits at K = 16384: 2.3e-6 -> 0.8e-6.
 #pragma once
 
 #include "gemm_impl.hpp"
@@ -41,18 +44,11 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 #define RSVD_INLINE __attribute__((always_inline))
 
 constexpr int kSplitBK = 32;                       // k-tile: one 16x16x32 instruction deep
-constexpr unsigned kSplitHuge = 0x7f000000u;       // 2^127
-constexpr unsigned kSplitTiny = 0x0a800000u;       // 2^-106
+constexpr float kSplitScale = 65536.f;             // on both operands
+constexpr int kRawStride = 144;                    // bytes of an LDS row of 32 fp32 values (redo)
 
 // Operand of s_waitcnt: at most n vector memory operations outstanding, no LDS operation.
 constexpr int wait_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; }
-
-// Flags of a k-tile, collected in LDS
-enum { SPLIT_BAD = 1, SPLIT_A_USUAL = 2, SPLIT_A_ANY = 4, SPLIT_B_USUAL = 8, SPLIT_B_ANY = 16 };
-__device__ __forceinline__ bool split_unfit(int f) {
-  return (f & SPLIT_BAD) || (f & (SPLIT_A_USUAL | SPLIT_A_ANY)) == SPLIT_A_ANY ||
-         (f & (SPLIT_B_USUAL | SPLIT_B_ANY)) == SPLIT_B_ANY;
-}
 
 // Byte offset of chunk c (eight k) of row r inside a plane of 64-byte rows.
 __device__ __forceinline__ int split_chunk(int r, int c) { return r * 64 + ((c ^ ((r >> 1) & 3)) << 4); }
@@ -125,21 +121,18 @@ struct SplitStage {
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[it][e] = row < rows_left ? x[it][e] : 0.f;
   }
-  // Splits iteration `it` and writes its three planes; pos, neg follow the largest magnitudes seen (see mag()).
-  __device__ __forceinline__ void store(int it, char *planes, int tid, int &pos, unsigned &neg) const {
+  // Element e of iteration `it`, the offset of its column taken away.
+  __device__ __forceinline__ float value(int it, int e) const {
+    return SHIFT ? (float)((double)x[it][e] - sh[KROWS ? 0 : e]) : x[it][e];
+  }
+  // Splits iteration `it` and writes its three planes.
+  __device__ __forceinline__ void store(int it, char *planes, int tid) const {
     int row, c;
     place(tid, it, row, c);
     u32x4 h, m, t;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-      float a = x[it][2 * p], b = x[it][2 * p + 1];
-      if (SHIFT) {
-        a = (float)((double)a - sh[KROWS ? 0 : 2 * p]);
-        b = (float)((double)b - sh[KROWS ? 0 : 2 * p + 1]);
-      }
-      const unsigned ua = __float_as_uint(a), ub = __float_as_uint(b);
-      neg = max(max(neg, ua), ub);                  // unsigned order: the largest negative magnitude, if any
-      pos = max(max(pos, (int)ua), (int)ub);        // signed order: the largest positive one
+      const float a = value(it, 2 * p) * kSplitScale, b = value(it, 2 * p + 1) * kSplitScale;
       h[p] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
       const float a1 = a - __uint_as_float(h[p] << 16), b1 = b - __uint_as_float(h[p] & 0xffff0000u);
       m[p] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a1, b1}, bf16x2));
@@ -151,39 +144,38 @@ struct SplitStage {
     *reinterpret_cast<u32x4 *>(dst + ROWS * 64) = m;
     *reinterpret_cast<u32x4 *>(dst + 2 * ROWS * 64) = t;
   }
+  // Writes iteration `it` as it is, in rows of kRawStride bytes.
+  __device__ __forceinline__ void store_raw(int it, char *rows, int tid) const {
+    int row, c;
+    place(tid, it, row, c);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      f32x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = value(it, 4 * q + e);
+      *reinterpret_cast<f32x4 *>(rows + row * kRawStride + c * 32 + q * 16) = v;
+    }
+  }
 };
-// largest magnitude (bit pattern) behind the two running maxima
-__device__ __forceinline__ unsigned split_mag(int pos, unsigned neg) { return max(neg & 0x7fffffffu, (unsigned)pos); }
-
 // Wide outputs: the column tiles of a row tile all need the same planes of B, and every row tile needs them again.
 // This kernel splits B once, into the bytes a k-tile of it occupies in LDS (planes of 64-byte rows, chunks swizzled,
 // zeros beyond N and K), tile after tile with the column tiles of a k-tile next to each other; the product kernel then
-// copies them without touching a register.  One flag word per tile.
+// copies them without touching a register.
 template <int BN>
-__global__ __launch_bounds__(256) void split_pack_kernel(const GemmParams P0, char *__restrict__ packed, int *__restrict__ flags) {
+__global__ __launch_bounds__(256) void split_pack_kernel(const GemmParams P0, char *__restrict__ packed) {
   const GemmParams P = select_problem(P0);
   if (P.skip_now) return;
   const int tile_n = (int)blockIdx.x % P.tiles_n, kt = (int)blockIdx.x / P.tiles_n;
   const int64_t k0 = (int64_t)kt * kSplitBK, n0 = (int64_t)tile_n * BN;
   const int tid = threadIdx.x;
-  __shared__ int fl;
-  if (tid == 0) fl = 0;
-  __syncthreads();
   SplitStage<256, BN, true> sb;
   char *dst = packed + (int64_t)blockIdx.x * (3 * BN * 64);
-  int pos = 0;
-  unsigned neg = 0u;
 #pragma unroll
   for (int it = 0; it < sb.ITERS; ++it) {
     sb.template load<false>(it, (const float *)P.B + k0 * P.ldb + n0, P.ldb, P.N - n0, P.K - k0, tid);
     sb.clear_beyond(it, P.N - n0, tid);
-    sb.store(it, dst, tid, pos, neg);
+    sb.store(it, dst, tid);
   }
-  const unsigned mb = split_mag(pos, neg);
-  const int f = (mb >= kSplitHuge ? SPLIT_BAD : 0) | (mb >= kSplitTiny ? SPLIT_B_USUAL : 0) | (mb != 0u ? SPLIT_B_ANY : 0);
-  if (f) atomicOr(&fl, f);
-  __syncthreads();
-  if (tid == 0) flags[blockIdx.x] = fl;
 }
 
 // Epilogues as in gemm_kernel: 0 plain, 1 full, 3 plain with the column offsets of A taken away while staging.
@@ -191,10 +183,10 @@ __global__ __launch_bounds__(256) void split_pack_kernel(const GemmParams P0, ch
 // CHAIN: no second set of accumulators; the six terms of a k-tile are summed from zero and added to the one set there is.
 // That is more vector instructions (9 % at 65536 x 16384, l = 576) but 16 registers instead of one set of accumulators, and
 // outputs of one column tile of 112 or 128 columns, which split B in place and wait for A from HBM besides, are faster
-// with it (100000 x 1000, l = 120: A X 262 -> 230 us, A^T X 191 -> 180 us; at 96 columns and below it is the other way round).
+// with it in A^T X (20000 x 5000, l = 120: 169 -> 155 us; 50000 x 2000, l = 112: 153 -> 145; 100000 x 1000, l = 128: 164 -> 156) and
+// within 2 % of the other in A X; at 96 columns and below it is the other way round (50000 x 2000, l = 80: 133 against 140 us).
 template <bool TA, int BM, int BN, int WGM, int WGN, int EPI, bool PACKED, bool CHAIN>
-__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const GemmParams P0, const char *__restrict__ packed,
-                                                                       const int *__restrict__ packed_flags) {
+__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const GemmParams P0, const char *__restrict__ packed) {
   const GemmParams P = select_problem(P0);
   if (P.skip_now) return;
   constexpr int BK = kSplitBK, NT = 64 * WGM * WGN;
@@ -203,7 +195,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const Gem
   constexpr bool CENTER = (EPI == 3);
   constexpr int PA = BM * 64, PB = BN * 64, BUF = 3 * (PA + PB);      // bytes of a plane, of both operands of a k-tile
   extern __shared__ __attribute__((aligned(16))) char split_lds[];
-  // behind the two buffers, one int per wavefront: flags of the tile in hand and of the next
+  // behind the two buffers, one int per wavefront: its accumulators have overflowed
   constexpr int WAVES = NT / 64;
   int *flags = reinterpret_cast<int *>(split_lds + 2 * BUF);
 
@@ -236,43 +228,31 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const Gem
   const int kt0 = (int)(k_begin / BK), nkt = k_begin < k_end ? (int)((k_end - k_begin + BK - 1) / BK) : 0;
   const int last_k = (int)(k_end - k_begin) - (nkt - 1) * BK;
   const int whole_tiles = last_k == BK ? nkt : nkt - 1;
-  const float *a_tile = TA ? A + k_begin * P.lda + m0 : A + m0 * P.lda + k_begin;      // the next tile to be loaded
-  const float *b_tile = B + k_begin * P.ldb + n0;
+  const float *const a_first = TA ? A + k_begin * P.lda + m0 : A + m0 * P.lda + k_begin, *a_tile = a_first;      // the next tile to be loaded
+  const float *const b_first = B + k_begin * P.ldb + n0, *b_tile = b_first;
   const double *s_tile = CENTER && !TA ? P.a_shift + k_begin : nullptr;
   const int64_t a_step = TA ? BK * P.lda : BK, b_step = BK * P.ldb;
   const int m_left = (int)(P.M - m0 < BM ? P.M - m0 : BM), n_left = (int)(P.N - n0 < BN ? P.N - n0 : BN);
-  // iteration w of the staging through registers: those of A, then those of B
+  // iteration w of the staging through registers: those of A, then those of B; in narrow products A X, which wait for A from
+  // HBM, the other way round, so that the pieces of A have the longer time to arrive (62393 x 2646, l = 36: 184 -> 175 us, but
+  // 30000 x 3000, l = 80: 135 -> 138)
+  constexpr bool B_FIRST = !TA && BN <= 64;
+  constexpr int FIRST_A = B_FIRST ? NB : 0, FIRST_B = B_FIRST ? 0 : NA;
+  auto is_a = [](int w) RSVD_INLINE { return w >= FIRST_A && w < FIRST_A + NA; };
   auto load_part = [&](auto whole, int w, int k_left) RSVD_INLINE {
     constexpr bool W = decltype(whole)::value;
-    if (w < NA) sa.template load<W>(w, a_tile, P.lda, m_left, k_left, tid);
-    else sb.template load<W>(w - NA, b_tile, P.ldb, n_left, k_left, tid);
-    if (CENTER && !TA && w == NA - 1) sa.load_shift(s_tile, 0, k_left, tid);     // (behind the last use of the old ones)
+    if (is_a(w)) sa.template load<W>(w - FIRST_A, a_tile, P.lda, m_left, k_left, tid);
+    else sb.template load<W>(w - FIRST_B, b_tile, P.ldb, n_left, k_left, tid);
+    if (CENTER && !TA && w - FIRST_A == NA - 1) sa.load_shift(s_tile, 0, k_left, tid);     // (behind the last use of the old ones)
     if (w == NA + NB - 1) {
       a_tile += a_step;
       if (!PACKED) b_tile += b_step;
       if (CENTER && !TA) s_tile += BK;
     }
   };
-  int pa = 0, pb = 0;
-  unsigned na = 0u, nb = 0u;
   auto store_part = [&](int w, int buf) RSVD_INLINE {
-    if (w < NA) sa.store(w, split_lds + buf * BUF, tid, pa, na);
-    else sb.store(w - NA, split_lds + buf * BUF + 3 * PA, tid, pb, nb);
-  };
-  // raises the flags of a staged tile from the maxima of its parts
-  auto put_flags = [&](int fl) RSVD_INLINE {
-    const unsigned ma = split_mag(pa, na), mb = split_mag(pb, nb);
-    pa = pb = 0;
-    na = nb = 0u;
-    int f = 0;
-    if (__ballot(ma >= kSplitHuge || mb >= kSplitHuge)) f |= SPLIT_BAD;
-    if (__ballot(ma >= kSplitTiny)) f |= SPLIT_A_USUAL;
-    if (__ballot(ma != 0u)) f |= SPLIT_A_ANY;
-    if (!PACKED) {
-      if (__ballot(mb >= kSplitTiny)) f |= SPLIT_B_USUAL;
-      if (__ballot(mb != 0u)) f |= SPLIT_B_ANY;
-    }
-    if (lane == 0) flags[fl * WAVES + wave] = f;
+    if (is_a(w)) sa.store(w - FIRST_A, split_lds + buf * BUF, tid);
+    else sb.store(w - FIRST_B, split_lds + buf * BUF + 3 * PA, tid);
   };
   // PACKED: the next tile of B straight into buffer `buf`, 1024 bytes a wavefront and instruction (a wavefront without a
   // piece of its own copies the last one again: no branches)
@@ -303,30 +283,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const Gem
   auto store_all = [&](int buf) RSVD_INLINE {
 #pragma unroll
     for (int w = 0; w < NA + NB; ++w) store_part(w, buf);
-  };
-  // A k-tile that the split does not represent: the fp32 instruction on operands fetched one by one.
-  auto slow_tile = [&](int64_t k0) RSVD_INLINE {
-#pragma unroll 1
-    for (int kk = 0; kk < BK; kk += 4) {
-      const int64_t k = k0 + kk + kq;
-      float af[TM], bf[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int64_t row = m0 + wm0 + i * 16 + r16;
-        const bool ok = row < P.M && k < k_end;
-        af[i] = ok ? A[TA ? k * P.lda + row : row * P.lda + k] : 0.f;
-        if (CENTER && ok) af[i] = (float)((double)af[i] - P.a_shift[TA ? row : k]);
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int64_t col = n0 + wn0 + j * 16 + r16;
-        bf[j] = (col < P.N && k < k_end) ? B[k * P.ldb + col] : 0.f;
-      }
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<float>::run(af[i], bf[j], acc[i][j]);
-    }
   };
   const char *ap0 = split_lds + split_chunk(wm0 + r16, kq);
   const char *bp0 = split_lds + 3 * PA + split_chunk(wn0 + r16, kq);
@@ -373,25 +329,38 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const Gem
     }
   };
 
-  // flags of the tile in buffer `buf`; f_b: what the packed tile of B holds
-  int buf = 1, kt = -1, f_b = 0;
-  auto tile_flags = [&]() RSVD_INLINE {
-    int f = f_b;
-    if (kt >= 0) {
-      const int seen = flags[buf * WAVES + (lane & (WAVES - 1))];
-#pragma unroll
-      for (int b = 1; b <= SPLIT_B_ANY; b <<= 1) f |= __ballot((seen & b) != 0) ? b : 0;
-    }
-    if (PACKED && kt + 1 < nkt) f_b = packed_flags[(int64_t)(kt0 + kt + 1) * P.tiles_n + tile_n];
-    return f;
+  // A barrier that leaves the last n loads in flight, which __syncthreads() would not.
+  auto wait_and_meet = [&](auto n) RSVD_INLINE {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(wait_imm(decltype(n)::value));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
   };
+  // Whether an accumulator of the workgroup is infinite or undefined.
+  auto overflowed = [&]() RSVD_INLINE {
+    unsigned largest = 0u;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) largest = max(largest, __float_as_uint(acc[i][j][v]) & 0x7fffffffu);
+    const bool mine = __ballot(largest >= 0x7f800000u) != 0;
+    if (lane == 0) flags[wave] = mine ? 1 : 0;
+    wait_and_meet(std::integral_constant<int, 63>());
+    return __ballot(flags[lane & (WAVES - 1)] != 0) != 0;
+  };
+
+  int buf = 1, kt = -1;
+  bool redo = false;
+  const int look = whole_tiles < 24 ? -1 : 1;        // (a long range looks for overflow behind its first tile)
   if (nkt > 0) load_all(nkt > 1 ? BK : last_k);
   // On entry of an iteration tile kt lies in buffer `buf` (none before the first), the next one (if any) in the registers
   // of the stages.
   while (kt < nkt) {
-    int f = tile_flags();
     // the rule: the next tile is split and the loads of the one after it are issued among the matrix instructions
-    while (kt >= 0 && kt + 2 < whole_tiles && !split_unfit(f)) {
+    while (kt >= 0 && kt + 2 < whole_tiles) {
       // (split first, then load: a wait for an older load while a copy to LDS is outstanding would wait for everything)
       multiply(buf, [&](int j) RSVD_INLINE {
         constexpr int LAST = NA + NB < TN ? NA + NB : TN - 1;
@@ -405,28 +374,22 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const Gem
           for (int w = 0; w < NA + NB; ++w) load_part(std::true_type(), w, BK);
         }
       });
-      put_flags(buf ^ 1);
-      // The packed tile has landed once at most the loads of A issued behind it (8 or 2 a part) are outstanding; those
-      // stay in flight across the barrier, which __syncthreads() would not let them.
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_waitcnt(wait_imm(PACKED ? (TA ? 8 : 2) * NA : 63));
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
+      // the packed tile has landed once at most the loads of A issued behind it (8 or 2 a part) are outstanding
+      wait_and_meet(std::integral_constant<int, PACKED ? (TA ? 8 : 2) * NA : 63>());
       ++kt;
       buf ^= 1;
-      f = tile_flags();
+      if (kt == look) {
+        redo = overflowed();
+        if (redo) kt = nkt;
+      }
     }
+    if (redo) break;
     if (kt + 1 < nkt) {
       copy_b(buf ^ 1);
       store_all(buf ^ 1);
-      put_flags(buf ^ 1);
       if (kt + 2 < nkt) load_all(kt + 2 < whole_tiles ? BK : last_k);
     }
-    if (kt >= 0) {
-      if (split_unfit(f)) slow_tile(k_begin + (int64_t)kt * BK);
-      else multiply(buf, [](int) RSVD_INLINE {});
-    }
+    if (kt >= 0) multiply(buf, [](int) RSVD_INLINE {});
     if (PACKED) __builtin_amdgcn_s_waitcnt(wait_imm(0));
     __syncthreads();
     ++kt;
@@ -437,6 +400,82 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_split_kernel(const Gem
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j % LN];
+  }
+  if (!redo) redo = overflowed();
+  if (!redo) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] *= 1.f / (kSplitScale * kSplitScale);
+  } else {
+    // The whole k range with the fp32 instruction: tiles as they are in LDS, double-buffered as well; of four consecutive k that a
+    // lane holds, one goes into each of four instructions.  (About what the fp32 kernel takes, see gemm_f32.hip.)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = (f32x4)0.f;
+    // (the thread number anew: addresses that follow from it were worked out before the main loop otherwise, and kept)
+    int tr = threadIdx.x;
+    asm volatile("" : "+v"(tr));
+    const int at0 = ((tr & 63) >> 4) * 16, row0 = tr & 15;
+    SplitStage<NT, BM, TA, CENTER> ra;
+    SplitStage<NT, BN, true> rb;
+    if (CENTER && TA) ra.load_shift(P.a_shift + m0, P.M - m0, 0, tr);
+    __syncthreads();                       // (the flags have been read)
+    a_tile = a_first;
+    b_tile = b_first;
+    if (CENTER && !TA) s_tile = P.a_shift + k_begin;
+    auto load_raw = [&](auto whole, int k_left) RSVD_INLINE {
+      constexpr bool W = decltype(whole)::value;
+#pragma unroll
+      for (int w = 0; w < NA; ++w) ra.template load<W>(w, a_tile, P.lda, m_left, k_left, tr);
+#pragma unroll
+      for (int w = 0; w < rb.ITERS; ++w) rb.template load<W>(w, b_tile, P.ldb, n_left, k_left, tr);
+      if (CENTER && !TA) { ra.load_shift(s_tile, 0, k_left, tr); s_tile += BK; }
+      a_tile += a_step;
+      b_tile += b_step;
+    };
+    auto load_next = [&](int t) RSVD_INLINE {
+      if (t < whole_tiles) load_raw(std::true_type(), BK);
+      else if (t < nkt) load_raw(std::false_type(), last_k);
+    };
+    constexpr int RAW = (BM + BN) * kRawStride, RAW_B = BM * kRawStride;
+    static_assert(RAW <= BUF, "two tiles as they are take no more LDS than two split ones");
+    auto store_next = [&](int t) RSVD_INLINE {
+      char *raw = split_lds + (t & 1) * RAW;
+#pragma unroll
+      for (int w = 0; w < NA; ++w) ra.store_raw(w, raw, tr);
+#pragma unroll
+      for (int w = 0; w < rb.ITERS; ++w) rb.store_raw(w, raw + RAW_B, tr);
+    };
+    load_next(0);
+    store_next(0);
+    load_next(1);
+#pragma unroll 1
+    for (int t = 0; t < nkt; ++t) {
+      const char *raw = split_lds + (t & 1) * RAW;
+      __syncthreads();
+      if (t + 1 < nkt) {
+        store_next(t + 1);
+        load_next(t + 2);
+      }
+#pragma unroll 1
+      for (int half = 0; half < 2; ++half) {
+        const int at = half * 64 + at0;
+        f32x4 af[TM];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+          af[i] = *reinterpret_cast<const f32x4 *>(raw + (wm0 + i * 16 + row0) * kRawStride + at);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const f32x4 bf = *reinterpret_cast<const f32x4 *>(raw + RAW_B + (wn0 + j * 16 + row0) * kRawStride + at);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < TM; ++i) acc[i][j] = Mfma<float>::run(af[i][e], bf[e], acc[i][j]);
+        }
+      }
+    }
   }
   gemm_epilogue<float, float, float, TM, TN, EPI>(P, acc, split, m0 + wm0, n0 + wn0, lane);
 }
@@ -452,10 +491,10 @@ inline int split_tile_n(int64_t N) {
   const int64_t tiles = N <= 128 ? 1 : ceil_div(N, 144);
   return (int)(ceil_div(ceil_div(N, tiles), 16) * 16);
 }
-// Bytes that split_pack_kernel leaves for a K x N operand, and the flags behind them.
+// Bytes that split_pack_kernel leaves for a K x N operand.
 inline size_t split_packed_bytes(int64_t K, int64_t N) {
   const int64_t bn = split_tile_n(N), tiles = ceil_div(N, bn) * ceil_div(K, kSplitBK);
-  return (size_t)tiles * (size_t)(3 * bn * 64) + align_up((size_t)tiles * sizeof(int), 256);
+  return (size_t)tiles * (size_t)(3 * bn * 64);
 }
 // 32 rows a wavefront, all columns of the tile.  Up to 80 columns two workgroups of four wavefronts fit in a CU beside each other
 // (20000 x 5000, l = 48: 134 -> 121 us against one of eight), beyond that one of eight.
@@ -463,7 +502,7 @@ constexpr int split_tile_m(int bn) { return bn <= 80 ? 128 : 256; }
 constexpr int split_wgs_per_cu(int bn) { return bn <= 80 ? 2 : 1; }
 template <int BN> struct SplitTile {
   static constexpr int BM = split_tile_m(BN), WAVES = BM / 32, WGN = 1, WGM = WAVES;
-  static constexpr size_t lds = (size_t)2 * 3 * 64 * (BM + BN) + 2 * WAVES * sizeof(int);      // planes, flags
+  static constexpr size_t lds = (size_t)2 * 3 * 64 * (BM + BN) + WAVES * sizeof(int);      // planes, flags of the wavefronts
 };
 
 template <bool TA, int BN, bool PACKED, bool CHAIN>
@@ -473,19 +512,19 @@ hipError_t split_run(hipStream_t s, const GemmParams &P, int batch, char *packed
   Q.tiles_n = (int)ceil_div(P.N, BN);
   Q.tiles_m = (int)ceil_div(P.M, T::BM);
   const dim3 grid((unsigned)((int64_t)Q.tiles_n * Q.tiles_m * P.splits), (unsigned)batch);
-  int *flags = nullptr;
   if (PACKED) {
     const int64_t tiles = Q.tiles_n * ceil_div(P.K, kSplitBK);
-    flags = reinterpret_cast<int *>(packed + tiles * (3 * BN * 64));
-    hipLaunchKernelGGL((split_pack_kernel<BN>), dim3((unsigned)tiles), dim3(256), 0, s, Q, packed, flags);
+    hipLaunchKernelGGL((split_pack_kernel<BN>), dim3((unsigned)tiles), dim3(256), 0, s, Q, packed);
   }
   const bool general = P.splits == 1 && (P.dead != nullptr || P.trans_c != 0);
-  if (P.a_shift != nullptr)
-    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 3, PACKED, CHAIN>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed, flags);
-  else if (general)
-    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 1, PACKED, CHAIN>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed, flags);
-  else
-    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 0, PACKED, CHAIN>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed, flags);
+  if (P.a_shift != nullptr) {
+    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 3, PACKED, CHAIN>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed);
+  } else if (general) {
+    if constexpr (TA) return hipErrorInvalidValue;           // (takes_split: such products have op(A) = A)
+    else hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 1, PACKED, CHAIN>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed);
+  } else {
+    hipLaunchKernelGGL((gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, 0, PACKED, CHAIN>), grid, dim3(64 * T::WAVES), T::lds, s, Q, packed);
+  }
   return hipGetLastError();
 }
 
@@ -523,21 +562,21 @@ void split_raise_lds(hipError_t &e) {
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_split_kernel<TA, T::BM, BN, T::WGM, T::WGN, EPI, PACKED, CHAIN>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::lds);
 }
+template <bool TA, int BN, bool PACKED, bool CHAIN>
+void split_raise_lds_all(hipError_t &e) {
+  split_raise_lds<TA, BN, 0, PACKED, CHAIN>(e);
+  if constexpr (!TA) split_raise_lds<TA, BN, 1, PACKED, CHAIN>(e);
+  split_raise_lds<TA, BN, 3, PACKED, CHAIN>(e);
+}
 template <bool TA>
 hipError_t split_init() {
   hipError_t e = hipSuccess;
-#define RSVD_SPLIT_RAISE(BN, PACKED, CHAIN) \
-  split_raise_lds<TA, BN, 0, PACKED, CHAIN>(e); split_raise_lds<TA, BN, 1, PACKED, CHAIN>(e); split_raise_lds<TA, BN, 3, PACKED, CHAIN>(e);
-#define RSVD_SPLIT_CASE(BN) RSVD_SPLIT_RAISE(BN, false, (BN >= 112))
+#define RSVD_SPLIT_CASE(BN) split_raise_lds_all<TA, BN, false, (BN >= 112)>(e);
   RSVD_SPLIT_TILES_ONE(RSVD_SPLIT_CASE)
 #undef RSVD_SPLIT_CASE
-#define RSVD_SPLIT_CASE(BN) RSVD_SPLIT_RAISE(BN, false, false)
+#define RSVD_SPLIT_CASE(BN) split_raise_lds_all<TA, BN, false, false>(e); split_raise_lds_all<TA, BN, true, false>(e);
   RSVD_SPLIT_TILES(RSVD_SPLIT_CASE)
 #undef RSVD_SPLIT_CASE
-#define RSVD_SPLIT_CASE(BN) RSVD_SPLIT_RAISE(BN, true, false)
-  RSVD_SPLIT_TILES(RSVD_SPLIT_CASE)
-#undef RSVD_SPLIT_CASE
-#undef RSVD_SPLIT_RAISE
   return e;
 }
 hipError_t split_init_n();

@@ -1,5 +1,5 @@
-"""fp32 products on the bf16 matrix cores (split operands): tile edges, k remainders, odd strides, values that the split
-does not represent, and the packed operand against the one split in place."""
+"""fp32 products on the bf16 matrix cores (split operands): tile edges, k remainders, odd strides, values of every size and
+beyond the range, and the packed operand against the one split in place."""
 import numpy as np
 import pytest
 
@@ -46,35 +46,84 @@ def test_products(m, n, l, pad):
     _check(ctx().rsvd_stage_gemm_atn(A, Q), A.T, Q)
 
 
-@pytest.mark.parametrize("l", [40, 160])
+def _by_rows(got, A, X, roundings, slack=2.0 ** -143):
+    """Element by element, where the result is finite: that many roundings of sum |a b|, whatever the row's size (slack: 64
+    roundings of partial sums in the subnormal range)."""
+    import torch
+    A, X = A.double().contiguous(), X.double().contiguous()
+    want, size = A @ X, A.abs() @ X.abs()
+    w32 = want.float()
+    assert bool((torch.isnan(got) == torch.isnan(w32)).all())
+    inf = torch.isinf(w32)
+    assert bool((got[inf] == w32[inf]).all())
+    fine = torch.isfinite(w32)
+    err = (got.double() - want).abs()[fine]
+    assert bool((err <= roundings * 0.5 * EPS * size[fine] + slack).all())
+
+
+@pytest.mark.parametrize("l", [40, 128, 160])
+@pytest.mark.parametrize("pad", [0, 1])
+@pytest.mark.parametrize("top", [0, 90, 127])
+def test_every_value_passes_through(l, pad, top):
+    """Products with columns of the identity give back what was put in, bit for bit: fp32 numbers of every size side by side, from
+    the smallest subnormal up to 2^top (2^96 and above: the workgroup computes its tile again)."""
+    import torch
+    say("split identity", l, pad, top)
+    m, n = 20000, 1056
+    A = _randn(m, n + pad, 4)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(5)
+    A = torch.ldexp(A, torch.randint(-149, top - 3, (m, n + pad), device="cuda:0", generator=g).float())[:, pad:]
+    cols, rows = torch.arange(l, device="cuda:0") * 5 % n, torch.arange(l, device="cuda:0") * 97 % m
+    X, Q = torch.zeros(n, l, device="cuda:0"), torch.zeros(m, l, device="cuda:0")
+    X[cols, torch.arange(l)] = 1.0
+    Q[rows, torch.arange(l)] = 1.0
+    assert bool((ctx().rsvd_stage_gemm_an(A, X) == A[:, cols]).all())
+    assert bool((ctx().rsvd_stage_gemm_atn(A, Q) == A[rows].T).all())
+
+
+@pytest.mark.parametrize("l", [40, 112, 160])
+def test_rows_of_any_size(l):
+    """Rows of 1e-37 beside ordinary ones, and a block of 1e-36 that ends inside the tiles."""
+    say("split rows", l)
+    m, n = 20000, 1024
+    A, X, Q = _randn(m, n, 4), _randn(n, l, 5), _randn(m, l, 6)
+    A[::7] *= 1e-37
+    A[3000:3333, 100:933] *= 1e-36
+    A[:, 5::11] *= 1e-5
+    for _ in range(2):
+        # one rounding per k-tile of 32 and those inside one
+        _by_rows(ctx().rsvd_stage_gemm_an(A, X), A, X, n // 32 + 48)
+        _by_rows(ctx().rsvd_stage_gemm_atn(A, Q), A.T, Q, m // 32 + 48)
+        A *= 1e-34                                    # (rows of zeros and subnormal numbers among them)
+
+
+@pytest.mark.parametrize("l", [40, 128, 160])
 def test_values_outside_the_split(l):
-    """Infinities, NaNs, values at the end of the range and tiles of nothing but tiny values."""
+    """Infinities, NaNs, values and results at the end of the range: the rest of such a tile is right as well."""
     import torch
     say("split extremes", l)
     m, n = 20000, 1024
-    A, X = _randn(m, n, 4), _randn(n, l, 5) * 0.05
+    A, X, Q = _randn(m, n, 4), _randn(n, l, 5) * 0.05, _randn(m, l, 6)
     A[7, 100] = float("inf")
     A[8, 101] = float("nan")
     A[300, 5] = -3.3e38
     A[301, 6] = 3.4e38
     A[512:1024] *= 1e-35
     A[1024:1536, ::2] = 0.0
-    A[2048:2560, 256:512] *= 1e-33
-    for got, want in ((ctx().rsvd_stage_gemm_an(A, X), A.double() @ X.double()),
-                      (ctx().rsvd_stage_gemm_atn(A[:, :n], _randn(m, l, 6)), A.double().T.contiguous() @ _randn(m, l, 6).double())):
-        want32 = want.float()
-        assert bool((torch.isnan(got) == torch.isnan(want32)).all())
-        inf = torch.isinf(want32)
-        assert bool((got[inf] == want32[inf]).all())
-        fine = torch.isfinite(want32)
-        # row by row (the rows differ in scale by 70 decades): 1024 terms at most along a row of A X
-        if got.shape[0] == m:
-            err = torch.where(fine, (got - want).abs(), 0.0).amax(1)
-            size = (torch.where(torch.isfinite(A), A, 0.0).double().norm(dim=1) * 0.05).clamp_min(1e-300)
-            assert float((err / size).max()) <= 64 * EPS
-    A = _randn(m, n, 7) * 1e-34                      # every tile takes the fp32 instruction
-    rel = (ctx().rsvd_stage_gemm_an(A, X).double() - A.double() @ X.double()).norm() / (A.double() @ X.double()).norm()
-    assert float(rel) <= 2 * np.sqrt(n) * EPS
+    A[5000:5100] *= 1e33
+    _by_rows(ctx().rsvd_stage_gemm_an(A, X), A, X, 2 * n)              # (any order of summation)
+    _by_rows(ctx().rsvd_stage_gemm_atn(A, Q), A.T, Q, 2 * m)
+    # products just below the largest number: their leading parts alone are above it
+    big = 1.8446e19
+    A = torch.full((m, n), big, device="cuda:0")
+    cols = torch.arange(l, device="cuda:0") * 5 % n
+    X, Q = torch.zeros(n, l, device="cuda:0"), torch.zeros(m, l, device="cuda:0")
+    X[cols, torch.arange(l)] = -big
+    Q[cols, torch.arange(l)] = big
+    assert bool((ctx().rsvd_stage_gemm_an(A, X) == (A[0, 0] * -A[0, 0])).all())
+    assert bool((ctx().rsvd_stage_gemm_atn(A, Q) == (A[0, 0] * A[0, 0])).all())
+    assert bool(torch.isfinite(A[0, 0] * A[0, 0]))
 
 
 # column tiles of 80 to 144, two and three of them; at 6000 x 1500, l = 280 and 20000 x 5000, l = 140 tiles of up to 128 columns, which
