@@ -121,9 +121,9 @@ enum GemmKind { GEMM_F32 = 0, GEMM_F64 = 1, GEMM_F32_ACC64 = 2 };  // last: fp32
 // Bytes of split-K scratch the heuristic would use for this shape.
 size_t gemm_partial_bytes(const rsvd_ctx *ctx, GemmKind kind, int trans_a, int64_t M, int64_t N, int64_t K);
 hipError_t gemm_launch(rsvd_ctx *ctx, hipStream_t s, GemmKind kind, const GemmDesc &d);
-// Bytes in which an fp32 product with a K x N operand B keeps that operand split once and for all tiles (0: not used).
+// Bytes in which an fp32 product of M x K and K x N keeps its second operand split once and for all tiles (0: not used).
 // Without them the product gives the same result, bit for bit, in more time.
-size_t gemm_packed_bytes(int64_t K, int64_t N);
+size_t gemm_packed_bytes(int64_t M, int64_t N, int64_t K);
 hipError_t gemm_split_init_device(rsvd_ctx *ctx);
 
 // ---------------------------------------------------------------- sketch

@@ -643,6 +643,16 @@ struct GemmDispatch {
     return c.splits > 1 ? (size_t)c.splits * (size_t)M * (size_t)N * sizeof(TAcc) : 0;
   }
 
+  // 16-byte vector loads need aligned bases, leading dimensions and extents.
+  static bool vector_loads(const GemmDesc &d) {
+    constexpr int V = 16 / sizeof(TIn);
+    const int64_t a_contig = d.trans_a ? d.M : d.K;
+    return ((uintptr_t)d.A % 16 == 0) && ((uintptr_t)d.B % 16 == 0) && d.lda % V == 0 &&
+           d.ldb % V == 0 && a_contig % V == 0 && d.N % V == 0 &&
+           (d.batch == 1 || (d.stride_a % 16 == 0 && d.stride_b % 16 == 0)) &&
+           (d.B_alt == nullptr || (uintptr_t)d.B_alt % 16 == 0);
+  }
+
   static hipError_t launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d) {
     if (d.M <= 0 || d.N <= 0) return hipSuccess;
     const TileChoice t = choose_tile(d.M, d.N, d.K, sizeof(TAcc), d.trans_a != 0, d.upper_only != 0);
@@ -657,13 +667,7 @@ struct GemmDispatch {
     if (d.a_shift != nullptr && (d.dead != nullptr || d.trans_c || d.alpha != 1.0 || d.beta != 0.0 || d.batch != 1))
       return hipErrorInvalidValue;
     const GemmParams P = make_params(d, c, d.upper_only ? t.bm : 0, d.upper_only ? t.bn : 0);
-    // 16-byte vector loads need aligned bases, leading dimensions and extents.
-    constexpr int V = 16 / sizeof(TIn);
-    const int64_t a_contig = d.trans_a ? d.M : d.K;
-    const bool vec = ((uintptr_t)d.A % 16 == 0) && ((uintptr_t)d.B % 16 == 0) && d.lda % V == 0 &&
-                     d.ldb % V == 0 && a_contig % V == 0 && d.N % V == 0 &&
-                     (d.batch == 1 || (d.stride_a % 16 == 0 && d.stride_b % 16 == 0)) &&
-                     (d.B_alt == nullptr || (uintptr_t)d.B_alt % 16 == 0);
+    const bool vec = vector_loads(d);
     hipError_t e;
     {
       ProfScope ps(ctx, s, d.prof_kind);

@@ -225,7 +225,7 @@ static Layout make_layout(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t m, int6
   L.packed = off;
   L.packed_bytes = 0;
   if (dtype == RSVD_F32) {
-    const size_t pn = gemm_packed_bytes(n, l), pm = gemm_packed_bytes(m, l);      // l <= min(m, n): R^-1 fits as well
+    const size_t pn = gemm_packed_bytes(m, l, n), pm = gemm_packed_bytes(n, l, m);      // l <= min(m, n): R^-1 fits as well
     L.packed_bytes = align_up(pn > pm ? pn : pm, 256);
   }
   return L;

@@ -31,9 +31,12 @@ def _check(got, A, X):
 
 
 # each with at least 2^29 multiply-adds, below which the fp32 instruction is used: column tiles of 48 to 144, one to
-# three of them, k and row counts around multiples of 32, 128 and 256
+# three of them, k and row counts around multiples of 32, 128 and 256; the second half fills the chip in both directions and with both
+# kinds of loads, so that every instance of the kernel is reached
 SHAPES = [(70000, 255, 33), (33000, 257, 64), (30011, 1001, 61), (20001, 383, 81), (13001, 513, 97), (10007, 769, 128),
-          (17000, 289, 129), (12001, 320, 145), (8003, 479, 176), (9001, 353, 289), (4999, 385, 383), (46000, 128, 128)]
+          (17000, 289, 129), (12001, 320, 145), (8003, 479, 176), (9001, 353, 289), (4999, 385, 383), (46000, 128, 128),
+          (30000, 1024, 48), (60000, 500, 60), (15000, 1504, 80), (11000, 1600, 96), (21000, 600, 112), (40001, 333, 129),
+          (18003, 640, 176), (24000, 700, 210), (15000, 1052, 380), (9004, 1004, 288), (12001, 1032, 160)]
 
 
 @pytest.mark.parametrize("m,n,l", SHAPES)

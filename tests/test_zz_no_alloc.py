@@ -61,12 +61,13 @@ def test_static_scratch_entry_matches_rsvd_run_twice_in_a_row():
             assert torch.equal(got, ref), f"{cfg.name}: {name} differs from rsvd_run (info = NULL)"
 
 
-# fp32 problems that fit without the room for the split operand of their products, but not with it
+# fp32 problems of more than 128 columns; those with at least 2000 rows and columns fit without the room for the split operand of
+# their products, but not with it
 @pytest.mark.parametrize("m,n,k,p", [(6000, 2000, 120, 10), (4000, 3000, 120, 10), (8561, 1035, 130, 10)])
 def test_static_scratch_entry_matches_rsvd_run_beyond_128_columns(m, n, k, p):
     say("static", m, n, k, p)
     c = ctx()
-    assert c.workspace_bytes(0, m, n, k, p) > 32 << 20
+    assert n < 2000 or c.workspace_bytes(0, m, n, k, p) > 32 << 20
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(m)
     A = torch.randn(m, 200, device="cuda:0", generator=gen) * torch.exp(-torch.arange(200, device="cuda:0") / 40.0)
