@@ -409,6 +409,40 @@ constexpr int kPanelThreads = 512;        // (1024: the factoring wavefront has 
 constexpr int kPanelMat = 16 * 17;
 constexpr size_t kPanelFixed = (8 * 256 + 256 + 16 + 3 * kPanelMat) * sizeof(double);
 
+// Replacement columns of a panel in LDS.  A group of the generator holds four consecutive elements of the panel: with many columns to
+// replace the threads share out the groups, with few of them the elements (1024 x 16, fifteen columns replaced: 131 us
+// element by element, 82 in groups).  A call of its own, or its registers cost the factorisation some of theirs.
+__device__ __attribute__((noinline)) void panel_refill(float *Y, int rows, int l, int ldy, unsigned dead, double scale,
+                                                       uint32_t stream, uint64_t seed) {
+  const int nf = __popc(dead);
+  const bool groups = 4 * nf >= l;
+  const int count = groups ? (rows * l + 3) / 4 : rows * nf;
+  for (int i = threadIdx.x; i < count; i += kPanelThreads) {
+    int e = 4 * i, only = -1;                        // first element of the group; the one that is asked for, or all of them
+    if (!groups) {
+      const int r = i / nf;
+      unsigned left = dead;
+      for (int n = i - r * nf; n > 0; --n) left &= left - 1u;
+      e = r * l + __ffs(left) - 1;
+      only = e & 3;
+      e &= ~3;
+    }
+    int r = e / l, c = e - r * l, at[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool take = r < rows && (only < 0 ? ((dead >> c) & 1u) != 0u : only == u);
+      at[u] = take ? r * ldy + c : -1;
+      if (++c == l) { c = 0; ++r; }
+    }
+    if (at[0] < 0 && at[1] < 0 && at[2] < 0 && at[3] < 0) continue;
+    double z[4];
+    philox_normals<true>((uint64_t)(e >> 2), stream, seed, z);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (at[u] >= 0) Y[at[u]] = (float)(scale * z[u]);
+  }
+}
+
 __global__ __launch_bounds__(kPanelThreads) void panel_qr_kernel(const PanelParams P) {
   constexpr int LD = 17, NT = kPanelThreads;
   if (P.skip_flag != nullptr && *P.skip_flag != 0) return;
@@ -523,41 +557,9 @@ __global__ __launch_bounds__(kPanelThreads) void panel_qr_kernel(const PanelPara
         for (int v = 0; v < 4; ++v) Y[(16 * t + Mfma<float>::row(lane, v)) * ldy + lc] = acc[v];
       }
     }
-    // ---- replacement columns.  A group of the generator holds four consecutive elements of the panel: with many columns to
-    // replace the threads share out the groups, with few of them the elements (1024 x 16, fifteen columns replaced: 131 us
-    // element by element, XXX in groups)
     if (dead != 0u) {
       __syncthreads();
-      const int nf = __popc(dead);
-      const bool groups = 4 * nf >= l;
-      for (int i = tid; i < (groups ? (rows * l + 3) / 4 : rows * nf); i += NT) {
-        int e = 4 * i, only = -1;                      // first element of the group; the one that is asked for, or all of them
-        if (!groups) {
-          const int r = i / nf;
-          unsigned left = dead;
-          for (int n = i - r * nf; n > 0; --n) left &= left - 1u;
-          e = r * l + __ffs(left) - 1;
-          only = e & 3;
-          e &= ~3;
-        }
-        int r = e / l, c = e - r * l;
-        unsigned take = 0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if (r < rows && (only < 0 ? ((dead >> c) & 1u) != 0u : only == u)) take |= 1u << u;
-          if (++c == l) { c = 0; ++r; }
-        }
-        if (take == 0u) continue;
-        double z[4];
-        philox_normals<true>((uint64_t)(e >> 2), P.refill_stream + (uint32_t)round, P.seed, z);
-        r = e / l;
-        c = e - r * l;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if ((take >> u) & 1u) Y[r * ldy + c] = (float)(P.refill_scale * z[u]);
-          if (++c == l) { c = 0; ++r; }
-        }
-      }
+      panel_refill(Y, rows, l, ldy, dead, P.refill_scale, P.refill_stream + (uint32_t)round, P.seed);
     }
   }
   __syncthreads();

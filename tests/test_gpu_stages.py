@@ -235,7 +235,7 @@ def test_jacobi_matches_oracle(dt, l):
 # Small fp32 panels are orthonormalised in one workgroup up to 16 columns and 1024 rows: one column, rows that are no multiple of
 # 16, the largest panel, the first ones beyond, and columns that depend on others (replaced, the same either way).
 @pytest.mark.parametrize("rows,l,rank", [(1, 1, 1), (17, 1, 1), (40, 16, 16), (333, 7, 7), (1024, 16, 16), (1025, 16, 16), (1024, 17, 17),
-                                         (500, 13, 9), (64, 16, 15)])
+                                         (500, 13, 9), (64, 16, 15), (1001, 15, 8), (777, 6, 3), (1024, 16, 14)])
 def test_orthonormalize_small_panels(rows, l, rank):
     say("small panel", rows, l, rank)
     c = ctx()
