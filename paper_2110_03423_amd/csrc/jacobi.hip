@@ -837,7 +837,9 @@ __global__ __launch_bounds__(1024) void jb_panel_kernel(T *__restrict__ Mt, T *_
 // accumulate T <- T J, and the panel is multiplied by T once, again on the matrix cores.  Rotation formulas, thresholds
 // and the stopping rule are those of the column-by-column kernel; the first round sees exact inner products, later
 // rounds the tracked ones (their error is of second order in the rotation angles and is wiped out by the next visit,
-// which forms G afresh).
+// which forms G afresh).  T is accumulated in fp64 and rounded once: an error of its large elements is common to a whole
+// column, where the errors of rotated columns average out, and those of (c, s) and of the updates in fp32 point the same way for
+// thousands of rotations (singular values off by 8, 22 and 34 eps at l = 129, 300, 576, now 1.2 to 1.7; 1 % more time).
 //
 // A sweep is a tournament over the column blocks: nblk2 - 1 steps of nblk2 / 2 block pairs.  A pair's task rotates the
 // b x b pairs of columns across its two blocks (b rounds: pair i of round r is (i, b + (i + r) mod b)), in the first step
@@ -893,6 +895,19 @@ template <bool INTRA> __device__ __forceinline__ void jg_pair(int i, int &p, int
     p = mp = i;
     q = kJgB + i;
     mq = kJgB + ((i - 1) & (kJgB - 1));
+  }
+}
+
+// The columns that pair i of round r rotates.
+template <bool INTRA> __device__ __forceinline__ void jg_columns(int i, int r, int &p, int &q) {
+  if (INTRA) {
+    const int h = i & 7, base = (i >> 3) * kJgB, n = kJgB - 1;
+    const int a = h - r, b = n - h - r;                            // (r < 15: one turn at most)
+    p = base + (a < 0 ? a + n : a);
+    q = base + (h == 0 ? n : (b < 0 ? b + n : b));
+  } else {
+    p = i;
+    q = kJgB + ((i + r) & (kJgB - 1));
   }
 }
 
@@ -975,7 +990,8 @@ __global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__
   extern __shared__ __attribute__((aligned(16))) double lds_raw[];
   T *Pc = reinterpret_cast<T *>(lds_raw);                      // [2b][ldp]: column c of the panel, zero padded
   T *G0 = Pc + (size_t)kJgN * ldp;                             // G, even rounds
-  T *R4 = G0 + kJgMat;                                         // four matrices: the five partial sums of G, then T0, T1, G1 and the (c, s) of every round
+  T *R4 = G0 + kJgMat;                                         // four matrices: the five partial sums of G, then T, G1 (the third) and the (c, s) of every round
+  double *Tm = reinterpret_cast<double *>(R4);                 // T[k][j], in the place of two of them in fp32, of one in fp64
   T *CS = R4 + 3 * kJgMat;                                     // [rounds][16 pairs][c, s]
   __shared__ int rotations, task;
   int ticket = 0;
@@ -1108,8 +1124,8 @@ __global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__
       // The rounds.  Wavefronts 0-3 (one per SIMD; what bounds a round is the number of instructions they issue, one every
       // four cycles): G <- J^T G J, thread (a, bb) the rows of pair a and the columns of pair bb; every lane works out the
       // rotation of pair bb, and the first sixteen leave (c, s) of the round in LDS.  Wavefronts 4-11: T <- T J one round
-      // behind, thread (rr, bb) row rr and the columns of pair bb.  One barrier per round (G and T alternate between two
-      // copies).
+      // behind, in fp64, thread (rr, bb) row rr and the columns of pair bb.  One barrier per round (G alternates between two
+      // copies; the two elements of T that a thread changes are its own in that round).
       float rho = 0.f;
       auto run_rounds = [&](auto kind, int r0, int count) {        // rounds r0, ... of the task
         constexpr bool INTRA = decltype(kind)::value;
@@ -1149,22 +1165,26 @@ __global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__
           __syncthreads();
         } else {
           const int rr = (tid - 256) >> 4, bb = tid & 15;
-          int pb, qb, mpb, mqb;
-          jg_pair<INTRA>(bb, pb, qb, mpb, mqb);
           const T *cs = CS + bb * 2;
+          double *Tr = Tm + rr * kJgLd;
           for (int r = -1; r < count; ++r) {                       // T <- T J_r, one round behind
             if (r >= 0 && wave < 12) {
-              const int odd = (r0 + r) & 1;
-              const T *Ts = R4 + odd * kJgMat + rr * kJgLd;
-              T *Td = R4 + (odd ^ 1) * kJgMat + rr * kJgLd;
-              const T cb = cs[r * 32], sb = cs[r * 32 + 1];
-              T tp = Ts[pb], tq = Ts[qb];
-              if (r0 + r == 0) {                                   // (T is the identity)
-                tp = rr == pb ? (T)1 : (T)0;
-                tq = rr == qb ? (T)1 : (T)0;
+              int pb, qb;
+              jg_columns<INTRA>(bb, r, pb, qb);
+              double cb = (double)cs[r * 32], sb = (double)cs[r * 32 + 1];
+              if (sizeof(T) == 4) {
+                // (c, s) of the fp32 instructions is off length 1 by up to 1e-7, to one side for small angles
+                const double off = 0.5 * fma(sb, sb, fma(cb, cb, -1.0));
+                cb -= cb * off;
+                sb -= sb * off;
               }
-              Td[mpb] = cb * tp - sb * tq;
-              Td[mqb] = sb * tp + cb * tq;
+              double tp = Tr[pb], tq = Tr[qb];
+              if (r0 + r == 0) {                                   // (T is the identity)
+                tp = rr == pb ? 1.0 : 0.0;
+                tq = rr == qb ? 1.0 : 0.0;
+              }
+              Tr[pb] = cb * tp - sb * tq;
+              Tr[qb] = sb * tp + cb * tq;
             }
             __syncthreads();
           }
@@ -1177,14 +1197,13 @@ __global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__
       rho_bits = rotations;
     }
 
-    const T *Tf = R4 + (rounds & 1) * kJgMat;                              // T[k][j]
     if (rho_bits != 0) {
       // panel out: (P T)^T = T^T P^T in 16 x 16 blocks; wavefront w takes the output columns jb * 16 ... and the row
       // blocks rb, rb + 8, ..., two of them at a time
       const int jb = wave & 1;
       T ta[kJgN / 4];
 #pragma unroll
-      for (int ks = 0; ks < kJgN / 4; ++ks) ta[ks] = Tf[(4 * ks + kq) * kJgLd + jb * 16 + r16];     // A[i = column][k] = T[k][column]
+      for (int ks = 0; ks < kJgN / 4; ++ks) ta[ks] = (T)Tm[(4 * ks + kq) * kJgLd + jb * 16 + r16];     // A[i = column][k] = T[k][column]
       const int nrb = lp / 16;
       for (int rb = wave >> 1; rb < nrb; rb += 16) {
         const int rb2 = rb + 8;
@@ -1230,8 +1249,8 @@ __global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__
       T ta[2][kJgN / 4];
 #pragma unroll
       for (int ks = 0; ks < kJgN / 4; ++ks) {
-        ta[0][ks] = Tf[(4 * ks + kq) * kJgLd + r16];
-        ta[1][ks] = Tf[(4 * ks + kq) * kJgLd + 16 + r16];
+        ta[0][ks] = (T)Tm[(4 * ks + kq) * kJgLd + r16];
+        ta[1][ks] = (T)Tm[(4 * ks + kq) * kJgLd + 16 + r16];
       }
       for (int rb = wave; rb < lp / 16; rb += 16) {
         const int row = rb * 16 + r16;

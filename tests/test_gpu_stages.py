@@ -276,6 +276,24 @@ def test_block_jacobi_edges(dt, l):
     assert np.abs(np.linalg.norm(W, axis=0) - 1).max() <= 4 * eps * np.sqrt(20 * l)
 
 
+@pytest.mark.parametrize("l", [129, 300, 576])
+@pytest.mark.parametrize("cond", [1.0, 1e3])
+def test_block_jacobi_values_do_not_drift(l, cond):
+    """The rotations of a visit are accumulated in fp64 and rounded once, and so are the columns: a random walk of two roundings per
+    visit of a column block, blocks x sweeps of them (rotations in fp32 shrink or stretch a column the same way every time: 8, 20 and 33
+    eps at these orders)."""
+    say("block jacobi values", l, cond)
+    M = workloads.gaussian_matrix(l, l, l, np.float32) if cond == 1.0 else workloads.graded_matrix(l, l, cond, seed=l, dtype=np.float32)
+    sig, X, W, info = ctx().rsvd_stage_jacobi(to_dev(M))
+    want = np.linalg.svd(M.astype(np.float64), compute_uv=False)
+    # relative to the value where it is resolved in fp32, else to what a rounding of the columns moves it by
+    err = (to_np(sig).astype(np.float64) - want) / np.maximum(want, want[0] * 1e-2)
+    eps = np.finfo(np.float32).eps
+    bound = 0.5 * eps * np.sqrt(-(-l // 16) * info.jacobi_sweeps)
+    assert info.status == 0
+    assert np.sqrt(np.mean(err ** 2)) <= bound and abs(np.mean(err)) <= bound / 2
+
+
 def test_block_jacobi_on_two_streams():
     """Two decompositions share the chip: neither waits for workgroups of its own that are not running yet."""
     import torch
