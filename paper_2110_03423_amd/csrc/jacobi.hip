@@ -10,7 +10,7 @@
 //
 // Stopping rule (the paper gives none): a sweep in which every pair satisfies
 // |a_p . a_q| <= tol * ||a_p|| * ||a_q||, tol = eps * sqrt(l); at most 60 sweeps (24 in the block path, whose
-// launches are all issued in advance).
+// launches beyond the orders of the one-launch kernel are all issued in advance).
 // The sweep that would only confirm this is saved when the rate of the last two sweeps says what it would find
 // (jacobi_done below): with rho the largest relative inner product a sweep rotated away, the next sweep meets about
 // rho^2 where the method converges quadratically (the paper: "3-4 iterations ... converges quadratically"; taken for
@@ -878,6 +878,9 @@ template <typename T> __host__ __device__ constexpr size_t jg_lds_bytes(int l) {
 
 // Longest columns (a wavefront stages a column through this many / 64 registers); LDS ends at about the same order.
 template <typename T> __host__ __device__ constexpr int jg_max_order() { return sizeof(T) == 4 ? 1088 : 512; }
+constexpr size_t kJgLds = 160 * 1024 - 1024;      // dynamic LDS of the kernel, beside the little it has by itself
+static_assert(jg_lds_bytes<float>(1088) <= kJgLds && jg_lds_bytes<float>(1089) > kJgLds, "largest fp32 order of the flow kernel");
+static_assert(jg_lds_bytes<double>(464) <= kJgLds && jg_lds_bytes<double>(465) > kJgLds, "largest fp64 order of the flow kernel");
 
 // Pair i of a round is always the columns in slots p and q of G and T; behind the round the contents of these slots move to
 // slots mp and mq, so that the next round finds its pairs in the same places: no address depends on the round.  INTRA,
@@ -1417,7 +1420,7 @@ size_t jacobi_scratch_bytes(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t l) {
 // are rotated in place by the panel kernel.
 template <typename T>
 static bool jb_takes_flow(const rsvd_ctx *ctx, int b, int l) {
-  return b == kJgB && l <= jg_max_order<T>() && jg_lds_bytes<T>(l) + 1024 <= ctx->lds_per_block;
+  return b == kJgB && l <= jg_max_order<T>() && jg_lds_bytes<T>(l) <= kJgLds && kJgLds + 1024 <= ctx->lds_per_block;
 }
 
 template <typename T>
@@ -1523,7 +1526,7 @@ static hipError_t launch_lds_g(hipStream_t s, int nt, int G, int rpl, size_t lds
   return hipErrorNotSupported;
 }
 
-// The kernels of this file are launched with up to 156 KB of dynamic LDS: the limit is raised here, once per
+// The kernels of this file are launched with up to 156 KB of dynamic LDS (jb_flow_kernel: kJgLds): the limit is raised here, once per
 // context (with its device current), for every instantiation the dispatch above can reach.
 template <typename T, typename TIn, int RPL>
 static void raise_lds_limit_lds(hipError_t &e) {
@@ -1566,10 +1569,10 @@ hipError_t jacobi_init_device(rsvd_ctx *ctx) {
   raise_lds_limit_panels<double>(e);
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(&jb_flow_kernel<float>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kJgLds);
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(&jb_flow_kernel<double>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kJgLds);
   return e;
 }
 
