@@ -1380,7 +1380,8 @@ static size_t jacobi_jglobal_bytes(int64_t l) {
   return (size_t)l * (size_t)jacobi_ldm((int)l, 16, 8) * 8;
 }
 
-// Units (8 bytes) per lane for order l: ceil(l / V / 32), rounded up to an instantiated value.
+// Units (8 bytes) per lane for order l: ceil(l / V / 32), rounded up to one of these values; kernels exist for those of orders beyond
+// the flow kernel (16 and more in fp64, 18 and more in fp32), from the others follows the block width only.
 static int jb_units_per_lane(rsvd_dtype dtype, int64_t l) {
   const int v = 8 / (int)dtype_size(dtype);
   const int need = (int)ceil_div(ceil_div(l, v), 32);
@@ -1472,8 +1473,16 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
     go(0, 0, kJbMaxSweeps, 0);                                 /* applies the T of the last round */            \
   } break
     switch (nv) {                                              // (smaller orders take the flow kernel)
-      RSVD_JB_CASE(14); RSVD_JB_CASE(16); RSVD_JB_CASE(18); RSVD_JB_CASE(20); RSVD_JB_CASE(24);
-      default: return hipErrorNotSupported;
+      RSVD_JB_CASE(18); RSVD_JB_CASE(20); RSVD_JB_CASE(24);
+      default:
+        if constexpr (sizeof(T) == 8) {
+          switch (nv) {
+            RSVD_JB_CASE(16);
+            default: return hipErrorNotSupported;
+          }
+        } else {
+          return hipErrorNotSupported;
+        }
     }
 #undef RSVD_JB_CASE
   }
@@ -1548,7 +1557,7 @@ static void raise_lds_limit_panel(hipError_t &e) {
 }
 template <typename T>
 static void raise_lds_limit_panels(hipError_t &e) {
-  raise_lds_limit_panel<T, 14>(e); raise_lds_limit_panel<T, 16>(e);
+  if constexpr (sizeof(T) == 8) raise_lds_limit_panel<T, 16>(e);
   raise_lds_limit_panel<T, 18>(e); raise_lds_limit_panel<T, 20>(e); raise_lds_limit_panel<T, 24>(e);
 }
 
