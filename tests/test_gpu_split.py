@@ -146,3 +146,59 @@ def test_without_room_for_the_packed_operand(m, n, k, p, q):
     assert a[3].status == 0 and b[3].status == 0
     for x, y in zip(a[:3], b[:3]):
         assert bool((x == y).all())
+
+
+def _low_rank(m, n, r, seed, batch=None):
+    """r singular values from 1 down to 0.05, exact to fp32 rounding."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(seed)
+    lead = () if batch is None else (batch,)
+    U = torch.linalg.qr(torch.randn(*lead, m, r, dtype=torch.float64, generator=g, device="cuda:0").cpu())[0].cuda()
+    V = torch.linalg.qr(torch.randn(*lead, n, r, dtype=torch.float64, generator=g, device="cuda:0").cpu())[0].cuda()
+    s = torch.logspace(0, np.log10(0.05), r, dtype=torch.float64, device="cuda:0")
+    return (torch.matmul((U * s).float(), V.transpose(-1, -2).float().contiguous())).contiguous()
+
+
+def _reconstructs(A, S, U, Vt):
+    """All of A lies in the k triplets: what is left is the rounding of A, of the factors and of k-term sums, and none of the values
+    is off by more than the norm of that."""
+    left = float((A.double() - (U.double() * S.double()) @ Vt.double()).norm() / A.double().norm())
+    assert left <= 16 * EPS * np.sqrt(U.shape[1]), left
+    I = np.eye(U.shape[1])
+    for B in (U.double().T.contiguous() @ U.double(), Vt.double() @ Vt.double().T.contiguous()):
+        assert np.abs(B.cpu().numpy() - I).max() <= 16 * EPS * np.sqrt(U.shape[1])
+
+
+# column tiles of 48, 96, 112, 128 and 144 (packed in both directions), odd sizes and 16-byte rows, k remainders of 3 to 32
+@pytest.mark.parametrize("m,n,k,p", [(40011, 1003, 30, 10), (30003, 1205, 80, 16), (20001, 1600, 100, 12), (20000, 1600, 100, 28),
+                                     (12001, 2203, 129, 8), (12000, 2208, 130, 10)])
+def test_centered(m, n, k, p):
+    """The column means are taken away while A is split."""
+    import torch
+    say("split centred", m, n, k, p)
+    A = _low_rank(m, n, k - 1, m)
+    A -= A.mean(0)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(n)
+    A += 0.01 * torch.randn(n, device="cuda:0", generator=g)          # (twice the size of the entries)
+    S, U, Vt, info, mean = ctx().rsvd_run_centered(A, k, p, 1, seed=5)
+    assert info.status == 0
+    mu = A.double().mean(0)
+    assert float((mean.double() - mu).abs().max()) <= 2 * EPS * float(mu.abs().max())
+    C = (A.double() - mu).float()
+    left = float((C.double() - (U.double() * S.double()) @ Vt.double()).norm() / C.double().norm())
+    # rounding of A, larger than C by |mu|, and of the factors
+    assert left <= (16 * np.sqrt(k) + 2 * float(A.double().norm() / C.double().norm())) * EPS, left
+
+
+@pytest.mark.parametrize("batch,m,n,k,p", [(24, 2003, 501, 30, 10), (16, 3000, 1000, 80, 16), (9, 2001, 1203, 100, 28), (3, 9000, 640, 48, 16)])
+def test_batched(batch, m, n, k, p):
+    say("split batch", batch, m, n, k, p)
+    A = _low_rank(m, n, k, batch, batch)
+    S, U, Vt, info = ctx().rsvd_run_batched(A, k, p, 1, seed=5)
+    assert info.status == 0
+    for b in range(batch):
+        _reconstructs(A[b], S[b], U[b], Vt[b])
+        one = ctx().rsvd_run(A[b].contiguous(), k, p, 1, seed=5 + b)[0]
+        assert float(((S[b] - one) / one).abs().max()) <= 64 * EPS
