@@ -27,10 +27,11 @@ if ROOT not in sys.path:
 
 # MI355X published peaks
 PEAK_HBM = 8.0e12                                # B/s
-PEAK_MFMA = {"f32": 157.3e12, "f64": 78.6e12}    # dense matrix FLOP/s
+# dense matrix FLOP/s; "split": fp32 products on the bf16 pipe (2.5 PFLOP/s), six of its products for one of fp32
+PEAK_MFMA = {"f32": 157.3e12, "f64": 78.6e12, "split": 2.5e15 / 6}
 
 # Kernel classes that are one kernel template doing one job are priced together: the two products with A
-# (Y = A X and Z = A^T X are `gemm_kernel` with op(A) = A / A^T, 2 m n l flops and one pass over A each).
+# (Y = A X and Z = A^T X are `gemm_kernel` or `gemm_split_kernel` with op(A) = A / A^T, 2 m n l flops and one pass over A each).
 GROUPS = {"a_pass": ("gemm_ax", "gemm_atx")}
 # Single-workgroup kernels on the serial path (a chain of dependent pivots / rotation rounds): bounded by latency,
 # not by a flop or byte rate; reported as time (and sweeps) only.
@@ -53,22 +54,33 @@ def measured_traffic(workload, kernel):
     return None
 
 
+def pipe(cfg, rows, cols, depth):
+    """The matrix pipe that a product of this shape is priced on: fp32 products of more than 32 columns with enough work are
+    split into bf16 parts (the library's own rule also looks at how the grid fills the chip)."""
+    if cfg.dtype == "f32" and cols > 32 and rows * cols * depth >= 1 << 29:
+        return "split"
+    return cfg.dtype
+
+
 def launch_model(name, cfg):
     """Algorithmic flops and bytes of ONE launch of a kernel class (every operand counted once), or None."""
     m, n, l, k, q = cfg.m, cfg.n, cfg.l, cfg.k, cfg.q
     sz = 4 if cfg.dtype == "f32" else 8
     if name in ("a_pass", "gemm_ax", "gemm_atx"):
         # read A once, read the skinny operand, write the result
-        return dict(flops=2.0 * m * n * l, bytes=(m * n + n * l + m * l) * sz, mfma=cfg.dtype)
+        return dict(flops=2.0 * m * n * l, bytes=(m * n + n * l + m * l) * sz, mfma=pipe(cfg, m, l, n))
     # classes whose launches alternate between m-row and n-row panels: q + 1 CholeskyQR passes on each side,
     # the average launch is priced
     rows = (m + n) / 2.0
     if name == "gram":
         return dict(flops=2.0 * rows * l * l, bytes=rows * l * sz + l * l * 8, mfma="f64")
     if name == "apply_rinv":
-        return dict(flops=2.0 * rows * l * l, bytes=2 * rows * l * sz + l * l * sz, mfma=cfg.dtype)
+        # (R^-1 is triangular; split only where its rows are no multiple of 16 bytes)
+        wide = cfg.dtype == "f32" and l > 128 and l % 4 != 0
+        return dict(flops=rows * l * (l + 1.0), bytes=2 * rows * l * sz + l * l * sz,
+                    mfma=pipe(cfg, rows, l, l) if wide else cfg.dtype)
     if name == "lift":
-        return dict(flops=2.0 * rows * l * k, bytes=rows * (l + k) * sz, mfma=cfg.dtype)
+        return dict(flops=2.0 * rows * l * k, bytes=rows * (l + k) * sz, mfma=pipe(cfg, rows, k, l))
     if name == "sketch":
         return dict(flops=None, bytes=n * l * sz)
     return None

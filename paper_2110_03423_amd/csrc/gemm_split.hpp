@@ -21,11 +21,12 @@
 // rows a quarter-wavefront touches over all banks without padding.  Loads are unaligned-safe (a vector load of
 // gfx950 needs the alignment of its element only): odd leading dimensions and odd N take the same path.
 //
-// Both operands are double-buffered in LDS.  What bounds the kernel is the matrix pipe as far as the chip's power lets it
-// run (65536 x 16384, l = 576: pipe busy 61 % of the cycles at 2.0 GHz), so everything else is put in its shadow: the vector
-// instructions that split the next tile of A are issued among the matrix instructions of the current one, the loads of
-// the tile after it stay in flight across the barrier, and a wide B is split once (split_pack_kernel) and copied to LDS
-// without registers.  Measured against the fp32 instruction: 65536 x 16384, l = 576: A X 9.21 -> 5.81 ms, A^T X 10.04 -> 5.96 ms;
+// Both operands are double-buffered in LDS, and everything but the matrix instructions is put in their shadow: the vector
+// instructions that split the next tile of A are issued among the matrix instructions of the current one, the loads of the tile
+// after it stay in flight across the barrier, and a wide B is split once (split_pack_kernel) and copied to LDS without registers.
+// What bounds a wide product is then the power of the chip: at 65536 x 16384, l = 576, the matrix pipe is busy for 68 % of the cycles
+// and the clock comes down to 1.6 GHz (2.0 to 2.1 under the fp32 instruction).  Narrow ones (up to 128 columns) wait for A.
+// Measured against the fp32 instruction: 65536 x 16384, l = 576: A X 9.21 -> 5.81 ms, A^T X 10.04 -> 5.96 ms;
 // 4001 x 50021, l = 210: 1.26 -> 0.54 and 1.27 -> 0.56 ms; 30011 x 2999, l = 61 (odd strides): 0.178 -> 0.122 and 0.206 -> 0.104 ms.
 // Relative error against 64 bits at K = 16384: 2.3e-6 -> 0.8e-6.
 #pragma once
