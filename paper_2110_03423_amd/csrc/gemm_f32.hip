@@ -13,40 +13,43 @@ hipError_t gemm_split_init_device(rsvd_ctx *ctx) {
   return e == hipSuccess ? split_init_t() : e;
 }
 
-// Which products are split, by their shape.  Up to 32 columns both kernels wait for memory and the fp32 one needs no conversion
-// (65536 x 16384, l = 16: 5.7 TB/s), and below 2^29 multiply-adds (2000 x 500, l = 33: 19 us split, 14 us not) the longer prologue of
-// the large tiles costs more than the faster instruction brings.  Where the fp32 kernel has its 16-byte loads it also wins on
-//  - a k range of a few k-tiles, unless all of a 96 to 128 column tile shares the traffic of A: 1000000 x 64, l = 64: 122 us against
-//    205; 69568 x 192, l = 192: 71, 82; but 57504 x 176, l = 112: 43, 36;
-//  - up to 48 columns of A X, whose tiles of A are half of all LDS traffic, unless the k range is long (69808 x 464: 50, 55;
-//    126064 x 592: 92, 95; 62208 x 1200: 90, 81) and there is work (1872 x 9760: 36, 40; 768 x 30640: 45, 43), and of A^T X with fewer
-//    than 96 rows in a tile of 128 (48 x 593552: 78, 98; 96 x 139920: 41, 40);
+// Which products are split, by their shape (times in us, fp32 kernel against split one).  Up to 32 columns both kernels wait for
+// memory and the fp32 one needs no conversion (65536 x 16384, l = 16: 5.8 TB/s), and below 2^29 multiply-adds (2000 x 500, l = 33:
+// 22, 25) the longer prologue of the large tiles costs more than the faster instruction brings.  Where the fp32 kernel has its
+// 16-byte loads it also wins on
+//  - a k range of a few k-tiles, unless one column tile of 96 to 144 shares the traffic of A: 1000000 x 64, l = 64: 131, 217; 69568 x
+//    192, l = 192: 73, 84; but 57504 x 176, l = 112: 45, 38;
+//  - up to 48 columns of A X, whose tiles of A are half of all LDS traffic, unless the k range is long (69808 x 464: 53, 58;
+//    126064 x 592: 93, 92; 62208 x 1200: 90, 81) and there is work (1872 x 9760: 38, 40; 768 x 30640: 43, 42), and of A^T X with fewer
+//    than 96 rows in a tile of 128 (48 x 593552: 75, 90; 96 x 139920: 40, 40);
 //  - a triangular B (the applies of R^-1), which leaves only part of a short k range per column tile: its narrower tiles waste less
 //    of that (65536 x 576: 176, 224).
-// Otherwise: 10000 x 2000, l = 80: 48 -> 40 us; 50021 x 210, triangular, scalar loads: 86 -> 72; 65536 x 16384, l = 576: 9.2 -> 5.8 ms.
+// Otherwise: 10000 x 2000, l = 80: 56 -> 47; 50021 x 210, triangular, scalar loads: 86 -> 72; 65536 x 16384, l = 576: 9179 -> 5512.
 static bool takes_split(const GemmDesc &d, bool vec) {
   const double madds = (double)d.M * (double)d.N * (double)d.K * (double)d.batch;
   if (d.N <= 32 || madds < 536870912.0 || d.upper_only || d.alpha != 1.0 || d.beta != 0.0 || !split_fits(d.lda, d.ldb)) return false;
   if (!vec) return true;
   if (d.b_upper != 0) return false;
-  if (d.K < 208 && (d.N < 96 || d.N > 128)) return false;
+  if (d.K < 208 && (d.N < 96 || d.N > 144)) return false;
   if (d.N <= 48) return d.trans_a ? d.M >= 96 : (d.K >= 640 && madds >= 1073741824.0);
   return true;
 }
 // ... and by how the workgroups fill the chip: a split one takes a CU or half of one for 256 or 128 rows, where the fp32 kernel
-// has four smaller ones per CU.  What share of the places has to be taken depends on the k-tiles of a range (fp32, split in us):
-//  six and fewer   0.72 (1168 x 5984, l = 80) 35, 39; 0.59 (336 x 15904, l = 80) 33, 37; 0.78 (256 x 25456, l = 96) 38, 34
-//  up to fifteen   0.50 (256 x 18240, l = 224) 45, 53; 0.41 (1696 x 1312, l = 304) 43, 51; 0.55 (17808 x 240, l = 176) 42, 39
-//  more            0.50 (32848 x 768, l = 96) 73, 67; 0.53 (11328 x 576, l = 304) 87, 66
-//  scalar loads    0.32 (551 x 2534, l = 413) 44, 51; 0.44 (1724 x 1220, l = 476) 63, 52; 0.51 (13410 x 209, l = 153) 34, 29
-//  l <= 48         0.63 (41145 x 1908, l = 44) 104, 115; 0.83 (62208 x 1200) 90, 81
+// has four smaller ones per CU.  What share of the places has to be taken depends on the k-tiles of a range:
+//  six and fewer   0.72 (1168 x 5984, l = 80) 34, 40; 0.59 (336 x 15904, l = 80) 33, 38; 0.78 (256 x 25456, l = 96) 39, 39
+//  up to fifteen   0.41 (1696 x 1312, l = 304) 44, 47; 0.55 (17808 x 240, l = 176) 43, 40; A^T X (k from the long side) and ranges that
+//                  are not cut: 0.50 (18240 x 256, l = 224) 45, 43; 0.53 (34352 x 240, l = 96) 45, 38
+//  more            0.50 (768 x 32848, l = 96) 76, 63; 0.53 (576 x 11328, l = 304) 88, 56
+//  scalar loads    0.32 (551 x 2534, l = 413) 43, 52; 0.44 (1220 x 1724, l = 476) 58, 48; not cut: 0.26 (16809 x 407, l = 136) 70, 55
+//  l <= 48         0.63 (41145 x 1908, l = 44) 108, 116; 0.83 (62208 x 1200) 90, 81
 // A last wave that is nearly empty costs more than the faster instruction brings in narrow products: l = 48, 1.2 waves: 78592 x
-// 1200 109, 127; 1.4: 91648 x 4000 372, 358; l = 96, 1.05 waves: 68608 x 400 73, 80; 68608 x 1200 182, 181; l = 128: 68160 x 128
-// 45, 56; 68608 x 400 97, 93.
+// 1200 107, 126; 1.4: 91648 x 4000 366, 361; l = 96, 1.05 waves: 68608 x 400 76, 79; 68608 x 1200 180, 176; l = 128: 68160 x 128
+// 43, 56; 68608 x 400 97, 92.  (Over 260 random shapes in both directions the rule is within 1 % of the better kernel each time.)
 static bool fills_chip(const rsvd_ctx *ctx, const GemmDesc &d, bool vec, int bn, const SplitChoice &c) {
   const int64_t wgs = ceil_div(d.M, split_tile_m(bn)) * ceil_div(d.N, bn) * d.batch * c.splits;
   const int64_t places = (int64_t)ctx->cu_count * split_wgs_per_cu(bn), ktiles = c.k_per_split / kSplitBK;
-  const int share = !vec ? 35 : ktiles <= 6 ? 75 : d.N <= 48 ? 70 : ktiles < 16 ? 55 : 40;
+  const bool whole = c.splits == 1;
+  const int share = !vec ? (whole ? 25 : 35) : ktiles <= 6 ? 75 : d.N <= 48 ? 70 : ktiles >= 16 ? 40 : d.trans_a || whole ? 50 : 55;
   if (wgs * 100 < places * share) return false;
   if (!vec || d.N > 128 || wgs <= places) return true;
   const bool full = wgs * 100 >= ceil_div(wgs, places) * places * 65;
@@ -57,8 +60,8 @@ static bool fills_chip(const rsvd_ctx *ctx, const GemmDesc &d, bool vec, int bn,
 // The packed operand pays from two column tiles on; with one, whichever kernel reads the fp32 operand reads it about as often
 // as the packed one would be read, and the extra launch stays (20000 x 5000, l = 128: 205 us either way).  And it pays as long as
 // enough row tiles read it: with fewer, what the packing reads and writes is more than it saves (160 x 154432, l = 160: 185 us, split
-// in place 104; 1500 x 30000, l = 300, six row tiles: 202, 180; 2244 x 67556, l = 411, nine: 735, 754; 20000 x 5000, l = 576:
-// 779, 928).
+// in place 102; 1500 x 30000, l = 300, six row tiles: 202, 176; 2244 x 67556, l = 411, nine: 716, 754; 20000 x 5000, l = 576:
+// 760, 928).
 size_t gemm_packed_bytes(int64_t M, int64_t N, int64_t K) {
   return N > 128 && ceil_div(M, split_tile_m(split_tile_n(N))) >= 8 ? split_packed_bytes(K, N) : 0;
 }
