@@ -410,36 +410,55 @@ constexpr int kPanelMat = 16 * 17;
 constexpr size_t kPanelFixed = (8 * 256 + 256 + 16 + 3 * kPanelMat) * sizeof(double);
 
 // Replacement columns of a panel in LDS.  A group of the generator holds four consecutive elements of the panel: with many columns to
-// replace the threads share out the groups, with few of them the elements (1024 x 16, fifteen columns replaced: 131 us
-// element by element, 82 in groups).  A call of its own, or its registers cost the factorisation some of theirs.
+// replace the threads share out the groups, those of the same four columns to the lanes of a wavefront where l allows it, and
+// pairs that nobody wants are left out; with few columns they share out the elements.  1024 x 16, two rounds: fifteen columns replaced
+// 132 us element by element, now 80 (separate kernels 99); eight 96, now 74 (95).  What is left is the generator's
+// arithmetic on one CU: a call of rank 3 and below with panels of 1000 rows takes up to 15 % longer than with separate kernels (1024 x
+// 1024, l = 16, two power iterations: 275, 325 us; full rank 255, 228).  A call of its own, or its registers cost the
+// factorisation some of theirs.
 __device__ __attribute__((noinline)) void panel_refill(float *Y, int rows, int l, int ldy, unsigned dead, double scale,
                                                        uint32_t stream, uint64_t seed) {
   const int nf = __popc(dead);
-  const bool groups = 4 * nf >= l;
+  const bool groups = 4 * nf >= l, by_columns = l % 4 == 0;      // by_columns: a wavefront stays with the same four columns
   const int count = groups ? (rows * l + 3) / 4 : rows * nf;
   for (int i = threadIdx.x; i < count; i += kPanelThreads) {
-    int e = 4 * i, only = -1;                        // first element of the group; the one that is asked for, or all of them
+    int r, c, only = -1;                             // first element of the group; the one that is asked for, or all of them
     if (!groups) {
-      const int r = i / nf;
+      r = i / nf;
       unsigned left = dead;
       for (int n = i - r * nf; n > 0; --n) left &= left - 1u;
-      e = r * l + __ffs(left) - 1;
+      const int e = r * l + __ffs(left) - 1;
       only = e & 3;
-      e &= ~3;
+      r = (e & ~3) / l;
+      c = (e & ~3) - r * l;
+    } else if (by_columns) {
+      c = i / rows;
+      r = i - c * rows;
+      c *= 4;
+    } else {
+      r = 4 * i / l;
+      c = 4 * i - r * l;
     }
-    int r = e / l, c = e - r * l, at[4];
+    const uint64_t g = (uint64_t)((r * l + c) >> 2);
+    int at[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const bool take = r < rows && (only < 0 ? ((dead >> c) & 1u) != 0u : only == u);
       at[u] = take ? r * ldy + c : -1;
       if (++c == l) { c = 0; ++r; }
     }
-    if (at[0] < 0 && at[1] < 0 && at[2] < 0 && at[3] < 0) continue;
-    double z[4];
-    philox_normals<true>((uint64_t)(e >> 2), stream, seed, z);
+    const bool first = at[0] >= 0 || at[1] >= 0, second = at[2] >= 0 || at[3] >= 0;
+    if (!first && !second) continue;
+    const Philox4 p = philox4x32_10(g, stream, seed);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (at[u] >= 0) Y[at[u]] = (float)(scale * z[u]);
+    for (int h = 0; h < 2; ++h) {
+      if (h == 0 ? first : second) {
+        double z0, z1;
+        box_muller(uniform24(p.x[2 * h]), uniform24(p.x[2 * h + 1]), z0, z1);
+        if (at[2 * h] >= 0) Y[at[2 * h]] = (float)(scale * z0);
+        if (at[2 * h + 1] >= 0) Y[at[2 * h + 1]] = (float)(scale * z1);
+      }
+    }
   }
 }
 
