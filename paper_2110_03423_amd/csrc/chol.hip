@@ -412,9 +412,10 @@ constexpr size_t kPanelFixed = (8 * 256 + 256 + 16 + 3 * kPanelMat) * sizeof(dou
 // Replacement columns of a panel in LDS.  A group of the generator holds four consecutive elements of the panel: with many columns to
 // replace the threads share out the groups, those of the same four columns to the lanes of a wavefront where l allows it, and
 // pairs that nobody wants are left out; with few columns they share out the elements.  1024 x 16, two rounds: fifteen columns replaced
-// 132 us element by element, now 80 (separate kernels 99); eight 96, now 74 (95).  What is left is the generator's
-// arithmetic on one CU: a call of rank 3 and below with panels of 1000 rows takes up to 15 % longer than with separate kernels (1024 x
-// 1024, l = 16, two power iterations: 275, 325 us; full rank 255, 228).  A call of its own, or its registers cost the
+// 132 us element by element, now 80 (separate kernels 99); eight 96, now 74 (95).  What is left is the generator's arithmetic on one
+// CU, which the separate kernels spread over many.  So calls with panels of 1000 rows, l = 16 and most columns to replace take longer
+// than with separate kernels: 1024 x 1024, two power iterations, rank 1 takes 314 us (separate kernels 261), rank 3 326 (274), rank 7
+// 320 (285), rank 9 319 (299); rank 14 297 (346) and full rank 233 (271) less.  A call of its own, or its registers cost the
 // factorisation some of theirs.
 __device__ __attribute__((noinline)) void panel_refill(float *Y, int rows, int l, int ldy, unsigned dead, double scale,
                                                        uint32_t stream, uint64_t seed) {
