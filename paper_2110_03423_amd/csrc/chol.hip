@@ -412,8 +412,8 @@ constexpr size_t kPanelFixed = (8 * 256 + 256 + 16 + 3 * kPanelMat) * sizeof(dou
 // Replacement columns of a panel in LDS.  A group of the generator holds four consecutive elements of the panel: with many columns to
 // replace the threads share out the groups, those of the same four columns to the lanes of a wavefront where l allows it, and
 // pairs that nobody wants are left out; with few columns they share out the elements.  1024 x 16, two rounds: fifteen columns replaced
-// 132 us element by element, now 80 (separate kernels 99); eight 96, now 74 (95).  What is left is the generator's arithmetic on one
-// CU, which the separate kernels spread over many.  So calls with panels of 1000 rows, l = 16 and most columns to replace take longer
+// 132 us element by element, now 80; eight 96, now 74; separate kernels 83 to 99 and 84 to 95 on three machines.  What is left is
+// the generator's arithmetic on one CU, which the separate kernels spread over many.  So calls with panels of 1000 rows, l = 16 and most columns to replace take longer
 // than with separate kernels: 1024 x 1024, two power iterations, rank 1 takes 314 us (separate kernels 261), rank 3 326 (274), rank 7
 // 320 (285), rank 9 319 (299); rank 14 297 (346) and full rank 233 (271) less.  A call of its own, or its registers cost the
 // factorisation some of theirs.

@@ -839,7 +839,8 @@ __global__ __launch_bounds__(1024) void jb_panel_kernel(T *__restrict__ Mt, T *_
 // rounds the tracked ones (their error is of second order in the rotation angles and is wiped out by the next visit,
 // which forms G afresh).  T is accumulated in fp64 and rounded once: an error of its large elements is common to a whole
 // column, where the errors of rotated columns average out, and those of (c, s) and of the updates in fp32 point the same way for
-// thousands of rotations (singular values off by 8, 22 and 34 eps at l = 129, 300, 576, now 1.2 to 1.7; 1 % more time).
+// thousands of rotations (singular values off by 5.4, 11.5 and 21.6 eps at l = 129, 300, 576, rms, geometric mean over five kinds of spectrum; now 1.2,
+// 1.4 and 1.7; up to 1 % more time).
 //
 // A sweep is a tournament over the column blocks: nblk2 - 1 steps of nblk2 / 2 block pairs.  A pair's task rotates the
 // b x b pairs of columns across its two blocks (b rounds: pair i of round r is (i, b + (i + r) mod b)), in the first step
@@ -858,8 +859,8 @@ __global__ __launch_bounds__(1024) void jb_panel_kernel(T *__restrict__ Mt, T *_
 // What bounds a step is its chain: panel in 2.1 us, G 3.0, 16 rounds of ~0.4 (fp64; 0.3 in fp32), panel out 1.9, the
 // stores' arrival 1.3, the wait for them elsewhere ~1 (fp64, l = 288).  Against one launch per step with the rotations of
 // J a step behind (the launches of sweeps that are not needed come to a quarter of the time): whole decomposition
-// with a spectrum over three decades 1009 -> 685 us (fp64, l = 120), 2751 -> 1717 (fp64, 288), 1516 -> 897 (fp32, 210),
-// 5157 -> 3289 (fp32, 576).
+// of the triangular factor of a Gaussian matrix of l + 37 rows, 9 to 10 sweeps (8 at l = 210): 1526 -> 1018 us (fp64, l = 128), 4115 -> 2844
+// (fp64, 288), 2147 -> 1446 (fp32, 210), 7834 -> 5164 (fp32, 576).
 constexpr int kJgB = 16;                    // block width this kernel is written for
 constexpr int kJgN = 2 * kJgB;              // columns of a panel
 constexpr int kJgLd = kJgN + 1;             // row stride of G and T in LDS
