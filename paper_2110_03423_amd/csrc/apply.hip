@@ -8,7 +8,7 @@
 // (the upper triangle only: 144 values per lane at l = 128), so that only the rows of Y pass through LDS; a
 // workgroup walks over row tiles (workgroup g takes tiles g, g + G, ...), has the next tile's rows in flight while
 // the matrix cores work on the current one, and issues only the matrix instructions whose k range reaches the column
-// block (4 (j + 1) of them for block j instead of 4 NBLK).  One workgroup per CU, one wavefront per SIMD (the
+// block (4 (j + 1) of them for block j instead of 4 NBLK).  At large l one workgroup per CU, one wavefront per SIMD (the
 // registers: 144 for R^-1, 32 each for the accumulators, the A operands of a tile and the rows in flight); the tile
 // buffer in LDS is double, so that a tile costs one barrier.  (R^-1 in LDS instead: one LDS read per matrix
 // instruction, no faster than the general kernel; two workgroups per CU: the 256 registers left per wavefront
@@ -36,8 +36,18 @@ template <typename T, int NBLK> struct ApplyLds {
   static constexpr size_t bytes = (size_t)2 * 64 * SA * sizeof(T);
 };
 
+// Workgroups that share a CU: what the registers of a wavefront allow (105 at two column blocks in fp32, 231 at three in fp64).  A
+// batch has one problem's tiles walked by as many workgroups as its share of these places, so that the prologue, R^-1 into
+// the registers, is paid a few times a problem and not once per tile: 256 problems of 2000 rows, l = 32, 80 us an apply with one
+// workgroup per tile and one per CU at a time.  With this and the row ranges of the Gram matrices chosen for the whole batch
+// (syrk_split) such a call (2000 x 500, q = 1) takes 1520 us (before: 1847), 32 of 4000 x 1000 in fp64, l = 48, q = 2, 2452 (2558).
+template <typename T, int NBLK> constexpr int apply_wgs_per_cu() {
+  constexpr int words = NBLK * (int)(sizeof(T) / 4);
+  return words <= 2 ? 6 : words <= 4 ? 4 : words <= 6 ? 2 : 1;
+}
+
 template <typename T, int NBLK, int VEC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (apply_wgs_per_cu<T, NBLK>()))))
 void apply_tri_kernel(const ApplyParams P0) {
   ApplyParams P = P0;
   {
@@ -178,9 +188,9 @@ void apply_tri_kernel(const ApplyParams P0) {
 template <typename T, int NBLK>
 static hipError_t apply_run(const rsvd_ctx *ctx, hipStream_t s, ApplyParams P, int batch, bool vec) {
   typedef ApplyLds<T, NBLK> L;
-  // one workgroup per CU: a wavefront has its SIMD, and all of its registers, to itself
-  int grid = ctx->cu_count;
+  int grid = ctx->cu_count * apply_wgs_per_cu<T, NBLK>() / batch;
   if (grid > P.tiles) grid = P.tiles;
+  if (grid < 1) grid = 1;
   constexpr int V = 16 / sizeof(T);
   if (vec) hipLaunchKernelGGL((apply_tri_kernel<T, NBLK, V>), dim3(grid, batch), dim3(256), L::bytes, s, P);
   else hipLaunchKernelGGL((apply_tri_kernel<T, NBLK, 1>), dim3(grid, batch), dim3(256), L::bytes, s, P);

@@ -100,8 +100,12 @@ __device__ __forceinline__ void syrk_wave(const SyrkParams &P, TIn *Ys, int64_t 
   syrk_store<NBLK, W>(acc, out, P.l, lane, std::make_integer_sequence<int, NMINE>());
 }
 
+// Workgroups that share a CU in a batch, whose many short row ranges wait for memory more than for the matrix cores (registers would
+// allow as many at any order; LDS four at l = 128 in fp32, two in fp64).
+constexpr int syrk_wgs_per_cu(int nblk) { return nblk <= 2 ? 8 : nblk <= 4 ? 4 : 2; }
+
 template <typename TIn, int NBLK, int VEC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, syrk_wgs_per_cu(NBLK))))
 void gram_syrk_kernel(const SyrkParams P0) {
   SyrkParams P = P0;
   {
@@ -126,14 +130,16 @@ void gram_syrk_kernel(const SyrkParams P0) {
 // Rows per workgroup and number of workgroups: one workgroup per CU when the panel is long enough for that; a short
 // panel is cut so that a workgroup works for ~3 us (a k-tile of 32 rows takes 2.2 us of matrix instructions at
 // l = 128, where a wavefront has nine blocks, in proportion less below, and never less than its loads take), since
-// every workgroup pays for the l x l partial sum it leaves.
-static void syrk_split(const rsvd_ctx *ctx, int64_t rows, int64_t l, int64_t &rows_per_wg, int &wgs) {
+// every workgroup pays for the l x l partial sum it leaves.  The problems of a batch share the places of the chip: 256 of 2000 rows,
+// l = 32, take 500 rows a workgroup and leave four partial sums each, which the factorisation adds (13 and a reduction before).
+static void syrk_split(const rsvd_ctx *ctx, int64_t rows, int64_t l, int batch, int64_t &rows_per_wg, int &wgs) {
   const int64_t nblk = ceil_div(l, 16), nb2 = nblk * (nblk + 1) / 2;
   double per_ktile = 2.2 * (double)nb2 / 36.0;          // us; never less than the ~0.6 us a k-tile's loads take
   if (per_ktile < 0.6) per_ktile = 0.6;
   int64_t ktiles = (int64_t)(3.0 / per_ktile);
   if (ktiles < 1) ktiles = 1;
-  rows_per_wg = ceil_div(ceil_div(rows, (int64_t)ctx->cu_count), 32) * 32;
+  const int64_t places = (int64_t)ctx->cu_count * (batch > 1 ? syrk_wgs_per_cu((int)nblk) : 1);
+  rows_per_wg = ceil_div(ceil_div(rows * batch, places), 32) * 32;
   if (rows_per_wg < 32 * ktiles) rows_per_wg = 32 * ktiles;
   wgs = (int)ceil_div(rows, rows_per_wg);
   if (wgs < 1) wgs = 1;
@@ -144,7 +150,7 @@ int gram_syrk_max_order() { return 128; }
 size_t gram_syrk_partial_bytes(const rsvd_ctx *ctx, int64_t rows, int64_t l) {
   if (l > gram_syrk_max_order()) return 0;
   int64_t rpw; int wgs;
-  syrk_split(ctx, rows, l, rpw, wgs);
+  syrk_split(ctx, rows, l, 1, rpw, wgs);
   return wgs > 1 ? (size_t)wgs * (size_t)l * (size_t)l * sizeof(double) : 0;
 }
 
@@ -202,7 +208,7 @@ hipError_t gram_syrk_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int6
                             int *parts_out, int batch, int64_t stride, const int *skip_flag) {
   if (l < 1 || l > gram_syrk_max_order() || rows < 1 || batch < 1 || batch > 65535) return hipErrorInvalidValue;
   int64_t rpw; int wgs;
-  syrk_split(ctx, rows, l, rpw, wgs);
+  syrk_split(ctx, rows, l, batch, rpw, wgs);
   if (wgs > 1 && (partial == nullptr || partial_bytes < (size_t)wgs * l * l * sizeof(double))) return hipErrorInvalidValue;
   SyrkParams P;
   P.rows = rows; P.l = (int)l; P.Y = Y; P.ldy = ldy;

@@ -53,6 +53,35 @@ CASES = [
 ]
 
 
+# Batches that leave a problem fewer workgroups than it has 64-row tiles (triangular applies) and than its rows are cut into
+# when alone (Gram matrices): 6, 4, 2 and 1 workgroups of a CU over the batch, remainders of tiles and of row ranges.
+MANY = [("f32", 1000, 70, 15, 200), ("f32", 641, 90, 30, 257), ("f32", 2100, 140, 47, 70), ("f32", 1100, 300, 90, 40),
+        ("f64", 700, 60, 14, 300), ("f64", 1290, 99, 33, 90), ("f64", 833, 160, 50, 60)]
+
+
+@pytest.mark.parametrize("dt,m,n,l,batch", MANY)
+def test_large_batches_match_single_calls(dt, m, n, l, batch):
+    import torch
+    say("large batch", dt, m, n, l, batch)
+    t = torch.float32 if dt == "f32" else torch.float64
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(5)
+    decay = torch.exp(-torch.arange(n, dtype=t, device="cuda:0") * (3.0 / l))
+    A = torch.randn((batch, m, n), dtype=t, device="cuda:0", generator=gen) * decay
+    k, c = l - 5, ctx()
+    S, U, Vt, info = c.rsvd_run_batched(A, k, 5, 1, seed=60)
+    assert info.status == 0
+    eye = torch.eye(k, dtype=t, device="cuda:0")
+    off = float((U.transpose(1, 2).contiguous() @ U.contiguous() - eye).abs().max())
+    assert off <= parity.jacobi_tol(l, dt), off
+    for b in range(0, batch, 7):
+        S1, U1, Vt1, _ = c.rsvd_run(A[b], k, 5, 1, seed=60 + b)
+        # same Omega, same algorithm, other order of the long sums (the bound of the comparison below)
+        assert float((S[b] - S1).abs().max()) <= 200 * parity.EPS[dt] * np.sqrt(max(m, n)) * float(S1[0]), b
+        err = float(torch.linalg.norm(A[b] - (U[b] * S[b]) @ Vt[b])), float(torch.linalg.norm(A[b] - (U1 * S1) @ Vt1))
+        assert err[0] <= 1.001 * err[1] + 50 * parity.EPS[dt] * float(torch.linalg.norm(A[b])), (b, err)
+
+
 @pytest.mark.parametrize("base,batch,q", CASES, ids=lambda v: getattr(v, "name", str(v)))
 def test_batched_matches_oracle_and_single_calls(base, batch, q):
     import torch
