@@ -62,7 +62,7 @@ typedef enum {
  * (host memory; filling it forces a stream synchronisation). */
 typedef struct {
   int32_t status;          /* rsvd_status accumulated on the device */
-  int32_t jacobi_sweeps;   /* sweeps the small SVD used */
+  int32_t jacobi_sweeps;   /* sweeps the small SVD used, and corrections of the whole matrix behind them */
   int32_t refilled_columns;/* columns found linearly dependent and replaced by
                               fresh Gaussian directions, summed over all
                               orthonormalisations of the call.  A column counts

@@ -507,13 +507,33 @@ constexpr int kJbFroParts = 64;
 struct JbHeader {
   double fro2;            // ||M||_F^2 of the scaled matrix
   double unscale;         // the singular values of M are those of the scaled matrix times this
-  int counters[64];       // per outer sweep: bit pattern of the largest relative inner product rotated away
+  int counters[64];       // jb_panel_kernel, per outer sweep: bit pattern of the largest relative inner product rotated away
   double partial[kJbFroParts];   // sums of squares, one per workgroup of jb_fro_kernel
-  // jb_flow_kernel
-  int ticket;             // next task
-  int stop;               // != 0: converged
-  int finished[32];       // per outer sweep: block pairs whose columns of M are done
 };
+
+// One run of sweeps (jb_flow_kernel, jacobi_lds_kernel).
+struct JbRun {
+  unsigned long long sumsq[32];      // per sweep: sum of s^2 over its rotations (c, s), times kJbSumScale
+  int counters[32];                  // per sweep: bit pattern of the largest relative inner product rotated away
+  int finished[32];                  // per sweep: block pairs whose columns of M are done
+  int ticket;                        // next task
+  int stop;                          // 1: converged, 2: what is left is for the corrections of the whole matrix
+  int used;                          // sweeps done when it stopped
+  int pad;
+};
+constexpr int kPolishSteps = 10, kPolishPhases = 13;
+// The corrections of the whole matrix behind the first run, and the run behind those.
+struct JbSync {
+  JbRun run[2];
+  unsigned long long x2[kPolishSteps];      // per correction: sum of its squared angles times kPolishScale
+  int rho[kPolishSteps];                    // and the largest relative inner product it found
+  int done[kPolishSteps * kPolishPhases];   // tiles finished, phase by phase
+  int updates, converged;                   // how the corrections ended
+  int ticket, pad;                          // next tile
+  double fro2, unscale;                     // as in JbHeader
+};
+static_assert(sizeof(JbSync) % 8 == 0 && sizeof(JbSync) <= 4096, "lies at the start of an l x l slot");
+constexpr float kJbSumScale = 65536.f;
 
 // ||M||_F^2 in kJbFroParts partial sums (fixed assignment of elements and fixed order: reproducible).
 __global__ __launch_bounds__(256) void jb_fro_kernel(const double *__restrict__ M, int l, JbHeader *hdr) {
@@ -537,7 +557,7 @@ __global__ __launch_bounds__(256) void jb_fro_kernel(const double *__restrict__ 
 template <typename T>
 __global__ __launch_bounds__(256) void jb_init_kernel(const double *__restrict__ M, int l, T *__restrict__ Mt,
                                                       T *__restrict__ Jt, JbHeader *hdr, int rows,
-                                                      int *__restrict__ ver, int nver) {
+                                                      int *__restrict__ ver, int nver, JbSync *sync, int *__restrict__ ver2) {
   double fro2 = 0;
   for (int i = 0; i < kJbFroParts; ++i) fro2 += hdr->partial[i];
   double sc = 1.0, unscale = 1.0;
@@ -555,13 +575,19 @@ __global__ __launch_bounds__(256) void jb_init_kernel(const double *__restrict__
   }
   if (blockIdx.x == 0) {
     if (threadIdx.x < 64) hdr->counters[threadIdx.x] = 0;
-    if (threadIdx.x < 32) hdr->finished[threadIdx.x] = 0;
     for (int i = threadIdx.x; i < nver; i += blockDim.x) ver[i] = 0;
+    if (sync != nullptr) {
+      int *p = reinterpret_cast<int *>(sync);
+      for (int i = threadIdx.x; i < (int)(offsetof(JbSync, fro2) / sizeof(int)); i += blockDim.x) p[i] = 0;
+      for (int i = threadIdx.x; i < nver; i += blockDim.x) ver2[i] = 0;
+    }
     if (threadIdx.x == 0) {
-      hdr->ticket = 0;
-      hdr->stop = 0;
       hdr->fro2 = fro2 * sc * sc;
       hdr->unscale = unscale;
+      if (sync != nullptr) {
+        sync->fro2 = fro2 * sc * sc;
+        sync->unscale = unscale;
+      }
     }
   }
 }
@@ -960,6 +986,180 @@ __device__ __forceinline__ float jg_pair_params(const T *G, int p, int q, T tol,
   return rot ? (float)rel : 0.f;
 }
 
+// ---- corrections of the whole matrix at once ----
+//
+// The last sweeps turn columns that are nearly orthogonal by small angles, and such rotations commute up to the square of
+// the angles: all of them can be taken from one Gram matrix and applied together, as the orthogonal matrix exp(X) with
+// X[i][j] the angle of the pair (i, j), X antisymmetric.  What remains is of second order, as behind a sweep, but a correction is
+// a handful of l x l products on all CUs where a sweep is l - 1 rounds that wait for each other.  Sweeps alone -> with corrections, whole
+// decomposition: triangular factor of a Gaussian matrix of l + 37 rows, fp64 l = 110 991 -> 766 us, 288 2839 -> 2265, fp32 210 1574 -> 1251,
+// 450 4062 -> 3538; nearly aligned factors with s_i = exp(-3 i / l), fp64 110 581 -> 354 us, 288 1722 -> 1035, fp32 210 740 -> 477; clusters of
+// relative width 1e-5 0.87 ... 1.15 times as fast.  The columns end closer to orthogonal: G is in fp64 for either type, and a correction takes
+// along the small angles below the threshold of a rotation (singular vectors of 4001 x 50021, l = 210, q = 1, twelve matrices: error against
+// 64 bits 2.8e-5 -> 9.2e-6).
+//   G = M^T M, X;  Y = X X, Y2 = Y Y, Y3, Y4 as far as the size of X asks for;  E = exp(X) - I;  M <- M + M E, J <- J + J E.
+// exp(X) of an antisymmetric X is orthogonal: the series is cut where it is so to rounding (x: the Frobenius norm of X; the same angles are met by M and J, and E keeps the relative size of its elements, so short columns of M
+// keep their relative accuracy as in a sweep).  Angles, thresholds and the floor for zero columns are those of a rotation.
+// A correction that meets a larger x than it may, or one that does not shrink, does nothing and leaves the rest to sweeps, as inside a
+// cluster of nearly equal singular values, where the angles stay large however small the inner products.
+// Everything is decided from the counters of JbSync, which are sums of whole numbers and maxima: no order of arrival shows in the result.
+constexpr float kPolishScale = 140737488355328.f;            // 2^47; a tile adds at most 128, more than any correction may
+
+// Largest x for a series cut behind X^2 / 2 (1), X^3 (2), X^5 (3) and X^9 (4).  The 2-norm of X is x / 1.41 if all of it is one rotation and
+// about x / 2 as met behind a sweep; off orthogonality by that much: fp64 1e-15 (4: 1e-16), fp32 1e-8.  Beyond the last, X is
+// halved until it is below, and E doubled as often: E <- 2 E + E E.
+template <typename T> __host__ __device__ constexpr float polish_limit(int order) {
+  if (sizeof(T) == 4) return order == 1 ? 2e-3f : order == 2 ? 0.02f : order == 3 ? 0.15f : 0.75f;
+  return order == 1 ? 1e-5f : order == 2 ? 4e-4f : order == 3 ? 0.01f : 0.15f;
+}
+// Sweeps end when the angles of the last one came to this (Frobenius norm again); it is also the largest x of a correction.  A sweep
+// that turned by 14 leaves 9 on triangular factors of every kind, one of 10 leaves 2 ... 6, one of 2 leaves 0.1 ... 0.35; from 9 it takes 6
+// corrections, from 2 three or four.  A large x costs corrections of 80 to 100 us each (9 to 12 products), a sweep 110 us at l = 110, 170 at
+// 210 and 450 at 450.
+__host__ __device__ constexpr float polish_start(int l) { return l < 160 ? 4.f : l < 256 ? 7.f : 12.f; }
+constexpr double kPolishFree = 0.01;        // angles up to this are taken whatever the inner product
+constexpr float kPolishRate = 0.75f;        // x of a correction in units of that before; above that they do not converge
+// (Large angles at tiny inner products are a cluster, which sweeps turn faster.)
+__device__ __forceinline__ bool sweeps_ready(unsigned long long sumsq, float rho, int l) {
+  const float x2 = (float)sumsq * (2.f / kJbSumScale);
+  return x2 <= polish_start(l) * polish_start(l) && (x2 <= 4.f || rho * rho >= 2.5e-9f * x2);
+}
+
+template <typename T> struct PolishParams {
+  T *b[7];                   // l x l: M (column after column), J (likewise), X, Y / next M, Y2 / next J, cosine part / E, sine part / E
+  JbSync *sync;
+  int l, tiles;
+  int64_t stride;            // bytes between the problems of a batch (blockIdx.y)
+};
+
+constexpr int kPoTile = 32, kPoLd = kPoTile + 1;
+
+// The sum of the four wavefronts' tiles, in a fixed order; thread t is left with elements t, t + 256, ...
+template <typename T>
+__device__ __forceinline__ void polish_sum(const typename Mfma<T>::vec (&acc)[2][2], T *red, T (&out)[4]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r16 = lane & 15;
+  __syncthreads();                       // (red may still be read from the product before)
+  T *mine = red + wave * kPoTile * kPoLd;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) mine[(16 * i + Mfma<T>::row(lane, v)) * kPoLd + 16 * j + r16] = acc[i][j][v];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int e = threadIdx.x + 256 * u, at = (e >> 5) * kPoLd + (e & 31);
+    out[u] = (red[at] + red[kPoTile * kPoLd + at]) + (red[2 * kPoTile * kPoLd + at] + red[3 * kPoTile * kPoLd + at]);
+  }
+}
+
+// A 32 x 32 tile of sum_k fa(k, i) fb(k, j): the four wavefronts share the k range, lane L supplies k = L / 16 of a group of four and
+// i, j = L % 16 + 16 h.
+template <typename T, typename FA, typename FB>
+__device__ __forceinline__ void polish_tile(int l, FA fa, FB fb, T *red, T (&out)[4]) {
+  typedef typename Mfma<T>::vec acc_t;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kq = lane >> 4;
+  const int groups = (l + 3) / 4, per = (groups + 3) / 4;
+  const int g0 = wave * per, g1 = g0 + per < groups ? g0 + per : groups;
+  acc_t acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = (acc_t)(T)0;
+  constexpr int U = sizeof(T) == 4 ? 14 : 10;
+  const int last = 4 * g1 < l ? 4 * g1 : l;
+  for (int g = g0; g < g1; g += U) {
+    T a[U][2], b[U][2];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = 4 * (g + u) + kq, kc = k < l ? k : l - 1;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        a[u][h] = fa(kc, h);
+        b[u][h] = fb(kc, h);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);       // (all loads in flight before the first is waited for)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = 4 * (g + u) + kq < last;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        a[u][h] = in ? a[u][h] : (T)0;
+        b[u][h] = in ? b[u][h] : (T)0;
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = Mfma<T>::run(a[u][i], b[u][j], acc[i][j]);
+    }
+  }
+  polish_sum<T>(acc, red, out);
+}
+
+// The same for the product of two sets of columns of M, which lie along k, in fp64 for either type: a lane reads four consecutive k at a
+// time, one for each of four matrix instructions, and adds up the squares of what it has read (ni, nj).
+template <typename T>
+__device__ __forceinline__ void polish_gram(int l, const T *M, const int (&ic)[2], const int (&jc)[2], double *red, double (&out)[4],
+                                            double (&ni)[2], double (&nj)[2]) {
+  typedef T piece __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kq = lane >> 4;
+  const int groups = (l + 15) / 16, per = (groups + 3) / 4;
+  const int g0 = wave * per, g1 = g0 + per < groups ? g0 + per : groups;
+  f64x4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = (f64x4)0.0;
+  constexpr int U = sizeof(T) == 4 ? 4 : 2;
+  for (int g = g0; g < g1; g += U) {
+    piece a[U][2], b[U][2];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      // (the last piece is read where it fits, l >= 4, and moved down below)
+      const int k = 16 * (g + u) + 4 * kq, at = k + 4 <= l ? k : l - 4;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        a[u][h] = *reinterpret_cast<const piece *>(M + (int64_t)ic[h] * l + at);
+        b[u][h] = *reinterpret_cast<const piece *>(M + (int64_t)jc[h] * l + at);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int left = g + u < g1 ? l - 16 * (g + u) - 4 * kq : 0, by = left >= 4 ? 0 : 4 - left;      // elements that exist; places to move
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        double x[2], y[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const T xv = by == 0 ? a[u][h][e] : by == 1 ? a[u][h][(e + 1) & 3] : by == 2 ? a[u][h][(e + 2) & 3] : a[u][h][(e + 3) & 3];
+          const T yv = by == 0 ? b[u][h][e] : by == 1 ? b[u][h][(e + 1) & 3] : by == 2 ? b[u][h][(e + 2) & 3] : b[u][h][(e + 3) & 3];
+          x[h] = e < left ? (double)xv : 0.0;
+          y[h] = e < left ? (double)yv : 0.0;
+          ni[h] = fma(x[h], x[h], ni[h]);
+          nj[h] = fma(y[h], y[h], nj[h]);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][j] = Mfma<double>::run(x[i], y[j], acc[i][j]);
+      }
+    }
+  }
+  polish_sum<double>(acc, red, out);
+}
+
+// Tile t of the tiles on or above the diagonal.
+__device__ __forceinline__ void upper_tile(int tiles, int t, int &ti, int &tj) {
+  ti = 0;
+  while (t >= tiles - ti) { t -= tiles - ti; ++ti; }
+  tj = ti + t;
+}
+
+enum { PO_ANGLES = 0, PO_SQUARE, PO_FOURTH, PO_PARTS, PO_EXP, PO_DOUBLE, PO_APPLY };
+
 // Loads and stores that every XCD sees.
 template <typename V> __device__ __forceinline__ V device_load(const V *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -982,13 +1182,271 @@ __device__ __forceinline__ bool jb_wait(const int *p, const int *p2, int want, c
   }
 }
 
+// All corrections in one launch.  Tasks are the tiles of a phase, phase after phase; they are handed out by a counter, and a workgroup goes
+// on to the next phase once every tile of the one before is finished.  As in jb_flow_kernel it waits for tasks with lower numbers only,
+// whose workgroups are running, so no number of resident workgroups is assumed.  What a phase stores goes through to where every
+// XCD sees it, and the wait ends by dropping what the caches of the reader hold.  The operands are l x l matrices, so a
+// phase is a chain of latencies: counter, loads, sums, stores' arrival.
+__device__ __forceinline__ void jb_wait_tiles(const int *p, int want) {
+  while (device_load(p) < want) __builtin_amdgcn_s_sleep(4);
+}
+
 template <typename T>
-__global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__restrict__ Jt, int l, int nblk,
-                                                       int max_sweeps, int *__restrict__ ver, JbHeader *hdr) {
+__global__ __launch_bounds__(256) void polish_kernel(PolishParams<T> P) {
+  if (blockIdx.y != 0) {
+    const int64_t off = (int64_t)blockIdx.y * P.stride;
+#pragma unroll
+    for (int i = 0; i < 7; ++i) P.b[i] = reinterpret_cast<T *>(reinterpret_cast<char *>(P.b[i]) + off);
+    P.sync = reinterpret_cast<JbSync *>(reinterpret_cast<char *>(P.sync) + off);
+  }
+  JbSync *sync = P.sync;
+  if (sync->run[0].stop != 2) return;
+  const int l = P.l, tiles = P.tiles, upper = tiles * (tiles + 1) / 2;
+  const T tol = Eps<T>::value * sqrt((T)l);
+  const double floor2 = (double)Eps<T>::value * (double)Eps<T>::value * sync->fro2;
+  __shared__ double red64[4 * kPoTile * kPoLd];
+  T *red = reinterpret_cast<T *>(red64);
+  __shared__ double part[4][2][kPoTile];
+  __shared__ int ticket_sh;
+  __shared__ float wave_rho[4], wave_x2[4];
+  T *M = P.b[0], *J = P.b[1], *X = P.b[2], *Y = P.b[3], *Y2 = P.b[4], *C = P.b[5], *S = P.b[6];
+  int step = 0, phase = PO_ANGLES, seq = 0, base = 0, count = upper, order = 0, halvings = 0, doublings = 0, updates = 0;
+  T half = (T)1;                                     // the series is taken of half * X
+  float x_before = 1e30f, x_now = 0.f, rho_now = 0.f;
+  int ticket = 0;
+  if (threadIdx.x == 0) ticket = atomicAdd(&sync->ticket, 1);
+
+  for (;;) {
+    if (threadIdx.x == 0) ticket_sh = ticket;
+    __syncthreads();
+    const int task = __builtin_amdgcn_readfirstlane(ticket_sh);
+    // ---- the phase of this task
+    while (task >= base + count) {
+      if (threadIdx.x == 0) (void)jb_wait_tiles(&sync->done[seq], count);
+      __syncthreads();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      base += count;
+      ++seq;
+      bool end = false, converged = false;
+      if (phase == PO_ANGLES) {
+        rho_now = __int_as_float(device_load(&sync->rho[step]));
+        x_now = sqrtf((float)device_load(&sync->x2[step]) * (2.f / kPolishScale));
+        order = x_now <= polish_limit<T>(1) ? 1 : x_now <= polish_limit<T>(2) ? 2 : x_now <= polish_limit<T>(3) ? 3 : 4;
+        converged = rho_now <= (float)tol;
+        end = converged || !(x_now <= polish_start(l)) || !(x_now <= kPolishRate * x_before);
+        halvings = 0;
+        for (float x = x_now; x > polish_limit<T>(4) && halvings < 7; x *= 0.5f) ++halvings;
+        doublings = halvings;
+        half = ldexp((T)1, -halvings);
+        phase = PO_SQUARE;
+        count = upper;
+      } else if (phase == PO_SQUARE && order >= 3) {
+        phase = PO_FOURTH;
+        count = upper;
+      } else if (phase == PO_FOURTH && order >= 4) {
+        phase = PO_PARTS;
+        count = upper;
+      } else if (phase < PO_EXP && order >= 2) {
+        phase = PO_EXP;
+        count = tiles * tiles;
+      } else if ((phase == PO_EXP || phase == PO_DOUBLE) && doublings > 0) {
+        if (phase == PO_DOUBLE) { T *t = C; C = S; S = t; }
+        --doublings;
+        phase = PO_DOUBLE;
+        count = tiles * tiles;
+      } else if (phase != PO_APPLY) {
+        if (phase == PO_DOUBLE) { T *t = C; C = S; S = t; }              // (E is in C)
+        phase = PO_APPLY;
+        count = 2 * tiles * tiles;
+      } else {
+        // M and J are the new ones, what they were is free
+        T *t = M; M = Y; Y = t;
+        t = J; J = Y2; Y2 = t;
+        ++updates;
+        converged = rho_now * x_now <= (float)tol;             // the next one would find about that
+        ++step;
+        end = converged || step == kPolishSteps;
+        x_before = x_now;
+        phase = PO_ANGLES;
+        count = upper;
+      }
+      if (end) {
+        if (threadIdx.x == 0) {                                // (the same from every workgroup)
+          device_store(&sync->updates, updates);
+          device_store(&sync->converged, converged ? 1 : 0);
+        }
+        return;
+      }
+    }
+    // ---- its tile
+    if (threadIdx.x == 0) ticket = atomicAdd(&sync->ticket, 1);       // (the next one, in good time)
+    int ti, tj;
+    const int n = task - base, z = n >= tiles * tiles ? 1 : 0;
+    const bool mirrored = phase <= PO_PARTS;               // symmetric or antisymmetric: tiles on or above the diagonal
+    if (mirrored) upper_tile(tiles, n, ti, tj);
+    else { ti = (n - z * tiles * tiles) / tiles; tj = (n - z * tiles * tiles) - ti * tiles; }
+    const int i0 = ti * kPoTile, j0 = tj * kPoTile;
+    // rows and columns beyond the last read the last one: what comes of them is not stored
+    int ic[2], jc[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int i = i0 + 16 * h + (int)(threadIdx.x & 15), j = j0 + 16 * h + (int)(threadIdx.x & 15);
+      ic[h] = i < l ? i : l - 1;
+      jc[h] = j < l ? j : l - 1;
+    }
+    // the elements of this tile that its result needs besides the product, in flight with the operands
+    T own[2][4];
+    const T *own0 = phase == PO_APPLY ? (z == 0 ? M : J) : phase == PO_PARTS || (phase == PO_EXP && order < 4) ? Y : phase == PO_SQUARE ? X : C;
+    const T *own1 = phase == PO_PARTS || (phase == PO_EXP && order == 3) ? Y2 : X;
+    if (phase >= PO_PARTS || (phase == PO_SQUARE && order == 1)) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = threadIdx.x + 256 * u, i = i0 + (e >> 5), j = j0 + (e & 31);
+        const int64_t at = (int64_t)(i < l ? i : l - 1) * l + (j < l ? j : l - 1);
+        own[0][u] = own0[at];
+        own[1][u] = own1[at];
+      }
+    }
+    T v[4], w[4];
+    auto store = [&](T *m, int i, int j, T a, T b) {
+      device_store(m + (int64_t)i * l + j, a);
+      if (mirrored && ti != tj) device_store(m + (int64_t)j * l + i, b);
+    };
+    auto each = [&](auto f) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = threadIdx.x + 256 * u, i = i0 + (e >> 5), j = j0 + (e & 31);
+        if (i < l && j < l) f(u, i, j, (int64_t)i * l + j);
+      }
+    };
+    auto at_i = [&](const T *m) { return [&, m](int k, int h) { return m[(int64_t)k * l + ic[h]]; }; };
+    auto at_j = [&](const T *m) { return [&, m](int k, int h) { return m[(int64_t)k * l + jc[h]]; }; };
+    auto minus_x = [&](int k, int h) { return -X[(int64_t)k * l + ic[h]]; };      // X[i][k]
+    if (phase == PO_ANGLES) {
+      double ni[2] = {0.0, 0.0}, nj[2] = {0.0, 0.0}, g[4];
+      polish_gram<T>(l, M, ic, jc, red64, g, ni, nj);
+      const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        ni[h] += __shfl_xor(ni[h], 16, 64); ni[h] += __shfl_xor(ni[h], 32, 64);
+        nj[h] += __shfl_xor(nj[h], 16, 64); nj[h] += __shfl_xor(nj[h], 32, 64);
+        if (lane < 16) { part[wave][0][16 * h + lane] = ni[h]; part[wave][1][16 * h + lane] = nj[h]; }
+      }
+      __syncthreads();
+      float rho = 0.f, x2 = 0.f;
+      each([&](int u, int i, int j, int64_t) {
+        if (ti == tj && i > j) return;
+        const int r = i - i0, c = j - j0;
+        const double di = (part[0][0][r] + part[1][0][r]) + (part[2][0][r] + part[3][0][r]);
+        const double dj = (part[0][1][c] + part[1][1][c]) + (part[2][1][c] + part[3][1][c]);
+        double angle = 0.0;
+        if (i != j && di > floor2 && dj > floor2 && g[u] != 0.0) {
+          const double rel = fabs(g[u]) / sqrt(di * dj);
+          // tan of the angle as in rotation_params, then the angle itself (to the fifth order: it only has to be a good one)
+          const double zeta = (dj - di) / (2.0 * g[u]), az = fabs(zeta);
+          double t = az > 1e7 ? 0.5 / az : 1.0 / (az + sqrt(1.0 + zeta * zeta));
+          t = zeta < 0.0 ? -t : t;
+          // below the threshold only where it is a small one: inside a cluster it would be large, and noise
+          if (rel > tol || fabs(t) <= kPolishFree) angle = t - t * t * t * (1.0 / 3.0 - 0.2 * t * t);
+          if (rel > tol) rho = fmaxf(rho, (float)rel);
+          x2 += (float)(angle * angle);
+        }
+        device_store(X + (int64_t)i * l + j, (T)angle);
+        if (i != j) device_store(X + (int64_t)j * l + i, -(T)angle);
+      });
+#pragma unroll
+      for (int m = 1; m < 64; m <<= 1) {
+        rho = fmaxf(rho, __shfl_xor(rho, m, 64));
+        x2 += __shfl_xor(x2, m, 64);
+      }
+      if (lane == 0) { wave_rho[wave] = rho; wave_x2[wave] = x2; }
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        rho = fmaxf(fmaxf(wave_rho[0], wave_rho[1]), fmaxf(wave_rho[2], wave_rho[3]));
+        x2 = (wave_x2[0] + wave_x2[1]) + (wave_x2[2] + wave_x2[3]);
+        if (rho > 0.f) {
+          atomicMax(&sync->rho[step], __float_as_int(rho));
+          atomicAdd(&sync->x2[step], (unsigned long long)ceilf(fminf(x2, 128.f) * kPolishScale));
+        }
+      }
+    } else if (phase == PO_SQUARE) {                 // Y = X X; with the shortest series E = X + Y / 2
+      polish_tile<T>(l, minus_x, at_j(X), red, v);
+      if (order == 1) {
+        each([&](int u, int i, int j, int64_t) {
+          const T x = own[0][u];
+          store(C, i, j, x + (T)0.5 * v[u], (T)0.5 * v[u] - x);
+        });
+      } else {
+        each([&](int u, int i, int j, int64_t) { store(Y, i, j, v[u], v[u]); });
+      }
+    } else if (phase == PO_FOURTH) {
+      polish_tile<T>(l, at_i(Y), at_j(Y), red, v);
+      each([&](int u, int i, int j, int64_t) { store(Y2, i, j, v[u], v[u]); });
+    } else if (phase == PO_PARTS) {                  // Y^3, Y^4; cosine and sine part of half * X, without the I
+      const T h2 = half * half, h4 = h2 * h2, h6 = h4 * h2, h8 = h4 * h4;
+      polish_tile<T>(l, at_i(Y), at_j(Y2), red, v);
+      polish_tile<T>(l, at_i(Y2), at_j(Y2), red, w);
+      each([&](int u, int i, int j, int64_t) {
+        const T y = h2 * own[0][u], y2 = h4 * own[1][u], y3 = h6 * v[u], y4 = h8 * w[u];
+        const T c = ((y3 * (T)(1.0 / 720.0) + y4 * (T)(1.0 / 40320.0)) + y2 * (T)(1.0 / 24.0)) + y * (T)0.5;
+        const T sn = ((y3 * (T)(1.0 / 5040.0) + y4 * (T)(1.0 / 362880.0)) + y2 * (T)(1.0 / 120.0)) + y * (T)(1.0 / 6.0);
+        store(C, i, j, c, c);
+        store(S, i, j, sn, sn);
+      });
+    } else if (phase == PO_EXP) {                    // E = cosine part + X + X (sine part)
+      if (order == 4) {
+        polish_tile<T>(l, minus_x, at_j(S), red, v);
+        each([&](int u, int i, int j, int64_t) { store(C, i, j, (own[0][u] + half * v[u]) + half * own[1][u], (T)0); });
+      } else if (order == 3) {
+        polish_tile<T>(l, minus_x, [&](int k, int h) {
+          const int64_t at = (int64_t)k * l + jc[h];
+          return Y[at] * (T)(1.0 / 6.0) + Y2[at] * (T)(1.0 / 120.0);
+        }, red, v);
+        each([&](int u, int i, int j, int64_t at) {
+          store(C, i, j, ((own[0][u] * (T)0.5 + own[1][u] * (T)(1.0 / 24.0)) + v[u]) + X[at], (T)0);
+        });
+      } else {
+        polish_tile<T>(l, minus_x, [&](int k, int h) { return Y[(int64_t)k * l + jc[h]] * (T)(1.0 / 6.0); }, red, v);
+        each([&](int u, int i, int j, int64_t) { store(C, i, j, (own[0][u] * (T)0.5 + v[u]) + own[1][u], (T)0); });
+      }
+    } else if (phase == PO_DOUBLE) {                 // exp(X)^2 - I = 2 E + E E, into S
+      polish_tile<T>(l, [&](int k, int h) { return C[(int64_t)ic[h] * l + k]; }, at_j(C), red, v);
+      each([&](int u, int i, int j, int64_t) { store(S, i, j, (T)2 * own[0][u] + v[u], (T)0); });
+    } else {                                         // column i of the new matrix = that of the old one + sum_k E[k][i] column k
+      const T *old = z == 0 ? M : J;
+      T *next = z == 0 ? Y : Y2;
+      polish_tile<T>(l, at_i(C), at_j(old), red, v);
+      each([&](int u, int i, int j, int64_t) { store(next, i, j, own[0][u] + v[u], (T)0); });
+    }
+    device_stores_done();
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(&sync->done[seq], 1);
+  }
+}
+
+template <typename T>
+static void polish_launch(const rsvd_ctx *ctx, hipStream_t s, const PolishParams<T> &P, int batch) {
+  int wgs = 2 * P.tiles * P.tiles;                   // tiles of the largest phase
+  if (wgs > ctx->cu_count) wgs = ctx->cu_count;
+  hipLaunchKernelGGL((polish_kernel<T>), dim3(wgs, batch), dim3(256), 0, s, P);
+}
+
+// which: 0 = the sweeps from the start, until they have converged or (`corrections` follow) leave little enough for those; 1 = the
+// sweeps behind the corrections, if those did not finish.  Mt2, Jt2: where an odd number of corrections has left M and J.
+template <typename T>
+__global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__restrict__ Jt, T *__restrict__ Mt2,
+                                                       T *__restrict__ Jt2, int l, int nblk, int max_sweeps,
+                                                       int *__restrict__ ver, JbSync *sync, int which, int corrections) {
   constexpr int b = kJgB;
   typedef typename Mfma<T>::vec acc_t;
   const T tol = Eps<T>::value * sqrt((T)l);
-  const T floor2 = (T)(Eps<T>::value * Eps<T>::value * hdr->fro2);
+  const T floor2 = (T)(Eps<T>::value * Eps<T>::value * sync->fro2);
+  JbRun *run = &sync->run[which];
+  if (which != 0) {
+    if (sync->run[0].stop != 2 || sync->converged != 0) return;
+    if (sync->updates & 1) { Mt = Mt2; Jt = Jt2; }
+    max_sweeps -= sync->run[0].used;
+  }
   const int nblk2 = nblk + (nblk & 1), pairs = nblk2 / 2, steps_per_sweep = nblk2 - 1;
   const int ldp = jg_ldp<T>(l), lp = (l + 15) / 16 * 16;
   extern __shared__ __attribute__((aligned(16))) double lds_raw[];
@@ -998,8 +1456,9 @@ __global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__
   double *Tm = reinterpret_cast<double *>(R4);                 // T[k][j], in the place of two of them in fp32, of one in fp64
   T *CS = R4 + 3 * kJgMat;                                     // [rounds][16 pairs][c, s]
   __shared__ int rotations, task;
+  __shared__ unsigned turned;                                  // sum of s^2 over the rotations of the task, times kJbSumScale
   int ticket = 0;
-  if (threadIdx.x == 0) ticket = atomicAdd(&hdr->ticket, 1);
+  if (threadIdx.x == 0) ticket = atomicAdd(&run->ticket, 1);
 
   for (;;) {
     // (worked out anew for every task: the addresses that follow from them were kept across tasks otherwise, in
@@ -1015,24 +1474,29 @@ __global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__
         const int sweep = n / steps_per_sweep, round = n - sweep * steps_per_sweep;
         if (round == 0) {
           if (sweep > 0) {
-            const int *f = &hdr->finished[sweep - 1];
-            go = jb_wait(f, f, steps_per_sweep * pairs, &hdr->stop);
+            const int *f = &run->finished[sweep - 1];
+            go = jb_wait(f, f, steps_per_sweep * pairs, &run->stop);
             if (go) {
-              const float rho = __int_as_float(device_load(&hdr->counters[sweep - 1]));
-              const float before = sweep > 1 ? __int_as_float(device_load(&hdr->counters[sweep - 2])) : -1.f;
-              if (jacobi_done(rho, before, (float)tol)) {
-                device_store(&hdr->stop, 1);
+              const float rho = __int_as_float(device_load(&run->counters[sweep - 1]));
+              const float before = sweep > 1 ? __int_as_float(device_load(&run->counters[sweep - 2])) : -1.f;
+              const int stop = jacobi_done(rho, before, (float)tol)                                             ? 1
+                               : corrections && sweeps_ready(device_load(&run->sumsq[sweep - 1]), rho, l) ? 2
+                                                                                                                : 0;
+              if (stop != 0) {
+                device_store(&run->used, sweep);
+                device_store(&run->stop, stop);
                 go = false;
               }
             }
           }
         } else {
           const JbPair pr = jb_pair(1, round, g, l, b, nblk);
-          go = jb_wait(ver + pr.bi, ver + (pr.valid ? pr.bj : pr.bi), n, &hdr->stop);
+          go = jb_wait(ver + pr.bi, ver + (pr.valid ? pr.bj : pr.bi), n, &run->stop);
         }
       }
       task = go ? ticket : -1;
       rotations = 0;
+      turned = 0u;
     }
     __syncthreads();
     if (task < 0) return;
@@ -1130,7 +1594,7 @@ __global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__
       // rotation of pair bb, and the first sixteen leave (c, s) of the round in LDS.  Wavefronts 4-11: T <- T J one round
       // behind, in fp64, thread (rr, bb) row rr and the columns of pair bb.  One barrier per round (G alternates between two
       // copies; the two elements of T that a thread changes are its own in that round).
-      float rho = 0.f;
+      float rho = 0.f, s2 = 0.f;
       auto run_rounds = [&](auto kind, int r0, int count) {        // rounds r0, ... of the task
         constexpr bool INTRA = decltype(kind)::value;
         if (wave < 4) {
@@ -1157,6 +1621,7 @@ __global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__
               n01 = (T)0;
               n10 = (T)0;
               rho = fmaxf(rho, rel);
+              s2 += (float)(sb * sb);
             }
             Gd[mpa * kJgLd + mpb] = n00; Gd[mpa * kJgLd + mqb] = n01;
             Gd[mqa * kJgLd + mpb] = n10; Gd[mqa * kJgLd + mqb] = n11;
@@ -1196,7 +1661,10 @@ __global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__
       };
       if (round == 0) run_rounds(JbKind<true>(), 0, intra);
       if (pr.valid) run_rounds(JbKind<false>(), intra, b);
-      if (rho > 0.f) atomicMax(&rotations, __float_as_int(rho));
+      if (rho > 0.f) {
+        atomicMax(&rotations, __float_as_int(rho));
+        atomicAdd(&turned, (unsigned)ceilf(s2 * kJbSumScale));             // (whole numbers: the sum does not depend on the order)
+      }
       __syncthreads();
       rho_bits = rotations;
     }
@@ -1239,10 +1707,13 @@ __global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__
     if (tid == 0) {
       device_store(ver + pr.bi, n + 1);
       if (pr.valid) device_store(ver + pr.bj, n + 1);
-      if (rho_bits != 0) atomicMax(&hdr->counters[sweep], rho_bits);
+      if (rho_bits != 0) {
+        atomicMax(&run->counters[sweep], rho_bits);
+        atomicAdd(&run->sumsq[sweep], (unsigned long long)turned);
+      }
       device_stores_done();                                      // (counters before finished)
-      atomicAdd(&hdr->finished[sweep], 1);
-      ticket = atomicAdd(&hdr->ticket, 1);
+      atomicAdd(&run->finished[sweep], 1);
+      ticket = atomicAdd(&run->ticket, 1);
       // J: the same two blocks of columns, after the step before
       int *verj = ver + nblk;
       (void)jb_wait(verj + pr.bi, verj + (pr.valid ? pr.bj : pr.bi), n, nullptr);
@@ -1291,7 +1762,9 @@ __global__ __launch_bounds__(1024) void jb_flow_kernel(T *__restrict__ Mt, T *__
 
 // Column norms (one wavefront per column), then ranks by counting, then the scatter.
 template <typename T>
-__global__ __launch_bounds__(256) void jb_norms_kernel(const T *__restrict__ Mt, int l, T *__restrict__ nrm) {
+__global__ __launch_bounds__(256) void jb_norms_kernel(const T *__restrict__ Mt, const T *__restrict__ Mt2, int l,
+                                                       T *__restrict__ nrm, const JbSync *sync) {
+  if (sync != nullptr && (sync->updates & 1)) Mt = Mt2;
   const int col = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (col >= l) return;
   T s2 = 0;
@@ -1303,44 +1776,55 @@ __global__ __launch_bounds__(256) void jb_norms_kernel(const T *__restrict__ Mt,
 
 template <typename T>
 __global__ __launch_bounds__(256) void jb_rank_kernel(const T *__restrict__ nrm, int l, int *__restrict__ rnk,
-                                                      T *__restrict__ sigma, JbHeader *hdr, int max_sweeps,
-                                                      DevInfo *info) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  // the norms go through LDS a chunk at a time (one after the other from global memory, the l comparisons of a
-  // thread took 33 us at l = 576)
-  __shared__ T chunk[1024];
-  const T mine = j < l ? nrm[j] : (T)0;
+                                                      T *__restrict__ sigma, const JbHeader *hdr, int max_sweeps,
+                                                      DevInfo *info, const JbSync *sync) {
+  // sixteen threads to a column, each compares it with a sixteenth of the others (one thread for all of them: 17 us at l = 210, 35 at 450)
+  const int sub = threadIdx.x & 15, j = blockIdx.x * 16 + (threadIdx.x >> 4);
+  const T mine = nrm[j < l ? j : 0];
   int rank = 0;
-  for (int c0 = 0; c0 < l; c0 += 1024) {
-    const int cn = (l - c0 < 1024) ? (l - c0) : 1024;
-    for (int i = threadIdx.x; i < cn; i += blockDim.x) chunk[i] = nrm[c0 + i];
-    __syncthreads();
-    if (j < l) {
-      for (int i = 0; i < cn; ++i) {
-        const T o = chunk[i];
-        rank += (o > mine || (o == mine && c0 + i < j)) ? 1 : 0;
-      }
-    }
-    __syncthreads();
+#pragma unroll 8
+  for (int i = sub; i < l; i += 16) {
+    const T o = nrm[i];
+    rank += (o > mine || (o == mine && i < j)) ? 1 : 0;
   }
-  if (j < l) {
+#pragma unroll
+  for (int m = 1; m < 16; m <<= 1) rank += __shfl_xor(rank, m, 16);
+  if (j < l && sub == 0) {
     rnk[j] = rank;
     sigma[rank] = mine * (T)hdr->unscale;
   }
-  if (j == 0 && info != nullptr) {
+  if (j == 0 && sub == 0 && info != nullptr) {
     const float tol = (float)(Eps<T>::value * sqrt((T)l));
     int used = max_sweeps;
-    for (int s = 1; s <= max_sweeps; ++s)
-      if (jacobi_done_before(hdr->counters, s, tol)) { used = s; break; }
+    bool done;
+    if (sync != nullptr) {
+      // a run that stopped says why; one that did not went on to the limit, with its last sweep yet to be looked at
+      const JbRun &first = sync->run[0], &second = sync->run[1];
+      if (first.stop == 2) {
+        const int left = max_sweeps - first.used;
+        used = first.used + sync->updates + (sync->converged ? 0 : second.stop != 0 ? second.used : left);
+        done = sync->converged || second.stop != 0 || jacobi_done_before(second.counters, left, tol);
+      } else {
+        if (first.stop != 0) used = first.used;
+        done = first.stop != 0 || jacobi_done_before(first.counters, max_sweeps, tol);
+      }
+    } else {
+      for (int s = 1; s <= max_sweeps; ++s)
+        if (jacobi_done_before(hdr->counters, s, tol)) { used = s; break; }
+      done = jacobi_done_before(hdr->counters, max_sweeps, tol);
+    }
     atomicMax(&info->jacobi_sweeps, used);
-    if (!jacobi_done_before(hdr->counters, max_sweeps, tol)) atomicMax(&info->status, (int)RSVD_ERR_NO_CONVERGENCE);
+    if (!done) atomicMax(&info->status, (int)RSVD_ERR_NO_CONVERGENCE);
   }
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void jb_scatter_kernel(const T *__restrict__ Mt, const T *__restrict__ Jt, int l,
+__global__ __launch_bounds__(256) void jb_scatter_kernel(const T *__restrict__ Mt, const T *__restrict__ Jt,
+                                                         const T *__restrict__ Mt2, const T *__restrict__ Jt2, int l,
                                                          const T *__restrict__ nrm, const int *__restrict__ rnk,
-                                                         const JbHeader *hdr, T *__restrict__ X, T *__restrict__ W) {
+                                                         const JbHeader *hdr, T *__restrict__ X, T *__restrict__ W,
+                                                         const JbSync *sync) {
+  if (sync != nullptr && (sync->updates & 1)) { Mt = Mt2; Jt = Jt2; }
   const T floor2 = (T)(Eps<T>::value * Eps<T>::value * hdr->fro2);
   for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < (int64_t)l * l;
        idx += (int64_t)gridDim.x * blockDim.x) {
@@ -1427,7 +1911,8 @@ static bool jb_takes_flow(const rsvd_ctx *ctx, int b, int l) {
 
 template <typename T>
 static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int l, const double *M,
-                                      T *sigma, T *X, T *W, DevInfo *info, char *scratch, int rows) {
+                                      T *sigma, T *X, T *W, DevInfo *info, char *scratch, int rows,
+                                      const JacobiSlots *slots) {
   const int b = jb_block_width(ctx, dtype, l);
   if (b == 0) return hipErrorNotSupported;
   const size_t es = sizeof(T);
@@ -1447,17 +1932,33 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
   const size_t lds_j = ((size_t)(2 * b) * (kJbRowChunk + 8) + (size_t)(2 * b) * (2 * b + 2)) * es;   // jb_apply_t
   const size_t lds = lds_rot > lds_j ? lds_rot : lds_j;
   const int chunks = (l + kJbRowChunk - 1) / kJbRowChunk;
+  // the flow kernel has no use for the ring: its counters lie there, the progress of the column blocks behind them
+  const bool flow = jb_takes_flow<T>(ctx, b, l);
+  JbSync *sync = flow ? reinterpret_cast<JbSync *>(Tring) : nullptr;
+  int *ver2 = reinterpret_cast<int *>(sync + 1);
   ProfScope ps(ctx, s, PK_JACOBI);
   hipLaunchKernelGGL(jb_fro_kernel, dim3(kJbFroParts), dim3(256), 0, s, M, l, hdr);
   {
     int64_t blocks = ((int64_t)l * l + 255) / 256;
     if (blocks > 1024) blocks = 1024;
     hipLaunchKernelGGL((jb_init_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, s, M, l, Mt, Jt, hdr, rows, chg,
-                       2 * nblk);
+                       2 * nblk, sync, ver2);
   }
-  if (jb_takes_flow<T>(ctx, b, l)) {
-    hipLaunchKernelGGL((jb_flow_kernel<T>), dim3(nblk2), dim3(1024), jg_lds_bytes<T>(l), s, Mt, Jt, l, nblk,
-                       kJbMaxSweeps, chg, hdr);
+  T *Mt2 = Mt, *Jt2 = Jt;
+  if (flow) {
+    const int corrections = slots != nullptr ? 1 : 0;
+    if (corrections) {
+      PolishParams<T> P;
+      P.b[0] = Mt; P.b[1] = Jt;
+      for (int i = 0; i < 5; ++i) P.b[2 + i] = (T *)slots->slot[i];
+      Mt2 = P.b[3]; Jt2 = P.b[4];
+      P.sync = sync; P.l = l; P.tiles = (l + kPoTile - 1) / kPoTile; P.stride = 0;
+      hipLaunchKernelGGL((jb_flow_kernel<T>), dim3(nblk2), dim3(1024), jg_lds_bytes<T>(l), s, Mt, Jt, Mt2, Jt2, l, nblk,
+                         kJbMaxSweeps, chg, sync, 0, 1);
+      polish_launch<T>(ctx, s, P, 1);
+    }
+    hipLaunchKernelGGL((jb_flow_kernel<T>), dim3(nblk2), dim3(1024), jg_lds_bytes<T>(l), s, Mt, Jt, Mt2, Jt2, l, nblk,
+                       kJbMaxSweeps, corrections ? ver2 : chg, sync, corrections, 0);
   } else {
 #define RSVD_JB_CASE(NVV)                                                                                        \
   case NVV: {                                                                                                    \
@@ -1487,10 +1988,10 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
     }
 #undef RSVD_JB_CASE
   }
-  hipLaunchKernelGGL((jb_norms_kernel<T>), dim3((l + 3) / 4), dim3(256), 0, s, Mt, l, nrm);
-  hipLaunchKernelGGL((jb_rank_kernel<T>), dim3((l + 255) / 256), dim3(256), 0, s, nrm, l, rnk, sigma, hdr,
-                     kJbMaxSweeps, info);
-  hipLaunchKernelGGL((jb_scatter_kernel<T>), dim3(256), dim3(256), 0, s, Mt, Jt, l, nrm, rnk, hdr, X, W);
+  hipLaunchKernelGGL((jb_norms_kernel<T>), dim3((l + 3) / 4), dim3(256), 0, s, Mt, Mt2, l, nrm, sync);
+  hipLaunchKernelGGL((jb_rank_kernel<T>), dim3((l + 15) / 16), dim3(256), 0, s, nrm, l, rnk, sigma, hdr,
+                     kJbMaxSweeps, info, sync);
+  hipLaunchKernelGGL((jb_scatter_kernel<T>), dim3(256), dim3(256), 0, s, Mt, Jt, Mt2, Jt2, l, nrm, rnk, hdr, X, W, sync);
   return hipGetLastError();
 }
 
@@ -1588,7 +2089,7 @@ hipError_t jacobi_init_device(rsvd_ctx *ctx) {
 
 hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t l, const void *M,
                          int m_is_f64, void *sigma, void *X, void *W, DevInfo *info, void *scratch,
-                         size_t scratch_bytes, int batch, int64_t stride, int rows) {
+                         size_t scratch_bytes, int batch, int64_t stride, int rows, const JacobiSlots *slots) {
   if (batch < 1 || batch > 65535) return hipErrorInvalidValue;
   if (l > jacobi_max_lds_order(ctx, dtype)) {
     if (batch != 1) {
@@ -1610,9 +2111,9 @@ hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t
     if (need == 0 || scratch == nullptr || scratch_bytes < need || !m_is_f64) return hipErrorNotSupported;
     if (dtype == RSVD_F32)
       return jacobi_block_launch<float>(ctx, s, dtype, (int)l, (const double *)M, (float *)sigma, (float *)X,
-                                        (float *)W, info, (char *)scratch, rows);
+                                        (float *)W, info, (char *)scratch, rows, slots);
     return jacobi_block_launch<double>(ctx, s, dtype, (int)l, (const double *)M, (double *)sigma, (double *)X,
-                                       (double *)W, info, (char *)scratch, rows);
+                                       (double *)W, info, (char *)scratch, rows, slots);
   }
   // one G-lane group per column pair of a round, all pairs of a round at once
   const int npairs = (int)((l + 1) / 2);

@@ -276,6 +276,36 @@ def test_block_jacobi_edges(dt, l):
     assert np.abs(np.linalg.norm(W, axis=0) - 1).max() <= 4 * eps * np.sqrt(20 * l)
 
 
+# What the corrections of the whole matrix behind the sweeps meet: angles of every size (each length of the series, halvings), clusters
+# that they leave to further sweeps, zero and negligible columns; orders with one and with 31 rows or columns in the last 32 x 32 tile,
+# and on either side of a limit on the angles.
+@pytest.mark.parametrize("dt,l", [("f64", 97), ("f64", 159), ("f64", 257), ("f32", 129), ("f32", 161), ("f32", 191), ("f32", 290)])
+@pytest.mark.parametrize("kind", ["fast", "slow", "steep", "clusters", "rank"])
+def test_block_jacobi_corrections(dt, l, kind):
+    say("block jacobi corrections", dt, l, kind)
+    i = np.arange(l)
+    rng = np.random.default_rng(l)
+    s = {"fast": np.exp(-3.0 * i / l), "slow": (1.0 + i) ** -0.1, "steep": 10.0 ** (-i / 12.0),
+         "clusters": np.where(i < l // 2, 1.0, 0.5) * (1 + 1e-6 * rng.random(l)), "rank": np.where(i < l - 40, 1.0 / (1 + i), 0.0)}[kind]
+    # nearly aligned factors, as a power iteration leaves them
+    near = np.linalg.qr(np.eye(l) + 0.02 * rng.standard_normal((l, l)))[0]
+    M = np.linalg.qr((workloads.orthonormal_factor(l, l, 1) * s) @ near)[1].T.astype(NPDT[dt])
+    c = ctx()
+    sig, X, W, info = c.rsvd_stage_jacobi(to_dev(M))
+    assert info.status == 0
+    again = c.rsvd_stage_jacobi(to_dev(M))        # whichever workgroup took which tile
+    for a, b in zip((sig, X, W), again[:3]):
+        assert np.array_equal(to_np(a), to_np(b))
+    sig, X, W = (to_np(t).astype(np.float64) for t in (sig, X, W))
+    M64, eps = M.astype(np.float64), np.finfo(NPDT[dt]).eps
+    _svd_check(sig, X, W, M64, dt, kind)
+    # a correction is exp of an antisymmetric matrix, orthogonal to a rounding or two per element: a random walk of ~20 l roundings over
+    # sweeps and corrections, as for the lengths of the columns above
+    assert np.abs(W.T @ W - np.eye(l)).max() <= 8 * eps * np.sqrt(20 * l)
+    want = np.linalg.svd(M64, compute_uv=False)
+    assert np.abs(sig - want).max() <= 20 * eps * np.sqrt(l) * want[0]
+
+
 @pytest.mark.parametrize("l", [129, 300, 576])
 @pytest.mark.parametrize("cond", [1.0, 1e3])
 def test_block_jacobi_values_do_not_drift(l, cond):
