@@ -231,12 +231,14 @@ hipError_t apply_tri_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int6
 // One-sided Jacobi SVD  M = X diag(sigma) W^T  of the l x l row-major matrix M
 // (ld l; fp64 when m_is_f64 else `dtype`).  Outputs in `dtype`, sigma descending.
 // batch > 1 (LDS-resident orders only): problem b = blockIdx.x adds b * stride bytes to M, sigma, X, W.
-// slots (may be NULL): eight more l x l matrices of type `dtype` to work in (of problem 0; strided like the rest), with which the last
-// sweeps give way to corrections of the whole matrix.  M, X and W may lie among them if they are dead or not yet written.
+// slots (may be NULL; one problem only): eight more l x l matrices of type `dtype` to work in, with which the last sweeps give way to
+// corrections of the whole matrix.  The sixth and seventh may be M and X: they are written when M has been read and before X is.
 // rows != 0: the rotations act on the rows of M, i.e. M^T = X diag(sigma) W^T is what is decomposed (the
 // caller swaps X and W to get the factors of M).  One-sided Jacobi converges much faster on vectors of graded
 // length; of a triangular factor those are the rows.
 struct JacobiSlots { void *slot[8]; };
+// One problem of this order, given in fp64 and with slots, takes the block path although it fits in the LDS of a workgroup.
+bool jacobi_prefers_blocks(rsvd_dtype dtype, int64_t l);
 hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t l,
                          const void *M, int m_is_f64, void *sigma, void *X, void *W,
                          DevInfo *info, void *scratch, size_t scratch_bytes, int batch = 1, int64_t stride = 0,

@@ -1891,6 +1891,14 @@ static int jb_block_width(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t l) {
   return 0;
 }
 
+// One workgroup that rotates columns in LDS, or many on blocks of columns with corrections behind (us; triangular factors of a Gaussian
+// matrix, and of nearly aligned factors with values exp(-3 i / l) and (1 + i)^-1/2):
+//   fp32  l = 80 448, 217, 218 against 488, 228, 269; 96 534, 260, 258 against 486, 249, 273; 104 740, 336, 342 against 652, 290, 332;
+//         120 796, 396, 399 against 662, 300, 354 (100000 x 1000 centred, l = 120, q = 3: 2898 -> 2715 for the whole call)
+//   fp64  l = 56 395, 239, 242 against 429, 245, 269; 64 479, 266, 275 against 393, 245, 271; 72 700, 409, 414 against 592, 296, 325;
+//         96 1064, 571, 583 against 582, 303, 365
+bool jacobi_prefers_blocks(rsvd_dtype dtype, int64_t l) { return l >= (dtype == RSVD_F32 ? 97 : 65); }
+
 // Scratch of the block path: header, Mt, Jt, norms, ranks.
 size_t jacobi_scratch_bytes(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t l) {
   if (l <= jacobi_max_lds_order(ctx, dtype)) return 0;
@@ -1916,14 +1924,18 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
   const int b = jb_block_width(ctx, dtype, l);
   if (b == 0) return hipErrorNotSupported;
   const size_t es = sizeof(T);
-  JbHeader *hdr = reinterpret_cast<JbHeader *>(scratch);
-  char *p = scratch + align_up(sizeof(JbHeader), 256);
-  T *Mt = reinterpret_cast<T *>(p); p += align_up((size_t)l * l * es, 256);
-  T *Jt = reinterpret_cast<T *>(p); p += align_up((size_t)l * l * es, 256);
-  T *nrm = reinterpret_cast<T *>(p); p += align_up((size_t)l * es, 256);
-  int *rnk = reinterpret_cast<int *>(p); p += align_up((size_t)l * sizeof(int), 256);
   const int nblk = (l + b - 1) / b;
-  T *Tring = reinterpret_cast<T *>(p); p += align_up((size_t)2 * nblk * 4 * b * b * es, 256);   // [2][nblk][2b][2b]
+  // (orders that the workspace has no scratch for work in the slots: M and J in the first two, all but the matrices in the last)
+  const bool in_slots = l <= jacobi_max_lds_order(ctx, dtype);
+  char *p = in_slots ? (char *)slots->slot[7] : scratch;
+  auto take = [&](size_t bytes) { char *at = p; p += align_up(bytes, 256); return at; };
+  JbHeader *hdr = reinterpret_cast<JbHeader *>(take(sizeof(JbHeader)));
+  T *Mt = in_slots ? (T *)slots->slot[0] : reinterpret_cast<T *>(take((size_t)l * l * es));
+  T *Jt = in_slots ? (T *)slots->slot[1] : reinterpret_cast<T *>(take((size_t)l * l * es));
+  T *nrm = reinterpret_cast<T *>(take((size_t)l * es));
+  int *rnk = reinterpret_cast<int *>(take((size_t)l * sizeof(int)));
+  // [2][nblk][2b][2b]; the flow kernel has no use for it: its counters lie there
+  T *Tring = reinterpret_cast<T *>(take(in_slots ? sizeof(JbSync) + (size_t)2 * nblk * sizeof(int) : (size_t)2 * nblk * 4 * b * b * es));
   int *chg = reinterpret_cast<int *>(p);                                                        // [2][nblk]
   const int nblk2 = nblk + (nblk & 1);
   const int nv = jb_units_per_lane(dtype, l);
@@ -1932,7 +1944,6 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
   const size_t lds_j = ((size_t)(2 * b) * (kJbRowChunk + 8) + (size_t)(2 * b) * (2 * b + 2)) * es;   // jb_apply_t
   const size_t lds = lds_rot > lds_j ? lds_rot : lds_j;
   const int chunks = (l + kJbRowChunk - 1) / kJbRowChunk;
-  // the flow kernel has no use for the ring: its counters lie there, the progress of the column blocks behind them
   const bool flow = jb_takes_flow<T>(ctx, b, l);
   JbSync *sync = flow ? reinterpret_cast<JbSync *>(Tring) : nullptr;
   int *ver2 = reinterpret_cast<int *>(sync + 1);
@@ -1950,7 +1961,7 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
     if (corrections) {
       PolishParams<T> P;
       P.b[0] = Mt; P.b[1] = Jt;
-      for (int i = 0; i < 5; ++i) P.b[2 + i] = (T *)slots->slot[i];
+      for (int i = 0; i < 5; ++i) P.b[2 + i] = (T *)slots->slot[i + (in_slots ? 2 : 0)];
       Mt2 = P.b[3]; Jt2 = P.b[4];
       P.sync = sync; P.l = l; P.tiles = (l + kPoTile - 1) / kPoTile; P.stride = 0;
       hipLaunchKernelGGL((jb_flow_kernel<T>), dim3(nblk2), dim3(1024), jg_lds_bytes<T>(l), s, Mt, Jt, Mt2, Jt2, l, nblk,
@@ -2091,7 +2102,7 @@ hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t
                          int m_is_f64, void *sigma, void *X, void *W, DevInfo *info, void *scratch,
                          size_t scratch_bytes, int batch, int64_t stride, int rows, const JacobiSlots *slots) {
   if (batch < 1 || batch > 65535) return hipErrorInvalidValue;
-  if (l > jacobi_max_lds_order(ctx, dtype)) {
+  if (l > jacobi_max_lds_order(ctx, dtype) || (batch == 1 && slots != nullptr && m_is_f64 && jacobi_prefers_blocks(dtype, l))) {
     if (batch != 1) {
       // the block path is not batched: fp64 orders up to 128 take the one-workgroup kernel with J in global memory
       // (the block path's scratch, which every problem of the batch has, is larger than one J)
@@ -2108,7 +2119,8 @@ hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t
     }
     // block path: needs the fp64 input (the triangular factor) and its scratch
     const size_t need = jacobi_scratch_bytes(ctx, dtype, l);
-    if (need == 0 || scratch == nullptr || scratch_bytes < need || !m_is_f64) return hipErrorNotSupported;
+    if (l > jacobi_max_lds_order(ctx, dtype) && (need == 0 || scratch == nullptr || scratch_bytes < need || !m_is_f64))
+      return hipErrorNotSupported;
     if (dtype == RSVD_F32)
       return jacobi_block_launch<float>(ctx, s, dtype, (int)l, (const double *)M, (float *)sigma, (float *)X,
                                         (float *)W, info, (char *)scratch, rows, slots);

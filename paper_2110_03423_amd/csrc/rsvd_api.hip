@@ -434,17 +434,19 @@ static int product(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, const Ws &w, 
   return 0;
 }
 
-// The matrices that the small SVD may work in once the triangular factor has been read: the fp64 ones of the orthonormalisations
-// (in fp32 two to each), the factor itself and the outputs.
-static JacobiSlots jacobi_slots(const Ws &w, rsvd_dtype dtype, int64_t l, void *X, void *W) {
+// The matrices that the small SVD may work in: the fp64 ones of the orthonormalisations (in fp32 two to each), the factor, which it reads
+// first, and X, which it writes last; `spare` has room for another.
+static JacobiSlots jacobi_slots(const Ws &w, rsvd_dtype dtype, int64_t l, void *X, void *spare) {
   const Layout &L = w.L;
   JacobiSlots j;
   if (dtype == RSVD_F64) {
-    void *const m[8] = {w.at<void>(L.G), w.at<void>(L.R1), w.at<void>(L.R2), w.at<void>(L.R3), w.at<void>(L.R4), w.at<void>(L.Rb), X, W};
+    void *const m[8] = {w.at<void>(L.G), w.at<void>(L.R1), w.at<void>(L.R2), w.at<void>(L.R3), w.at<void>(L.R4), w.at<void>(L.Rb), X, spare};
     for (int i = 0; i < 8; ++i) j.slot[i] = m[i];
   } else {
     const size_t m[4] = {L.G, L.R1, L.R2, L.Rb};
-    for (int i = 0; i < 8; ++i) j.slot[i] = w.at<float>(m[i >> 1]) + (i & 1) * l * l;
+    for (int i = 0; i < 5; ++i) j.slot[i] = w.at<float>(m[i >> 1]) + (i & 1) * l * l;
+    for (int i = 0; i < 2; ++i) j.slot[5 + i] = w.at<float>(L.Rb) + i * l * l;
+    j.slot[7] = spare;
   }
   return j;
 }
@@ -459,7 +461,7 @@ static int small_svd(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, const Ws &w
   // Rb = X Sigma W^T from the rows of Rb, i.e. from Rb^T = W Sigma X^T (hence the swapped outputs): the rows of the
   // triangular factor are graded like the singular values, its columns are not, and the rotations converge in
   // about half the sweeps on the former when the spectrum is steep (a third when the factor is rank deficient)
-  const JacobiSlots slots = jacobi_slots(w, dtype, l, w.at<void>(L.Wj), w.at<void>(L.Xj));
+  const JacobiSlots slots = jacobi_slots(w, dtype, l, w.at<void>(L.Wj), tmp);
   hipError_t e = jacobi_launch(ctx, s, dtype, l, w.at<void>(L.Rb), 1, w.at<void>(L.sigma), w.at<void>(L.Wj),
                                w.at<void>(L.Xj), w.at<DevInfo>(L.info), w.at<void>(L.jac_scratch),
                                L.jac_scratch_bytes, w.batch, w.stride, 1, &slots);
@@ -972,13 +974,13 @@ int rsvd_stage_jacobi(rsvd_ctx *ctx, void *stream, rsvd_dtype dtype, int64_t l, 
   RSVD_TRY(zero_ints_launch(s, w.at<int>(w.L.info), kDevInfoInts), "zero info");
   const void *Min = M;
   int min_f64 = dtype == RSVD_F64;
-  if (dtype == RSVD_F32 && l > jacobi_max_lds_order(ctx, dtype)) {
+  if (dtype == RSVD_F32 && (l > jacobi_max_lds_order(ctx, dtype) || jacobi_prefers_blocks(dtype, l))) {
     // the block path reads an fp64 matrix: widen M into the slot of the triangular factor
     RSVD_TRY(widen_launch(s, (const float *)M, w.at<double>(w.L.Rb), l * l), "widen");
     Min = w.at<void>(w.L.Rb);
     min_f64 = 1;
   }
-  const JacobiSlots slots = jacobi_slots(w, dtype, l, X, W);
+  const JacobiSlots slots = jacobi_slots(w, dtype, l, X, w.at<void>(w.L.bufM[0]));
   hipError_t e = jacobi_launch(ctx, s, dtype, l, Min, min_f64, sigma, X, W, w.at<DevInfo>(w.L.info),
                                w.at<void>(w.L.jac_scratch), w.L.jac_scratch_bytes, 1, 0, 0, &slots);
   if (e == hipErrorNotSupported) return RSVD_ERR_UNSUPPORTED;

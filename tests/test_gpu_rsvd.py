@@ -390,3 +390,22 @@ def test_two_contexts_on_two_streams():
         torch.cuda.synchronize()
         for got, want in zip(res, alone):
             assert all(torch.equal(g, w) for g, w in zip(got[:3], want)), f"repetition {rep}"
+
+
+@pytest.mark.parametrize("dt,m,n,k,p", [("f32", 100, 97, 97, 0), ("f32", 128, 128, 120, 8), ("f64", 65, 65, 60, 5), ("f64", 96, 131, 90, 6),
+                                        ("f64", 97, 97, 97, 0)])
+def test_sketch_as_wide_as_the_matrix(dt, m, n, k, p):
+    """k + p = min(m, n): the small SVD works in buffers of the call that have room for l x l and no more."""
+    say("full width", dt, m, n, k, p)
+    T = np.float32 if dt == "f32" else np.float64
+    A = workloads.graded_matrix(max(m, n), max(m, n), 1e3, seed=m, dtype=T)[:m, :n].copy()
+    S, U, Vt, info = ctx().rsvd_run(to_dev(A), k, p, 1, seed=2)
+    assert info.status == 0
+    S, U, Vt = (to_np(t).astype(np.float64) for t in (S, U, Vt))
+    want = np.linalg.svd(A.astype(np.float64), compute_uv=False)
+    eps = np.finfo(T).eps
+    # the basis is the whole space: what is off are the roundings of the products, ~l terms each
+    assert np.abs(S - want[:k]).max() <= 32 * eps * np.sqrt(k + p) * want[0]
+    assert parity.orthonormality(U) <= parity.jacobi_tol(k + p, dt) and parity.orthonormality(Vt.T) <= parity.jacobi_tol(k + p, dt)
+    if p == 0:
+        assert np.linalg.norm(A - (U * S) @ Vt) <= 64 * eps * np.linalg.norm(A)

@@ -278,8 +278,8 @@ def test_block_jacobi_edges(dt, l):
 
 # What the corrections of the whole matrix behind the sweeps meet: angles of every size (each length of the series, halvings), clusters
 # that they leave to further sweeps, zero and negligible columns; orders with one and with 31 rows or columns in the last 32 x 32 tile,
-# and on either side of a limit on the angles.
-@pytest.mark.parametrize("dt,l", [("f64", 97), ("f64", 159), ("f64", 257), ("f32", 129), ("f32", 161), ("f32", 191), ("f32", 290)])
+# and on either side of a limit on the angles.  The first four are the smallest and largest orders that would fit into one workgroup.
+@pytest.mark.parametrize("dt,l", [("f64", 65), ("f64", 96), ("f32", 97), ("f32", 128), ("f64", 97), ("f64", 159), ("f64", 257), ("f32", 129), ("f32", 161), ("f32", 191), ("f32", 290)])
 @pytest.mark.parametrize("kind", ["fast", "slow", "steep", "clusters", "rank"])
 def test_block_jacobi_corrections(dt, l, kind):
     say("block jacobi corrections", dt, l, kind)
