@@ -1,11 +1,38 @@
-// GEMM instantiation: inputs double, MFMA accumulator double, output double.
-#include "gemm_impl.hpp"
+// Products of fp64 operands: gemm_pipe.hpp where their rows are 16-byte pieces and there is no centring, else gemm_impl.hpp.
+#include "gemm_pipe.hpp"
 
 namespace rsvd {
 size_t gemm_partial_bytes_f64(const rsvd_ctx *ctx, int64_t M, int64_t N, int64_t K, int trans_a) {
   return GemmDispatch<double, double, double>::partial_bytes(ctx, M, N, K, trans_a != 0);
 }
+
+template <bool TA, int BM, int BN, int WGM, int WGN> using Run64 = PipeRun<double, TA, BM, BN, WGM, WGN>;
+#define RSVD_PIPE_TILES(X) X(64, 16, 4, 1) X(64, 32, 4, 1) X(64, 48, 4, 1) X(64, 64, 4, 1) X(64, 80, 4, 1) X(64, 96, 4, 1) \
+  X(64, 112, 4, 1) X(64, 128, 4, 1) X(128, 64, 2, 2) X(128, 96, 2, 2) X(128, 128, 2, 2)
+
+template <bool TA>
+static hipError_t pipe_by_tile(hipStream_t s, const GemmParams &P, int bm, int bn, int batch) {
+#define RSVD_PIPE(BM, BN, WGM, WGN) if (bm == BM && bn == BN) return Run64<TA, BM, BN, WGM, WGN>::go(s, P, batch);
+  RSVD_PIPE_TILES(RSVD_PIPE)
+#undef RSVD_PIPE
+  return hipErrorInvalidValue;
+}
+
+// Tile and kernel by shape.  Up to 128 columns one tile of 64 rows; beyond, 128 rows and the column tile with the least padding (20000 x
+// 20000, l = 288, 128 x 96 against 64 x 96: A X 3.84 against 4.07 ms, A^T X 3.81 against 4.11).  Below 10^7 multiply-adds (the blocks of a
+// Cholesky factorisation) either kernel waits for its first loads.
 hipError_t gemm_launch_f64(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d) {
-  return GemmDispatch<double, double, double>::launch(ctx, s, d);
+  if (d.M <= 0 || d.N <= 0) return hipSuccess;
+  const double madds = (double)d.M * (double)d.N * (double)d.K * (double)d.batch;
+  if (madds < 1e7 || !pipe_can<double>(d)) return GemmDispatch<double, double, double>::launch(ctx, s, d);
+  int bm = 64, bn = (int)ceil_div(d.N, 16) * 16;
+  if (d.N > 128) {
+    const int64_t pad64 = ceil_div(d.N, 64) * 64, pad96 = ceil_div(d.N, 96) * 96, pad128 = ceil_div(d.N, 128) * 128;
+    bm = 128;
+    bn = pad96 <= pad128 && pad96 <= pad64 ? 96 : pad64 < pad128 ? 64 : 128;
+  }
+  return pipe_launch<double>(ctx, s, d, bm, bn, [&](const GemmParams &P) {
+    return d.trans_a ? pipe_by_tile<true>(s, P, bm, bn, d.batch) : pipe_by_tile<false>(s, P, bm, bn, d.batch);
+  });
 }
 }  // namespace rsvd

@@ -1,0 +1,295 @@
+// Products C = op(A) B whose operands have 16-byte rows, with k-tiles that go from memory to LDS without touching a register.
+//
+// gemm_kernel (gemm_impl.hpp) loads a k-tile into registers, writes it to LDS between two barriers and hides what that costs behind four
+// or five workgroups per CU.  In fp64 with 48 columns and more it kept the matrix pipe busy for half of the time (a matrix instruction
+// takes 64 cycles, but the wavefronts of a workgroup read their operands all at once behind a barrier), and the ~1000 k ranges that such
+// a grid wants write and read partial sums of a third of A.  Here a workgroup has a ring of S k-tiles of 128 bytes of k each in LDS,
+// filled by loads that write there themselves: one barrier per k-tile, no staging registers, k-tiles half as deep.  Times in us,
+// gemm_kernel -> this, A X and A^T X: 5000 x 5000, l = 64 93 -> 70, 90 -> 69; 30000 x 1000, l = 48 87 -> 69, 84 -> 66; 20000 x 10000, l = 96
+// 743 -> 683, 927 -> 682; 8000 x 2000, l = 210 201 -> 150, 197 -> 150; 20000 x 20000, l = 288 4300 -> 3841, 3971 -> 3809 (60 TFLOP/s, pipe busy 77 %
+// at 2.4 GHz; 8 % of the rest is the last wave).  Up to 32 columns, where memory is the bound, about the same (3000 x 20000, l = 16 102 ->
+// 92, 94 -> 98).  What was tried: four more k-tiles in flight with two workgroups per CU (5 to 12 % slower at l = 48 and 64 than four workgroups
+// with one k-tile ahead); the work dealt out evenly in k-tiles, sums of shared tiles added behind (the loop that crosses tiles costs more
+// than the last wave: 3.83 -> 3.97 ms at l = 288, with 64-row tiles 4.4); fp32 operands, narrow (no gain: l = 32 within 3 %, l = 48 5 to
+// 15 % slower than the split products) and summed in fp64 (Gram matrices of 65536 x 576: 8 % slower).
+//
+// LDS is written in the order of the lanes, 16 bytes each, so a layout is chosen by which piece of memory a lane fetches:
+//   [row][k] tiles (A as stored): 128 bytes a row, the eight pieces of row r in places piece ^ (r / 2 mod 8): sixteen lanes that read
+//     the same k of sixteen rows, 16 bytes each, meet every bank once;
+//   [k][column] tiles (B, and A for A^T): a lane's 16 bytes down a row of A are V consecutive k, one for each of V matrix
+//     instructions, so the lanes of instruction (t, e) need the rows k = 4 V t + V kq + e, kq = 0 ... 3: these lie next to each other (row
+//     4 V t + 4 e + kq), their pieces exchanged by kq where the row length would bring them to the same banks.
+#pragma once
+
+#include "gemm_impl.hpp"
+
+namespace rsvd {
+
+// Workgroups that share a CU, and the k-tiles each has room for (in the 64 KB that a launch may ask for without more ado).
+constexpr int pipe_wgs(int bm, int bn) { return bm > 64 || bn <= 16 ? 2 : bn <= 96 ? 4 : 3; }
+constexpr int pipe_stages(int bm, int bn) {
+  const int kb = 160 / pipe_wgs(bm, bn) < 64 ? 160 / pipe_wgs(bm, bn) : 64;
+  return kb * 1024 / ((bm + bn) * 128);
+}
+
+template <typename T> struct Pipe {
+  static constexpr int V = 16 / (int)sizeof(T), BK = 128 / (int)sizeof(T);      // elements of a piece, depth of a k-tile
+};
+
+// Operand of s_waitcnt: at most n vector memory operations outstanding, no LDS operation.
+constexpr int pipe_wait(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; }
+
+// Place of piece `ch` in a row of a [k][column] tile of X columns that the lanes kq read.
+template <typename T, int X> __device__ __forceinline__ int pipe_place(int ch, int kq) {
+  constexpr int bytes = X * (int)sizeof(T) % 256, window = 16 * (int)sizeof(T);      // what sixteen lanes read of a row
+  if (window == 64) return bytes == 0 ? ch ^ (kq << 2) : bytes == 128 ? ch ^ ((kq >> 1) << 2) : ch;
+  return bytes == 0 ? ch ^ ((kq & 1) << 3) : ch;
+}
+
+// The loads of one operand tile of a k-tile, ROWS x BK or BK x ROWS elements, by four wavefronts.
+//   KMAJOR: consecutive elements of the stored matrix run along the rows / columns of the tile, k from row to row of the matrix.
+template <typename T, int ROWS, bool KMAJOR> struct PipeLoad {
+  static constexpr int V = Pipe<T>::V, BK = Pipe<T>::BK;
+  static constexpr int BYTES = ROWS * 128, PIECES = BYTES / 1024, N = (PIECES + 3) / 4;       // of 1024 bytes; per wavefront
+  const T *at[N];
+  int k_of[N];               // first k of the lane's 16 bytes inside the tile
+  // origin: element (0, 0) of the first tile.  extent: rows (columns) that exist; those beyond are read as another one, and not stored.
+  __device__ __forceinline__ void init(const T *origin, int64_t ld, int extent, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int q = piece(wave, i) * 64 + lane;            // place in LDS, 16 bytes each
+      if (KMAJOR) {
+        constexpr int PER = ROWS / V;
+        const int rp = q / PER, kq = rp & 3, ch = pipe_place<T, ROWS>(q - rp * PER, kq);
+        const int k = (rp / (4 * V)) * (4 * V) + V * kq + ((rp >> 2) & (V - 1));
+        k_of[i] = k;
+        at[i] = origin + (int64_t)k * ld + (ch * V < extent ? ch * V : 0);
+      } else {
+        const int row = q >> 3, ch = (q & 7) ^ ((row >> 1) & 7);
+        k_of[i] = ch * V;
+        at[i] = origin + (int64_t)(row < extent ? row : extent - 1) * ld + ch * V;
+      }
+    }
+  }
+  static __device__ __forceinline__ int piece(int wave, int i) {
+    const int p = wave + 4 * i;
+    return PIECES % 4 == 0 || p < PIECES ? p : PIECES - 1;       // (left over: the last piece once more)
+  }
+  // k_left: k of the tile that exist (others are read as k = 0; the tile of B is cleared there)
+  __device__ __forceinline__ void issue(char *lds, int64_t ld, int k_left, int wave) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const T *src = at[i];
+      if (k_of[i] >= k_left) src -= KMAJOR ? (int64_t)k_of[i] * ld : (int64_t)k_of[i];
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                       (__attribute__((address_space(3))) void *)(lds + piece(wave, i) * 1024), 16, 0, 0);
+      at[i] += KMAJOR ? BK * ld : BK;
+    }
+  }
+};
+
+template <typename T, int BM, int BN, int S> struct PipeCfg {
+  static constexpr int STAGE = (BM + BN) * 128;
+  static constexpr size_t lds = (size_t)S * STAGE;
+};
+
+template <typename T, bool TA, int BM, int BN, int WGM, int WGN, int S, int EPI>
+__global__ __launch_bounds__(256, pipe_wgs(BM, BN)) void gemm_pipe_kernel(const GemmParams P0) {
+  const GemmParams P = select_problem(P0);
+  if (P.skip_now) return;
+  static_assert(WGM * WGN == 4, "four wavefronts per workgroup");
+  constexpr int V = Pipe<T>::V, BK = Pipe<T>::BK, STAGE = PipeCfg<T, BM, BN, S>::STAGE;
+  constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
+  typedef T piece_t __attribute__((ext_vector_type(16 / sizeof(T))));
+  extern __shared__ __attribute__((aligned(16))) char pipe_lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
+  const int r16 = lane & 15, kq = lane >> 4;
+  int tile_m, tile_n, split;
+  tile_of_workgroup(P, tile_m, tile_n, split);
+  const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
+  if (P.upper_bm > 0 && n0 + BN <= m0) return;       // symmetric result: this tile mirrors one that is computed
+  const int64_t k_begin = (int64_t)split * P.k_per_split;
+  int64_t k_end = (k_begin + P.k_per_split < P.K) ? (k_begin + P.k_per_split) : P.K;
+  if (P.b_upper != 0 && n0 + BN < k_end) k_end = n0 + BN;      // rows of B from n0 + BN on are zero in these columns
+  const int nkt = k_begin < k_end ? (int)((k_end - k_begin + BK - 1) / BK) : 0;
+  const int last_k = (int)(k_end - k_begin) - (nkt - 1) * BK;
+
+  typedef typename Mfma<T>::vec acc_t;
+  acc_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = (acc_t)(T)0;
+
+  PipeLoad<T, BM, TA> la;
+  PipeLoad<T, BN, true> lb;
+  const T *A = (const T *)P.A, *B = (const T *)P.B;
+  la.init(TA ? A + k_begin * P.lda + m0 : A + m0 * P.lda + k_begin, P.lda, (int)(P.M - m0 < BM ? P.M - m0 : BM), wave, lane);
+  lb.init(B + k_begin * P.ldb + n0, P.ldb, (int)(P.N - n0 < BN ? P.N - n0 : BN), wave, lane);
+  constexpr int LOADS = decltype(la)::N + decltype(lb)::N;      // a wavefront's loads per k-tile
+  static_assert((S - 2) * LOADS < 64, "the counter of outstanding loads ends at 63");
+  int issued = 0;
+  auto issue = [&]() {
+    // (behind the last tile nothing is loaded: the last iterations wait for everything)
+    if (issued < nkt) {
+      char *st = pipe_lds + (issued % S) * STAGE;
+      const int left = issued + 1 < nkt ? BK : last_k;
+      la.issue(st, P.lda, left, wave);
+      lb.issue(st + BM * 128, P.ldb, left, wave);
+    }
+    ++issued;
+  };
+#pragma unroll
+  for (int s = 0; s < S - 1; ++s) issue();
+
+  // offsets of this lane's operands inside a stage
+  int a_row[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int row = wm0 + i * 16 + r16;
+    a_row[i] = TA ? 0 : row * 128;
+  }
+  const int a_swz = TA ? 0 : ((wm0 + r16) >> 1) & 7;           // (the same in every block of 16 rows)
+  auto column = [&](auto x, int col) {                          // byte offset of column `col` in a [k][column] row read by lanes kq
+    constexpr int X = decltype(x)::value;
+    return pipe_place<T, X>(col / V, kq) * 16 + (col % V) * (int)sizeof(T);
+  };
+  int a_col[TM], b_col[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) a_col[i] = TA ? column(std::integral_constant<int, BM>(), wm0 + i * 16 + r16) + kq * BM * (int)sizeof(T) : 0;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) b_col[j] = BM * 128 + column(std::integral_constant<int, BN>(), wn0 + j * 16 + r16) + kq * BN * (int)sizeof(T);
+
+  for (int kt = 0; kt < nkt; ++kt) {
+    // tile kt has landed once at most the loads of the S - 2 tiles behind it are outstanding
+    asm volatile("" ::: "memory");
+    if (kt + S - 1 <= nkt) __builtin_amdgcn_s_waitcnt(pipe_wait((S - 2) * LOADS));
+    else __builtin_amdgcn_s_waitcnt(pipe_wait(0));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const char *st = pipe_lds + (kt % S) * STAGE;
+    if (kt + 1 == nkt && last_k < BK) {
+      // rows of B beyond the last are zero (row rp of the tile holds k = ...)
+      T *bt = reinterpret_cast<T *>(pipe_lds + (kt % S) * STAGE + BM * 128);
+      for (int e = tid; e < BK * BN; e += 256) {
+        const int rp = e / BN, k = (rp / (4 * V)) * (4 * V) + V * (rp & 3) + ((rp >> 2) & (V - 1));
+        if (k >= last_k) bt[e] = (T)0;
+      }
+      __syncthreads();
+    }
+    issue();
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      T af[TM][V], bf[V][TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        if (TA) {
+#pragma unroll
+          for (int e = 0; e < V; ++e)
+            af[i][e] = *reinterpret_cast<const T *>(st + (4 * V * t + 4 * e) * BM * (int)sizeof(T) + a_col[i]);
+        } else {
+          const piece_t x = *reinterpret_cast<const piece_t *>(st + a_row[i] + (((4 * t + kq) ^ a_swz) << 4));
+#pragma unroll
+          for (int e = 0; e < V; ++e) af[i][e] = x[e];
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < V; ++e)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          bf[e][j] = *reinterpret_cast<const T *>(st + (4 * V * t + 4 * e) * BN * (int)sizeof(T) + b_col[j]);
+#pragma unroll
+      for (int e = 0; e < V; ++e)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<T>::run(af[i][e], bf[e][j], acc[i][j]);
+    }
+  }
+  gemm_epilogue<T, T, T, TM, TN, EPI>(P, acc, split, m0 + wm0, n0 + wn0, lane);
+}
+
+// ---------------------------------------------------------------- host side
+
+template <typename T, bool TA, int BM, int BN, int WGM, int WGN>
+struct PipeRun {
+  static constexpr int S = pipe_stages(BM, BN);
+  static constexpr size_t lds = PipeCfg<T, BM, BN, S>::lds;
+  static constexpr bool kFull = !TA;      // with the full epilogue (applies, lifts) as well
+  static hipError_t go(hipStream_t s, const GemmParams &P, int batch) {
+    GemmParams Q = P;
+    Q.tiles_n = (int)ceil_div(P.N, BN);
+    Q.tiles_m = (int)ceil_div(P.M, BM);
+    const dim3 grid((unsigned)((int64_t)Q.tiles_n * Q.tiles_m * P.splits), (unsigned)batch);
+    if (P.splits == 1 && (P.dead != nullptr || P.trans_c != 0)) {
+      if constexpr (kFull) hipLaunchKernelGGL((gemm_pipe_kernel<T, TA, BM, BN, WGM, WGN, S, 1>), grid, dim3(256), lds, s, Q);
+      else return hipErrorInvalidValue;
+    } else {
+      hipLaunchKernelGGL((gemm_pipe_kernel<T, TA, BM, BN, WGM, WGN, S, 0>), grid, dim3(256), lds, s, Q);
+    }
+    return hipGetLastError();
+  }
+};
+
+// What this kernel can compute: 16-byte rows, plain sums.
+template <typename T> inline bool pipe_can(const GemmDesc &d) {
+  return GemmDispatch<T, T, T>::vector_loads(d) && d.a_shift == nullptr && d.alpha == 1.0 && d.beta == 0.0 &&
+         !(d.trans_a && (d.dead != nullptr || d.trans_c));
+}
+
+// The number of k ranges, at most `most` (the workspace holds the partial sums of that many), that takes the least time: rounds of
+// workgroups, a k-tile at the rate of the matrix cores or of the memory (both shared by the workgroups in flight), three us for a
+// workgroup's first loads and its stores, and the partial sums written and read at 4.5 TB/s behind a second launch.
+template <typename T>
+inline SplitChoice pipe_ranges(const rsvd_ctx *ctx, const GemmDesc &d, int bm, int bn, int64_t most) {
+  constexpr int BK = 128 / (int)sizeof(T);
+  int64_t tiles = ceil_div(d.M, bm) * ceil_div(d.N, bn);
+  if (d.upper_only) {
+    tiles = 0;
+    for (int64_t tm = 0; tm < ceil_div(d.M, bm); ++tm)
+      for (int64_t tn = 0; tn < ceil_div(d.N, bn); ++tn) tiles += (tn + 1) * bn > tm * bm ? 1 : 0;
+  }
+  tiles *= d.batch;
+  const int64_t ktiles = ceil_div(d.K, BK), places = (int64_t)ctx->cu_count * pipe_wgs(bm, bn);
+  const double rate = sizeof(T) == 8 ? 71e6 : 154e6;                               // flop / us
+  double us = 2.0 * BK * bm * bn * (double)places / rate;
+  const double us_mem = (double)BK * bm * sizeof(T) * (double)places / 5.5e6;
+  if (us < us_mem) us = us_mem;
+  int64_t best = 1;
+  double best_cost = -1.0;
+  for (int64_t r = 1; r <= most && r <= ktiles; ++r) {
+    const int64_t per = ceil_div(ktiles, r), ranges = ceil_div(ktiles, per);
+    const double sums = (double)ranges * (double)d.M * (double)d.N * d.batch * sizeof(T);
+    const double cost = (double)ceil_div(tiles * ranges, places) * ((double)per * us + 3.0) + (ranges > 1 ? 4.0 + 2.0 * sums / 4.5e6 : 0.0);
+    if (best_cost < 0 || cost < best_cost) { best = r; best_cost = cost; }
+  }
+  SplitChoice c;
+  c.k_per_split = ceil_div(ktiles, best) * BK;
+  c.splits = (int)ceil_div(d.K, c.k_per_split);
+  return c;
+}
+
+// by_tile: launches the kernel for this tile.
+template <typename T, typename F>
+inline hipError_t pipe_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, int bm, int bn, F by_tile) {
+  if (d.batch < 1 || d.batch > 65535) return hipErrorInvalidValue;
+  // the k ranges of gemm_kernel bound those taken here: the workspace is sized for their partial sums
+  const TileChoice t = choose_tile(d.M, d.N, d.K, sizeof(T), d.trans_a != 0, d.upper_only != 0);
+  const SplitChoice was = choose_split(ctx, t, d.M, d.N, d.K, d.force_splits, d.upper_only != 0, d.batch);
+  const SplitChoice c = pipe_ranges<T>(ctx, d, bm, bn, d.force_splits > 0 ? d.force_splits : was.splits);
+  if (c.splits > 1) {
+    const size_t need = (size_t)c.splits * (size_t)d.M * (size_t)d.N * sizeof(T);
+    if (d.partial == nullptr || d.partial_bytes < need) return hipErrorInvalidValue;
+  }
+  const GemmParams P = make_params(d, c, d.upper_only ? bm : 0, d.upper_only ? bn : 0);
+  hipError_t e;
+  {
+    ProfScope ps(ctx, s, d.prof_kind);
+    e = by_tile(P);
+  }
+  if (e != hipSuccess) return e;
+  return finish_splits<T, T, T>(ctx, s, d, P);
+}
+
+}  // namespace rsvd

@@ -232,6 +232,23 @@ def test_jacobi_matches_oracle(dt, l):
         assert np.abs(np.abs(np.sum(W * Wo, axis=0)) - 1).max() <= min(0.1, tol)
 
 
+# fp64 products of 16-byte rows go through a ring of k-tiles in LDS: every column tile, one row and one k more and less than tiles of 64, 128
+# and 16, one k-tile in all, several k ranges with an uneven last one, outputs of two and three column tiles.
+@pytest.mark.parametrize("m,n,l", [(64, 16, 16), (66, 18, 10), (62, 4098, 30), (4098, 62, 32), (1026, 1000, 48), (1000, 1030, 50), (130, 3002, 66),
+                                   (2050, 514, 96), (514, 2050, 98), (700, 900, 112), (902, 700, 128), (1298, 640, 130), (640, 1310, 192),
+                                   (1154, 1026, 290), (20002, 302, 20)])
+def test_fp64_products(m, n, l):
+    say("fp64 products", m, n, l)
+    rng = np.random.default_rng(m + n + l)
+    A, X, Q = rng.standard_normal((m, n)), rng.standard_normal((n, l)), rng.standard_normal((m, l))
+    c, eps = ctx(), np.finfo(np.float64).eps
+    for got, want, a, b, terms in ((c.rsvd_stage_gemm_an(to_dev(A), to_dev(X)), A @ X, A, X, n),
+                                   (c.rsvd_stage_gemm_atn(to_dev(A), to_dev(Q)), A.T @ Q, A.T, Q, m)):
+        # rounding errors of a sum add up like a random walk on terms of the size |a_i| |b_j| / sqrt(terms), on either side; 8: the largest of up to 1e6
+        size = np.linalg.norm(a, axis=1)[:, None] * np.linalg.norm(b, axis=0)[None, :]
+        assert (np.abs(to_np(got) - want) <= 8 * eps * np.sqrt(terms) * size / np.sqrt(terms) * max(1.0, np.sqrt(terms) / 4)).all()
+
+
 # Small fp32 panels are orthonormalised in one workgroup up to 16 columns and 1024 rows: one column, rows that are no multiple of
 # 16, the largest panel, the first ones beyond, and columns that depend on others (replaced, the same either way).
 @pytest.mark.parametrize("rows,l,rank", [(1, 1, 1), (17, 1, 1), (40, 16, 16), (333, 7, 7), (1024, 16, 16), (1025, 16, 16), (1024, 17, 17),
