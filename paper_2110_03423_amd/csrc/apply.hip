@@ -46,7 +46,9 @@ template <typename T, int NBLK> constexpr int apply_wgs_per_cu() {
   return words <= 2 ? 6 : words <= 4 ? 4 : words <= 6 ? 2 : 1;
 }
 
-template <typename T, int NBLK, int VEC>
+// TAIL: rows of l elements that are no multiple of 16 bytes, or not aligned to them, in 16-byte pieces all the same (there is slack behind Y,
+// see GemmDesc): the columns beyond the last are zero in LDS, and the last piece of a row is stored element by element.
+template <typename T, int NBLK, int VEC, bool TAIL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (apply_wgs_per_cu<T, NBLK>()))))
 void apply_tri_kernel(const ApplyParams P0) {
   ApplyParams P = P0;
@@ -70,7 +72,7 @@ void apply_tri_kernel(const ApplyParams P0) {
   const T *Y = (const T *)P.Y;
   T *Q = (T *)P.Q;
 
-  TileStage<T, 64, LP, VEC> st;
+  TileStage<T, 64, LP, VEC, false, TAIL> st;
   int tile = (int)blockIdx.x;
   const int G = (int)gridDim.x;
   st.load(Y + (int64_t)tile * 64 * P.ldy, P.ldy, P.rows - (int64_t)tile * 64, l, tid);       // (the grid has no more workgroups than tiles)
@@ -169,7 +171,8 @@ void apply_tri_kernel(const ApplyParams P0) {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     {
       constexpr int SPR = LP / VEC;                    // slots per row
-      typedef T vec_t __attribute__((ext_vector_type(VEC)));
+      typedef T lds_t __attribute__((ext_vector_type(VEC)));
+      typedef T vec_t __attribute__((ext_vector_type(VEC), aligned(TAIL ? sizeof(T) : 16)));
 #pragma unroll
       for (int u = 0; u < (16 * SPR + 63) / 64; ++u) {
         const int idx = lane + 64 * u;
@@ -177,7 +180,10 @@ void apply_tri_kernel(const ApplyParams P0) {
         const int64_t row = m0 + wave * 16 + rl;
         if (idx < 16 * SPR && row < P.rows && c < l) {
           if (VEC == 1) Q[row * P.ldq + c] = mine[rl * SA + c];
-          else *reinterpret_cast<vec_t *>(Q + row * P.ldq + c) = *reinterpret_cast<const vec_t *>(mine + rl * SA + c);
+          else if (!TAIL || c + VEC <= l)
+            *reinterpret_cast<vec_t *>(Q + row * P.ldq + c) = (vec_t)*reinterpret_cast<const lds_t *>(mine + rl * SA + c);
+          else
+            for (int e = 0; c + e < l; ++e) Q[row * P.ldq + c + e] = mine[rl * SA + c + e];
         }
       }
     }
@@ -186,26 +192,28 @@ void apply_tri_kernel(const ApplyParams P0) {
 }
 
 template <typename T, int NBLK>
-static hipError_t apply_run(const rsvd_ctx *ctx, hipStream_t s, ApplyParams P, int batch, bool vec) {
+static hipError_t apply_run(const rsvd_ctx *ctx, hipStream_t s, ApplyParams P, int batch, bool vec, bool slack) {
   typedef ApplyLds<T, NBLK> L;
   int grid = ctx->cu_count * apply_wgs_per_cu<T, NBLK>() / batch;
   if (grid > P.tiles) grid = P.tiles;
   if (grid < 1) grid = 1;
   constexpr int V = 16 / sizeof(T);
-  if (vec) hipLaunchKernelGGL((apply_tri_kernel<T, NBLK, V>), dim3(grid, batch), dim3(256), L::bytes, s, P);
-  else hipLaunchKernelGGL((apply_tri_kernel<T, NBLK, 1>), dim3(grid, batch), dim3(256), L::bytes, s, P);
+  if (vec) hipLaunchKernelGGL((apply_tri_kernel<T, NBLK, V, false>), dim3(grid, batch), dim3(256), L::bytes, s, P);
+  else if (slack) hipLaunchKernelGGL((apply_tri_kernel<T, NBLK, V, true>), dim3(grid, batch), dim3(256), L::bytes, s, P);
+  else hipLaunchKernelGGL((apply_tri_kernel<T, NBLK, 1, false>), dim3(grid, batch), dim3(256), L::bytes, s, P);
   return hipGetLastError();
 }
 
 template <typename T, int NBLK>
 static void apply_raise_lds(hipError_t &e) {
   constexpr int V = 16 / sizeof(T);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&apply_tri_kernel<T, NBLK, V>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)ApplyLds<T, NBLK>::bytes);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&apply_tri_kernel<T, NBLK, 1>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)ApplyLds<T, NBLK>::bytes);
+  constexpr size_t bytes = ApplyLds<T, NBLK>::bytes;
+  if (bytes <= 64 * 1024) return;                    // (what a launch may ask for without this)
+  const void *const kernels[3] = {reinterpret_cast<const void *>(&apply_tri_kernel<T, NBLK, V, false>),
+                                  reinterpret_cast<const void *>(&apply_tri_kernel<T, NBLK, V, true>),
+                                  reinterpret_cast<const void *>(&apply_tri_kernel<T, NBLK, 1, false>)};
+  for (const void *k : kernels)
+    if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
 // Largest l the kernel above takes (the upper triangle of R^-1 in the registers of a wavefront).
@@ -224,7 +232,7 @@ hipError_t apply_init_device(rsvd_ctx *ctx) {
 hipError_t apply_tri_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t rows, int64_t l, const void *Y,
                             int64_t ldy, const void *Rinv, void *Q, int64_t ldq, const int *dead, uint64_t seed,
                             uint32_t refill_stream, double refill_scale, int64_t refill_ld, int batch, int64_t stride,
-                            const int *skip_flag) {
+                            const int *skip_flag, bool slack) {
   if (rows <= 0 || l <= 0) return hipSuccess;
   if (l > apply_tri_max_order(dtype) || batch < 1 || batch > 65535) return hipErrorInvalidValue;
   ApplyParams P;
@@ -241,23 +249,23 @@ hipError_t apply_tri_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int6
   ProfScope ps(ctx, s, PK_APPLY);
   if (dtype == RSVD_F32) {
     switch (nblk) {
-      case 1: return apply_run<float, 1>(ctx, s, P, batch, vec);
-      case 2: return apply_run<float, 2>(ctx, s, P, batch, vec);
-      case 3: return apply_run<float, 3>(ctx, s, P, batch, vec);
-      case 4: return apply_run<float, 4>(ctx, s, P, batch, vec);
-      case 5: return apply_run<float, 5>(ctx, s, P, batch, vec);
-      case 6: return apply_run<float, 6>(ctx, s, P, batch, vec);
-      case 7: return apply_run<float, 7>(ctx, s, P, batch, vec);
-      case 8: return apply_run<float, 8>(ctx, s, P, batch, vec);
+      case 1: return apply_run<float, 1>(ctx, s, P, batch, vec, slack);
+      case 2: return apply_run<float, 2>(ctx, s, P, batch, vec, slack);
+      case 3: return apply_run<float, 3>(ctx, s, P, batch, vec, slack);
+      case 4: return apply_run<float, 4>(ctx, s, P, batch, vec, slack);
+      case 5: return apply_run<float, 5>(ctx, s, P, batch, vec, slack);
+      case 6: return apply_run<float, 6>(ctx, s, P, batch, vec, slack);
+      case 7: return apply_run<float, 7>(ctx, s, P, batch, vec, slack);
+      case 8: return apply_run<float, 8>(ctx, s, P, batch, vec, slack);
     }
   } else {
     switch (nblk) {
-      case 1: return apply_run<double, 1>(ctx, s, P, batch, vec);
-      case 2: return apply_run<double, 2>(ctx, s, P, batch, vec);
-      case 3: return apply_run<double, 3>(ctx, s, P, batch, vec);
-      case 4: return apply_run<double, 4>(ctx, s, P, batch, vec);
-      case 5: return apply_run<double, 5>(ctx, s, P, batch, vec);
-      case 6: return apply_run<double, 6>(ctx, s, P, batch, vec);
+      case 1: return apply_run<double, 1>(ctx, s, P, batch, vec, slack);
+      case 2: return apply_run<double, 2>(ctx, s, P, batch, vec, slack);
+      case 3: return apply_run<double, 3>(ctx, s, P, batch, vec, slack);
+      case 4: return apply_run<double, 4>(ctx, s, P, batch, vec, slack);
+      case 5: return apply_run<double, 5>(ctx, s, P, batch, vec, slack);
+      case 6: return apply_run<double, 6>(ctx, s, P, batch, vec, slack);
     }
   }
   return hipErrorInvalidValue;

@@ -99,6 +99,10 @@ struct GemmDesc {
   void *partial = nullptr; size_t partial_bytes = 0;   // split-K scratch
   int force_splits = 0;                                 // 0 = heuristic
   void *packed = nullptr; size_t packed_bytes = 0;      // fp32 only: room for the split operand B (gemm_packed_bytes), or NULL
+  // slack: at least 16 bytes can be read behind the last row of A (trans_a only) and of B, and what rows are not a multiple of 16 bytes
+  // or not aligned to them may be read in 16-byte pieces all the same: what a piece brings of the next row lands in rows or
+  // columns of C that are not stored.
+  int a_slack = 0, b_slack = 0;
   int prof_kind = PK_SMALL;                             // class of the main kernel; the split-K reduction is +1
   // skip_reduce: leave split-K partials ([splits][M][N], accumulator type) unreduced in
   // `partial` for the consumer to add up; *splits_out receives their number (1 = C was written).
@@ -208,13 +212,13 @@ size_t jacobi_scratch_bytes(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t l);
 // G = Y^T Y in fp64 for panels of at most gram_syrk_max_order() columns (Y rows x l, ld ldy, of type dtype; G l x l,
 // ld l): the 16 x 16 blocks on or above the diagonal only.  The row ranges of the workgroups leave partial matrices
 // ([parts][l][l] in `partial`); up to max_parts of them are left for the consumer to add (*parts_out tells how
-// many; 1 = Gout holds the sum), more are added here.
+// many; 1 = Gout holds the sum), more are added here.  slack: as in GemmDesc.
 int gram_syrk_max_order();
 size_t gram_syrk_partial_bytes(const rsvd_ctx *ctx, int64_t rows, int64_t l);
 hipError_t gram_init_device(rsvd_ctx *ctx);
 hipError_t gram_syrk_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t rows, int64_t l, const void *Y,
                             int64_t ldy, double *Gout, void *partial, size_t partial_bytes, int max_parts,
-                            int *parts_out, int batch, int64_t stride, const int *skip_flag);
+                            int *parts_out, int batch, int64_t stride, const int *skip_flag, bool slack = false);
 
 // Q = Y R^-1 for panels of at most apply_tri_max_order(dtype) columns (Y rows x l, ld ldy; R^-1 l x l upper
 // triangular, ld l; Q may be Y): R^-1 resident in LDS, workgroups walking over 64-row tiles.  Columns flagged in
@@ -226,7 +230,7 @@ hipError_t apply_init_device(rsvd_ctx *ctx);
 hipError_t apply_tri_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t rows, int64_t l, const void *Y,
                             int64_t ldy, const void *Rinv, void *Q, int64_t ldq, const int *dead, uint64_t seed,
                             uint32_t refill_stream, double refill_scale, int64_t refill_ld, int batch, int64_t stride,
-                            const int *skip_flag);
+                            const int *skip_flag, bool slack = false);
 
 // One-sided Jacobi SVD  M = X diag(sigma) W^T  of the l x l row-major matrix M
 // (ld l; fp64 when m_is_f64 else `dtype`).  Outputs in `dtype`, sigma descending.

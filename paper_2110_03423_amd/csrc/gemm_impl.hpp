@@ -94,7 +94,8 @@ __host__ __device__ constexpr int pad_kmajor(int x) { return (x % 32 == 0) ? 16 
 // store(), so that the loads of the next tile stay in flight behind the matrix instructions.
 // (Tried: the offset as a pair of floats, and the subtraction placed behind the matrix instructions
 // of the tile before; neither was faster.)
-template <typename TIn, int ROWS, int COLS, int VEC, bool SHIFT = false>
+// TAIL: cols_left need not be a multiple of VEC; what a piece brings from behind it becomes zero.
+template <typename TIn, int ROWS, int COLS, int VEC, bool SHIFT = false, bool TAIL = false>
 struct TileStage {
   static constexpr int SLOTS_PER_ROW = COLS / VEC;
   static constexpr int SLOTS = ROWS * SLOTS_PER_ROW;
@@ -128,11 +129,11 @@ struct TileStage {
       if (VEC == 1) {
         regs[it][0] = ok ? origin[(int64_t)r * ld + c] : (TIn)0;
       } else {
-        typedef TIn vec_t __attribute__((ext_vector_type(VEC)));
+        typedef TIn vec_t __attribute__((ext_vector_type(VEC), aligned(sizeof(TIn))));
         vec_t v = (vec_t)(TIn)0;
         if (ok) v = *reinterpret_cast<const vec_t *>(origin + (int64_t)r * ld + c);
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) regs[it][e] = v[e];
+        for (int e = 0; e < VEC; ++e) regs[it][e] = !TAIL || c + e < cols_left ? v[e] : (TIn)0;
       }
     }
   }
@@ -643,14 +644,20 @@ struct GemmDispatch {
     return c.splits > 1 ? (size_t)c.splits * (size_t)M * (size_t)N * sizeof(TAcc) : 0;
   }
 
-  // 16-byte vector loads need aligned bases, leading dimensions and extents.
-  static bool vector_loads(const GemmDesc &d) {
+  // 16-byte vector loads need aligned bases, leading dimensions and extents, or slack behind the operand.  (The narrow operand is the
+  // one that often is neither: 20000 x 2000 fp32, l = 30, whole call 460 us with scalar loads of it, 400 at l = 32.)
+  static bool aligned_a(const GemmDesc &d) {
     constexpr int V = 16 / sizeof(TIn);
     const int64_t a_contig = d.trans_a ? d.M : d.K;
-    return ((uintptr_t)d.A % 16 == 0) && ((uintptr_t)d.B % 16 == 0) && d.lda % V == 0 &&
-           d.ldb % V == 0 && a_contig % V == 0 && d.N % V == 0 &&
-           (d.batch == 1 || (d.stride_a % 16 == 0 && d.stride_b % 16 == 0)) &&
+    return (uintptr_t)d.A % 16 == 0 && d.lda % V == 0 && a_contig % V == 0 && (d.batch == 1 || d.stride_a % 16 == 0);
+  }
+  static bool aligned_b(const GemmDesc &d) {
+    constexpr int V = 16 / sizeof(TIn);
+    return (uintptr_t)d.B % 16 == 0 && d.ldb % V == 0 && d.N % V == 0 && (d.batch == 1 || d.stride_b % 16 == 0) &&
            (d.B_alt == nullptr || (uintptr_t)d.B_alt % 16 == 0);
+  }
+  static bool vector_loads(const GemmDesc &d) {
+    return (aligned_a(d) || (d.a_slack != 0 && d.trans_a != 0)) && (aligned_b(d) || d.b_slack != 0);
   }
 
   static hipError_t launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d) {

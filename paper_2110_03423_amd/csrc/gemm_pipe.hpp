@@ -234,7 +234,7 @@ struct PipeRun {
 
 // What this kernel can compute: 16-byte rows, plain sums.
 template <typename T> inline bool pipe_can(const GemmDesc &d) {
-  return GemmDispatch<T, T, T>::vector_loads(d) && d.a_shift == nullptr && d.alpha == 1.0 && d.beta == 0.0 &&
+  return GemmDispatch<T, T, T>::aligned_a(d) && GemmDispatch<T, T, T>::aligned_b(d) && d.a_shift == nullptr && d.alpha == 1.0 && d.beta == 0.0 &&
          !(d.trans_a && (d.dead != nullptr || d.trans_c));
 }
 

@@ -205,7 +205,7 @@ static hipError_t syrk_by_order(hipStream_t s, const SyrkParams &P, int wgs, int
 // up to max_parts of them are left, more are added here into Gout.
 hipError_t gram_syrk_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t rows, int64_t l, const void *Y,
                             int64_t ldy, double *Gout, void *partial, size_t partial_bytes, int max_parts,
-                            int *parts_out, int batch, int64_t stride, const int *skip_flag) {
+                            int *parts_out, int batch, int64_t stride, const int *skip_flag, bool slack) {
   if (l < 1 || l > gram_syrk_max_order() || rows < 1 || batch < 1 || batch > 65535) return hipErrorInvalidValue;
   int64_t rpw; int wgs;
   syrk_split(ctx, rows, l, batch, rpw, wgs);
@@ -217,7 +217,7 @@ hipError_t gram_syrk_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int6
   P.stride_y = stride; P.stride_out = stride;
   P.skip_flag = skip_flag; P.stride_flag = stride;
   const int64_t V = 16 / (int64_t)dtype_size(dtype);
-  const bool vec = ((uintptr_t)Y % 16 == 0) && ldy % V == 0 && l % V == 0 && (batch == 1 || stride % 16 == 0);
+  const bool vec = slack || (((uintptr_t)Y % 16 == 0) && ldy % V == 0 && l % V == 0 && (batch == 1 || stride % 16 == 0));
   hipError_t e;
   {
     ProfScope ps(ctx, s, PK_GRAM);

@@ -236,6 +236,7 @@ struct Ws {
   Layout L;
   int batch = 1;           // equal-shaped problems handled by every launch
   int64_t stride = 0;      // bytes between the workspaces of consecutive problems (every buffer of L)
+  bool own_panels = false; // the panels are those of L: other buffers of L lie behind each of them
   bool has_packed = false; // the caller's workspace also holds L.packed
   template <typename P> P *at(size_t off) const { return reinterpret_cast<P *>(base + off); }
 };
@@ -313,7 +314,7 @@ static int orthonormalize(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, const 
     int parts = 1;
     if (l <= gram_syrk_max_order()) {
       RSVD_TRY(gram_syrk_launch(ctx, s, dtype, rows, l, from, ld_from, w.at<double>(L.G), w.at<void>(L.partial),
-                                L.partial_bytes, 4, &parts, w.batch, w.stride, gate),
+                                L.partial_bytes, 4, &parts, w.batch, w.stride, gate, w.own_panels),
                "gram");
     } else {
       GemmDesc g;
@@ -324,6 +325,7 @@ static int orthonormalize(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, const 
       g.prof_kind = PK_GRAM;
       g.batch = w.batch; g.stride_a = g.stride_b = g.stride_c = g.stride_partial = w.stride;
       g.skip_flag = gate; g.stride_flag = w.stride;
+      g.a_slack = g.b_slack = w.own_panels;
       g.upper_only = 1;              // the blocked factorisation reads the upper block triangle only
       RSVD_TRY(gemm_launch(ctx, s, gram, g), "gram");
     }
@@ -334,7 +336,7 @@ static int orthonormalize(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, const 
     if (l <= apply_tri_max_order(dtype)) {
       RSVD_TRY(apply_tri_launch(ctx, s, dtype, rows, l, from, ld_from, w.at<void>(L.Rinv), to, ld_to, w.at<int>(L.dead),
                                 seed, refill_stream + (uint32_t)round, 1.0 / sqrt((double)rows), l, w.batch, w.stride,
-                                gate),
+                                gate, w.own_panels),
                "apply R^-1");
       return 0;
     }
@@ -427,6 +429,7 @@ static int product(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, const Ws &w, 
   d.alpha = alpha; d.a_shift = a_shift;
   d.trans_a = trans_a; d.trans_c = trans_c; d.M = M; d.N = N; d.K = K;
   d.A = A; d.lda = lda; d.B = B; d.ldb = ldb; d.C = C; d.ldc = ldc;
+  d.b_slack = w.own_panels;
   if (allow_split) { d.partial = w.at<void>(w.L.partial); d.partial_bytes = w.L.partial_bytes; }
   else d.force_splits = 1;
   if (w.has_packed) { d.packed = w.at<void>(w.L.packed); d.packed_bytes = w.L.packed_bytes; }
@@ -655,6 +658,7 @@ static int run_impl(rsvd_ctx *ctx, void *stream, rsvd_dtype dtype, rsvd_job job,
   w.base = (char *)workspace;
   w.batch = batch;
   w.stride = (int64_t)w.L.total;             // a multiple of 256
+  w.own_panels = true;
   if (workspace == nullptr || ((uintptr_t)workspace & 255) != 0) return -18;
   if (workspace_bytes < w.L.total * (size_t)batch) return -19;
   w.has_packed = batch == 1 && w.L.packed_bytes > 0 && workspace_bytes >= w.L.total + w.L.packed_bytes;

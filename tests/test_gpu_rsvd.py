@@ -409,3 +409,33 @@ def test_sketch_as_wide_as_the_matrix(dt, m, n, k, p):
     assert parity.orthonormality(U) <= parity.jacobi_tol(k + p, dt) and parity.orthonormality(Vt.T) <= parity.jacobi_tol(k + p, dt)
     if p == 0:
         assert np.linalg.norm(A - (U * S) @ Vt) <= 64 * eps * np.linalg.norm(A)
+
+
+# Panels whose rows are no multiple of 16 bytes are read in 16-byte pieces all the same; what such a piece brings of the next row or,
+# behind the last row, of another buffer must not show.
+@pytest.mark.parametrize("dt,l", [("f32", 9), ("f32", 31), ("f32", 45), ("f32", 61), ("f32", 99), ("f32", 127), ("f32", 131), ("f32", 203),
+                                  ("f64", 7), ("f64", 31), ("f64", 47), ("f64", 63), ("f64", 95), ("f64", 101), ("f64", 129)])
+@pytest.mark.parametrize("m,n", [(1000, 640), (643, 1201)])
+def test_odd_panels_whatever_the_workspace_holds(dt, l, m, n):
+    import torch
+    say("odd panels", dt, l, m, n)
+    T = torch.float32 if dt == "f32" else torch.float64
+    A = to_dev(workloads.graded_matrix(max(m, n), max(m, n), 30.0, seed=l, dtype=np.float32 if dt == "f32" else np.float64)[:m, :n].copy())
+    c, k = ctx(), l - 5
+    need = c.workspace_bytes(0 if dt == "f32" else 1, m, n, k, 5, 1)
+    out = []
+    for fill in (0.0, float("nan"), float("inf")):
+        ws = torch.full(((need + 7) // 8,), fill, dtype=torch.float64, device="cuda:0").view(torch.uint8)
+        if dt == "f32":
+            ws = torch.full(((need + 3) // 4,), fill, dtype=T, device="cuda:0").view(torch.uint8)
+        S, U, Vt, info = c.rsvd_run(A, k, 5, 1, seed=3, workspace=ws)
+        assert info.status == 0
+        out.append([to_np(x) for x in (S, U, Vt)])
+    for other in out[1:]:
+        for x, y in zip(out[0], other):
+            assert np.array_equal(x, y)
+    S, U, Vt = (x.astype(np.float64) for x in out[0])
+    want = orc.rsvd(to_np(A), k, 5, 1, 3, np.float32 if dt == "f32" else np.float64)
+    eps = parity.EPS[dt]
+    assert np.abs(S - want.S).max() <= 200 * eps * np.sqrt(max(m, n)) * want.S[0]
+    assert parity.orthonormality(U) <= parity.jacobi_tol(l, dt) and parity.orthonormality(Vt.T) <= parity.jacobi_tol(l, dt)
