@@ -844,10 +844,23 @@ hipError_t chol_init_device(rsvd_ctx *ctx) {
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(&panel_qr_kernel),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)panel_lds_bytes(1024, 16));
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&tri_inverse_strip_kernel<6>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
+  const void *const strips[3] = {reinterpret_cast<const void *>(&tri_inverse_strip_kernel<6>),
+                                 reinterpret_cast<const void *>(&tri_inverse_strip_kernel<7>),
+                                 reinterpret_cast<const void *>(&tri_inverse_strip_kernel<8>)};
+  for (const void *k : strips)
+    if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
   return e;
+}
+
+static size_t tri_strip_lds(int64_t l, int nb) { return ((size_t)(l + nb) * 17 + (size_t)nb * 34) * sizeof(double); }
+
+// Block of the blocked factorisation: 96, or wider and even where that makes a block less (a block costs a factorisation, a panel and a
+// trailing update that wait for each other): l = 210 as 112 + 98 and not 96 + 96 + 18.  Whole calls with six factorisations: 4001 x 50021 fp32,
+// l = 210, q = 1 4576 -> 4468 us; 8000 x 2000 fp64, q = 1, l = 211 3306 -> 3187, 310 4765 -> 4693, 380 5927 -> 5804.
+static int chol_block(const rsvd_ctx *ctx, int64_t l) {
+  const int64_t blocks = ceil_div(l, 128);
+  const int nb = (int)ceil_div(l, 16 * blocks) * 16;
+  return blocks < ceil_div(l, 96) && tri_strip_lds(l, nb) + 4096 <= (size_t)ctx->lds_per_block ? nb : 96;
 }
 
 hipError_t chol_inverse_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype out_dtype, int64_t l, double *G,
@@ -869,11 +882,11 @@ hipError_t chol_inverse_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype out_dtyp
 
   // Blocked right-looking factorisation; diagonal blocks by the kernel above,
   // panels and trailing updates by the fp64 GEMM.  Rf/Xf hold R and R^-1 in fp64.
-  const int nb = 96 <= nbmax ? 96 : nbmax;
   // R^-1 above the diagonal blocks: one strip kernel after the factorisation when its strip fits in LDS
   // (l up to ~1000), else two products per block column inside the loop
-  const size_t strip_lds = ((size_t)(l + nb) * 17 + (size_t)nb * 34) * sizeof(double);
-  const bool strips = nb == 96 && strip_lds + 4096 <= (size_t)ctx->lds_per_block;
+  const size_t strip_lds = tri_strip_lds(l, chol_block(ctx, l));
+  const int nb = chol_block(ctx, l);
+  const bool strips = strip_lds + 4096 <= (size_t)ctx->lds_per_block;
   double *g0 = scratch;
   double *Xf = g0 + ((l + 1) & ~(int64_t)1);
   double *Rf = Xf + l * l;
@@ -934,8 +947,10 @@ hipError_t chol_inverse_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype out_dtyp
   }
   if (strips) {
     ProfScope ps(ctx, s, PK_SMALL);
-    hipLaunchKernelGGL((tri_inverse_strip_kernel<6>), dim3((unsigned)ceil_div(l, 16)), dim3(384), strip_lds, s, Rf, Xf,
-                       (int)l, skip_flag);
+    const dim3 grid((unsigned)ceil_div(l, 16)), threads((unsigned)(nb * 4));
+    if (nb == 96) hipLaunchKernelGGL((tri_inverse_strip_kernel<6>), grid, threads, strip_lds, s, Rf, Xf, (int)l, skip_flag);
+    else if (nb == 112) hipLaunchKernelGGL((tri_inverse_strip_kernel<7>), grid, threads, strip_lds, s, Rf, Xf, (int)l, skip_flag);
+    else hipLaunchKernelGGL((tri_inverse_strip_kernel<8>), grid, threads, strip_lds, s, Rf, Xf, (int)l, skip_flag);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (out_dtype == RSVD_F32) {

@@ -232,6 +232,26 @@ def test_jacobi_matches_oracle(dt, l):
         assert np.abs(np.abs(np.sum(W * Wo, axis=0)) - 1).max() <= min(0.1, tol)
 
 
+# The blocked factorisation cuts l into blocks of 96, or of 112 and 128 where that makes one less: the first and the last order of each choice,
+# last blocks of one column, of one more and one less than 16, and whole ones; a column that depends on others in a late block.
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+@pytest.mark.parametrize("l", [192, 193, 209, 224, 225, 240, 241, 256, 257, 288, 289, 337, 384, 385])
+def test_orthonormalize_blocked(dt, l):
+    say("blocked factorisation", dt, l)
+    rows = 2 * l + 17
+    Y = workloads.gaussian_matrix(rows, l, l, NPDT[dt])
+    Y[:, l - 2] = Y[:, 5] - Y[:, l // 2]
+    Q, R, info = ctx().rsvd_stage_orth(to_dev(Y), want_r=True)
+    Q, R = to_np(Q).astype(np.float64), to_np(R)
+    eps = np.finfo(NPDT[dt]).eps
+    assert info.status == 0 and info.refilled_columns >= 1
+    # as for the small panels; the condition of a Gaussian panel of twice as many rows is below 10
+    assert np.abs(Q.T @ Q - np.eye(l)).max() <= 16 * eps * np.sqrt(l)
+    assert np.abs(np.tril(R, -1)).max() == 0
+    norms = np.linalg.norm(Y.astype(np.float64), axis=0)
+    assert (np.linalg.norm(Q @ R - Y, axis=0) <= (64 * np.sqrt(l) * eps) * norms.max()).all()
+
+
 # fp64 products of 16-byte rows go through a ring of k-tiles in LDS: every column tile, one row and one k more and less than tiles of 64, 128
 # and 16, one k-tile in all, several k ranges with an uneven last one, outputs of two and three column tiles.
 @pytest.mark.parametrize("m,n,l", [(64, 16, 16), (66, 18, 10), (62, 4098, 30), (4098, 62, 32), (1026, 1000, 48), (1000, 1030, 50), (130, 3002, 66),
