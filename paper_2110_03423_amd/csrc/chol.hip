@@ -8,6 +8,8 @@
 // R and its column of R^-1 are set to zero (the caller replaces the column of
 // Q by a fresh Gaussian direction), so a rank-deficient Y still gives a full
 // orthonormal basis that contains range(Y).
+#include <type_traits>
+
 #include "common.hpp"
 #include "mfma.hpp"
 #include "philox_dev.hpp"
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(NB * 64) void chol_mfma_kernel(const double *__rest
                                                                   int64_t stride, const int *skip_flag, int raise,
                                                                   double floor_abs, double abs_thr, int *redo_skip,
                                                                   int redo_mode, double *__restrict__ Rinv_elim,
-                                                                  int64_t ldre) {
+                                                                  int64_t ldre, double *__restrict__ diag_out, int diag_n) {
   typedef CholLds<NB> L;
   // redo_skip (device int, strided like the rest in a batch; may be NULL): the switch of the additional
   // CholeskyQR round that follows a factorisation with raised pivots; non-zero = that round is skipped.
@@ -166,6 +168,7 @@ __global__ __launch_bounds__(NB * 64) void chol_mfma_kernel(const double *__rest
   // Rinv_elim (fp64, ld ldre, may be NULL): a second copy of R^-1 whose columns of set-aside rows are zero.  A blocked
   // factorisation forms its panel R[j, rest] = X_jj^T G[j, rest] with it, so that the rows set aside come out zero
   // there as they do inside this kernel, and take no part in the trailing update.
+  // diag_out (may be NULL): the first diag_n diagonal elements of G as they are now, for the pivot tests of the blocks behind this one.
   if (redo_skip != nullptr)
     redo_skip = reinterpret_cast<int *>(reinterpret_cast<char *>(redo_skip) + (int64_t)blockIdx.x * stride);
   if (skip_flag != nullptr &&
@@ -180,6 +183,8 @@ __global__ __launch_bounds__(NB * 64) void chol_mfma_kernel(const double *__rest
     if (R != nullptr) R = reinterpret_cast<double *>(reinterpret_cast<char *>(R) + off);
     dead = reinterpret_cast<int *>(reinterpret_cast<char *>(dead) + off);
   }
+  if (diag_out != nullptr)
+    for (int j = threadIdx.x; j < diag_n; j += NB * 64) diag_out[j] = G[(int64_t)j * ldg + j];
   constexpr int LP = L::LP, LD = L::LD, TLD = L::TLD;
   extern __shared__ double smem[];
   double *Sm = smem;                       // LP x LD: rows of [R | Z]
@@ -619,16 +624,6 @@ hipError_t panel_qr_launch(rsvd_ctx *ctx, hipStream_t s, const PanelQr &q) {
   return hipGetLastError();
 }
 
-// First launch of a blocked factorisation: keeps the original diagonal for the pivot tests and arms the switch
-// of the additional round (see chol_mfma_kernel) - also when the factorisation itself is switched off.
-__global__ void save_diag_kernel(const double *__restrict__ G, int64_t ldg, int l, double *__restrict__ g0,
-                                 const int *skip_flag, int *redo_skip) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j == 0 && redo_skip != nullptr) *redo_skip = 1;
-  if (skip_flag != nullptr && *skip_flag != 0) return;
-  if (j < l) g0[j] = G[(int64_t)j * ldg + j];
-}
-
 template <typename TOut>
 __global__ void convert_matrix_kernel(const double *__restrict__ src, int64_t n_elems, TOut *__restrict__ dst,
                                       const int *skip_flag) {
@@ -644,32 +639,67 @@ __global__ void fill_zero_f64_kernel(double *__restrict__ p, int64_t n, const in
     p[e] = 0.0;
 }
 
-__global__ void triu_product_kernel(int l, const double *__restrict__ R2, const double *__restrict__ R1,
-                                    double *__restrict__ Rb, int64_t stride, const int *skip_flag) {
+// out = R2 R1, then R3 out, then R4 out (those whose switch is not NULL and reads 0) for upper triangular fp64 matrices, l x l, ld l.
+// The columns of the product are independent of each other: a workgroup takes sixteen through the whole chain.  A row of the
+// product wants the rows from its own on, so groups of kChainRows rows are done from the top, in place, a group in registers
+// before the first of it is stored.  What bounds it is the trip to L2 per 32 columns of R, which the row blocks of a wavefront share.
+// One launch where every factor had one of its own and a copy.  With the strip kernel above writing its results in their final type and the
+// first block keeping the diagonal (four to five launches less per blocked factorisation, 4 to 5 us each, skipped or not): 4001 x 50021 fp32, l = 210, q = 1
+// 4522 -> 4452 us; 20000 x 20000 fp64, l = 288, q = 2 27997 -> 27716.
+constexpr int kChainBlocks = 5, kChainRows = 16 * 8 * kChainBlocks;
+__global__ __launch_bounds__(512) void r_chain_kernel(int l, const double *R1, const double *R2, const double *R3, const double *R4,
+                                                      double *out, int64_t stride, const int *skip3, const int *skip4) {
   const int64_t off = (int64_t)blockIdx.y * stride;        // batched: bytes between problems
-  if (skip_flag != nullptr && *reinterpret_cast<const int *>(reinterpret_cast<const char *>(skip_flag) + off) != 0)
-    return;
-  R2 = reinterpret_cast<const double *>(reinterpret_cast<const char *>(R2) + off);
-  R1 = reinterpret_cast<const double *>(reinterpret_cast<const char *>(R1) + off);
-  Rb = reinterpret_cast<double *>(reinterpret_cast<char *>(Rb) + off);
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (int64_t)l * l) return;
-  const int i = (int)(e / l), j = (int)(e - (int64_t)i * l);
-  // eight products per step with all their loads issued first (one at a time, every term would wait
-  // for its own memory round trip)
-  double acc = 0.0;
-  for (int t0 = i; t0 <= j; t0 += 8) {
-    double a[8], b[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = t0 + u;
-      a[u] = (t <= j) ? R2[(int64_t)i * l + t] : 0.0;
-      b[u] = (t <= j) ? R1[(int64_t)t * l + j] : 0.0;
+  auto at = [&](const double *p) { return reinterpret_cast<const double *>(reinterpret_cast<const char *>(p) + off); };
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), r16 = lane & 15, kq = lane >> 4;
+  const int c0 = (int)blockIdx.x * 16, col = c0 + r16, ccol = min(col, l - 1);
+  const int lp = (l + 15) & ~15, kend = min(c0 + 16, lp);  // below kend these columns are zero
+  double *dst = reinterpret_cast<double *>(reinterpret_cast<char *>(out) + off);
+  for (int f = 0; f < 3; ++f) {
+    const double *R = f == 0 ? R2 : f == 1 ? R3 : R4;
+    if (f > 0) {
+      const int *skip = f == 1 ? skip3 : skip4;
+      if (skip == nullptr || *reinterpret_cast<const int *>(reinterpret_cast<const char *>(skip) + off) != 0) continue;
     }
+    R = at(R);
+    const double *S = f == 0 ? at(R1) : dst;
+    for (int g0 = 0; g0 < lp; g0 += kChainRows) {
+      f64x4 acc[kChainBlocks];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) acc = fma(a[u], b[u], acc);
+      for (int n = 0; n < kChainBlocks; ++n) acc[n] = f64x4{0.0, 0.0, 0.0, 0.0};
+      for (int k0 = g0 + 16 * wave; k0 < kend; k0 += 32) {
+        double a[kChainBlocks][8], b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int k = k0 + 4 * u + kq, kc = min(k, l - 1);
+          b[u] = S[(int64_t)kc * l + ccol];
+#pragma unroll
+          for (int n = 0; n < kChainBlocks; ++n) a[n][u] = R[(int64_t)min(g0 + 16 * (wave + 8 * n) + r16, l - 1) * l + kc];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < kChainBlocks; ++n) {
+          const int row = g0 + 16 * (wave + 8 * n);
+          if (row >= k0 + 32 || row >= kend) break;
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const int k = k0 + 4 * u + kq;
+            acc[n] = Mfma<double>::run(k >= row + r16 && k < l ? a[n][u] : 0.0, k <= col ? b[u] : 0.0, acc[n]);
+          }
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int n = 0; n < kChainBlocks; ++n)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = g0 + 16 * (wave + 8 * n) + Mfma<double>::row(lane, v);
+          if (row < l && col < l) dst[(int64_t)row * l + col] = row <= col ? acc[n][v] : 0.0;
+        }
+      __threadfence_block();
+      __syncthreads();
+    }
   }
-  Rb[e] = acc;
 }
 
 __global__ void zero_ints_kernel(int *p, int n, int64_t stride) {
@@ -695,12 +725,13 @@ static hipError_t launch_block(hipStream_t s, const double *G, int64_t ldg, int 
                                const double *g0, double tau, TOut *Rinv, int64_t ldri, double *R, int64_t ldr,
                                int *dead, DevInfo *info, int batch, int64_t stride, const int *skip_flag,
                                const CholPivoting &pv, int redo_mode, double *Rinv_elim = nullptr,
-                               int64_t ldre = 0) {
+                               int64_t ldre = 0, double *diag_out = nullptr, int diag_n = 0) {
   // one workgroup, one wavefront per 16-row block
 #define RSVD_CHOL_CASE(NBV)                                                                                         \
   hipLaunchKernelGGL((chol_mfma_kernel<TOut, NBV>), dim3(batch), dim3(NBV * 64), CholLds<NBV>::bytes, s, G,         \
                      ldg, n_parts, part_stride, nb, g0, tau, Rinv, ldri, R, ldr, dead, info, stride, skip_flag,     \
-                     pv.raise, pv.floor_abs, pv.abs_thr, pv.redo_skip, redo_mode, Rinv_elim, ldre)
+                     pv.raise, pv.floor_abs, pv.abs_thr, pv.redo_skip, redo_mode, Rinv_elim, ldre,      \
+                     diag_out, diag_n)
   switch ((nb + 15) / 16) {
     case 1: RSVD_CHOL_CASE(1); break;
     case 2: RSVD_CHOL_CASE(2); break;
@@ -738,15 +769,16 @@ static hipError_t chol_raise_lds_limits() {
 // waiting for the one before.  Wavefront w owns rows 16 w .. 16 w + 15 of the block row in hand.
 //   LDS: the strip ((rows up to the end of its diagonal block) x 17), one block row of products (nb x 17) and
 //   a chunk of R (nb x 34).
-template <int NW>
+// The strip goes to Xout in its type, and that of R to Rout if it is wanted, both with zeros below the diagonal (l x l, ld l).
+template <int NW, typename TOut>
 __global__ __launch_bounds__(64 * NW) void tri_inverse_strip_kernel(const double *__restrict__ R,
-                                                                    double *__restrict__ X, int l,
+                                                                    const double *__restrict__ X, int l,
+                                                                    TOut *__restrict__ Xout, double *__restrict__ Rout,
                                                                     const int *skip_flag) {
   if (skip_flag != nullptr && *skip_flag != 0) return;
   constexpr int nb = 16 * NW, LDS_ = 17;
   const int c0 = (int)blockIdx.x * 16;
   const int j = c0 / nb, j0 = j * nb;
-  if (j == 0) return;                                   // the first block column is its diagonal block
   const int kend = (j0 + nb < l) ? j0 + nb : l;         // rows of the strip that the diagonal block supplies end here
   extern __shared__ double tri_smem[];
   double *Xs = tri_smem;                                // [kend][17]
@@ -831,9 +863,12 @@ __global__ __launch_bounds__(64 * NW) void tri_inverse_strip_kernel(const double
     }
     __syncthreads();
   }
-  for (int idx = tid; idx < j0 * 16; idx += 64 * NW) {
+  for (int idx = tid; idx < l * 16; idx += 64 * NW) {
     const int r = idx / 16, c = idx % 16;
-    if (c0 + c < l) X[(int64_t)r * l + c0 + c] = Xs[r * LDS_ + c];
+    if (c0 + c >= l) continue;
+    const int64_t at = (int64_t)r * l + c0 + c;
+    Xout[at] = r < kend ? (TOut)Xs[r * LDS_ + c] : (TOut)0;
+    if (Rout != nullptr) Rout[at] = r <= c0 + c ? R[at] : 0.0;
   }
 }
 
@@ -844,9 +879,10 @@ hipError_t chol_init_device(rsvd_ctx *ctx) {
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(&panel_qr_kernel),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)panel_lds_bytes(1024, 16));
-  const void *const strips[3] = {reinterpret_cast<const void *>(&tri_inverse_strip_kernel<6>),
-                                 reinterpret_cast<const void *>(&tri_inverse_strip_kernel<7>),
-                                 reinterpret_cast<const void *>(&tri_inverse_strip_kernel<8>)};
+  const void *const strips[6] = {
+      reinterpret_cast<const void *>(&tri_inverse_strip_kernel<6, float>), reinterpret_cast<const void *>(&tri_inverse_strip_kernel<6, double>),
+      reinterpret_cast<const void *>(&tri_inverse_strip_kernel<7, float>), reinterpret_cast<const void *>(&tri_inverse_strip_kernel<7, double>),
+      reinterpret_cast<const void *>(&tri_inverse_strip_kernel<8, float>), reinterpret_cast<const void *>(&tri_inverse_strip_kernel<8, double>)};
   for (const void *k : strips)
     if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
   return e;
@@ -894,10 +930,10 @@ hipError_t chol_inverse_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype out_dtyp
   double *E = T + l * l;               // nb x nb (ld nb): X_jj without the columns of rows set aside
   const bool aside = pv.raise != 0;
   hipError_t e;
-  hipLaunchKernelGGL(save_diag_kernel, dim3((unsigned)ceil_div(l, 256)), dim3(256), 0, s, G, ldg, (int)l, g0,
-                     skip_flag, pv.redo_skip);
-  hipLaunchKernelGGL(fill_zero_f64_kernel, dim3(1024), dim3(256), 0, s, Xf, 2 * l * l, skip_flag);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (!strips) {                       // (the strip kernel reads the blocks that are written below and nothing else)
+    hipLaunchKernelGGL(fill_zero_f64_kernel, dim3(1024), dim3(256), 0, s, Xf, 2 * l * l, skip_flag);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
 
   for (int64_t j0 = 0; j0 < l; j0 += nb) {
     const int64_t b = (l - j0 < nb) ? (l - j0) : nb;
@@ -905,8 +941,10 @@ hipError_t chol_inverse_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype out_dtyp
     // diagonal block: R_jj and X_jj = R_jj^-1
     {
       ProfScope ps(ctx, s, PK_CHOL);
-      e = launch_block<double>(s, G + j0 * ldg + j0, ldg, 1, 0, (int)b, g0 + j0, tau, Xf + j0 * l + j0, l,
-                               Rf + j0 * l + j0, l, dead + j0, info, 1, 0, skip_flag, pv, 2, aside ? E : nullptr, nb);
+      // (the first one keeps the diagonal for the pivot tests of the others, before the trailing updates, and sets the switch)
+      e = launch_block<double>(s, G + j0 * ldg + j0, ldg, 1, 0, (int)b, j0 > 0 ? g0 + j0 : nullptr, tau, Xf + j0 * l + j0, l,
+                               Rf + j0 * l + j0, l, dead + j0, info, 1, 0, skip_flag, pv, j0 > 0 ? 2 : 1, aside ? E : nullptr, nb,
+                               j0 > 0 ? nullptr : g0, (int)l);
     }
     if (e != hipSuccess) return e;
     if (rest > 0) {
@@ -948,10 +986,15 @@ hipError_t chol_inverse_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype out_dtyp
   if (strips) {
     ProfScope ps(ctx, s, PK_SMALL);
     const dim3 grid((unsigned)ceil_div(l, 16)), threads((unsigned)(nb * 4));
-    if (nb == 96) hipLaunchKernelGGL((tri_inverse_strip_kernel<6>), grid, threads, strip_lds, s, Rf, Xf, (int)l, skip_flag);
-    else if (nb == 112) hipLaunchKernelGGL((tri_inverse_strip_kernel<7>), grid, threads, strip_lds, s, Rf, Xf, (int)l, skip_flag);
-    else hipLaunchKernelGGL((tri_inverse_strip_kernel<8>), grid, threads, strip_lds, s, Rf, Xf, (int)l, skip_flag);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    auto go = [&](auto *out) {
+      typedef typename std::remove_pointer<decltype(out)>::type T;
+      if (nb == 96) hipLaunchKernelGGL((tri_inverse_strip_kernel<6, T>), grid, threads, strip_lds, s, Rf, Xf, (int)l, out, R, skip_flag);
+      else if (nb == 112) hipLaunchKernelGGL((tri_inverse_strip_kernel<7, T>), grid, threads, strip_lds, s, Rf, Xf, (int)l, out, R, skip_flag);
+      else hipLaunchKernelGGL((tri_inverse_strip_kernel<8, T>), grid, threads, strip_lds, s, Rf, Xf, (int)l, out, R, skip_flag);
+    };
+    if (out_dtype == RSVD_F32) go((float *)Rinv);
+    else go((double *)Rinv);
+    return hipGetLastError();
   }
   if (out_dtype == RSVD_F32) {
     hipLaunchKernelGGL((convert_matrix_kernel<float>), dim3(512), dim3(256), 0, s, Xf, l * l, (float *)Rinv, skip_flag);
@@ -1025,10 +1068,10 @@ hipError_t cond_flag_launch(hipStream_t s, rsvd_dtype dtype, int64_t l, const do
   return hipGetLastError();
 }
 
-hipError_t triu_product_launch(hipStream_t s, int64_t l, const double *R2, const double *R1, double *Rb, int batch,
-                               int64_t stride, const int *skip_flag) {
-  hipLaunchKernelGGL(triu_product_kernel, dim3((unsigned)ceil_div(l * l, 256), (unsigned)batch), dim3(256), 0, s,
-                     (int)l, R2, R1, Rb, stride, skip_flag);
+hipError_t r_chain_launch(hipStream_t s, int64_t l, const double *R1, const double *R2, double *out, int batch, int64_t stride,
+                          const double *R3, const int *skip3, const double *R4, const int *skip4) {
+  hipLaunchKernelGGL(r_chain_kernel, dim3((unsigned)ceil_div(l, 16), (unsigned)batch), dim3(512), 0, s, (int)l, R1, R2, R3, R4, out, stride,
+                     skip3, skip4);
   return hipGetLastError();
 }
 

@@ -198,9 +198,9 @@ hipError_t panel_qr_launch(rsvd_ctx *ctx, hipStream_t s, const PanelQr &q);
 hipError_t cond_flag_launch(hipStream_t s, rsvd_dtype dtype, int64_t l, const double *R, const void *Rinv,
                             double limit, int *flag, DevInfo *info, int batch = 1, int64_t stride = 0,
                             const int *redo_skip = nullptr);
-// Rb = R2 * R1 for upper triangular fp64 l x l matrices (ld l).
-hipError_t triu_product_launch(hipStream_t s, int64_t l, const double *R2, const double *R1, double *Rb,
-                               int batch = 1, int64_t stride = 0, const int *skip_flag = nullptr);
+// out = R2 R1 for upper triangular fp64 l x l matrices (ld l), multiplied by R3 and R4 from the left where *skip3 and *skip4 are zero.
+hipError_t r_chain_launch(hipStream_t s, int64_t l, const double *R1, const double *R2, double *out, int batch = 1, int64_t stride = 0,
+                          const double *R3 = nullptr, const int *skip3 = nullptr, const double *R4 = nullptr, const int *skip4 = nullptr);
 hipError_t zero_ints_launch(hipStream_t s, int *p, int n, int batch = 1, int64_t stride = 0);
 
 // ---------------------------------------------------------------- Jacobi

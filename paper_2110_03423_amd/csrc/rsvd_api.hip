@@ -399,15 +399,9 @@ static int orthonormalize(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, const 
   }
   if (Rout) {
     ProfScope ps(ctx, s, PK_SMALL);
-    RSVD_TRY(triu_product_launch(s, l, w.at<double>(L.R2), w.at<double>(L.R1), Rout, w.batch, w.stride), "R product");
-    for (int x = 0; x < extra; ++x) {
-      // R = R3 (R2 R1), then R4 (R3 R2 R1), for the additional rounds that ran
-      const int *gate = x == 0 ? redo_skip : redo2_skip;
-      RSVD_TRY(triu_product_launch(s, l, w.at<double>(x == 0 ? L.R3 : L.R4), Rout, w.at<double>(L.G), w.batch,
-                                   w.stride, gate),
-               "R product");
-      RSVD_TRY(copy_launch(s, RSVD_F64, w.at<void>(L.G), Rout, l * l, w.batch, w.stride, w.stride, gate), "copy R");
-    }
+    RSVD_TRY(r_chain_launch(s, l, w.at<double>(L.R1), w.at<double>(L.R2), Rout, w.batch, w.stride, w.at<double>(L.R3),
+                            extra > 0 ? redo_skip : nullptr, w.at<double>(L.R4), extra > 1 ? redo2_skip : nullptr),
+             "R product");
   }
   return 0;
 }

@@ -252,6 +252,22 @@ def test_orthonormalize_blocked(dt, l):
     assert (np.linalg.norm(Q @ R - Y, axis=0) <= (64 * np.sqrt(l) * eps) * norms.max()).all()
 
 
+# The product of the rounds' triangular factors: strips of 16 columns, wavefronts of up to five 16-row blocks, groups of 640 rows and what is left of
+# them, orders whose inverse no longer goes by strips.  In fp64 the dependent column adds the factors of the additional rounds.
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+@pytest.mark.parametrize("l", [18, 33, 127, 128, 129, 639, 640, 641, 657, 1296])
+def test_triangular_factor_of_all_rounds(dt, l):
+    say("product of the factors", dt, l)
+    Y = workloads.gaussian_matrix(2 * l + 17, l, l + 1, NPDT[dt])
+    Y[:, l - 2] = Y[:, 5] - Y[:, l // 2]
+    Q, R, info = ctx().rsvd_stage_orth(to_dev(Y), want_r=True)
+    Q, R = to_np(Q).astype(np.float64), to_np(R)
+    assert info.status == 0 and info.refilled_columns >= 1
+    assert np.abs(np.tril(R, -1)).max() == 0
+    norms = np.linalg.norm(Y.astype(np.float64), axis=0)      # bound as for the blocked factorisation above
+    assert (np.linalg.norm(Q @ R - Y, axis=0) <= (64 * np.sqrt(l) * np.finfo(NPDT[dt]).eps) * norms.max()).all()
+
+
 # fp64 products of 16-byte rows go through a ring of k-tiles in LDS: every column tile, one row and one k more and less than tiles of 64, 128
 # and 16, one k-tile in all, several k ranges with an uneven last one, outputs of two and three column tiles.
 @pytest.mark.parametrize("m,n,l", [(64, 16, 16), (66, 18, 10), (62, 4098, 30), (4098, 62, 32), (1026, 1000, 48), (1000, 1030, 50), (130, 3002, 66),
