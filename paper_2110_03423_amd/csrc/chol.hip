@@ -702,8 +702,7 @@ __global__ __launch_bounds__(512) void r_chain_kernel(int l, const double *R1, c
   }
 }
 
-__global__ void zero_ints_kernel(int *p, int n, int64_t stride) {
-  p = reinterpret_cast<int *>(reinterpret_cast<char *>(p) + (int64_t)blockIdx.y * stride);
+__global__ void zero_ints_kernel(int *p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
 }
@@ -1075,9 +1074,8 @@ hipError_t r_chain_launch(hipStream_t s, int64_t l, const double *R1, const doub
   return hipGetLastError();
 }
 
-hipError_t zero_ints_launch(hipStream_t s, int *p, int n, int batch, int64_t stride) {
-  hipLaunchKernelGGL(zero_ints_kernel, dim3((unsigned)ceil_div(n, 256), (unsigned)batch), dim3(256), 0, s, p, n,
-                     stride);
+hipError_t zero_ints_launch(hipStream_t s, int *p, int n) {
+  hipLaunchKernelGGL(zero_ints_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, p, n);
   return hipGetLastError();
 }
 

@@ -131,9 +131,9 @@ size_t gemm_packed_bytes(int64_t M, int64_t N, int64_t K);
 hipError_t gemm_split_init_device(rsvd_ctx *ctx);
 
 // ---------------------------------------------------------------- sketch
-// batch > 1: problem b (blockIdx.y) writes to out + b * stride_out bytes with seed + b.
+// batch > 1: problem b (blockIdx.y) writes to out + b * stride_out bytes with seed + b.  zero: n_zero ints are cleared on the way.
 hipError_t sketch_launch(hipStream_t s, rsvd_dtype dtype, uint64_t seed, uint32_t stream_id,
-                         int64_t rows, int64_t cols, void *out, int64_t ld, int batch = 1, int64_t stride_out = 0);
+                         int64_t rows, int64_t cols, void *out, int64_t ld, int batch = 1, int64_t stride_out = 0, int *zero = nullptr, int n_zero = 0);
 hipError_t philox_raw_launch(hipStream_t s, uint64_t seed, uint32_t stream_id, uint64_t first_group,
                              int64_t n_groups, uint32_t *out);
 
@@ -201,7 +201,7 @@ hipError_t cond_flag_launch(hipStream_t s, rsvd_dtype dtype, int64_t l, const do
 // out = R2 R1 for upper triangular fp64 l x l matrices (ld l), multiplied by R3 and R4 from the left where *skip3 and *skip4 are zero.
 hipError_t r_chain_launch(hipStream_t s, int64_t l, const double *R1, const double *R2, double *out, int batch = 1, int64_t stride = 0,
                           const double *R3 = nullptr, const int *skip3 = nullptr, const double *R4 = nullptr, const int *skip4 = nullptr);
-hipError_t zero_ints_launch(hipStream_t s, int *p, int n, int batch = 1, int64_t stride = 0);
+hipError_t zero_ints_launch(hipStream_t s, int *p, int n);
 
 // ---------------------------------------------------------------- Jacobi
 // Largest order the single-workgroup LDS-resident Jacobi kernel handles.
@@ -234,7 +234,7 @@ hipError_t apply_tri_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int6
 
 // One-sided Jacobi SVD  M = X diag(sigma) W^T  of the l x l row-major matrix M
 // (ld l; fp64 when m_is_f64 else `dtype`).  Outputs in `dtype`, sigma descending.
-// batch > 1 (LDS-resident orders only): problem b = blockIdx.x adds b * stride bytes to M, sigma, X, W.
+// batch > 1 (LDS-resident orders only): problem b = blockIdx.x adds b * stride bytes to M, X, W.
 // slots (may be NULL; one problem only): eight more l x l matrices of type `dtype` to work in, with which the last sweeps give way to
 // corrections of the whole matrix.  The sixth and seventh may be M and X: they are written when M has been read and before X is.
 // rows != 0: the rotations act on the rows of M, i.e. M^T = X diag(sigma) W^T is what is decomposed (the
@@ -243,8 +243,10 @@ hipError_t apply_tri_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int6
 struct JacobiSlots { void *slot[8]; };
 // One problem of this order, given in fp64 and with slots, takes the block path although it fits in the LDS of a workgroup.
 bool jacobi_prefers_blocks(rsvd_dtype dtype, int64_t l);
+// The n largest values go to p (of the matrix type; the problems of a batch `stride` bytes apart).
+struct SigmaOut { void *p; int n; int64_t stride; };
 hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t l,
-                         const void *M, int m_is_f64, void *sigma, void *X, void *W,
+                         const void *M, int m_is_f64, const SigmaOut &sig, void *X, void *W,
                          DevInfo *info, void *scratch, size_t scratch_bytes, int batch = 1, int64_t stride = 0,
                          int rows = 0, const JacobiSlots *slots = nullptr);
 

@@ -227,14 +227,13 @@ __host__ __device__ inline int jacobi_ldm(int l, int G, int elem_size) {
 // there together (fp64 beyond 96).  Its columns travel through the cache of the CU: a round takes longer, but
 // the problems of a batch still run side by side, one workgroup each.
 template <typename T, typename TIn, int RPL, int G, bool JG = false>
-__global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restrict__ M, int l, T *__restrict__ sigma,
+__global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restrict__ M, int l, SigmaOut sig,
                                                          T *__restrict__ X, T *__restrict__ W, DevInfo *info,
                                                          int64_t stride, int rows, T *__restrict__ Jglobal) {
   extern __shared__ __attribute__((aligned(16))) double lds_raw[];
   if (blockIdx.x != 0) {              // batched launch: one problem per workgroup, `stride` bytes apart
     const int64_t off = (int64_t)blockIdx.x * stride;
     M = reinterpret_cast<const TIn *>(reinterpret_cast<const char *>(M) + off);
-    sigma = reinterpret_cast<T *>(reinterpret_cast<char *>(sigma) + off);
     X = reinterpret_cast<T *>(reinterpret_cast<char *>(X) + off);
     W = reinterpret_cast<T *>(reinterpret_cast<char *>(W) + off);
     if (JG) Jglobal = reinterpret_cast<T *>(reinterpret_cast<char *>(Jglobal) + off);
@@ -367,7 +366,7 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
       rank += (o > mine || (o == mine && i < j)) ? 1 : 0;
     }
     rnk[j] = rank;
-    sigma[rank] = mine * unscale;
+    if (rank < sig.n) reinterpret_cast<T *>(reinterpret_cast<char *>(sig.p) + (int64_t)blockIdx.x * sig.stride)[rank] = mine * unscale;
   }
   __syncthreads();
   for (int idx = tid; idx < l * l; idx += nt) {
@@ -1776,7 +1775,7 @@ __global__ __launch_bounds__(256) void jb_norms_kernel(const T *__restrict__ Mt,
 
 template <typename T>
 __global__ __launch_bounds__(256) void jb_rank_kernel(const T *__restrict__ nrm, int l, int *__restrict__ rnk,
-                                                      T *__restrict__ sigma, const JbHeader *hdr, int max_sweeps,
+                                                      SigmaOut sig, const JbHeader *hdr, int max_sweeps,
                                                       DevInfo *info, const JbSync *sync) {
   // sixteen threads to a column, each compares it with a sixteenth of the others (one thread for all of them: 17 us at l = 210, 35 at 450)
   const int sub = threadIdx.x & 15, j = blockIdx.x * 16 + (threadIdx.x >> 4);
@@ -1791,7 +1790,7 @@ __global__ __launch_bounds__(256) void jb_rank_kernel(const T *__restrict__ nrm,
   for (int m = 1; m < 16; m <<= 1) rank += __shfl_xor(rank, m, 16);
   if (j < l && sub == 0) {
     rnk[j] = rank;
-    sigma[rank] = mine * (T)hdr->unscale;
+    if (rank < sig.n) reinterpret_cast<T *>(sig.p)[rank] = mine * (T)hdr->unscale;
   }
   if (j == 0 && sub == 0 && info != nullptr) {
     const float tol = (float)(Eps<T>::value * sqrt((T)l));
@@ -1919,7 +1918,7 @@ static bool jb_takes_flow(const rsvd_ctx *ctx, int b, int l) {
 
 template <typename T>
 static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int l, const double *M,
-                                      T *sigma, T *X, T *W, DevInfo *info, char *scratch, int rows,
+                                      SigmaOut sig, T *X, T *W, DevInfo *info, char *scratch, int rows,
                                       const JacobiSlots *slots) {
   const int b = jb_block_width(ctx, dtype, l);
   if (b == 0) return hipErrorNotSupported;
@@ -2000,48 +1999,48 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
 #undef RSVD_JB_CASE
   }
   hipLaunchKernelGGL((jb_norms_kernel<T>), dim3((l + 3) / 4), dim3(256), 0, s, Mt, Mt2, l, nrm, sync);
-  hipLaunchKernelGGL((jb_rank_kernel<T>), dim3((l + 15) / 16), dim3(256), 0, s, nrm, l, rnk, sigma, hdr,
+  hipLaunchKernelGGL((jb_rank_kernel<T>), dim3((l + 15) / 16), dim3(256), 0, s, nrm, l, rnk, sig, hdr,
                      kJbMaxSweeps, info, sync);
   hipLaunchKernelGGL((jb_scatter_kernel<T>), dim3(256), dim3(256), 0, s, Mt, Jt, Mt2, Jt2, l, nrm, rnk, hdr, X, W, sync);
   return hipGetLastError();
 }
 
 template <typename T, typename TIn, int RPL, int G>
-static hipError_t launch_lds(hipStream_t s, int nt, size_t lds, const void *M, int l, void *sigma, void *X, void *W,
+static hipError_t launch_lds(hipStream_t s, int nt, size_t lds, const void *M, int l, const SigmaOut &sig, void *X, void *W,
                              DevInfo *info, int batch, int64_t stride, int rows) {
   hipLaunchKernelGGL((jacobi_lds_kernel<T, TIn, RPL, G>), dim3(batch), dim3(nt), lds, s, (const TIn *)M, l,
-                     (T *)sigma, (T *)X, (T *)W, info, stride, rows, (T *)nullptr);
+                     sig, (T *)X, (T *)W, info, stride, rows, (T *)nullptr);
   return hipGetLastError();
 }
 // fp64 orders 97 .. 128: M in LDS, J in global memory
 template <int RPL>
-static hipError_t launch_lds_jg(hipStream_t s, int nt, size_t lds, const void *M, int l, void *sigma, void *X, void *W,
+static hipError_t launch_lds_jg(hipStream_t s, int nt, size_t lds, const void *M, int l, const SigmaOut &sig, void *X, void *W,
                                 DevInfo *info, int batch, int64_t stride, int rows, void *Jglobal) {
   hipLaunchKernelGGL((jacobi_lds_kernel<double, double, RPL, 16, true>), dim3(batch), dim3(nt), lds, s,
-                     (const double *)M, l, (double *)sigma, (double *)X, (double *)W, info, stride, rows,
+                     (const double *)M, l, sig, (double *)X, (double *)W, info, stride, rows,
                      (double *)Jglobal);
   return hipGetLastError();
 }
 
 // rows per lane = padded rows / G
 template <typename T, typename TIn>
-static hipError_t launch_lds_g(hipStream_t s, int nt, int G, int rpl, size_t lds, const void *M, int l, void *sigma,
+static hipError_t launch_lds_g(hipStream_t s, int nt, int G, int rpl, size_t lds, const void *M, int l, const SigmaOut &sig,
                                void *X, void *W, DevInfo *info, int batch, int64_t stride, int rows) {
   if (G == 16) {
     // fp32 rows come in pairs (8-byte units), fp64 rows singly
     if constexpr (sizeof(T) == 8) {
       switch (rpl) {
-        case 1: return launch_lds<T, TIn, 1, 16>(s, nt, lds, M, l, sigma, X, W, info, batch, stride, rows);
-        case 3: return launch_lds<T, TIn, 3, 16>(s, nt, lds, M, l, sigma, X, W, info, batch, stride, rows);
-        case 5: return launch_lds<T, TIn, 5, 16>(s, nt, lds, M, l, sigma, X, W, info, batch, stride, rows);
+        case 1: return launch_lds<T, TIn, 1, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
+        case 3: return launch_lds<T, TIn, 3, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
+        case 5: return launch_lds<T, TIn, 5, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
         default: break;
       }
     }
     switch (rpl) {
-      case 2: return launch_lds<T, TIn, 2, 16>(s, nt, lds, M, l, sigma, X, W, info, batch, stride, rows);
-      case 4: return launch_lds<T, TIn, 4, 16>(s, nt, lds, M, l, sigma, X, W, info, batch, stride, rows);
-      case 6: return launch_lds<T, TIn, 6, 16>(s, nt, lds, M, l, sigma, X, W, info, batch, stride, rows);
-      case 8: return launch_lds<T, TIn, 8, 16>(s, nt, lds, M, l, sigma, X, W, info, batch, stride, rows);
+      case 2: return launch_lds<T, TIn, 2, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
+      case 4: return launch_lds<T, TIn, 4, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
+      case 6: return launch_lds<T, TIn, 6, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
+      case 8: return launch_lds<T, TIn, 8, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
       default: return hipErrorNotSupported;
     }
   }
@@ -2099,7 +2098,7 @@ hipError_t jacobi_init_device(rsvd_ctx *ctx) {
 }
 
 hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t l, const void *M,
-                         int m_is_f64, void *sigma, void *X, void *W, DevInfo *info, void *scratch,
+                         int m_is_f64, const SigmaOut &sig, void *X, void *W, DevInfo *info, void *scratch,
                          size_t scratch_bytes, int batch, int64_t stride, int rows, const JacobiSlots *slots) {
   if (batch < 1 || batch > 65535) return hipErrorInvalidValue;
   if (l > jacobi_max_lds_order(ctx, dtype) || (batch == 1 && slots != nullptr && m_is_f64 && jacobi_prefers_blocks(dtype, l))) {
@@ -2114,17 +2113,17 @@ hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t
       const int nt = (int)align_up((size_t)((l + 1) / 2) * 16, 64);
       ProfScope ps(ctx, s, PK_JACOBI);
       if (jacobi_rows_padded((int)l, 16, 8) / 16 == 7)
-        return launch_lds_jg<7>(s, nt, lds, M, (int)l, sigma, X, W, info, batch, stride, rows, scratch);
-      return launch_lds_jg<8>(s, nt, lds, M, (int)l, sigma, X, W, info, batch, stride, rows, scratch);
+        return launch_lds_jg<7>(s, nt, lds, M, (int)l, sig, X, W, info, batch, stride, rows, scratch);
+      return launch_lds_jg<8>(s, nt, lds, M, (int)l, sig, X, W, info, batch, stride, rows, scratch);
     }
     // block path: needs the fp64 input (the triangular factor) and its scratch
     const size_t need = jacobi_scratch_bytes(ctx, dtype, l);
     if (l > jacobi_max_lds_order(ctx, dtype) && (need == 0 || scratch == nullptr || scratch_bytes < need || !m_is_f64))
       return hipErrorNotSupported;
     if (dtype == RSVD_F32)
-      return jacobi_block_launch<float>(ctx, s, dtype, (int)l, (const double *)M, (float *)sigma, (float *)X,
+      return jacobi_block_launch<float>(ctx, s, dtype, (int)l, (const double *)M, sig, (float *)X,
                                         (float *)W, info, (char *)scratch, rows, slots);
-    return jacobi_block_launch<double>(ctx, s, dtype, (int)l, (const double *)M, (double *)sigma, (double *)X,
+    return jacobi_block_launch<double>(ctx, s, dtype, (int)l, (const double *)M, sig, (double *)X,
                                        (double *)W, info, (char *)scratch, rows, slots);
   }
   // one G-lane group per column pair of a round, all pairs of a round at once
@@ -2136,10 +2135,10 @@ hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t
   const size_t lds = jacobi_lds_bytes(dtype, l);
   ProfScope ps(ctx, s, PK_JACOBI);
   if (dtype == RSVD_F32) {
-    if (m_is_f64) return launch_lds_g<float, double>(s, nt, G, g, lds, M, (int)l, sigma, X, W, info, batch, stride, rows);
-    return launch_lds_g<float, float>(s, nt, G, g, lds, M, (int)l, sigma, X, W, info, batch, stride, rows);
+    if (m_is_f64) return launch_lds_g<float, double>(s, nt, G, g, lds, M, (int)l, sig, X, W, info, batch, stride, rows);
+    return launch_lds_g<float, float>(s, nt, G, g, lds, M, (int)l, sig, X, W, info, batch, stride, rows);
   }
-  return launch_lds_g<double, double>(s, nt, G, g, lds, M, (int)l, sigma, X, W, info, batch, stride, rows);
+  return launch_lds_g<double, double>(s, nt, G, g, lds, M, (int)l, sig, X, W, info, batch, stride, rows);
 }
 
 }  // namespace rsvd

@@ -34,15 +34,8 @@ hipError_t gemm_launch(rsvd_ctx *ctx, hipStream_t s, GemmKind kind, const GemmDe
   }
 }
 
-// skip_flag (device int, stride_flag bytes between the problems of a batch; may be NULL): non-zero = do nothing
 template <typename T>
-__global__ void copy_kernel(const T *__restrict__ src, T *__restrict__ dst, int64_t n, int64_t stride_src,
-                            int64_t stride_dst, const int *skip_flag, int64_t stride_flag) {
-  if (skip_flag != nullptr &&
-      *reinterpret_cast<const int *>(reinterpret_cast<const char *>(skip_flag) + (int64_t)blockIdx.y * stride_flag) != 0)
-    return;
-  src = reinterpret_cast<const T *>(reinterpret_cast<const char *>(src) + (int64_t)blockIdx.y * stride_src);
-  dst = reinterpret_cast<T *>(reinterpret_cast<char *>(dst) + (int64_t)blockIdx.y * stride_dst);
+__global__ void copy_kernel(const T *__restrict__ src, T *__restrict__ dst, int64_t n) {
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
     dst[e] = src[e];
 }
@@ -125,20 +118,14 @@ static hipError_t colmean_launch(hipStream_t s, rsvd_dtype dtype, const void *X,
   return hipGetLastError();
 }
 
-// batch > 1: problem b copies from src + b * stride_src to dst + b * stride_dst (bytes)
-static hipError_t copy_launch(hipStream_t s, rsvd_dtype dtype, const void *src, void *dst, int64_t n, int batch = 1,
-                              int64_t stride_src = 0, int64_t stride_dst = 0, const int *skip_flag = nullptr) {
+static hipError_t copy_launch(hipStream_t s, rsvd_dtype dtype, const void *src, void *dst, int64_t n) {
   if (n <= 0) return hipSuccess;
   int64_t blocks = ceil_div(n, 256);
   if (blocks > 4096) blocks = 4096;
-  const dim3 grid((unsigned)blocks, (unsigned)batch);
-  // (a gate lives in the workspace of its problem: same stride as the workspace buffers)
   if (dtype == RSVD_F32)
-    hipLaunchKernelGGL(copy_kernel<float>, grid, dim3(256), 0, s, (const float *)src, (float *)dst, n, stride_src,
-                       stride_dst, skip_flag, stride_src);
+    hipLaunchKernelGGL(copy_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, s, (const float *)src, (float *)dst, n);
   else
-    hipLaunchKernelGGL(copy_kernel<double>, grid, dim3(256), 0, s, (const double *)src, (double *)dst, n, stride_src,
-                       stride_dst, skip_flag, stride_src);
+    hipLaunchKernelGGL(copy_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, s, (const double *)src, (double *)dst, n);
   return hipGetLastError();
 }
 
@@ -178,7 +165,7 @@ struct Layout {
   size_t flags;                     // device-side switches (ints): [0] = the power scheme may skip one side,
                                     // [1], [2] = no pivot was raised in the first / second CholeskyQR round:
                                     // the additional round that would resolve it is skipped
-  size_t sigma, Wj, Xj;             // all l triplets of step 5: sigma, Ub (= W), X
+  size_t Wj, Xj;                    // all l pairs of vectors of step 5: Ub (= W), X
   size_t jac_scratch, jac_scratch_bytes;
   size_t mean;                      // centred variant: column means (n, fp64)
   size_t total;                     // what a call cannot do without
@@ -215,7 +202,6 @@ static Layout make_layout(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t m, int6
   L.dead = take((size_t)l * sizeof(int));
   L.info = take(sizeof(DevInfo));
   L.flags = take(16 * sizeof(int));
-  L.sigma = take((size_t)l * es);
   L.Wj = take((size_t)l * l * es);
   L.Xj = take((size_t)l * l * es);
   L.jac_scratch_bytes = jacobi_scratch_bytes(ctx, dtype, l);
@@ -449,9 +435,9 @@ static JacobiSlots jacobi_slots(const Ws &w, rsvd_dtype dtype, int64_t l, void *
 }
 
 // Step 5 on Bt (n x l, ld ldbt): Bt = Qb Rb, Rb = X Sigma W^T.  On exit Bt holds Qb,
-// and sigma / W / X sit in the workspace.
+// W / X sit in the workspace and the values in sig (written by the kernel that orders them: a copy behind it was a launch of 4 to 5 us).
 static int small_svd(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, const Ws &w, int64_t n, int64_t l, void *Bt,
-                     int64_t ldbt, void *tmp, uint64_t seed, uint32_t refill_stream) {
+                     int64_t ldbt, void *tmp, uint64_t seed, uint32_t refill_stream, const SigmaOut &sig) {
   const Layout &L = w.L;
   int rc = orthonormalize(ctx, s, dtype, w, n, l, Bt, ldbt, tmp, w.at<double>(L.Rb), seed, refill_stream);
   if (rc) return rc;
@@ -459,7 +445,7 @@ static int small_svd(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, const Ws &w
   // triangular factor are graded like the singular values, its columns are not, and the rotations converge in
   // about half the sweeps on the former when the spectrum is steep (a third when the factor is rank deficient)
   const JacobiSlots slots = jacobi_slots(w, dtype, l, w.at<void>(L.Wj), tmp);
-  hipError_t e = jacobi_launch(ctx, s, dtype, l, w.at<void>(L.Rb), 1, w.at<void>(L.sigma), w.at<void>(L.Wj),
+  hipError_t e = jacobi_launch(ctx, s, dtype, l, w.at<void>(L.Rb), 1, sig, w.at<void>(L.Wj),
                                w.at<void>(L.Xj), w.at<DevInfo>(L.info), w.at<void>(L.jac_scratch),
                                L.jac_scratch_bytes, w.batch, w.stride, 1, &slots);
   if (e == hipErrorNotSupported) return RSVD_ERR_UNSUPPORTED;
@@ -666,7 +652,6 @@ static int run_impl(rsvd_ctx *ctx, void *stream, rsvd_dtype dtype, rsvd_job job,
   void *bN0 = w.at<void>(L.bufN[0]), *bN1 = w.at<void>(L.bufN[1]);
   int rc;
 
-  RSVD_TRY(zero_ints_launch(s, w.at<int>(L.info), kDevInfoInts), "zero info");
   double *mean = center ? w.at<double>(L.mean) : nullptr;
   if (center) {
     // mu = A^T 1 / m, kept in fp64 for the products and handed out in the matrix type
@@ -686,7 +671,7 @@ static int run_impl(rsvd_ctx *ctx, void *stream, rsvd_dtype dtype, rsvd_job job,
   // step 1
   {
     ProfScope ps(ctx, s, PK_SKETCH);
-    RSVD_TRY(sketch_launch(s, dtype, seed, 0u, n, l, bN0, l, batch, w.stride), "sketch");
+    RSVD_TRY(sketch_launch(s, dtype, seed, 0u, n, l, bN0, l, batch, w.stride, w.at<int>(L.info), kDevInfoInts), "sketch");
   }
   // step 2: Y = A Omega, then q rounds of Z = A^T Q, Y = A Z.  Every product is
   // re-orthonormalised; all but the last with a single CholeskyQR round (result in
@@ -745,8 +730,7 @@ static int run_impl(rsvd_ctx *ctx, void *stream, rsvd_dtype dtype, rsvd_job job,
   // step 4: B^T = A^T Q
   if ((rc = times_at(curM, curN))) return rc;
   // step 5
-  if ((rc = small_svd(ctx, s, dtype, w, n, l, curN, l, othN, seed, refill))) return rc;
-  RSVD_TRY(copy_launch(s, dtype, w.at<void>(L.sigma), S, k, batch, w.stride, stride_s * es), "copy S");
+  if ((rc = small_svd(ctx, s, dtype, w, n, l, curN, l, othN, seed, refill, {S, k, stride_s * es}))) return rc;
   if (job >= RSVD_JOB_SV) {
     // V^T = (Qb X[:, :k])^T
     if ((rc = product(ctx, s, dtype, w, 0, n, k, l, curN, l, w.at<void>(L.Xj), l, Vt, ldvt, 1, false, PK_LIFT, 1.0,
@@ -945,9 +929,8 @@ int rsvd_stage_small_svd(rsvd_ctx *ctx, void *stream, rsvd_dtype dtype, int64_t 
   if (ctx->device < 0) return RSVD_ERR_NO_DEVICE;
   hipStream_t s = (hipStream_t)stream;
   RSVD_TRY(zero_ints_launch(s, w.at<int>(w.L.info), kDevInfoInts), "zero info");
-  int rc = small_svd(ctx, s, dtype, w, n, l, Bt, ldbt, w.at<void>(w.L.bufM[1]), seed, 16u);
+  int rc = small_svd(ctx, s, dtype, w, n, l, Bt, ldbt, w.at<void>(w.L.bufM[1]), seed, 16u, {sigma, (int)l, 0});
   if (rc) return rc;
-  RSVD_TRY(copy_launch(s, dtype, w.at<void>(w.L.sigma), sigma, l), "copy sigma");
   RSVD_TRY(copy_launch(s, dtype, w.at<void>(w.L.Wj), Ub, l * l), "copy Ub");
   if ((rc = product(ctx, s, dtype, w, 0, n, l, l, Bt, ldbt, w.at<void>(w.L.Xj), l, V, ldv, 0, false, PK_LIFT))) return rc;
   return finish_info(ctx, s, w, info);
@@ -979,7 +962,7 @@ int rsvd_stage_jacobi(rsvd_ctx *ctx, void *stream, rsvd_dtype dtype, int64_t l, 
     min_f64 = 1;
   }
   const JacobiSlots slots = jacobi_slots(w, dtype, l, X, w.at<void>(w.L.bufM[0]));
-  hipError_t e = jacobi_launch(ctx, s, dtype, l, Min, min_f64, sigma, X, W, w.at<DevInfo>(w.L.info),
+  hipError_t e = jacobi_launch(ctx, s, dtype, l, Min, min_f64, {sigma, (int)l, 0}, X, W, w.at<DevInfo>(w.L.info),
                                w.at<void>(w.L.jac_scratch), w.L.jac_scratch_bytes, 1, 0, 0, &slots);
   if (e == hipErrorNotSupported) return RSVD_ERR_UNSUPPORTED;
   RSVD_TRY(e, "jacobi");

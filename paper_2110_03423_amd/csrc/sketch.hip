@@ -10,7 +10,10 @@ namespace rsvd {
 template <typename T, bool F32>
 __global__ __launch_bounds__(256) void sketch_kernel(uint64_t seed, uint32_t stream, int64_t cols,
                                                      int64_t total, T *__restrict__ out, int64_t ld,
-                                                     int64_t stride_out) {
+                                                     int64_t stride_out, int *zero, int n_zero) {
+  // (n_zero ints that a call wants cleared before its later kernels: a launch of their own was 2 us on every call)
+  if (blockIdx.x == 0 && blockIdx.y == 0)
+    for (int i = threadIdx.x; i < n_zero; i += 256) zero[i] = 0;
   constexpr int PER = F32 ? 4 : 2;
   seed += (uint64_t)blockIdx.y;
   out = reinterpret_cast<T *>(reinterpret_cast<char *>(out) + (int64_t)blockIdx.y * stride_out);
@@ -59,16 +62,16 @@ static int grid_for(int64_t items) {
 }
 
 hipError_t sketch_launch(hipStream_t s, rsvd_dtype dtype, uint64_t seed, uint32_t stream_id,
-                         int64_t rows, int64_t cols, void *out, int64_t ld, int batch, int64_t stride_out) {
+                         int64_t rows, int64_t cols, void *out, int64_t ld, int batch, int64_t stride_out, int *zero, int n_zero) {
   const int64_t total = rows * cols;
   if (total == 0) return hipSuccess;
   if (batch < 1 || batch > 65535) return hipErrorInvalidValue;
   if (dtype == RSVD_F32) {
     hipLaunchKernelGGL((sketch_kernel<float, true>), dim3(grid_for((total + 3) / 4), batch), dim3(256), 0, s,
-                       seed, stream_id, cols, total, (float *)out, ld, stride_out);
+                       seed, stream_id, cols, total, (float *)out, ld, stride_out, zero, n_zero);
   } else {
     hipLaunchKernelGGL((sketch_kernel<double, false>), dim3(grid_for((total + 1) / 2), batch), dim3(256), 0, s,
-                       seed, stream_id, cols, total, (double *)out, ld, stride_out);
+                       seed, stream_id, cols, total, (double *)out, ld, stride_out, zero, n_zero);
   }
   return hipGetLastError();
 }

@@ -439,3 +439,29 @@ def test_odd_panels_whatever_the_workspace_holds(dt, l, m, n):
     eps = parity.EPS[dt]
     assert np.abs(S - want.S).max() <= 200 * eps * np.sqrt(max(m, n)) * want.S[0]
     assert parity.orthonormality(U) <= parity.jacobi_tol(l, dt) and parity.orthonormality(Vt.T) <= parity.jacobi_tol(l, dt)
+
+
+# The kernels that order the singular values write the k wanted ones to the caller's array and nothing behind them: one workgroup, blocks in
+# buffers of the call, blocks in their own scratch.
+@pytest.mark.parametrize("dt,l", [("f32", 8), ("f32", 40), ("f32", 100), ("f32", 140), ("f64", 24), ("f64", 70), ("f64", 110)])
+def test_only_k_values_are_written(dt, l):
+    import ctypes as C
+    import torch
+    say("k values", dt, l)
+    c, k, m, n = ctx(), l - 5, 500, 400
+    A = to_dev(workloads.graded_matrix(m, m, 30.0, seed=l, dtype=np.float32 if dt == "f32" else np.float64)[:, :n].copy())
+    S, U, Vt, _ = c.rsvd_run(A, k, 5, 1, seed=3)
+    out = torch.full((l + 3,), -7.0, dtype=A.dtype, device="cuda:0")
+    code = 0 if dt == "f32" else 1
+    need = c.workspace_bytes(code, m, n, k, 5, 1)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+    torch.cuda.synchronize()
+    for base in (0, 3):                           # any element of an array may be the first
+        out.fill_(-7.0)
+        rc = c.lib.rsvd_run(c.h, C.c_void_p(torch.cuda.current_stream().cuda_stream), code, 0, m, n, C.c_void_p(A.data_ptr()), A.stride(0),
+                            k, 5, 1, 3, C.c_void_p(out.data_ptr() + base * out.element_size()), None, 0, None, 0,
+                            C.c_void_p(ws.data_ptr()), need, None)
+        torch.cuda.synchronize()
+        got = to_np(out)
+        assert rc == 0 and np.array_equal(got[base:base + k], to_np(S))
+        assert (np.delete(got, np.arange(base, base + k)) == -7.0).all()
