@@ -8,8 +8,6 @@
 // R and its column of R^-1 are set to zero (the caller replaces the column of
 // Q by a fresh Gaussian direction), so a rank-deficient Y still gives a full
 // orthonormal basis that contains range(Y).
-#include <type_traits>
-
 #include "common.hpp"
 #include "mfma.hpp"
 #include "philox_dev.hpp"
@@ -768,11 +766,11 @@ static hipError_t chol_raise_lds_limits() {
 // waiting for the one before.  Wavefront w owns rows 16 w .. 16 w + 15 of the block row in hand.
 //   LDS: the strip ((rows up to the end of its diagonal block) x 17), one block row of products (nb x 17) and
 //   a chunk of R (nb x 34).
-// The strip goes to Xout in its type, and that of R to Rout if it is wanted, both with zeros below the diagonal (l x l, ld l).
-template <int NW, typename TOut>
+// The strip goes to Xout as float or double, and that of R to Rout if it is wanted, both with zeros below the diagonal (l x l, ld l).
+template <int NW>
 __global__ __launch_bounds__(64 * NW) void tri_inverse_strip_kernel(const double *__restrict__ R,
                                                                     const double *__restrict__ X, int l,
-                                                                    TOut *__restrict__ Xout, double *__restrict__ Rout,
+                                                                    void *Xout, int out_f32, double *__restrict__ Rout,
                                                                     const int *skip_flag) {
   if (skip_flag != nullptr && *skip_flag != 0) return;
   constexpr int nb = 16 * NW, LDS_ = 17;
@@ -866,7 +864,9 @@ __global__ __launch_bounds__(64 * NW) void tri_inverse_strip_kernel(const double
     const int r = idx / 16, c = idx % 16;
     if (c0 + c >= l) continue;
     const int64_t at = (int64_t)r * l + c0 + c;
-    Xout[at] = r < kend ? (TOut)Xs[r * LDS_ + c] : (TOut)0;
+    const double x = r < kend ? Xs[r * LDS_ + c] : 0.0;
+    if (out_f32) reinterpret_cast<float *>(Xout)[at] = (float)x;
+    else reinterpret_cast<double *>(Xout)[at] = x;
     if (Rout != nullptr) Rout[at] = r <= c0 + c ? R[at] : 0.0;
   }
 }
@@ -878,10 +878,9 @@ hipError_t chol_init_device(rsvd_ctx *ctx) {
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(&panel_qr_kernel),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)panel_lds_bytes(1024, 16));
-  const void *const strips[6] = {
-      reinterpret_cast<const void *>(&tri_inverse_strip_kernel<6, float>), reinterpret_cast<const void *>(&tri_inverse_strip_kernel<6, double>),
-      reinterpret_cast<const void *>(&tri_inverse_strip_kernel<7, float>), reinterpret_cast<const void *>(&tri_inverse_strip_kernel<7, double>),
-      reinterpret_cast<const void *>(&tri_inverse_strip_kernel<8, float>), reinterpret_cast<const void *>(&tri_inverse_strip_kernel<8, double>)};
+  const void *const strips[3] = {reinterpret_cast<const void *>(&tri_inverse_strip_kernel<6>),
+                                 reinterpret_cast<const void *>(&tri_inverse_strip_kernel<7>),
+                                 reinterpret_cast<const void *>(&tri_inverse_strip_kernel<8>)};
   for (const void *k : strips)
     if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
   return e;
@@ -985,14 +984,10 @@ hipError_t chol_inverse_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype out_dtyp
   if (strips) {
     ProfScope ps(ctx, s, PK_SMALL);
     const dim3 grid((unsigned)ceil_div(l, 16)), threads((unsigned)(nb * 4));
-    auto go = [&](auto *out) {
-      typedef typename std::remove_pointer<decltype(out)>::type T;
-      if (nb == 96) hipLaunchKernelGGL((tri_inverse_strip_kernel<6, T>), grid, threads, strip_lds, s, Rf, Xf, (int)l, out, R, skip_flag);
-      else if (nb == 112) hipLaunchKernelGGL((tri_inverse_strip_kernel<7, T>), grid, threads, strip_lds, s, Rf, Xf, (int)l, out, R, skip_flag);
-      else hipLaunchKernelGGL((tri_inverse_strip_kernel<8, T>), grid, threads, strip_lds, s, Rf, Xf, (int)l, out, R, skip_flag);
-    };
-    if (out_dtype == RSVD_F32) go((float *)Rinv);
-    else go((double *)Rinv);
+    const int f32 = out_dtype == RSVD_F32;
+    if (nb == 96) hipLaunchKernelGGL((tri_inverse_strip_kernel<6>), grid, threads, strip_lds, s, Rf, Xf, (int)l, Rinv, f32, R, skip_flag);
+    else if (nb == 112) hipLaunchKernelGGL((tri_inverse_strip_kernel<7>), grid, threads, strip_lds, s, Rf, Xf, (int)l, Rinv, f32, R, skip_flag);
+    else hipLaunchKernelGGL((tri_inverse_strip_kernel<8>), grid, threads, strip_lds, s, Rf, Xf, (int)l, Rinv, f32, R, skip_flag);
     return hipGetLastError();
   }
   if (out_dtype == RSVD_F32) {
