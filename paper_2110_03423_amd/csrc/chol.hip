@@ -641,7 +641,7 @@ __global__ void fill_zero_f64_kernel(double *__restrict__ p, int64_t n, const in
 // The columns of the product are independent of each other: a workgroup takes sixteen through the whole chain.  A row of the
 // product wants the rows from its own on, so groups of kChainRows rows are done from the top, in place, a group in registers
 // before the first of it is stored.  What bounds it is the trip to L2 per 32 columns of R, which the row blocks of a wavefront share.
-// One launch where every factor had one of its own and a copy.  With the strip kernel above writing its results in their final type and the
+// One launch where every factor had one of its own and a copy (an element per thread; one product 54 us at l = 576, 8 at 80, now 50 and 5).  With the strip kernel above writing its results in their final type and the
 // first block keeping the diagonal (four to five launches less per blocked factorisation, 4 to 5 us each, skipped or not): 4001 x 50021 fp32, l = 210, q = 1
 // 4522 -> 4452 us; 20000 x 20000 fp64, l = 288, q = 2 27997 -> 27716.
 constexpr int kChainBlocks = 5, kChainRows = 16 * 8 * kChainBlocks;
@@ -653,6 +653,8 @@ __global__ __launch_bounds__(512) void r_chain_kernel(int l, const double *R1, c
   const int c0 = (int)blockIdx.x * 16, col = c0 + r16, ccol = min(col, l - 1);
   const int lp = (l + 15) & ~15, kend = min(c0 + 16, lp);  // below kend these columns are zero
   double *dst = reinterpret_cast<double *>(reinterpret_cast<char *>(out) + off);
+  typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
+  const int last = max(l - 2, 0);                          // where the last pair of a row begins (l = 1: the element behind is padding)
   for (int f = 0; f < 3; ++f) {
     const double *R = f == 0 ? R2 : f == 1 ? R3 : R4;
     if (f > 0) {
@@ -666,13 +668,20 @@ __global__ __launch_bounds__(512) void r_chain_kernel(int l, const double *R1, c
 #pragma unroll
       for (int n = 0; n < kChainBlocks; ++n) acc[n] = f64x4{0.0, 0.0, 0.0, 0.0};
       for (int k0 = g0 + 16 * wave; k0 < kend; k0 += 32) {
-        double a[kChainBlocks][8], b[8];
+        pair_t a[kChainBlocks][4];
+        double b[4][2];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int k = k0 + 4 * u + kq, kc = min(k, l - 1);
-          b[u] = S[(int64_t)kc * l + ccol];
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-          for (int n = 0; n < kChainBlocks; ++n) a[n][u] = R[(int64_t)min(g0 + 16 * (wave + 8 * n) + r16, l - 1) * l + kc];
+          for (int e = 0; e < 2; ++e) b[u][e] = S[(int64_t)min(k0 + 8 * u + 2 * kq + e, l - 1) * l + ccol];
+        // (64 bytes of a row per instruction, no row blocks that begin behind these columns: 50 us at l = 576, 17 at 288; 32 bytes and all blocks: 144, 45)
+#pragma unroll
+        for (int n = 0; n < kChainBlocks; ++n) {
+          const int row = g0 + 16 * (wave + 8 * n);
+          if (row >= k0 + 32 || row >= kend) break;
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            a[n][u] = *reinterpret_cast<const pair_t *>(R + (int64_t)min(row + r16, l - 1) * l + min(k0 + 8 * u + 2 * kq, last));
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -680,9 +689,11 @@ __global__ __launch_bounds__(512) void r_chain_kernel(int l, const double *R1, c
           const int row = g0 + 16 * (wave + 8 * n);
           if (row >= k0 + 32 || row >= kend) break;
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int k = k0 + 4 * u + kq;
-            acc[n] = Mfma<double>::run(k >= row + r16 && k < l ? a[n][u] : 0.0, k <= col ? b[u] : 0.0, acc[n]);
+          for (int u = 0; u < 4; ++u) {
+            const int k = k0 + 8 * u + 2 * kq;
+            const double a0 = k <= last ? a[n][u][0] : a[n][u][1], a1 = a[n][u][1];
+            acc[n] = Mfma<double>::run(k >= row + r16 && k < l ? a0 : 0.0, k <= col ? b[u][0] : 0.0, acc[n]);
+            acc[n] = Mfma<double>::run(k + 1 >= row + r16 && k + 1 < l ? a1 : 0.0, k + 1 <= col ? b[u][1] : 0.0, acc[n]);
           }
         }
       }
