@@ -202,6 +202,7 @@ static Layout make_layout(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t m, int6
   L.dead = take((size_t)l * sizeof(int));
   L.info = take(sizeof(DevInfo));
   L.flags = take(16 * sizeof(int));
+  take((size_t)l * es);              // (not used: keeps the sizes that callers may have stored, and what the static buffer refuses)
   L.Wj = take((size_t)l * l * es);
   L.Xj = take((size_t)l * l * es);
   L.jac_scratch_bytes = jacobi_scratch_bytes(ctx, dtype, l);
