@@ -524,7 +524,8 @@ constexpr int kPolishSteps = 10, kPolishPhases = 13;
 // The corrections of the whole matrix behind the first run, and the run behind those.
 struct JbSync {
   JbRun run[2];
-  unsigned long long x2[kPolishSteps];      // per correction: sum of its squared angles times kPolishScale
+  unsigned long long x2[kPolishSteps];      // per correction: sum of the squared angles of all pairs times kPolishScale
+  unsigned long long x2_open[kPolishSteps]; // and of the pairs above the threshold of a rotation
   int rho[kPolishSteps];                    // and the largest relative inner product it found
   int done[kPolishSteps * kPolishPhases];   // tiles finished, phase by phase
   int updates, converged;                   // how the corrections ended
@@ -999,6 +1000,10 @@ __device__ __forceinline__ float jg_pair_params(const T *G, int p, int q, T tol,
 //   G = M^T M, X;  Y = X X, Y2 = Y Y, Y3, Y4 as far as the size of X asks for;  E = exp(X) - I;  M <- M + M E, J <- J + J E.
 // exp(X) of an antisymmetric X is orthogonal: the series is cut where it is so to rounding (x: the Frobenius norm of X; the same angles are met by M and J, and E keeps the relative size of its elements, so short columns of M
 // keep their relative accuracy as in a sweep).  Angles, thresholds and the floor for zero columns are those of a rotation.
+// The length of the series and the halvings follow from the x of ALL angles, those below the threshold of a rotation too: with many equal
+// singular values they are most of it (l = 160, 96 equal values: the pairs above the threshold 4e-5, all 9e-2), and a series cut for the others'
+// sum left W off orthogonality by 2e-8 in fp64.  The limit on x and the rule that it shrinks look at the pairs above the threshold alone: inside
+// a cluster the others are rounding noise and do not shrink.
 // A correction that meets a larger x than it may, or one that does not shrink, does nothing and leaves the rest to sweeps, as inside a
 // cluster of nearly equal singular values, where the angles stay large however small the inner products.
 // Everything is decided from the counters of JbSync, which are sums of whole numbers and maxima: no order of arrival shows in the result.
@@ -1207,11 +1212,11 @@ __global__ __launch_bounds__(256) void polish_kernel(PolishParams<T> P) {
   T *red = reinterpret_cast<T *>(red64);
   __shared__ double part[4][2][kPoTile];
   __shared__ int ticket_sh;
-  __shared__ float wave_rho[4], wave_x2[4];
+  __shared__ float wave_rho[4], wave_x2[4], wave_open[4];
   T *M = P.b[0], *J = P.b[1], *X = P.b[2], *Y = P.b[3], *Y2 = P.b[4], *C = P.b[5], *S = P.b[6];
   int step = 0, phase = PO_ANGLES, seq = 0, base = 0, count = upper, order = 0, halvings = 0, doublings = 0, updates = 0;
   T half = (T)1;                                     // the series is taken of half * X
-  float x_before = 1e30f, x_now = 0.f, rho_now = 0.f;
+  float x_before = 1e30f, x_now = 0.f, x_all = 0.f, rho_now = 0.f;
   int ticket = 0;
   if (threadIdx.x == 0) ticket = atomicAdd(&sync->ticket, 1);
 
@@ -1229,12 +1234,13 @@ __global__ __launch_bounds__(256) void polish_kernel(PolishParams<T> P) {
       bool end = false, converged = false;
       if (phase == PO_ANGLES) {
         rho_now = __int_as_float(device_load(&sync->rho[step]));
-        x_now = sqrtf((float)device_load(&sync->x2[step]) * (2.f / kPolishScale));
-        order = x_now <= polish_limit<T>(1) ? 1 : x_now <= polish_limit<T>(2) ? 2 : x_now <= polish_limit<T>(3) ? 3 : 4;
+        x_all = sqrtf((float)device_load(&sync->x2[step]) * (2.f / kPolishScale));
+        x_now = sqrtf((float)device_load(&sync->x2_open[step]) * (2.f / kPolishScale));
+        order = x_all <= polish_limit<T>(1) ? 1 : x_all <= polish_limit<T>(2) ? 2 : x_all <= polish_limit<T>(3) ? 3 : 4;
         converged = rho_now <= (float)tol;
         end = converged || !(x_now <= polish_start(l)) || !(x_now <= kPolishRate * x_before);
         halvings = 0;
-        for (float x = x_now; x > polish_limit<T>(4) && halvings < 7; x *= 0.5f) ++halvings;
+        for (float x = x_all; x > polish_limit<T>(4) && halvings < 7; x *= 0.5f) ++halvings;
         doublings = halvings;
         half = ldexp((T)1, -halvings);
         phase = PO_SQUARE;
@@ -1262,7 +1268,7 @@ __global__ __launch_bounds__(256) void polish_kernel(PolishParams<T> P) {
         T *t = M; M = Y; Y = t;
         t = J; J = Y2; Y2 = t;
         ++updates;
-        converged = rho_now * x_now <= (float)tol;             // the next one would find about that
+        converged = rho_now * x_all <= (float)tol;             // the next one would find about that
         ++step;
         end = converged || step == kPolishSteps;
         x_before = x_now;
@@ -1332,7 +1338,7 @@ __global__ __launch_bounds__(256) void polish_kernel(PolishParams<T> P) {
         if (lane < 16) { part[wave][0][16 * h + lane] = ni[h]; part[wave][1][16 * h + lane] = nj[h]; }
       }
       __syncthreads();
-      float rho = 0.f, x2 = 0.f;
+      float rho = 0.f, x2 = 0.f, open = 0.f;
       each([&](int u, int i, int j, int64_t) {
         if (ti == tj && i > j) return;
         const int r = i - i0, c = j - j0;
@@ -1347,7 +1353,10 @@ __global__ __launch_bounds__(256) void polish_kernel(PolishParams<T> P) {
           t = zeta < 0.0 ? -t : t;
           // below the threshold only where it is a small one: inside a cluster it would be large, and noise
           if (rel > tol || fabs(t) <= kPolishFree) angle = t - t * t * t * (1.0 / 3.0 - 0.2 * t * t);
-          if (rel > tol) rho = fmaxf(rho, (float)rel);
+          if (rel > tol) {
+            rho = fmaxf(rho, (float)rel);
+            open += (float)(angle * angle);
+          }
           x2 += (float)(angle * angle);
         }
         device_store(X + (int64_t)i * l + j, (T)angle);
@@ -1357,15 +1366,19 @@ __global__ __launch_bounds__(256) void polish_kernel(PolishParams<T> P) {
       for (int m = 1; m < 64; m <<= 1) {
         rho = fmaxf(rho, __shfl_xor(rho, m, 64));
         x2 += __shfl_xor(x2, m, 64);
+        open += __shfl_xor(open, m, 64);
       }
-      if (lane == 0) { wave_rho[wave] = rho; wave_x2[wave] = x2; }
+      if (lane == 0) { wave_rho[wave] = rho; wave_x2[wave] = x2; wave_open[wave] = open; }
       __syncthreads();
       if (threadIdx.x == 0) {
         rho = fmaxf(fmaxf(wave_rho[0], wave_rho[1]), fmaxf(wave_rho[2], wave_rho[3]));
         x2 = (wave_x2[0] + wave_x2[1]) + (wave_x2[2] + wave_x2[3]);
+        open = (wave_open[0] + wave_open[1]) + (wave_open[2] + wave_open[3]);
+        auto whole = [](float x) { return (unsigned long long)ceilf(fminf(x, 128.f) * kPolishScale); };
+        if (x2 > 0.f) atomicAdd(&sync->x2[step], whole(x2));
         if (rho > 0.f) {
           atomicMax(&sync->rho[step], __float_as_int(rho));
-          atomicAdd(&sync->x2[step], (unsigned long long)ceilf(fminf(x2, 128.f) * kPolishScale));
+          atomicAdd(&sync->x2_open[step], whole(open));
         }
       }
     } else if (phase == PO_SQUARE) {                 // Y = X X; with the shortest series E = X + Y / 2

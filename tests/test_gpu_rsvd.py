@@ -465,3 +465,20 @@ def test_only_k_values_are_written(dt, l):
         got = to_np(out)
         assert rc == 0 and np.array_equal(got[base:base + k], to_np(S))
         assert (np.delete(got, np.arange(base, base + k)) == -7.0).all()
+
+
+# A leading value that is repeated many times (what is left of it in the small SVD are angles of rounding size).
+@pytest.mark.parametrize("l,equal,rate", [(110, 64, 0.4), (128, 96, 0.05), (160, 96, 0.02), (200, 180, 0.1)])
+def test_repeated_leading_value(l, equal, rate):
+    say("repeated value", l, equal, rate)
+    k, m, n = l - 10, 700, 500
+    i = np.arange(l + 20)
+    s = np.where(i < equal, 1.0, 0.8 * np.exp(-rate * np.maximum(i - equal, 0)))
+    A = (workloads.orthonormal_factor(m, l + 20, l) * s) @ workloads.orthonormal_factor(n, l + 20, l + 1).T
+    for seed in range(4):
+        S, U, Vt, info = ctx().rsvd_run(to_dev(A), k, 10, 2, seed=seed)
+        assert info.status == 0
+        S, U, Vt = (to_np(t) for t in (S, U, Vt))
+        want, eps = orc.rsvd(A, k, 10, 2, seed, np.float64), parity.EPS["f64"]
+        assert np.abs(S - want.S).max() <= 20 * eps * np.sqrt(max(m, n))
+        assert parity.orthonormality(U) <= parity.jacobi_tol(l, "f64") and parity.orthonormality(Vt.T) <= parity.jacobi_tol(l, "f64")

@@ -359,6 +359,32 @@ def test_block_jacobi_corrections(dt, l, kind):
     assert np.abs(sig - want).max() <= 20 * eps * np.sqrt(l) * want[0]
 
 
+# Many equal values above a decaying rest: angles below the threshold of a rotation, rounding noise each, are most of what a correction
+# turns by, and its series has to be long enough for them.  Factors as q subspace iterations leave them.
+@pytest.mark.parametrize("dt,l,equal,q,rate", [("f64", 70, 40, 2, 0.02), ("f64", 98, 90, 1, 0.05), ("f64", 110, 64, 2, 0.4), ("f64", 128, 96, 2, 0.05),
+                                               ("f64", 160, 96, 0, 0.2), ("f64", 160, 96, 1, 0.02), ("f64", 200, 180, 0, 0.1),
+                                               ("f64", 288, 100, 1, 0.02), ("f32", 110, 64, 2, 0.4), ("f32", 160, 96, 1, 0.05)])
+def test_block_jacobi_equal_values(dt, l, equal, q, rate):
+    say("block jacobi equal values", dt, l, equal, q, rate)
+    rng = np.random.default_rng(1000 * l + equal + q)
+    i = np.arange(l + 20)
+    s = np.where(i < equal, 1.0, 0.8 * np.exp(-rate * np.maximum(i - equal, 0)))
+    U, V = (np.linalg.qr(rng.standard_normal((2 * l, l + 20)))[0] for _ in range(2))
+    A = (U * s) @ V.T
+    Q = np.linalg.qr(A @ rng.standard_normal((2 * l, l)))[0]
+    for _ in range(q):
+        Q = np.linalg.qr(A @ np.linalg.qr(A.T @ Q)[0])[0]
+    M = np.linalg.qr(A.T @ Q)[1].T.astype(NPDT[dt])
+    sig, X, W, info = ctx().rsvd_stage_jacobi(to_dev(M))
+    assert info.status == 0
+    sig, X, W = (to_np(t).astype(np.float64) for t in (sig, X, W))
+    M64, eps = M.astype(np.float64), np.finfo(NPDT[dt]).eps
+    _svd_check(sig, X, W, M64, dt, "equal values")
+    assert np.abs(W.T @ W - np.eye(l)).max() <= 8 * eps * np.sqrt(20 * l)          # bounds as for the corrections above
+    want = np.linalg.svd(M64, compute_uv=False)
+    assert np.abs(sig - want).max() <= 20 * eps * np.sqrt(l) * want[0]
+
+
 @pytest.mark.parametrize("l", [129, 300, 576])
 @pytest.mark.parametrize("cond", [1.0, 1e3])
 def test_block_jacobi_values_do_not_drift(l, cond):
