@@ -132,14 +132,17 @@ void gram_syrk_kernel(const SyrkParams P0) {
 // l = 128, where a wavefront has nine blocks, in proportion less below, and never less than its loads take), since
 // every workgroup pays for the l x l partial sum it leaves.  The problems of a batch share the places of the chip: 256 of 2000 rows,
 // l = 32, take 500 rows a workgroup and leave four partial sums each, which the factorisation adds (13 and a reduction before).
+// A problem is never cut into more ranges than it would be alone: the workspace has room for that many partial sums (with fewer
+// problems than workgroups per CU the places would allow more).
 static void syrk_split(const rsvd_ctx *ctx, int64_t rows, int64_t l, int batch, int64_t &rows_per_wg, int &wgs) {
   const int64_t nblk = ceil_div(l, 16), nb2 = nblk * (nblk + 1) / 2;
   double per_ktile = 2.2 * (double)nb2 / 36.0;          // us; never less than the ~0.6 us a k-tile's loads take
   if (per_ktile < 0.6) per_ktile = 0.6;
   int64_t ktiles = (int64_t)(3.0 / per_ktile);
   if (ktiles < 1) ktiles = 1;
-  const int64_t places = (int64_t)ctx->cu_count * (batch > 1 ? syrk_wgs_per_cu((int)nblk) : 1);
-  rows_per_wg = ceil_div(ceil_div(rows * batch, places), 32) * 32;
+  const int64_t alone = ceil_div(rows, (int64_t)ctx->cu_count);
+  const int64_t shared = ceil_div(rows * batch, (int64_t)ctx->cu_count * syrk_wgs_per_cu((int)nblk));
+  rows_per_wg = ceil_div(shared > alone ? shared : alone, 32) * 32;
   if (rows_per_wg < 32 * ktiles) rows_per_wg = 32 * ktiles;
   wgs = (int)ceil_div(rows, rows_per_wg);
   if (wgs < 1) wgs = 1;

@@ -82,6 +82,34 @@ def test_large_batches_match_single_calls(dt, m, n, l, batch):
         assert err[0] <= 1.001 * err[1] + 50 * parity.EPS[dt] * float(torch.linalg.norm(A[b])), (b, err)
 
 
+# A few problems of many rows and few columns: the partial sums of their Gram matrices are the largest there are, and the workspace
+# has room for those of a problem alone.
+TALL = [("f32", 50000, 64, 40, 2), ("f32", 100000, 32, 16, 2), ("f32", 200000, 40, 20, 4), ("f32", 200000, 100, 30, 3),
+        ("f64", 60000, 80, 50, 2), ("f64", 100000, 64, 32, 2), ("f64", 64, 60000, 24, 7)]
+
+
+@pytest.mark.parametrize("dt,m,n,l,batch", TALL)
+def test_few_tall_problems_match_single_calls(dt, m, n, l, batch):
+    import torch
+    say("few tall", dt, m, n, l, batch)
+    t = torch.float32 if dt == "f32" else torch.float64
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(6)
+    decay = torch.exp(-torch.arange(min(m, n), dtype=t, device="cuda:0") * (3.0 / l))
+    A = torch.randn((batch, max(m, n), min(m, n)), dtype=t, device="cuda:0", generator=gen) * decay
+    if m < n:
+        A = A.transpose(1, 2).contiguous()
+    k, c = l - 5, ctx()
+    S, U, Vt, info = c.rsvd_run_batched(A, k, 5, 1, seed=60)
+    assert info.status == 0
+    for b in range(batch):
+        S1, U1, Vt1, _ = c.rsvd_run(A[b], k, 5, 1, seed=60 + b)
+        # (bounds as above)
+        assert float((S[b] - S1).abs().max()) <= 200 * parity.EPS[dt] * np.sqrt(max(m, n)) * float(S1[0]), b
+        err = float(torch.linalg.norm(A[b] - (U[b] * S[b]) @ Vt[b])), float(torch.linalg.norm(A[b] - (U1 * S1) @ Vt1))
+        assert err[0] <= 1.001 * err[1] + 50 * parity.EPS[dt] * float(torch.linalg.norm(A[b])), (b, err)
+
+
 @pytest.mark.parametrize("base,batch,q", CASES, ids=lambda v: getattr(v, "name", str(v)))
 def test_batched_matches_oracle_and_single_calls(base, batch, q):
     import torch
