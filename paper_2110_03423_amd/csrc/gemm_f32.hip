@@ -15,8 +15,8 @@ hipError_t gemm_split_init_device(rsvd_ctx *ctx) {
 
 // Which products are split, by their shape (times in us, fp32 kernel against split one).  Up to 32 columns both kernels wait for
 // memory and the fp32 one needs no conversion (65536 x 16384, l = 16: 5.8 TB/s), and below 2^29 multiply-adds (2000 x 500, l = 33:
-// 22, 25) the longer prologue of the large tiles costs more than the faster instruction brings.  Where the fp32 kernel has its
-// 16-byte loads it also wins on
+// 22, 25) the longer prologue of the large tiles costs more than the faster instruction brings.  Where both operands are aligned for
+// 16-byte loads the fp32 kernel also wins on
 //  - a k range of a few k-tiles, unless one column tile of 96 to 144 shares the traffic of A: 1000000 x 64, l = 64: 131, 217; 69568 x
 //    192, l = 192: 73, 84; but 57504 x 176, l = 112: 45, 38;
 //  - up to 48 columns of A X, whose tiles of A are half of all LDS traffic, unless the k range is long (69808 x 464: 53, 58;
@@ -25,10 +25,12 @@ hipError_t gemm_split_init_device(rsvd_ctx *ctx) {
 //  - a triangular B (the applies of R^-1), which leaves only part of a short k range per column tile: its narrower tiles waste less
 //    of that (65536 x 576: 176, 224).
 // Otherwise: 10000 x 2000, l = 80: 56 -> 47; 50021 x 210, triangular, scalar loads: 86 -> 72; 65536 x 16384, l = 576: 9179 -> 5512.
-static bool takes_split(const GemmDesc &d, bool vec) {
+// A narrow operand of the workspace that is not aligned, which the fp32 kernel reads in 16-byte pieces all the same, counts as one that it
+// cannot: the split kernel's error against 64 bits is 2.8 to 5 times smaller, and these rules decide where it is given up.
+static bool takes_split(const GemmDesc &d, bool aligned) {
   const double madds = (double)d.M * (double)d.N * (double)d.K * (double)d.batch;
   if (d.N <= 32 || madds < 536870912.0 || d.upper_only || d.alpha != 1.0 || d.beta != 0.0 || !split_fits(d.lda, d.ldb)) return false;
-  if (!vec) return true;
+  if (!aligned) return true;
   if (d.b_upper != 0) return false;
   if (d.K < 208 && (d.N < 96 || d.N > 144)) return false;
   if (d.N <= 48) return d.trans_a ? d.M >= 96 : (d.K >= 640 && madds >= 1073741824.0);
@@ -45,13 +47,13 @@ static bool takes_split(const GemmDesc &d, bool vec) {
 // A last wave that is nearly empty costs more than the faster instruction brings in narrow products: l = 48, 1.2 waves: 78592 x
 // 1200 107, 126; 1.4: 91648 x 4000 366, 361; l = 96, 1.05 waves: 68608 x 400 76, 79; 68608 x 1200 180, 176; l = 128: 68160 x 128
 // 43, 56; 68608 x 400 97, 92.  (Over 260 random shapes in both directions the rule is within 1 % of the better kernel each time.)
-static bool fills_chip(const rsvd_ctx *ctx, const GemmDesc &d, bool vec, int bn, const SplitChoice &c) {
+static bool fills_chip(const rsvd_ctx *ctx, const GemmDesc &d, bool aligned, int bn, const SplitChoice &c) {
   const int64_t wgs = ceil_div(d.M, split_tile_m(bn)) * ceil_div(d.N, bn) * d.batch * c.splits;
   const int64_t places = (int64_t)ctx->cu_count * split_wgs_per_cu(bn), ktiles = c.k_per_split / kSplitBK;
   const bool whole = c.splits == 1;
-  const int share = !vec ? (whole ? 25 : 35) : ktiles <= 6 ? 75 : d.N <= 48 ? 70 : ktiles >= 16 ? 40 : d.trans_a || whole ? 50 : 55;
+  const int share = !aligned ? (whole ? 25 : 35) : ktiles <= 6 ? 75 : d.N <= 48 ? 70 : ktiles >= 16 ? 40 : d.trans_a || whole ? 50 : 55;
   if (wgs * 100 < places * share) return false;
-  if (!vec || d.N > 128 || wgs <= places) return true;
+  if (!aligned || d.N > 128 || wgs <= places) return true;
   const bool full = wgs * 100 >= ceil_div(wgs, places) * places * 65;
   if (d.N <= 48) return full && d.K >= 2048;
   return full || d.K >= (d.N <= 96 ? 512 : 256);
@@ -86,8 +88,8 @@ static SplitChoice split_ranges(const rsvd_ctx *ctx, const GemmDesc &d, int bn, 
 hipError_t gemm_launch_f32(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d) {
   typedef GemmDispatch<float, float, float> Plain;
   if (d.M <= 0 || d.N <= 0) return hipSuccess;
-  const bool vec = Plain::vector_loads(d);
-  if (!takes_split(d, vec)) return Plain::launch(ctx, s, d);
+  const bool aligned = Plain::aligned_a(d) && Plain::aligned_b(d);
+  if (!takes_split(d, aligned)) return Plain::launch(ctx, s, d);
   if (d.batch < 1 || d.batch > 65535) return hipErrorInvalidValue;
   if (d.a_shift != nullptr && (d.dead != nullptr || d.trans_c || d.batch != 1)) return hipErrorInvalidValue;
   // the k ranges of the fp32 kernel bound those taken here: the workspace is sized for their partial sums
@@ -95,7 +97,7 @@ hipError_t gemm_launch_f32(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d) {
   SplitChoice c = choose_split(ctx, t, d.M, d.N, d.K, d.force_splits, false, d.batch);
   const int bn = split_tile_n(d.N);
   if (d.force_splits <= 0) c = split_ranges(ctx, d, bn, c.splits);
-  if (!fills_chip(ctx, d, vec, bn, c)) return Plain::launch(ctx, s, d);
+  if (!fills_chip(ctx, d, aligned, bn, c)) return Plain::launch(ctx, s, d);
   if (c.splits > 1) {
     const size_t need = (size_t)c.splits * (size_t)d.M * (size_t)d.N * sizeof(float);
     if (d.partial == nullptr || d.partial_bytes < need) return hipErrorInvalidValue;

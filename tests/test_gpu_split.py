@@ -202,3 +202,26 @@ def test_batched(batch, m, n, k, p):
         _reconstructs(A[b], S[b], U[b], Vt[b])
         one = ctx().rsvd_run(A[b].contiguous(), k, p, 1, seed=5 + b)[0]
         assert float(((S[b] - one) / one).abs().max()) <= 64 * EPS
+
+
+# A width that is no multiple of four leaves the workspace's panels unaligned; the fp32 kernel reads them in 16-byte pieces all the same, but
+# is the less exact of the two.  Short k ranges, narrow outputs and last waves that are nearly empty are where it would be taken otherwise.
+@pytest.mark.parametrize("m,n,l,k", [(68683, 130, 112, 102), (100000, 130, 120, 45), (40001, 260, 200, 77), (90000, 240, 160, 43)])
+def test_products_of_odd_width_stay_split(m, n, l, k):
+    """U = Q W of a whole call: Q is what the call leaves in the first panel of its workspace, W follows from U and Q (the roundings of m rows
+    average out), and what is left are the roundings of the product: those of the stage call, which has no slack behind its operands, with
+    the same Q and W.  The fp32 kernel's are 2.8 to 5 times as large."""
+    import torch
+    say("odd lift", m, n, l, k)
+    A = _randn(m, n, 9) * torch.exp(-torch.arange(n, device="cuda:0") * (2.0 / n))
+    c = ctx()
+    ws = torch.empty(c.workspace_bytes(0, m, n, k, l - k, 0), dtype=torch.uint8, device="cuda:0")
+    U = c.rsvd_run(A, k, l - k, 0, seed=4, workspace=ws)[1]
+    Q = ws[: m * l * 4].view(torch.float32).view(m, l).clone()
+    Q64 = Q.double()
+    Qt = Q64.T.contiguous()
+    W = torch.linalg.solve(Qt @ Q64, Qt @ U.double()).float().contiguous()
+    exact = Q64 @ W.double()
+    run, stage = (float((x.double() - exact).norm() / exact.norm()) for x in (U, c.rsvd_stage_lift(Q, W, k)))
+    say("  errors", run, stage)
+    assert run <= 1.5 * stage, (run, stage)
