@@ -6,13 +6,14 @@ size_t gemm_partial_bytes_f64(const rsvd_ctx *ctx, int64_t M, int64_t N, int64_t
   return GemmDispatch<double, double, double>::partial_bytes(ctx, M, N, K, trans_a != 0);
 }
 
-template <bool TA, int BM, int BN, int WGM, int WGN> using Run64 = PipeRun<double, TA, BM, BN, WGM, WGN>;
-#define RSVD_PIPE_TILES(X) X(64, 16, 4, 1) X(64, 32, 4, 1) X(64, 48, 4, 1) X(64, 64, 4, 1) X(64, 80, 4, 1) X(64, 96, 4, 1) \
-  X(64, 112, 4, 1) X(64, 128, 4, 1) X(128, 64, 2, 2) X(128, 96, 2, 2) X(128, 128, 2, 2)
+// (chains: tiles of products with up to 128 columns)
+#define RSVD_PIPE_TILES(X) X(64, 16, 4, 1, true) X(64, 32, 4, 1, true) X(64, 48, 4, 1, true) X(64, 64, 4, 1, true) X(64, 80, 4, 1, true) \
+  X(64, 96, 4, 1, true) X(64, 112, 4, 1, true) X(64, 128, 4, 1, true) X(128, 64, 2, 2, false) X(128, 96, 2, 2, false) X(128, 128, 2, 2, false)
 
 template <bool TA>
-static hipError_t pipe_by_tile(hipStream_t s, const GemmParams &P, int bm, int bn, int batch) {
-#define RSVD_PIPE(BM, BN, WGM, WGN) if (bm == BM && bn == BN) return Run64<TA, BM, BN, WGM, WGN>::go(s, P, batch);
+static hipError_t pipe_by_tile(hipStream_t s, const GemmParams &P, int bm, int bn, bool chains, int batch) {
+#define RSVD_PIPE(BM, BN, WGM, WGN, CHAINS) \
+  if (bm == BM && bn == BN && chains == CHAINS) return PipeRun<double, TA, BM, BN, WGM, WGN, CHAINS>::go(s, P, batch);
   RSVD_PIPE_TILES(RSVD_PIPE)
 #undef RSVD_PIPE
   return hipErrorInvalidValue;
@@ -31,8 +32,9 @@ hipError_t gemm_launch_f64(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d) {
     bm = 128;
     bn = pad96 <= pad128 && pad96 <= pad64 ? 96 : pad64 < pad128 ? 64 : 128;
   }
-  return pipe_launch<double>(ctx, s, d, bm, bn, [&](const GemmParams &P) {
-    return d.trans_a ? pipe_by_tile<true>(s, P, bm, bn, d.batch) : pipe_by_tile<false>(s, P, bm, bn, d.batch);
+  const bool chains = d.N <= 128;
+  return pipe_launch<double>(ctx, s, d, bm, bn, chains, [&](const GemmParams &P) {
+    return d.trans_a ? pipe_by_tile<true>(s, P, bm, bn, chains, d.batch) : pipe_by_tile<false>(s, P, bm, bn, chains, d.batch);
   });
 }
 }  // namespace rsvd

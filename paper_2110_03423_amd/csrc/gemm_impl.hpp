@@ -29,6 +29,7 @@ struct GemmParams {
   void *C; int64_t ldc;
   void *partial;            // [splits][M][N] accumulator-typed, used when splits > 1
   int64_t k_per_split;
+  int64_t k_chain;          // gemm_pipe_kernel: terms that go into one accumulator (a multiple of its k-tile)
   int splits;
   int tiles_n, tiles_m;     // grid shape in tiles; the launch is one-dimensional
   int upper_bm, upper_bn;   // > 0: symmetric result, tiles (of this size) strictly below the diagonal are skipped
@@ -538,7 +539,7 @@ inline GemmParams make_params(const GemmDesc &d, const SplitChoice &c, int upper
   GemmParams P;
   P.M = d.M; P.N = d.N; P.K = d.K;
   P.A = d.A; P.lda = d.lda; P.B = d.B; P.ldb = d.ldb; P.C = d.C; P.ldc = d.ldc;
-  P.partial = d.partial; P.k_per_split = c.k_per_split; P.splits = c.splits;
+  P.partial = d.partial; P.k_per_split = c.k_per_split; P.k_chain = 0; P.splits = c.splits;
   P.trans_c = d.trans_c; P.alpha = d.alpha; P.beta = d.beta;
   P.upper_bm = upper_bm; P.upper_bn = upper_bn;
   P.b_upper = d.b_upper;

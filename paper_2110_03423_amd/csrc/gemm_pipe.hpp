@@ -25,10 +25,14 @@
 
 namespace rsvd {
 
-// Workgroups that share a CU, and the k-tiles each has room for (in the 64 KB that a launch may ask for without more ado).
-constexpr int pipe_wgs(int bm, int bn) { return bm > 64 || bn <= 16 ? 2 : bn <= 96 ? 4 : 3; }
-constexpr int pipe_stages(int bm, int bn) {
-  const int kb = 160 / pipe_wgs(bm, bn) < 64 ? 160 / pipe_wgs(bm, bn) : 64;
+// Workgroups that share a CU, and the k-tiles each has room for (in the 64 KB that a launch may ask for without more ado).  chains: with a
+// second set of accumulators, for which the wider tiles take the registers of a workgroup.
+constexpr int pipe_wgs(int bm, int bn, bool chains) {
+  if (bm > 64 || bn <= 16) return 2;
+  return chains ? (bn <= 80 ? 4 : bn <= 112 ? 3 : 2) : bn <= 96 ? 4 : 3;
+}
+constexpr int pipe_stages(int bm, int bn, bool chains) {
+  const int wgs = pipe_wgs(bm, bn, chains), kb = 160 / wgs < 64 ? 160 / wgs : 64;
   return kb * 1024 / ((bm + bn) * 128);
 }
 
@@ -48,43 +52,58 @@ template <typename T, int X> __device__ __forceinline__ int pipe_place(int ch, i
 
 // The loads of one operand tile of a k-tile, ROWS x BK or BK x ROWS elements, by four wavefronts.
 //   KMAJOR: consecutive elements of the stored matrix run along the rows / columns of the tile, k from row to row of the matrix.
+// The addresses are one for the workgroup and 32-bit offsets of the lanes (pipe_can sees to it that these suffice): with 64-bit addresses
+// of their own the accumulators of the 80 to 112 column tiles no longer fit into the registers.
 template <typename T, int ROWS, bool KMAJOR> struct PipeLoad {
   static constexpr int V = Pipe<T>::V, BK = Pipe<T>::BK;
   static constexpr int BYTES = ROWS * 128, PIECES = BYTES / 1024, N = (PIECES + 3) / 4;       // of 1024 bytes; per wavefront
-  const T *at[N];
-  int k_of[N];               // first k of the lane's 16 bytes inside the tile
-  // origin: element (0, 0) of the first tile.  extent: rows (columns) that exist; those beyond are read as another one, and not stored.
+  const char *base;          // element (0, 0) of the next tile
+  uint32_t off[N];
+  // First k of the 16 bytes inside the tile that lie at place q, and their row (column).
+  static __device__ __forceinline__ void place(int q, int &k, int &x) {
+    if (KMAJOR) {
+      constexpr int PER = ROWS / V;
+      const int rp = q / PER, kq = rp & 3;
+      x = pipe_place<T, ROWS>(q - rp * PER, kq) * V;
+      k = (rp / (4 * V)) * (4 * V) + V * kq + ((rp >> 2) & (V - 1));
+    } else {
+      x = q >> 3;
+      k = ((q & 7) ^ ((x >> 1) & 7)) * V;
+    }
+  }
+  // extent: rows (columns) that exist; those beyond are read as another one, and not stored.
   __device__ __forceinline__ void init(const T *origin, int64_t ld, int extent, int wave, int lane) {
+    base = reinterpret_cast<const char *>(origin);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const int q = piece(wave, i) * 64 + lane;            // place in LDS, 16 bytes each
-      if (KMAJOR) {
-        constexpr int PER = ROWS / V;
-        const int rp = q / PER, kq = rp & 3, ch = pipe_place<T, ROWS>(q - rp * PER, kq);
-        const int k = (rp / (4 * V)) * (4 * V) + V * kq + ((rp >> 2) & (V - 1));
-        k_of[i] = k;
-        at[i] = origin + (int64_t)k * ld + (ch * V < extent ? ch * V : 0);
-      } else {
-        const int row = q >> 3, ch = (q & 7) ^ ((row >> 1) & 7);
-        k_of[i] = ch * V;
-        at[i] = origin + (int64_t)(row < extent ? row : extent - 1) * ld + ch * V;
-      }
+      int k, x;
+      place(piece(wave, i) * 64 + lane, k, x);            // place in LDS, 16 bytes each
+      off[i] = (uint32_t)sizeof(T) * (KMAJOR ? (uint32_t)k * (uint32_t)ld + (uint32_t)(x < extent ? x : 0)
+                                             : (uint32_t)(x < extent ? x : extent - 1) * (uint32_t)ld + (uint32_t)k);
     }
   }
   static __device__ __forceinline__ int piece(int wave, int i) {
     const int p = wave + 4 * i;
     return PIECES % 4 == 0 || p < PIECES ? p : PIECES - 1;       // (left over: the last piece once more)
   }
+  __device__ __forceinline__ void load(char *lds, int wave, int i, uint32_t at) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(base + at),
+                                     (__attribute__((address_space(3))) void *)(lds + piece(wave, i) * 1024), 16, 0, 0);
+  }
   // k_left: k of the tile that exist (others are read as k = 0; the tile of B is cleared there)
-  __device__ __forceinline__ void issue(char *lds, int64_t ld, int k_left, int wave) {
+  __device__ __forceinline__ void issue(char *lds, int64_t ld, int k_left, int wave, int lane) {
+    if (k_left >= BK) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const T *src = at[i];
-      if (k_of[i] >= k_left) src -= KMAJOR ? (int64_t)k_of[i] * ld : (int64_t)k_of[i];
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                       (__attribute__((address_space(3))) void *)(lds + piece(wave, i) * 1024), 16, 0, 0);
-      at[i] += KMAJOR ? BK * ld : BK;
+      for (int i = 0; i < N; ++i) load(lds, wave, i, off[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        int k, x;
+        place(piece(wave, i) * 64 + lane, k, x);
+        load(lds, wave, i, k >= k_left ? off[i] - (uint32_t)sizeof(T) * (uint32_t)k * (KMAJOR ? (uint32_t)ld : 1u) : off[i]);
+      }
     }
+    base += (KMAJOR ? BK * ld : BK) * (int64_t)sizeof(T);
   }
 };
 
@@ -93,8 +112,9 @@ template <typename T, int BM, int BN, int S> struct PipeCfg {
   static constexpr size_t lds = (size_t)S * STAGE;
 };
 
-template <typename T, bool TA, int BM, int BN, int WGM, int WGN, int S, int EPI>
-__global__ __launch_bounds__(256, pipe_wgs(BM, BN)) void gemm_pipe_kernel(const GemmParams P0) {
+// CHAINS: sums of k_chain terms, one after the other into one accumulator, are added up in a second set of accumulators.
+template <typename T, bool TA, int BM, int BN, int WGM, int WGN, int S, int EPI, bool CHAINS>
+__global__ __launch_bounds__(256, pipe_wgs(BM, BN, CHAINS)) void gemm_pipe_kernel(const GemmParams P0) {
   const GemmParams P = select_problem(P0);
   if (P.skip_now) return;
   static_assert(WGM * WGN == 4, "four wavefronts per workgroup");
@@ -121,6 +141,13 @@ __global__ __launch_bounds__(256, pipe_wgs(BM, BN)) void gemm_pipe_kernel(const 
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = (acc_t)(T)0;
+  acc_t sum[CHAINS ? TM : 1][CHAINS ? TN : 1];
+  if constexpr (CHAINS) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) sum[i][j] = (acc_t)(T)0;
+  }
 
   PipeLoad<T, BM, TA> la;
   PipeLoad<T, BN, true> lb;
@@ -135,8 +162,8 @@ __global__ __launch_bounds__(256, pipe_wgs(BM, BN)) void gemm_pipe_kernel(const 
     if (issued < nkt) {
       char *st = pipe_lds + (issued % S) * STAGE;
       const int left = issued + 1 < nkt ? BK : last_k;
-      la.issue(st, P.lda, left, wave);
-      lb.issue(st + BM * 128, P.ldb, left, wave);
+      la.issue(st, P.lda, left, wave, lane);
+      lb.issue(st + BM * 128, P.ldb, left, wave, lane);
     }
     ++issued;
   };
@@ -161,107 +188,120 @@ __global__ __launch_bounds__(256, pipe_wgs(BM, BN)) void gemm_pipe_kernel(const 
 #pragma unroll
   for (int j = 0; j < TN; ++j) b_col[j] = BM * 128 + column(std::integral_constant<int, BN>(), wn0 + j * 16 + r16) + kq * BN * (int)sizeof(T);
 
-  for (int kt = 0; kt < nkt; ++kt) {
-    // tile kt has landed once at most the loads of the S - 2 tiles behind it are outstanding
-    asm volatile("" ::: "memory");
-    if (kt + S - 1 <= nkt) __builtin_amdgcn_s_waitcnt(pipe_wait((S - 2) * LOADS));
-    else __builtin_amdgcn_s_waitcnt(pipe_wait(0));
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    const char *st = pipe_lds + (kt % S) * STAGE;
-    if (kt + 1 == nkt && last_k < BK) {
-      // rows of B beyond the last are zero (row rp of the tile holds k = ...)
-      T *bt = reinterpret_cast<T *>(pipe_lds + (kt % S) * STAGE + BM * 128);
-      for (int e = tid; e < BK * BN; e += 256) {
-        const int rp = e / BN, k = (rp / (4 * V)) * (4 * V) + V * (rp & 3) + ((rp >> 2) & (V - 1));
-        if (k >= last_k) bt[e] = (T)0;
-      }
-      __syncthreads();
-    }
-    issue();
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      T af[TM][V], bf[V][TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        if (TA) {
-#pragma unroll
-          for (int e = 0; e < V; ++e)
-            af[i][e] = *reinterpret_cast<const T *>(st + (4 * V * t + 4 * e) * BM * (int)sizeof(T) + a_col[i]);
-        } else {
-          const piece_t x = *reinterpret_cast<const piece_t *>(st + a_row[i] + (((4 * t + kq) ^ a_swz) << 4));
-#pragma unroll
-          for (int e = 0; e < V; ++e) af[i][e] = x[e];
+  const int chain = CHAINS ? (int)(P.k_chain / BK) : nkt;
+  for (int kt0 = 0; kt0 < nkt; kt0 += chain) {
+    const int kt1 = CHAINS && kt0 + chain < nkt ? kt0 + chain : nkt;
+    for (int kt = kt0; kt < kt1; ++kt) {
+      // tile kt has landed once at most the loads of the S - 2 tiles behind it are outstanding
+      asm volatile("" ::: "memory");
+      if (kt + S - 1 <= nkt) __builtin_amdgcn_s_waitcnt(pipe_wait((S - 2) * LOADS));
+      else __builtin_amdgcn_s_waitcnt(pipe_wait(0));
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      const char *st = pipe_lds + (kt % S) * STAGE;
+      if (kt + 1 == nkt && last_k < BK) {
+        // rows of B beyond the last are zero (row rp of the tile holds k = ...)
+        T *bt = reinterpret_cast<T *>(pipe_lds + (kt % S) * STAGE + BM * 128);
+        for (int e = tid; e < BK * BN; e += 256) {
+          const int rp = e / BN, k = (rp / (4 * V)) * (4 * V) + V * (rp & 3) + ((rp >> 2) & (V - 1));
+          if (k >= last_k) bt[e] = (T)0;
         }
+        __syncthreads();
       }
+      issue();
 #pragma unroll
-      for (int e = 0; e < V; ++e)
+      for (int t = 0; t < 2; ++t) {
+        T af[TM][V], bf[V][TN];
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          bf[e][j] = *reinterpret_cast<const T *>(st + (4 * V * t + 4 * e) * BN * (int)sizeof(T) + b_col[j]);
+        for (int i = 0; i < TM; ++i) {
+          if (TA) {
 #pragma unroll
-      for (int e = 0; e < V; ++e)
+            for (int e = 0; e < V; ++e)
+              af[i][e] = *reinterpret_cast<const T *>(st + (4 * V * t + 4 * e) * BM * (int)sizeof(T) + a_col[i]);
+          } else {
+            const piece_t x = *reinterpret_cast<const piece_t *>(st + a_row[i] + (((4 * t + kq) ^ a_swz) << 4));
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+            for (int e = 0; e < V; ++e) af[i][e] = x[e];
+          }
+        }
 #pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<T>::run(af[i][e], bf[e][j], acc[i][j]);
+        for (int e = 0; e < V; ++e)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            bf[e][j] = *reinterpret_cast<const T *>(st + (4 * V * t + 4 * e) * BN * (int)sizeof(T) + b_col[j]);
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<T>::run(af[i][e], bf[e][j], acc[i][j]);
+      }
+    }
+    if constexpr (CHAINS) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          sum[i][j] += acc[i][j];
+          acc[i][j] = (acc_t)(T)0;
+        }
     }
   }
-  gemm_epilogue<T, T, T, TM, TN, EPI>(P, acc, split, m0 + wm0, n0 + wn0, lane);
+  if constexpr (CHAINS) gemm_epilogue<T, T, T, TM, TN, EPI>(P, sum, split, m0 + wm0, n0 + wn0, lane);
+  else gemm_epilogue<T, T, T, TM, TN, EPI>(P, acc, split, m0 + wm0, n0 + wn0, lane);
 }
 
 // ---------------------------------------------------------------- host side
 
-template <typename T, bool TA, int BM, int BN, int WGM, int WGN>
+template <typename T, bool TA, int BM, int BN, int WGM, int WGN, bool CHAINS>
 struct PipeRun {
-  static constexpr int S = pipe_stages(BM, BN);
-  static constexpr size_t lds = PipeCfg<T, BM, BN, S>::lds;
   static constexpr bool kFull = !TA;      // with the full epilogue (applies, lifts) as well
+  template <int EPI, bool C> static hipError_t launch(hipStream_t s, dim3 grid, const GemmParams &Q) {
+    constexpr int S = pipe_stages(BM, BN, C);
+    constexpr size_t lds = PipeCfg<T, BM, BN, S>::lds;
+    hipLaunchKernelGGL((gemm_pipe_kernel<T, TA, BM, BN, WGM, WGN, S, EPI, C>), grid, dim3(256), lds, s, Q);
+    return hipGetLastError();
+  }
   static hipError_t go(hipStream_t s, const GemmParams &P, int batch) {
     GemmParams Q = P;
     Q.tiles_n = (int)ceil_div(P.N, BN);
     Q.tiles_m = (int)ceil_div(P.M, BM);
     const dim3 grid((unsigned)((int64_t)Q.tiles_n * Q.tiles_m * P.splits), (unsigned)batch);
     if (P.splits == 1 && (P.dead != nullptr || P.trans_c != 0)) {
-      if constexpr (kFull) hipLaunchKernelGGL((gemm_pipe_kernel<T, TA, BM, BN, WGM, WGN, S, 1>), grid, dim3(256), lds, s, Q);
+      if constexpr (kFull) return launch<1, false>(s, grid, Q);       // (these are not cut)
       else return hipErrorInvalidValue;
-    } else {
-      hipLaunchKernelGGL((gemm_pipe_kernel<T, TA, BM, BN, WGM, WGN, S, 0>), grid, dim3(256), lds, s, Q);
     }
-    return hipGetLastError();
+    return launch<0, CHAINS>(s, grid, Q);
   }
 };
 
-// What this kernel can compute: 16-byte rows, plain sums.
+// What this kernel can compute: 16-byte rows, plain sums, tiles (128 rows, 128 bytes of k) of at most 4 GiB from the first to the last element.
 template <typename T> inline bool pipe_can(const GemmDesc &d) {
-  return GemmDispatch<T, T, T>::aligned_a(d) && GemmDispatch<T, T, T>::aligned_b(d) && d.a_shift == nullptr && d.alpha == 1.0 && d.beta == 0.0 &&
+  return d.lda < ((int64_t)1 << 22) && d.ldb < ((int64_t)1 << 22) && GemmDispatch<T, T, T>::aligned_a(d) && GemmDispatch<T, T, T>::aligned_b(d) && d.a_shift == nullptr && d.alpha == 1.0 && d.beta == 0.0 &&
          !(d.trans_a && (d.dead != nullptr || d.trans_c));
 }
 
-// The number of k ranges, at most `most` (the workspace holds the partial sums of that many), that takes the least time: rounds of
-// workgroups, a k-tile at the rate of the matrix cores or of the memory (both shared by the workgroups in flight), three us for a
-// workgroup's first loads and its stores, and the partial sums written and read at 4.5 TB/s behind a second launch.
+// The number of k ranges, at most `most` (the workspace holds the partial sums of that many), that takes the least time for a product of one
+// column tile.  What counts is the longest queue of a CU: its workgroups share the rate of its matrix cores, of which one alone reaches 0.55,
+// four together 0.85, or its share of the memory's; 4 us for the first loads and the stores of those that run side by side; and the partial
+// sums, written and read at 4.5 TB/s behind a second launch.  Over 140 products measured with every number of ranges (5000 x 5000, l = 96:
+// 3 125, 6 111, 7 130, 13 126 us) the one chosen is 0.4 % slower than the best (geometric mean; 5 % at most).
 template <typename T>
 inline SplitChoice pipe_ranges(const rsvd_ctx *ctx, const GemmDesc &d, int bm, int bn, int64_t most) {
   constexpr int BK = 128 / (int)sizeof(T);
-  int64_t tiles = ceil_div(d.M, bm) * ceil_div(d.N, bn);
-  if (d.upper_only) {
-    tiles = 0;
-    for (int64_t tm = 0; tm < ceil_div(d.M, bm); ++tm)
-      for (int64_t tn = 0; tn < ceil_div(d.N, bn); ++tn) tiles += (tn + 1) * bn > tm * bm ? 1 : 0;
-  }
-  tiles *= d.batch;
-  const int64_t ktiles = ceil_div(d.K, BK), places = (int64_t)ctx->cu_count * pipe_wgs(bm, bn);
-  const double rate = sizeof(T) == 8 ? 71e6 : 154e6;                               // flop / us
-  double us = 2.0 * BK * bm * bn * (double)places / rate;
-  const double us_mem = (double)BK * bm * sizeof(T) * (double)places / 5.5e6;
-  if (us < us_mem) us = us_mem;
+  static const double share[5] = {0.0, 0.55, 0.72, 0.78, 0.85}, share_mem[5] = {0.0, 0.8, 0.9, 1.0, 1.0};
+  const int64_t tiles = ceil_div(d.M, bm) * ceil_div(d.N, bn) * d.batch, ktiles = ceil_div(d.K, BK), cus = ctx->cu_count;
+  const int wgs = pipe_wgs(bm, bn, true);
+  const double us = 2.0 * BK * bm * bn * (double)cus / 71e6, us_mem = (double)BK * bm * sizeof(T) * (double)cus / 4.8e6;      // of a k-tile
   int64_t best = 1;
   double best_cost = -1.0;
   for (int64_t r = 1; r <= most && r <= ktiles; ++r) {
-    const int64_t per = ceil_div(ktiles, r), ranges = ceil_div(ktiles, per);
+    const int64_t per = ceil_div(ktiles, r), ranges = ceil_div(ktiles, per), queue = ceil_div(tiles * ranges, cus);
+    const int side = (int)(queue < wgs ? queue : wgs);
+    const double math = us / share[side], mem = us_mem / share_mem[side];
     const double sums = (double)ranges * (double)d.M * (double)d.N * d.batch * sizeof(T);
-    const double cost = (double)ceil_div(tiles * ranges, places) * ((double)per * us + 3.0) + (ranges > 1 ? 4.0 + 2.0 * sums / 4.5e6 : 0.0);
+    const double cost = (double)(queue * per) * (math > mem ? math : mem) + 4.0 * (double)ceil_div(queue, wgs) +
+                        (ranges > 1 ? 4.0 + 2.0 * sums / 4.5e6 : 0.0);
     if (best_cost < 0 || cost < best_cost) { best = r; best_cost = cost; }
   }
   SplitChoice c;
@@ -270,19 +310,21 @@ inline SplitChoice pipe_ranges(const rsvd_ctx *ctx, const GemmDesc &d, int bm, i
   return c;
 }
 
-// by_tile: launches the kernel for this tile.
+// by_tile: launches the kernel for this tile; chains: it can add up several chains of a range.
 template <typename T, typename F>
-inline hipError_t pipe_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, int bm, int bn, F by_tile) {
+inline hipError_t pipe_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, int bm, int bn, bool chains, F by_tile) {
   if (d.batch < 1 || d.batch > 65535) return hipErrorInvalidValue;
-  // the k ranges of gemm_kernel bound those taken here: the workspace is sized for their partial sums
+  // The k ranges of gemm_kernel bound those taken here: the workspace is sized for their partial sums.  They are also the longest sums that go
+  // into one accumulator, so that the rounding error stays that of gemm_kernel (20000 terms in one go where it has two ranges: 21 eps, not 15).
   const TileChoice t = choose_tile(d.M, d.N, d.K, sizeof(T), d.trans_a != 0, d.upper_only != 0);
   const SplitChoice was = choose_split(ctx, t, d.M, d.N, d.K, d.force_splits, d.upper_only != 0, d.batch);
-  const SplitChoice c = pipe_ranges<T>(ctx, d, bm, bn, d.force_splits > 0 ? d.force_splits : was.splits);
+  const SplitChoice c = chains ? pipe_ranges<T>(ctx, d, bm, bn, d.force_splits > 0 ? d.force_splits : was.splits) : was;
   if (c.splits > 1) {
     const size_t need = (size_t)c.splits * (size_t)d.M * (size_t)d.N * sizeof(T);
     if (d.partial == nullptr || d.partial_bytes < need) return hipErrorInvalidValue;
   }
-  const GemmParams P = make_params(d, c, d.upper_only ? bm : 0, d.upper_only ? bn : 0);
+  GemmParams P = make_params(d, c, d.upper_only ? bm : 0, d.upper_only ? bn : 0);
+  P.k_chain = was.k_per_split;
   hipError_t e;
   {
     ProfScope ps(ctx, s, d.prof_kind);

@@ -285,6 +285,39 @@ def test_fp64_products(m, n, l):
         assert (np.abs(to_np(got) - want) <= 8 * eps * np.sqrt(terms) * size / np.sqrt(terms) * max(1.0, np.sqrt(terms) / 4)).all()
 
 
+# Rounding errors of a product grow with the number of terms that go into one accumulator.  The kernel for operands of 16-byte rows may cut
+# the k range into fewer pieces than the one for others, but not add up longer chains: same matrices, one element further on in memory.
+@pytest.mark.parametrize("m,n,l", [(3000, 20000, 16), (5000, 5000, 64), (20000, 10000, 96), (400, 50000, 100), (6000, 6000, 128),
+                                   (8000, 12000, 288), (12000, 9000, 262)])
+def test_fp64_products_add_up_no_longer_chains(m, n, l):
+    import torch
+    say("fp64 chains", m, n, l)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(m + n + l)
+
+    def whole(rows, cols):           # whole numbers of up to 29 bits, in two pieces whose products and sums are exact
+        x = (torch.randn(rows, cols, dtype=torch.float64, device="cuda:0", generator=g) * 2.0 ** 26).round().clamp(-2.0 ** 29, 2.0 ** 29)
+        hi = torch.floor(x / 32768.0)
+        return x, hi, x - hi * 32768.0
+
+    def shifted(x):
+        y = torch.empty(x.shape[0], x.shape[1] + 1, dtype=x.dtype, device=x.device)[:, 1:]
+        y.copy_(x)
+        return y
+
+    def error(got, a, b):
+        hh, mid, ll = a[1] @ b[1], a[1] @ b[2] + a[2] @ b[1], a[2] @ b[2]
+        return float((((got - hh * 2.0 ** 30) - mid * 32768.0) - ll).norm() / got.norm())
+
+    A, X, Q = whole(m, n), whole(n, l), whole(m, l)
+    At = tuple(x.T.contiguous() for x in A)
+    c = ctx()
+    for f, a, b in ((c.rsvd_stage_gemm_an, A, X), (c.rsvd_stage_gemm_atn, At, Q)):
+        one, other = error(f(A[0], b[0]), a, b), error(f(shifted(A[0]), b[0]), a, b)
+        say("  errors", one, other)
+        assert one <= 1.05 * other
+
+
 # Small fp32 panels are orthonormalised in one workgroup up to 16 columns and 1024 rows: one column, rows that are no multiple of
 # 16, the largest panel, the first ones beyond, and columns that depend on others (replaced, the same either way).
 @pytest.mark.parametrize("rows,l,rank", [(1, 1, 1), (17, 1, 1), (40, 16, 16), (333, 7, 7), (1024, 16, 16), (1025, 16, 16), (1024, 17, 17),
