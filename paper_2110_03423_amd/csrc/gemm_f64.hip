@@ -8,7 +8,8 @@ size_t gemm_partial_bytes_f64(const rsvd_ctx *ctx, int64_t M, int64_t N, int64_t
 
 // (chains: tiles of products with up to 128 columns)
 #define RSVD_PIPE_TILES(X) X(64, 16, 4, 1, true) X(64, 32, 4, 1, true) X(64, 48, 4, 1, true) X(64, 64, 4, 1, true) X(64, 80, 4, 1, true) \
-  X(64, 96, 4, 1, true) X(64, 112, 4, 1, true) X(64, 128, 4, 1, true) X(128, 64, 2, 2, false) X(128, 96, 2, 2, false) X(128, 128, 2, 2, false)
+  X(64, 96, 4, 1, true) X(64, 112, 4, 1, true) X(64, 128, 4, 1, true) X(64, 64, 4, 1, false) X(64, 80, 4, 1, false) X(64, 96, 4, 1, false) \
+  X(128, 64, 2, 2, false) X(128, 96, 2, 2, false)
 
 template <bool TA>
 static hipError_t pipe_by_tile(hipStream_t s, const GemmParams &P, int bm, int bn, bool chains, int batch) {
@@ -19,21 +20,12 @@ static hipError_t pipe_by_tile(hipStream_t s, const GemmParams &P, int bm, int b
   return hipErrorInvalidValue;
 }
 
-// Tile and kernel by shape.  Up to 128 columns one tile of 64 rows; beyond, 128 rows and the column tile with the least padding (20000 x
-// 20000, l = 288, 128 x 96 against 64 x 96: A X 3.84 against 4.07 ms, A^T X 3.81 against 4.11).  Below 10^7 multiply-adds (the blocks of a
-// Cholesky factorisation) either kernel waits for its first loads.
+// Below 10^7 multiply-adds (the blocks of a Cholesky factorisation) either kernel waits for its first loads.
 hipError_t gemm_launch_f64(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d) {
   if (d.M <= 0 || d.N <= 0) return hipSuccess;
   const double madds = (double)d.M * (double)d.N * (double)d.K * (double)d.batch;
   if (madds < 1e7 || !pipe_can<double>(d)) return GemmDispatch<double, double, double>::launch(ctx, s, d);
-  int bm = 64, bn = (int)ceil_div(d.N, 16) * 16;
-  if (d.N > 128) {
-    const int64_t pad64 = ceil_div(d.N, 64) * 64, pad96 = ceil_div(d.N, 96) * 96, pad128 = ceil_div(d.N, 128) * 128;
-    bm = 128;
-    bn = pad96 <= pad128 && pad96 <= pad64 ? 96 : pad64 < pad128 ? 64 : 128;
-  }
-  const bool chains = d.N <= 128;
-  return pipe_launch<double>(ctx, s, d, bm, bn, chains, [&](const GemmParams &P) {
+  return pipe_launch<double>(ctx, s, d, [&](const GemmParams &P, int bm, int bn, bool chains) {
     return d.trans_a ? pipe_by_tile<true>(s, P, bm, bn, chains, d.batch) : pipe_by_tile<false>(s, P, bm, bn, chains, d.batch);
   });
 }

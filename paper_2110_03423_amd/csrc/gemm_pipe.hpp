@@ -281,6 +281,15 @@ template <typename T> inline bool pipe_can(const GemmDesc &d) {
          !(d.trans_a && (d.dead != nullptr || d.trans_c));
 }
 
+// Tiles of the result that are computed (of a symmetric one those that reach the diagonal or lie above it).
+inline int64_t pipe_tiles(const GemmDesc &d, int bm, int bn) {
+  const int64_t tm = ceil_div(d.M, bm), tn = ceil_div(d.N, bn);
+  if (!d.upper_only) return tm * tn * d.batch;
+  int64_t tiles = 0;
+  for (int64_t i = 0; i < tm; ++i) tiles += tn - i * bm / bn;
+  return tiles * d.batch;
+}
+
 // The number of k ranges, at most `most` (the workspace holds the partial sums of that many), that takes the least time for a product of one
 // column tile.  What counts is the longest queue of a CU: its workgroups share the rate of its matrix cores, of which one alone reaches 0.55,
 // four together 0.85, or its share of the memory's; 4 us for the first loads and the stores of those that run side by side; and the partial
@@ -290,7 +299,7 @@ template <typename T>
 inline SplitChoice pipe_ranges(const rsvd_ctx *ctx, const GemmDesc &d, int bm, int bn, int64_t most) {
   constexpr int BK = 128 / (int)sizeof(T);
   static const double share[5] = {0.0, 0.55, 0.72, 0.78, 0.85}, share_mem[5] = {0.0, 0.8, 0.9, 1.0, 1.0};
-  const int64_t tiles = ceil_div(d.M, bm) * ceil_div(d.N, bn) * d.batch, ktiles = ceil_div(d.K, BK), cus = ctx->cu_count;
+  const int64_t tiles = pipe_tiles(d, bm, bn), ktiles = ceil_div(d.K, BK), cus = ctx->cu_count;
   const int wgs = pipe_wgs(bm, bn, true);
   const double us = 2.0 * BK * bm * bn * (double)cus / 71e6, us_mem = (double)BK * bm * sizeof(T) * (double)cus / 4.8e6;      // of a k-tile
   int64_t best = 1;
@@ -312,13 +321,29 @@ inline SplitChoice pipe_ranges(const rsvd_ctx *ctx, const GemmDesc &d, int bm, i
 
 // by_tile: launches the kernel for this tile; chains: it can add up several chains of a range.
 template <typename T, typename F>
-inline hipError_t pipe_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, int bm, int bn, bool chains, F by_tile) {
+inline hipError_t pipe_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, F by_tile) {
   if (d.batch < 1 || d.batch > 65535) return hipErrorInvalidValue;
   // The k ranges of gemm_kernel bound those taken here: the workspace is sized for their partial sums.  They are also the longest sums that go
   // into one accumulator, so that the rounding error stays that of gemm_kernel (20000 terms in one go where it has two ranges: 21 eps, not 15).
   const TileChoice t = choose_tile(d.M, d.N, d.K, sizeof(T), d.trans_a != 0, d.upper_only != 0);
   const SplitChoice was = choose_split(ctx, t, d.M, d.N, d.K, d.force_splits, d.upper_only != 0, d.batch);
-  const SplitChoice c = chains ? pipe_ranges<T>(ctx, d, bm, bn, d.force_splits > 0 ? d.force_splits : was.splits) : was;
+  // One column tile up to 128 columns, beyond the tile with the shortest longest queue of a CU, a tile's time being its area by what
+  // share of the matrix cores' rate it reached.  Two fixed rules were slower: 128 rows and the column tile with the least padding
+  // needs 1530 us for A^T X of 12000 x 9000, l = 200 (128 x 128 tiles; gemm_kernel 1130, 64 x 64 now 990), 64 x 96 everywhere 4000 us for A X
+  // of 20000 x 20000, l = 288 (128 x 96: 3640).  70 shapes in both directions: within 0.2 % of the best tile (3.4 % at most).
+  const bool chains = d.N <= 128;
+  int bm = 64, bn = (int)ceil_div(d.N, 16) * 16;
+  SplitChoice c = was;
+  if (chains) {
+    c = pipe_ranges<T>(ctx, d, bm, bn, d.force_splits > 0 ? d.force_splits : was.splits);
+  } else {
+    static const struct { int bm, bn; double share; } tiles[5] = {{128, 96, 0.94}, {128, 64, 0.95}, {64, 96, 0.93}, {64, 80, 0.91}, {64, 64, 0.89}};
+    double best = -1.0;
+    for (const auto &t : tiles) {
+      const double cost = (double)(ceil_div(pipe_tiles(d, t.bm, t.bn) * was.splits, ctx->cu_count) * t.bm * t.bn) / t.share;
+      if (best < 0 || cost < best) { best = cost; bm = t.bm; bn = t.bn; }
+    }
+  }
   if (c.splits > 1) {
     const size_t need = (size_t)c.splits * (size_t)d.M * (size_t)d.N * sizeof(T);
     if (d.partial == nullptr || d.partial_bytes < need) return hipErrorInvalidValue;
@@ -328,7 +353,7 @@ inline hipError_t pipe_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, i
   hipError_t e;
   {
     ProfScope ps(ctx, s, d.prof_kind);
-    e = by_tile(P);
+    e = by_tile(P, bm, bn, chains);
   }
   if (e != hipSuccess) return e;
   return finish_splits<T, T, T>(ctx, s, d, P);

@@ -269,10 +269,12 @@ def test_triangular_factor_of_all_rounds(dt, l):
 
 
 # fp64 products of 16-byte rows go through a ring of k-tiles in LDS: every column tile, one row and one k more and less than tiles of 64, 128
-# and 16, one k-tile in all, several k ranges with an uneven last one, outputs of two and three column tiles.
+# and 16, one k-tile in all, several k ranges with an uneven last one, outputs of two and three column tiles; each of the five tiles for more
+# than 128 columns in either direction.
 @pytest.mark.parametrize("m,n,l", [(64, 16, 16), (66, 18, 10), (62, 4098, 30), (4098, 62, 32), (1026, 1000, 48), (1000, 1030, 50), (130, 3002, 66),
                                    (2050, 514, 96), (514, 2050, 98), (700, 900, 112), (902, 700, 128), (1298, 640, 130), (640, 1310, 192),
-                                   (1154, 1026, 290), (20002, 302, 20)])
+                                   (1154, 1026, 290), (20002, 302, 20), (2800, 2630, 162), (4778, 782, 382), (8288, 478, 286), (2100, 3570, 260),
+                                   (2050, 1026, 194), (3644, 2876, 280)])
 def test_fp64_products(m, n, l):
     say("fp64 products", m, n, l)
     rng = np.random.default_rng(m + n + l)
