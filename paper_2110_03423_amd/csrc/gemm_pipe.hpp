@@ -90,7 +90,7 @@ template <typename T, int ROWS, bool KMAJOR> struct PipeLoad {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(base + at),
                                      (__attribute__((address_space(3))) void *)(lds + piece(wave, i) * 1024), 16, 0, 0);
   }
-  // k_left: k of the tile that exist (others are read as k = 0; the tile of B is cleared there)
+  // k_left: k of the tile that exist (others are read as k = 0, and cleared before they are used)
   __device__ __forceinline__ void issue(char *lds, int64_t ld, int k_left, int wave, int lane) {
     if (k_left >= BK) {
 #pragma unroll
@@ -104,6 +104,17 @@ template <typename T, int ROWS, bool KMAJOR> struct PipeLoad {
       }
     }
     base += (KMAJOR ? BK * ld : BK) * (int64_t)sizeof(T);
+  }
+  // The k from k_left on of a tile in LDS become zero.
+  static __device__ __forceinline__ void clear(char *lds, int k_left, int tid) {
+    for (int q = tid; q < BYTES / 16; q += 256) {
+      int k, x;
+      place(q, k, x);
+      T *at = reinterpret_cast<T *>(lds + q * 16);
+#pragma unroll
+      for (int e = 0; e < V; ++e)
+        if ((KMAJOR ? k : k + e) >= k_left) at[e] = (T)0;
+    }
   }
 };
 
@@ -200,12 +211,10 @@ __global__ __launch_bounds__(256, pipe_wgs(BM, BN, CHAINS)) void gemm_pipe_kerne
       asm volatile("" ::: "memory");
       const char *st = pipe_lds + (kt % S) * STAGE;
       if (kt + 1 == nkt && last_k < BK) {
-        // rows of B beyond the last are zero (row rp of the tile holds k = ...)
-        T *bt = reinterpret_cast<T *>(pipe_lds + (kt % S) * STAGE + BM * 128);
-        for (int e = tid; e < BK * BN; e += 256) {
-          const int rp = e / BN, k = (rp / (4 * V)) * (4 * V) + V * (rp & 3) + ((rp >> 2) & (V - 1));
-          if (k >= last_k) bt[e] = (T)0;
-        }
+        // (of both operands: an infinity among what was read would make a NaN of zeros on one side)
+        char *at = pipe_lds + (kt % S) * STAGE;
+        PipeLoad<T, BM, TA>::clear(at, last_k, tid);
+        PipeLoad<T, BN, true>::clear(at + BM * 128, last_k, tid);
         __syncthreads();
       }
       issue();

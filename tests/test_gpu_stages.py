@@ -287,6 +287,28 @@ def test_fp64_products(m, n, l):
         assert (np.abs(to_np(got) - want) <= 8 * eps * np.sqrt(terms) * size / np.sqrt(terms) * max(1.0, np.sqrt(terms) / 4)).all()
 
 
+# The last k-tile of a product whose k range is no multiple of 16 is filled up with what does not count, whatever it is: infinite results
+# stay infinite, in the rows where an operand is and nowhere else.
+@pytest.mark.parametrize("m,n,l", [(1002, 1000, 32), (998, 1004, 130)])
+def test_fp64_products_with_infinities(m, n, l):
+    import torch
+    say("fp64 infinities", m, n, l)
+    rng = np.random.default_rng(l)
+    A, X, Q = rng.uniform(0.5, 1.5, (m, n)), rng.uniform(0.5, 1.5, (n, l)), rng.uniform(0.5, 1.5, (m, l))
+    kx, kq = (n - 1) // 16 * 16, (m - 1) // 16 * 16       # where the last k-tile begins, for A X and for A^T Q
+    c = ctx()
+    for place in ("a", "b"):
+        B, Y, Z = A.copy(), X.copy(), Q.copy()
+        if place == "a":
+            B[5, kx], B[kq, 7] = np.inf, -np.inf
+        else:
+            Y[kx, 3], Z[kq, l - 1] = np.inf, -np.inf
+        for got, want in ((c.rsvd_stage_gemm_an(to_dev(B), to_dev(Y)), B @ Y), (c.rsvd_stage_gemm_atn(to_dev(B), to_dev(Z)), B.T @ Z)):
+            got, fine = to_np(got), np.isfinite(want)
+            assert (got[~fine] == want[~fine]).all()
+            assert np.abs(got[fine] - want[fine]).max() <= 4 * max(m, n) * np.finfo(np.float64).eps * 1.5 * 1.5
+
+
 # Rounding errors of a product grow with the number of terms that go into one accumulator.  The kernel for operands of 16-byte rows may cut
 # the k range into fewer pieces than the one for others, but not add up longer chains: same matrices, one element further on in memory.
 @pytest.mark.parametrize("m,n,l", [(3000, 20000, 16), (5000, 5000, 64), (20000, 10000, 96), (400, 50000, 100), (6000, 6000, 128),
