@@ -14,7 +14,7 @@ size_t gemm_partial_bytes_f64(const rsvd_ctx *ctx, int64_t M, int64_t N, int64_t
 template <bool TA>
 static hipError_t pipe_by_tile(hipStream_t s, const GemmParams &P, int bm, int bn, bool chains, int batch) {
 #define RSVD_PIPE(BM, BN, WGM, WGN, CHAINS) \
-  if (bm == BM && bn == BN && chains == CHAINS) return PipeRun<double, TA, BM, BN, WGM, WGN, CHAINS>::go(s, P, batch);
+  if (bm == BM && bn == BN && chains == CHAINS) return PipeRun<TA, BM, BN, WGM, WGN, CHAINS>::go(s, P, batch);
   RSVD_PIPE_TILES(RSVD_PIPE)
 #undef RSVD_PIPE
   return hipErrorInvalidValue;
@@ -24,8 +24,8 @@ static hipError_t pipe_by_tile(hipStream_t s, const GemmParams &P, int bm, int b
 hipError_t gemm_launch_f64(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d) {
   if (d.M <= 0 || d.N <= 0) return hipSuccess;
   const double madds = (double)d.M * (double)d.N * (double)d.K * (double)d.batch;
-  if (madds < 1e7 || !pipe_can<double>(d)) return GemmDispatch<double, double, double>::launch(ctx, s, d);
-  return pipe_launch<double>(ctx, s, d, [&](const GemmParams &P, int bm, int bn, bool chains) {
+  if (madds < 1e7 || !pipe_can(d)) return GemmDispatch<double, double, double>::launch(ctx, s, d);
+  return pipe_launch(ctx, s, d, [&](const GemmParams &P, int bm, int bn, bool chains) {
     return d.trans_a ? pipe_by_tile<true>(s, P, bm, bn, chains, d.batch) : pipe_by_tile<false>(s, P, bm, bn, chains, d.batch);
   });
 }

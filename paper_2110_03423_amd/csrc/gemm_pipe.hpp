@@ -1,4 +1,4 @@
-// Products C = op(A) B whose operands have 16-byte rows, with k-tiles that go from memory to LDS without touching a register.
+// Products C = op(A) B of fp64 operands that have 16-byte rows, with k-tiles that go from memory to LDS without touching a register.
 //
 // gemm_kernel (gemm_impl.hpp) loads a k-tile into registers, writes it to LDS between two barriers and hides what that costs behind four
 // or five workgroups per CU.  In fp64 with 48 columns and more it kept the matrix pipe busy for half of the time (a matrix instruction
@@ -36,26 +36,21 @@ constexpr int pipe_stages(int bm, int bn, bool chains) {
   return kb * 1024 / ((bm + bn) * 128);
 }
 
-template <typename T> struct Pipe {
-  static constexpr int V = 16 / (int)sizeof(T), BK = 128 / (int)sizeof(T);      // elements of a piece, depth of a k-tile
-};
+constexpr int kPipeV = 2, kPipeBK = 16;      // elements of a piece, depth of a k-tile
 
 // Operand of s_waitcnt: at most n vector memory operations outstanding, no LDS operation.
 constexpr int pipe_wait(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0070; }
 
-// Place of piece `ch` in a row of a [k][column] tile of X columns that the lanes kq read.
-template <typename T, int X> __device__ __forceinline__ int pipe_place(int ch, int kq) {
-  constexpr int bytes = X * (int)sizeof(T) % 256, window = 16 * (int)sizeof(T);      // what sixteen lanes read of a row
-  if (window == 64) return bytes == 0 ? ch ^ (kq << 2) : bytes == 128 ? ch ^ ((kq >> 1) << 2) : ch;
-  return bytes == 0 ? ch ^ ((kq & 1) << 3) : ch;
-}
+// Place of piece `ch` in a row of a [k][column] tile of X columns: sixteen lanes read 128 bytes of it, and rows of a multiple of 256 bytes
+// begin at the same bank.
+template <int X> __device__ __forceinline__ int pipe_place(int ch, int kq) { return X % 32 == 0 ? ch ^ ((kq & 1) << 3) : ch; }
 
 // The loads of one operand tile of a k-tile, ROWS x BK or BK x ROWS elements, by four wavefronts.
 //   KMAJOR: consecutive elements of the stored matrix run along the rows / columns of the tile, k from row to row of the matrix.
 // The addresses are one for the workgroup and 32-bit offsets of the lanes (pipe_can sees to it that these suffice): with 64-bit addresses
 // of their own the accumulators of the 80 to 112 column tiles no longer fit into the registers.
-template <typename T, int ROWS, bool KMAJOR> struct PipeLoad {
-  static constexpr int V = Pipe<T>::V, BK = Pipe<T>::BK;
+template <int ROWS, bool KMAJOR> struct PipeLoad {
+  static constexpr int V = kPipeV, BK = kPipeBK;
   static constexpr int BYTES = ROWS * 128, PIECES = BYTES / 1024, N = (PIECES + 3) / 4;       // of 1024 bytes; per wavefront
   const char *base;          // element (0, 0) of the next tile
   uint32_t off[N];
@@ -64,7 +59,7 @@ template <typename T, int ROWS, bool KMAJOR> struct PipeLoad {
     if (KMAJOR) {
       constexpr int PER = ROWS / V;
       const int rp = q / PER, kq = rp & 3;
-      x = pipe_place<T, ROWS>(q - rp * PER, kq) * V;
+      x = pipe_place<ROWS>(q - rp * PER, kq) * V;
       k = (rp / (4 * V)) * (4 * V) + V * kq + ((rp >> 2) & (V - 1));
     } else {
       x = q >> 3;
@@ -72,13 +67,13 @@ template <typename T, int ROWS, bool KMAJOR> struct PipeLoad {
     }
   }
   // extent: rows (columns) that exist; those beyond are read as another one, and not stored.
-  __device__ __forceinline__ void init(const T *origin, int64_t ld, int extent, int wave, int lane) {
+  __device__ __forceinline__ void init(const double *origin, int64_t ld, int extent, int wave, int lane) {
     base = reinterpret_cast<const char *>(origin);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       int k, x;
       place(piece(wave, i) * 64 + lane, k, x);            // place in LDS, 16 bytes each
-      off[i] = (uint32_t)sizeof(T) * (KMAJOR ? (uint32_t)k * (uint32_t)ld + (uint32_t)(x < extent ? x : 0)
+      off[i] = (uint32_t)sizeof(double) * (KMAJOR ? (uint32_t)k * (uint32_t)ld + (uint32_t)(x < extent ? x : 0)
                                              : (uint32_t)(x < extent ? x : extent - 1) * (uint32_t)ld + (uint32_t)k);
     }
   }
@@ -100,38 +95,38 @@ template <typename T, int ROWS, bool KMAJOR> struct PipeLoad {
       for (int i = 0; i < N; ++i) {
         int k, x;
         place(piece(wave, i) * 64 + lane, k, x);
-        load(lds, wave, i, k >= k_left ? off[i] - (uint32_t)sizeof(T) * (uint32_t)k * (KMAJOR ? (uint32_t)ld : 1u) : off[i]);
+        load(lds, wave, i, k >= k_left ? off[i] - (uint32_t)sizeof(double) * (uint32_t)k * (KMAJOR ? (uint32_t)ld : 1u) : off[i]);
       }
     }
-    base += (KMAJOR ? BK * ld : BK) * (int64_t)sizeof(T);
+    base += (KMAJOR ? BK * ld : BK) * (int64_t)sizeof(double);
   }
   // The k from k_left on of a tile in LDS become zero.
   static __device__ __forceinline__ void clear(char *lds, int k_left, int tid) {
     for (int q = tid; q < BYTES / 16; q += 256) {
       int k, x;
       place(q, k, x);
-      T *at = reinterpret_cast<T *>(lds + q * 16);
+      double *at = reinterpret_cast<double *>(lds + q * 16);
 #pragma unroll
       for (int e = 0; e < V; ++e)
-        if ((KMAJOR ? k : k + e) >= k_left) at[e] = (T)0;
+        if ((KMAJOR ? k : k + e) >= k_left) at[e] = 0.0;
     }
   }
 };
 
-template <typename T, int BM, int BN, int S> struct PipeCfg {
+template <int BM, int BN, int S> struct PipeCfg {
   static constexpr int STAGE = (BM + BN) * 128;
   static constexpr size_t lds = (size_t)S * STAGE;
 };
 
 // CHAINS: sums of k_chain terms, one after the other into one accumulator, are added up in a second set of accumulators.
-template <typename T, bool TA, int BM, int BN, int WGM, int WGN, int S, int EPI, bool CHAINS>
+template <bool TA, int BM, int BN, int WGM, int WGN, int S, int EPI, bool CHAINS>
 __global__ __launch_bounds__(256, pipe_wgs(BM, BN, CHAINS)) void gemm_pipe_kernel(const GemmParams P0) {
   const GemmParams P = select_problem(P0);
   if (P.skip_now) return;
   static_assert(WGM * WGN == 4, "four wavefronts per workgroup");
-  constexpr int V = Pipe<T>::V, BK = Pipe<T>::BK, STAGE = PipeCfg<T, BM, BN, S>::STAGE;
+  constexpr int V = kPipeV, BK = kPipeBK, STAGE = PipeCfg<BM, BN, S>::STAGE;
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
-  typedef T piece_t __attribute__((ext_vector_type(16 / sizeof(T))));
+  typedef double piece_t __attribute__((ext_vector_type(kPipeV)));
   extern __shared__ __attribute__((aligned(16))) char pipe_lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
@@ -146,23 +141,22 @@ __global__ __launch_bounds__(256, pipe_wgs(BM, BN, CHAINS)) void gemm_pipe_kerne
   const int nkt = k_begin < k_end ? (int)((k_end - k_begin + BK - 1) / BK) : 0;
   const int last_k = (int)(k_end - k_begin) - (nkt - 1) * BK;
 
-  typedef typename Mfma<T>::vec acc_t;
-  acc_t acc[TM][TN];
+  f64x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = (acc_t)(T)0;
-  acc_t sum[CHAINS ? TM : 1][CHAINS ? TN : 1];
+    for (int j = 0; j < TN; ++j) acc[i][j] = (f64x4)0.0;
+  f64x4 sum[CHAINS ? TM : 1][CHAINS ? TN : 1];
   if constexpr (CHAINS) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) sum[i][j] = (acc_t)(T)0;
+      for (int j = 0; j < TN; ++j) sum[i][j] = (f64x4)0.0;
   }
 
-  PipeLoad<T, BM, TA> la;
-  PipeLoad<T, BN, true> lb;
-  const T *A = (const T *)P.A, *B = (const T *)P.B;
+  PipeLoad<BM, TA> la;
+  PipeLoad<BN, true> lb;
+  const double *A = (const double *)P.A, *B = (const double *)P.B;
   la.init(TA ? A + k_begin * P.lda + m0 : A + m0 * P.lda + k_begin, P.lda, (int)(P.M - m0 < BM ? P.M - m0 : BM), wave, lane);
   lb.init(B + k_begin * P.ldb + n0, P.ldb, (int)(P.N - n0 < BN ? P.N - n0 : BN), wave, lane);
   constexpr int LOADS = decltype(la)::N + decltype(lb)::N;      // a wavefront's loads per k-tile
@@ -191,13 +185,13 @@ __global__ __launch_bounds__(256, pipe_wgs(BM, BN, CHAINS)) void gemm_pipe_kerne
   const int a_swz = TA ? 0 : ((wm0 + r16) >> 1) & 7;           // (the same in every block of 16 rows)
   auto column = [&](auto x, int col) {                          // byte offset of column `col` in a [k][column] row read by lanes kq
     constexpr int X = decltype(x)::value;
-    return pipe_place<T, X>(col / V, kq) * 16 + (col % V) * (int)sizeof(T);
+    return pipe_place<X>(col / V, kq) * 16 + (col % V) * (int)sizeof(double);
   };
   int a_col[TM], b_col[TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) a_col[i] = TA ? column(std::integral_constant<int, BM>(), wm0 + i * 16 + r16) + kq * BM * (int)sizeof(T) : 0;
+  for (int i = 0; i < TM; ++i) a_col[i] = TA ? column(std::integral_constant<int, BM>(), wm0 + i * 16 + r16) + kq * BM * (int)sizeof(double) : 0;
 #pragma unroll
-  for (int j = 0; j < TN; ++j) b_col[j] = BM * 128 + column(std::integral_constant<int, BN>(), wn0 + j * 16 + r16) + kq * BN * (int)sizeof(T);
+  for (int j = 0; j < TN; ++j) b_col[j] = BM * 128 + column(std::integral_constant<int, BN>(), wn0 + j * 16 + r16) + kq * BN * (int)sizeof(double);
 
   const int chain = CHAINS ? (int)(P.k_chain / BK) : nkt;
   for (int kt0 = 0; kt0 < nkt; kt0 += chain) {
@@ -213,20 +207,20 @@ __global__ __launch_bounds__(256, pipe_wgs(BM, BN, CHAINS)) void gemm_pipe_kerne
       if (kt + 1 == nkt && last_k < BK) {
         // (of both operands: an infinity among what was read would make a NaN of zeros on one side)
         char *at = pipe_lds + (kt % S) * STAGE;
-        PipeLoad<T, BM, TA>::clear(at, last_k, tid);
-        PipeLoad<T, BN, true>::clear(at + BM * 128, last_k, tid);
+        PipeLoad<BM, TA>::clear(at, last_k, tid);
+        PipeLoad<BN, true>::clear(at + BM * 128, last_k, tid);
         __syncthreads();
       }
       issue();
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        T af[TM][V], bf[V][TN];
+        double af[TM][V], bf[V][TN];
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
           if (TA) {
 #pragma unroll
             for (int e = 0; e < V; ++e)
-              af[i][e] = *reinterpret_cast<const T *>(st + (4 * V * t + 4 * e) * BM * (int)sizeof(T) + a_col[i]);
+              af[i][e] = *reinterpret_cast<const double *>(st + (4 * V * t + 4 * e) * BM * (int)sizeof(double) + a_col[i]);
           } else {
             const piece_t x = *reinterpret_cast<const piece_t *>(st + a_row[i] + (((4 * t + kq) ^ a_swz) << 4));
 #pragma unroll
@@ -237,13 +231,13 @@ __global__ __launch_bounds__(256, pipe_wgs(BM, BN, CHAINS)) void gemm_pipe_kerne
         for (int e = 0; e < V; ++e)
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            bf[e][j] = *reinterpret_cast<const T *>(st + (4 * V * t + 4 * e) * BN * (int)sizeof(T) + b_col[j]);
+            bf[e][j] = *reinterpret_cast<const double *>(st + (4 * V * t + 4 * e) * BN * (int)sizeof(double) + b_col[j]);
 #pragma unroll
         for (int e = 0; e < V; ++e)
 #pragma unroll
           for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<T>::run(af[i][e], bf[e][j], acc[i][j]);
+            for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<double>::run(af[i][e], bf[e][j], acc[i][j]);
       }
     }
     if constexpr (CHAINS) {
@@ -252,23 +246,23 @@ __global__ __launch_bounds__(256, pipe_wgs(BM, BN, CHAINS)) void gemm_pipe_kerne
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
           sum[i][j] += acc[i][j];
-          acc[i][j] = (acc_t)(T)0;
+          acc[i][j] = (f64x4)0.0;
         }
     }
   }
-  if constexpr (CHAINS) gemm_epilogue<T, T, T, TM, TN, EPI>(P, sum, split, m0 + wm0, n0 + wn0, lane);
-  else gemm_epilogue<T, T, T, TM, TN, EPI>(P, acc, split, m0 + wm0, n0 + wn0, lane);
+  if constexpr (CHAINS) gemm_epilogue<double, double, double, TM, TN, EPI>(P, sum, split, m0 + wm0, n0 + wn0, lane);
+  else gemm_epilogue<double, double, double, TM, TN, EPI>(P, acc, split, m0 + wm0, n0 + wn0, lane);
 }
 
 // ---------------------------------------------------------------- host side
 
-template <typename T, bool TA, int BM, int BN, int WGM, int WGN, bool CHAINS>
+template <bool TA, int BM, int BN, int WGM, int WGN, bool CHAINS>
 struct PipeRun {
   static constexpr bool kFull = !TA;      // with the full epilogue (applies, lifts) as well
   template <int EPI, bool C> static hipError_t launch(hipStream_t s, dim3 grid, const GemmParams &Q) {
     constexpr int S = pipe_stages(BM, BN, C);
-    constexpr size_t lds = PipeCfg<T, BM, BN, S>::lds;
-    hipLaunchKernelGGL((gemm_pipe_kernel<T, TA, BM, BN, WGM, WGN, S, EPI, C>), grid, dim3(256), lds, s, Q);
+    constexpr size_t lds = PipeCfg<BM, BN, S>::lds;
+    hipLaunchKernelGGL((gemm_pipe_kernel<TA, BM, BN, WGM, WGN, S, EPI, C>), grid, dim3(256), lds, s, Q);
     return hipGetLastError();
   }
   static hipError_t go(hipStream_t s, const GemmParams &P, int batch) {
@@ -285,8 +279,8 @@ struct PipeRun {
 };
 
 // What this kernel can compute: 16-byte rows, plain sums, tiles (128 rows, 128 bytes of k) of at most 4 GiB from the first to the last element.
-template <typename T> inline bool pipe_can(const GemmDesc &d) {
-  return d.lda < ((int64_t)1 << 22) && d.ldb < ((int64_t)1 << 22) && GemmDispatch<T, T, T>::aligned_a(d) && GemmDispatch<T, T, T>::aligned_b(d) && d.a_shift == nullptr && d.alpha == 1.0 && d.beta == 0.0 &&
+inline bool pipe_can(const GemmDesc &d) {
+  return d.lda < ((int64_t)1 << 22) && d.ldb < ((int64_t)1 << 22) && GemmDispatch<double, double, double>::aligned_a(d) && GemmDispatch<double, double, double>::aligned_b(d) && d.a_shift == nullptr && d.alpha == 1.0 && d.beta == 0.0 &&
          !(d.trans_a && (d.dead != nullptr || d.trans_c));
 }
 
@@ -304,20 +298,19 @@ inline int64_t pipe_tiles(const GemmDesc &d, int bm, int bn) {
 // four together 0.85, or its share of the memory's; 4 us for the first loads and the stores of those that run side by side; and the partial
 // sums, written and read at 4.5 TB/s behind a second launch.  Over 140 products measured with every number of ranges (5000 x 5000, l = 96:
 // 3 125, 6 111, 7 130, 13 126 us) the one chosen is 0.4 % slower than the best (geometric mean; 5 % at most).
-template <typename T>
 inline SplitChoice pipe_ranges(const rsvd_ctx *ctx, const GemmDesc &d, int bm, int bn, int64_t most) {
-  constexpr int BK = 128 / (int)sizeof(T);
+  constexpr int BK = kPipeBK;
   static const double share[5] = {0.0, 0.55, 0.72, 0.78, 0.85}, share_mem[5] = {0.0, 0.8, 0.9, 1.0, 1.0};
   const int64_t tiles = pipe_tiles(d, bm, bn), ktiles = ceil_div(d.K, BK), cus = ctx->cu_count;
   const int wgs = pipe_wgs(bm, bn, true);
-  const double us = 2.0 * BK * bm * bn * (double)cus / 71e6, us_mem = (double)BK * bm * sizeof(T) * (double)cus / 4.8e6;      // of a k-tile
+  const double us = 2.0 * BK * bm * bn * (double)cus / 71e6, us_mem = (double)BK * bm * sizeof(double) * (double)cus / 4.8e6;      // of a k-tile
   int64_t best = 1;
   double best_cost = -1.0;
   for (int64_t r = 1; r <= most && r <= ktiles; ++r) {
     const int64_t per = ceil_div(ktiles, r), ranges = ceil_div(ktiles, per), queue = ceil_div(tiles * ranges, cus);
     const int side = (int)(queue < wgs ? queue : wgs);
     const double math = us / share[side], mem = us_mem / share_mem[side];
-    const double sums = (double)ranges * (double)d.M * (double)d.N * d.batch * sizeof(T);
+    const double sums = (double)ranges * (double)d.M * (double)d.N * d.batch * sizeof(double);
     const double cost = (double)(queue * per) * (math > mem ? math : mem) + 4.0 * (double)ceil_div(queue, wgs) +
                         (ranges > 1 ? 4.0 + 2.0 * sums / 4.5e6 : 0.0);
     if (best_cost < 0 || cost < best_cost) { best = r; best_cost = cost; }
@@ -329,12 +322,12 @@ inline SplitChoice pipe_ranges(const rsvd_ctx *ctx, const GemmDesc &d, int bm, i
 }
 
 // by_tile: launches the kernel for this tile; chains: it can add up several chains of a range.
-template <typename T, typename F>
+template <typename F>
 inline hipError_t pipe_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, F by_tile) {
   if (d.batch < 1 || d.batch > 65535) return hipErrorInvalidValue;
   // The k ranges of gemm_kernel bound those taken here: the workspace is sized for their partial sums.  They are also the longest sums that go
   // into one accumulator, so that the rounding error stays that of gemm_kernel (20000 terms in one go where it has two ranges: 21 eps, not 15).
-  const TileChoice t = choose_tile(d.M, d.N, d.K, sizeof(T), d.trans_a != 0, d.upper_only != 0);
+  const TileChoice t = choose_tile(d.M, d.N, d.K, sizeof(double), d.trans_a != 0, d.upper_only != 0);
   const SplitChoice was = choose_split(ctx, t, d.M, d.N, d.K, d.force_splits, d.upper_only != 0, d.batch);
   // One column tile up to 128 columns, beyond the tile with the shortest longest queue of a CU, a tile's time being its area by what
   // share of the matrix cores' rate it reached.  Two fixed rules were slower: 128 rows and the column tile with the least padding
@@ -344,7 +337,7 @@ inline hipError_t pipe_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, F
   int bm = 64, bn = (int)ceil_div(d.N, 16) * 16;
   SplitChoice c = was;
   if (chains) {
-    c = pipe_ranges<T>(ctx, d, bm, bn, d.force_splits > 0 ? d.force_splits : was.splits);
+    c = pipe_ranges(ctx, d, bm, bn, d.force_splits > 0 ? d.force_splits : was.splits);
   } else {
     static const struct { int bm, bn; double share; } tiles[5] = {{128, 96, 0.94}, {128, 64, 0.95}, {64, 96, 0.93}, {64, 80, 0.91}, {64, 64, 0.89}};
     double best = -1.0;
@@ -354,7 +347,7 @@ inline hipError_t pipe_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, F
     }
   }
   if (c.splits > 1) {
-    const size_t need = (size_t)c.splits * (size_t)d.M * (size_t)d.N * sizeof(T);
+    const size_t need = (size_t)c.splits * (size_t)d.M * (size_t)d.N * sizeof(double);
     if (d.partial == nullptr || d.partial_bytes < need) return hipErrorInvalidValue;
   }
   GemmParams P = make_params(d, c, d.upper_only ? bm : 0, d.upper_only ? bn : 0);
@@ -365,7 +358,7 @@ inline hipError_t pipe_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, F
     e = by_tile(P, bm, bn, chains);
   }
   if (e != hipSuccess) return e;
-  return finish_splits<T, T, T>(ctx, s, d, P);
+  return finish_splits<double, double, double>(ctx, s, d, P);
 }
 
 }  // namespace rsvd

@@ -510,7 +510,7 @@ struct JbHeader {
   double partial[kJbFroParts];   // sums of squares, one per workgroup of jb_fro_kernel
 };
 
-// One run of sweeps (jb_flow_kernel, jacobi_lds_kernel).
+// One run of sweeps of jb_flow_kernel.
 struct JbRun {
   unsigned long long sumsq[32];      // per sweep: sum of s^2 over its rotations (c, s), times kJbSumScale
   int counters[32];                  // per sweep: bit pattern of the largest relative inner product rotated away
@@ -1033,7 +1033,6 @@ template <typename T> struct PolishParams {
   T *b[7];                   // l x l: M (column after column), J (likewise), X, Y / next M, Y2 / next J, cosine part / E, sine part / E
   JbSync *sync;
   int l, tiles;
-  int64_t stride;            // bytes between the problems of a batch (blockIdx.y)
 };
 
 constexpr int kPoTile = 32, kPoLd = kPoTile + 1;
@@ -1197,12 +1196,6 @@ __device__ __forceinline__ void jb_wait_tiles(const int *p, int want) {
 
 template <typename T>
 __global__ __launch_bounds__(256) void polish_kernel(PolishParams<T> P) {
-  if (blockIdx.y != 0) {
-    const int64_t off = (int64_t)blockIdx.y * P.stride;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) P.b[i] = reinterpret_cast<T *>(reinterpret_cast<char *>(P.b[i]) + off);
-    P.sync = reinterpret_cast<JbSync *>(reinterpret_cast<char *>(P.sync) + off);
-  }
   JbSync *sync = P.sync;
   if (sync->run[0].stop != 2) return;
   const int l = P.l, tiles = P.tiles, upper = tiles * (tiles + 1) / 2;
@@ -1437,10 +1430,10 @@ __global__ __launch_bounds__(256) void polish_kernel(PolishParams<T> P) {
 }
 
 template <typename T>
-static void polish_launch(const rsvd_ctx *ctx, hipStream_t s, const PolishParams<T> &P, int batch) {
+static void polish_launch(const rsvd_ctx *ctx, hipStream_t s, const PolishParams<T> &P) {
   int wgs = 2 * P.tiles * P.tiles;                   // tiles of the largest phase
   if (wgs > ctx->cu_count) wgs = ctx->cu_count;
-  hipLaunchKernelGGL((polish_kernel<T>), dim3(wgs, batch), dim3(256), 0, s, P);
+  hipLaunchKernelGGL((polish_kernel<T>), dim3(wgs), dim3(256), 0, s, P);
 }
 
 // which: 0 = the sweeps from the start, until they have converged or (`corrections` follow) leave little enough for those; 1 = the
@@ -1975,10 +1968,10 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
       P.b[0] = Mt; P.b[1] = Jt;
       for (int i = 0; i < 5; ++i) P.b[2 + i] = (T *)slots->slot[i + (in_slots ? 2 : 0)];
       Mt2 = P.b[3]; Jt2 = P.b[4];
-      P.sync = sync; P.l = l; P.tiles = (l + kPoTile - 1) / kPoTile; P.stride = 0;
+      P.sync = sync; P.l = l; P.tiles = (l + kPoTile - 1) / kPoTile;
       hipLaunchKernelGGL((jb_flow_kernel<T>), dim3(nblk2), dim3(1024), jg_lds_bytes<T>(l), s, Mt, Jt, Mt2, Jt2, l, nblk,
                          kJbMaxSweeps, chg, sync, 0, 1);
-      polish_launch<T>(ctx, s, P, 1);
+      polish_launch<T>(ctx, s, P);
     }
     hipLaunchKernelGGL((jb_flow_kernel<T>), dim3(nblk2), dim3(1024), jg_lds_bytes<T>(l), s, Mt, Jt, Mt2, Jt2, l, nblk,
                        kJbMaxSweeps, corrections ? ver2 : chg, sync, corrections, 0);
