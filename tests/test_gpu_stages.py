@@ -280,11 +280,25 @@ def test_fp64_products(m, n, l):
     rng = np.random.default_rng(m + n + l)
     A, X, Q = rng.standard_normal((m, n)), rng.standard_normal((n, l)), rng.standard_normal((m, l))
     c, eps = ctx(), np.finfo(np.float64).eps
-    for got, want, a, b, terms in ((c.rsvd_stage_gemm_an(to_dev(A), to_dev(X)), A @ X, A, X, n),
-                                   (c.rsvd_stage_gemm_atn(to_dev(A), to_dev(Q)), A.T @ Q, A.T, Q, m)):
-        # rounding errors of a sum add up like a random walk on terms of the size |a_i| |b_j| / sqrt(terms), on either side; 8: the largest of up to 1e6
+    for got, want, a, b in ((c.rsvd_stage_gemm_an(to_dev(A), to_dev(X)), A @ X, A, X), (c.rsvd_stage_gemm_atn(to_dev(A), to_dev(Q)), A.T @ Q, A.T, Q)):
+        # partial sums of up to |a_i| |b_j| / sqrt(terms), whose roundings add up like a random walk over the terms, on either side: eps |a_i| |b_j|; 8:
+        # the largest of up to 1e6
         size = np.linalg.norm(a, axis=1)[:, None] * np.linalg.norm(b, axis=0)[None, :]
-        assert (np.abs(to_np(got) - want) <= 8 * eps * np.sqrt(terms) * size / np.sqrt(terms) * max(1.0, np.sqrt(terms) / 4)).all()
+        assert (np.abs(to_np(got) - want) <= 8 * eps * size).all()
+
+
+# Of the Gram matrix of an fp64 panel of more than 128 columns only the tiles on or above the diagonal are computed: long panels, whose rows are
+# cut into ranges with an uneven last one.  An error of the second round's Gram matrix is one of Q^T Q.
+@pytest.mark.parametrize("rows,l", [(5003, 130), (3001, 290), (20001, 256), (9000, 144)])
+def test_fp64_gram_of_long_panels(rows, l):
+    say("fp64 gram", rows, l)
+    Y = workloads.gaussian_matrix(rows, l, l, np.float64)
+    Q, R, info = ctx().rsvd_stage_orth(to_dev(Y), want_r=True)
+    Q, R, eps = to_np(Q), to_np(R), np.finfo(np.float64).eps
+    assert info.status == 0 and info.refilled_columns == 0 and info.raised_pivots == 0
+    assert np.abs(Q.T @ Q - np.eye(l)).max() <= 16 * eps * np.sqrt(l)          # (bounds as for the blocked factorisation)
+    assert np.abs(np.tril(R, -1)).max() == 0
+    assert (np.linalg.norm(Q @ R - Y, axis=0) <= (64 * np.sqrt(l) * eps) * np.linalg.norm(Y, axis=0).max()).all()
 
 
 # The last k-tile of a product whose k range is no multiple of 16 is filled up with what does not count, whatever it is: infinite results
