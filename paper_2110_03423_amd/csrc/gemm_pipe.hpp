@@ -4,14 +4,17 @@
 // or five workgroups per CU.  In fp64 with 48 columns and more it kept the matrix pipe busy for half of the time (a matrix instruction
 // takes 64 cycles, but the wavefronts of a workgroup read their operands all at once behind a barrier), and the ~1000 k ranges that such
 // a grid wants write and read partial sums of a third of A.  Here a workgroup has a ring of S k-tiles of 128 bytes of k each in LDS,
-// filled by loads that write there themselves: one barrier per k-tile, no staging registers, k-tiles half as deep.  Times in us,
-// gemm_kernel -> this, A X and A^T X: 5000 x 5000, l = 64 93 -> 70, 90 -> 69; 30000 x 1000, l = 48 87 -> 69, 84 -> 66; 20000 x 10000, l = 96
-// 743 -> 683, 927 -> 682; 8000 x 2000, l = 210 201 -> 150, 197 -> 150; 20000 x 20000, l = 288 4300 -> 3841, 3971 -> 3809 (60 TFLOP/s, pipe busy 77 %
-// at 2.4 GHz; 8 % of the rest is the last wave).  Up to 32 columns, where memory is the bound, about the same (3000 x 20000, l = 16 102 ->
-// 92, 94 -> 98).  What was tried: four more k-tiles in flight with two workgroups per CU (5 to 12 % slower at l = 48 and 64 than four workgroups
-// with one k-tile ahead); the work dealt out evenly in k-tiles, sums of shared tiles added behind (the loop that crosses tiles costs more
-// than the last wave: 3.83 -> 3.97 ms at l = 288, with 64-row tiles 4.4); fp32 operands, narrow (no gain: l = 32 within 3 %, l = 48 5 to
-// 15 % slower than the split products) and summed in fp64 (Gram matrices of 65536 x 576: 8 % slower).
+// filled by loads that write there themselves: one barrier per k-tile, no staging registers, k-tiles half as deep.  Calls of
+// rsvd_stage_gemm_an / _atn in us, gemm_kernel -> this:
+//   5000 x 5000, l = 64      113 -> 86, 107 -> 85          8000 x 2000, l = 210     211 -> 148, 207 -> 146
+//   30000 x 1000, l = 48     103 -> 78, 98 -> 78           12000 x 9000, l = 200    1028 -> 905, 1113 -> 958
+//   20000 x 10000, l = 96    790 -> 699, 941 -> 709        20000 x 20000, l = 288   4296 -> 3643, 3964 -> 3755 (63, 61 TFLOP/s)
+// Up to 16 columns, where memory is the bound, about the same (3000 x 20000, l = 16: 112 -> 101, 104 -> 107; 1624 x 39874, l = 14: 113 -> 123,
+// 111 -> 108).
+// What was tried: four more k-tiles in flight with two workgroups per CU (5 to 12 % slower at l = 48 and 64 than four workgroups with one
+// k-tile ahead); the work dealt out evenly in k-tiles, sums of shared tiles added behind (the loop that crosses tiles costs more than the
+// last wave: 3.83 -> 3.97 ms at l = 288, with 64-row tiles 4.4); fp32 operands, narrow (no gain: l = 32 within 3 %, l = 48 5 to 15 % slower
+// than the split products) and summed in fp64 (Gram matrices of 65536 x 576: 8 % slower).
 //
 // LDS is written in the order of the lanes, 16 bytes each, so a layout is chosen by which piece of memory a lane fetches:
 //   [row][k] tiles (A as stored): 128 bytes a row, the eight pieces of row r in places piece ^ (r / 2 mod 8): sixteen lanes that read
@@ -296,7 +299,7 @@ inline int64_t pipe_tiles(const GemmDesc &d, int bm, int bn) {
 // The number of k ranges, at most `most` (the workspace holds the partial sums of that many), that takes the least time for a product of one
 // column tile.  What counts is the longest queue of a CU: its workgroups share the rate of its matrix cores, of which one alone reaches 0.55,
 // four together 0.85, or its share of the memory's; 4 us for the first loads and the stores of those that run side by side; and the partial
-// sums, written and read at 4.5 TB/s behind a second launch.  Over 140 products measured with every number of ranges (5000 x 5000, l = 96:
+// sums, written and read at 4.5 TB/s behind a second launch.  Over 140 products measured with up to 25 numbers of ranges each (5000 x 5000, l = 96:
 // 3 125, 6 111, 7 130, 13 126 us) the one chosen is 0.4 % slower than the best (geometric mean; 5 % at most).
 inline SplitChoice pipe_ranges(const rsvd_ctx *ctx, const GemmDesc &d, int bm, int bn, int64_t most) {
   constexpr int BK = kPipeBK;
@@ -330,9 +333,10 @@ inline hipError_t pipe_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, F
   const TileChoice t = choose_tile(d.M, d.N, d.K, sizeof(double), d.trans_a != 0, d.upper_only != 0);
   const SplitChoice was = choose_split(ctx, t, d.M, d.N, d.K, d.force_splits, d.upper_only != 0, d.batch);
   // One column tile up to 128 columns, beyond the tile with the shortest longest queue of a CU, a tile's time being its area by what
-  // share of the matrix cores' rate it reached.  Two fixed rules were slower: 128 rows and the column tile with the least padding
-  // needs 1530 us for A^T X of 12000 x 9000, l = 200 (128 x 128 tiles; gemm_kernel 1130, 64 x 64 now 990), 64 x 96 everywhere 4000 us for A X
-  // of 20000 x 20000, l = 288 (128 x 96: 3640).  70 shapes in both directions: within 0.2 % of the best tile (3.4 % at most).
+  // share of the matrix cores' rate it reached (128 rows whose workgroup is alone on its CU: less, two of 64 rows hide each other's loads).
+  // Two fixed rules were slower: 128 rows and the column tile with the least padding (A^T X of 12000 x 9000, l = 200, 128 x 128 tiles 1453 us,
+  // gemm_kernel 1113, now 958), and 64 x 96 everywhere (A X of 20000 x 20000, l = 288, 3886 us, now 3643; of 12000 x 9000, l = 200, 1299, now 905).
+  // 70 shapes in both directions: within 0.2 % of the best tile (3.2 % at most).
   const bool chains = d.N <= 128;
   int bm = 64, bn = (int)ceil_div(d.N, 16) * 16;
   SplitChoice c = was;
@@ -342,7 +346,8 @@ inline hipError_t pipe_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d, F
     static const struct { int bm, bn; double share; } tiles[5] = {{128, 96, 0.94}, {128, 64, 0.95}, {64, 96, 0.93}, {64, 80, 0.91}, {64, 64, 0.89}};
     double best = -1.0;
     for (const auto &t : tiles) {
-      const double cost = (double)(ceil_div(pipe_tiles(d, t.bm, t.bn) * was.splits, ctx->cu_count) * t.bm * t.bn) / t.share;
+      const int64_t queue = ceil_div(pipe_tiles(d, t.bm, t.bn) * was.splits, ctx->cu_count);
+      const double cost = (double)(queue * t.bm * t.bn) / (queue == 1 && t.bm == 128 ? 0.8 * t.share : t.share);
       if (best < 0 || cost < best) { best = cost; bm = t.bm; bn = t.bn; }
     }
   }
