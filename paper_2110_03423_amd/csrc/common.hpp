@@ -221,7 +221,7 @@ hipError_t gram_syrk_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int6
                             int *parts_out, int batch, int64_t stride, const int *skip_flag, bool slack = false);
 
 // Q = Y R^-1 for panels of at most apply_tri_max_order(dtype) columns (Y rows x l, ld ldy; R^-1 l x l upper
-// triangular, ld l; Q may be Y): R^-1 resident in LDS, workgroups walking over 64-row tiles.  Columns flagged in
+// triangular, ld l; Q may be Y): R^-1 in the registers of each wavefront, workgroups walking over 64-row tiles.  Columns flagged in
 // `dead` are replaced by Gaussian directions (element (row, col) from counter row * refill_ld + col of Philox stream
 // refill_stream, times refill_scale).  batch problems `stride` bytes apart (every pointer and the flag);
 // *skip_flag != 0: nothing is done.

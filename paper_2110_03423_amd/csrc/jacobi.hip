@@ -1902,6 +1902,9 @@ static int jb_block_width(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t l) {
 //         120 796, 396, 399 against 662, 300, 354 (100000 x 1000 centred, l = 120, q = 3: 2898 -> 2715 for the whole call)
 //   fp64  l = 56 395, 239, 242 against 429, 245, 269; 64 479, 266, 275 against 393, 245, 271; 72 700, 409, 414 against 592, 296, 325;
 //         96 1064, 571, 583 against 582, 303, 365
+// In fp32 the line lies where all three are faster (at 96 one is not).  In fp64 the blocks win at 64 already, and lose at 56; the orders between
+// are not measured, and the line is the first order behind them.  Factors with many equal values, which the corrections leave to sweeps, gain
+// less: l = 98 with 90 of them, 45 matrices, fp64 1318 -> 1306, fp32 514 -> 629.
 bool jacobi_prefers_blocks(rsvd_dtype dtype, int64_t l) { return l >= (dtype == RSVD_F32 ? 97 : 65); }
 
 // Scratch of the block path: header, Mt, Jt, norms, ranks.
