@@ -9,8 +9,8 @@
 // convergence  M J = X diag(sigma)  and  M = X diag(sigma) J^T.
 //
 // Stopping rule (the paper gives none): a sweep in which every pair satisfies
-// |a_p . a_q| <= tol * ||a_p|| * ||a_q||, tol = eps * sqrt(l); at most 60 sweeps (24 in the block path, whose
-// launches beyond the orders of the one-launch kernel are all issued in advance).
+// |a_p . a_q| <= tol * ||a_p|| * ||a_q||, tol = eps * sqrt(l); at most 60 sweeps (24 beyond the orders of the one-launch
+// block kernel, where every sweep is launched in advance).
 // The sweep that would only confirm this is saved when the rate of the last two sweeps says what it would find
 // (jacobi_done below): with rho the largest relative inner product a sweep rotated away, the next sweep meets about
 // rho^2 where the method converges quadratically (the paper: "3-4 iterations ... converges quadratically"; taken for
@@ -511,10 +511,12 @@ struct JbHeader {
 };
 
 // One run of sweeps of jb_flow_kernel.
+constexpr int kRunSweeps = 64;
+static_assert(kJacobiMaxSweeps <= kRunSweeps, "a record for every sweep");
 struct JbRun {
-  unsigned long long sumsq[32];      // per sweep: sum of s^2 over its rotations (c, s), times kJbSumScale
-  int counters[32];                  // per sweep: bit pattern of the largest relative inner product rotated away
-  int finished[32];                  // per sweep: block pairs whose columns of M are done
+  unsigned long long sumsq[kRunSweeps];      // per sweep: sum of s^2 over its rotations (c, s), times kJbSumScale
+  int counters[kRunSweeps];                  // per sweep: bit pattern of the largest relative inner product rotated away
+  int finished[kRunSweeps];                  // per sweep: block pairs whose columns of M are done
   int ticket;                        // next task
   int stop;                          // 1: converged, 2: what is left is for the corrections of the whole matrix
   int used;                          // sweeps done when it stopped
@@ -1841,7 +1843,7 @@ __global__ __launch_bounds__(256) void jb_scatter_kernel(const T *__restrict__ M
   }
 }
 
-constexpr int kJbMaxSweeps = 24;
+constexpr int kJbMaxSweeps = 24;           // of jb_panel_kernel, whose every sweep is launched
 
 // Lanes per column pair of the LDS-resident kernel.
 static int jacobi_group(rsvd_dtype dtype, int64_t l) {
@@ -1973,11 +1975,11 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
       Mt2 = P.b[3]; Jt2 = P.b[4];
       P.sync = sync; P.l = l; P.tiles = (l + kPoTile - 1) / kPoTile;
       hipLaunchKernelGGL((jb_flow_kernel<T>), dim3(nblk2), dim3(1024), jg_lds_bytes<T>(l), s, Mt, Jt, Mt2, Jt2, l, nblk,
-                         kJbMaxSweeps, chg, sync, 0, 1);
+                         kJacobiMaxSweeps, chg, sync, 0, 1);
       polish_launch<T>(ctx, s, P);
     }
     hipLaunchKernelGGL((jb_flow_kernel<T>), dim3(nblk2), dim3(1024), jg_lds_bytes<T>(l), s, Mt, Jt, Mt2, Jt2, l, nblk,
-                       kJbMaxSweeps, corrections ? ver2 : chg, sync, corrections, 0);
+                       kJacobiMaxSweeps, corrections ? ver2 : chg, sync, corrections, 0);
   } else {
 #define RSVD_JB_CASE(NVV)                                                                                        \
   case NVV: {                                                                                                    \
@@ -2009,7 +2011,7 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
   }
   hipLaunchKernelGGL((jb_norms_kernel<T>), dim3((l + 3) / 4), dim3(256), 0, s, Mt, Mt2, l, nrm, sync);
   hipLaunchKernelGGL((jb_rank_kernel<T>), dim3((l + 15) / 16), dim3(256), 0, s, nrm, l, rnk, sig, hdr,
-                     kJbMaxSweeps, info, sync);
+                     flow ? kJacobiMaxSweeps : kJbMaxSweeps, info, sync);
   hipLaunchKernelGGL((jb_scatter_kernel<T>), dim3(256), dim3(256), 0, s, Mt, Jt, Mt2, Jt2, l, nrm, rnk, hdr, X, W, sync);
   return hipGetLastError();
 }

@@ -430,6 +430,22 @@ def test_block_jacobi_corrections(dt, l, kind):
     assert np.abs(sig - want).max() <= 20 * eps * np.sqrt(l) * want[0]
 
 
+# Matrices in general position with steep spectra, whose columns do not show their grading, take more sweeps than others; the limit is 60 on one
+# workgroup and in the one-launch block kernel.
+@pytest.mark.parametrize("l", [56, 66, 72, 80, 89, 96, 97, 110])
+@pytest.mark.parametrize("decades", [8.5, 11, 12])
+def test_jacobi_takes_the_sweeps_it_needs(l, decades):
+    say("jacobi many sweeps", l, decades)
+    M = (workloads.orthonormal_factor(l, l, 1) * 10.0 ** (-np.arange(l) * decades / l)) @ workloads.orthonormal_factor(l, l, 2).T
+    sig, X, W, info = ctx().rsvd_stage_jacobi(to_dev(M))
+    say("  sweeps", info.jacobi_sweeps)
+    assert info.status == 0 and info.jacobi_sweeps <= 60
+    sig, W = to_np(sig), to_np(W)
+    tol = parity.jacobi_tol(l, "f64")
+    assert np.abs(sig - np.linalg.svd(M, compute_uv=False)).max() <= tol and np.linalg.norm(W.T @ W - np.eye(l)) <= tol
+    assert np.linalg.norm(to_np(X) * sig @ W.T - M) <= tol
+
+
 # Many equal values above a decaying rest: angles below the threshold of a rotation, rounding noise each, are most of what a correction
 # turns by, and its series has to be long enough for them.  Factors as q subspace iterations leave them.
 @pytest.mark.parametrize("dt,l,equal,q,rate", [("f64", 70, 40, 2, 0.02), ("f64", 98, 90, 1, 0.05), ("f64", 110, 64, 2, 0.4), ("f64", 128, 96, 2, 0.05),
