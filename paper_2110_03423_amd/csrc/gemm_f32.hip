@@ -1,6 +1,7 @@
 // Products of fp32 operands: on the bf16 matrix cores with split operands (gemm_split.hpp) where there is enough work for
-// that, else on the fp32 matrix cores (gemm_impl.hpp).
+// that, narrow ones with A^T by gemm_stream.hpp, else on the fp32 matrix cores (gemm_impl.hpp).
 #include "gemm_split.hpp"
+#include "gemm_stream.hpp"
 
 namespace rsvd {
 size_t gemm_partial_bytes_f32(const rsvd_ctx *ctx, int64_t M, int64_t N, int64_t K, int trans_a) {
@@ -88,6 +89,7 @@ static SplitChoice split_ranges(const rsvd_ctx *ctx, const GemmDesc &d, int bn, 
 hipError_t gemm_launch_f32(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d) {
   typedef GemmDispatch<float, float, float> Plain;
   if (d.M <= 0 || d.N <= 0) return hipSuccess;
+  if (stream_takes<float>(d)) return stream_launch<float>(ctx, s, d);
   const bool aligned = Plain::aligned_a(d) && Plain::aligned_b(d);
   if (!takes_split(d, aligned)) return Plain::launch(ctx, s, d);
   if (d.batch < 1 || d.batch > 65535) return hipErrorInvalidValue;

@@ -1,5 +1,7 @@
-// Products of fp64 operands: gemm_pipe.hpp where their rows are 16-byte pieces and there is no centring, else gemm_impl.hpp.
+// Products of fp64 operands: narrow ones with A^T by gemm_stream.hpp, gemm_pipe.hpp where their rows are 16-byte pieces and there is
+// no centring, else gemm_impl.hpp.
 #include "gemm_pipe.hpp"
+#include "gemm_stream.hpp"
 
 namespace rsvd {
 size_t gemm_partial_bytes_f64(const rsvd_ctx *ctx, int64_t M, int64_t N, int64_t K, int trans_a) {
@@ -23,6 +25,7 @@ static hipError_t pipe_by_tile(hipStream_t s, const GemmParams &P, int bm, int b
 // Below 10^7 multiply-adds (the blocks of a Cholesky factorisation) either kernel waits for its first loads.
 hipError_t gemm_launch_f64(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d) {
   if (d.M <= 0 || d.N <= 0) return hipSuccess;
+  if (stream_takes<double>(d)) return stream_launch<double>(ctx, s, d);
   const double madds = (double)d.M * (double)d.N * (double)d.K * (double)d.batch;
   if (madds < 1e7 || !pipe_can(d)) return GemmDispatch<double, double, double>::launch(ctx, s, d);
   return pipe_launch(ctx, s, d, [&](const GemmParams &P, int bm, int bn, bool chains) {

@@ -49,10 +49,9 @@ struct GemmParams {
   int reduce_groups;        // split-K reduction: threads per output element (1, 2, 4 or 8)
 };
 
-// The parameters of problem blockIdx.y of a batched launch.
-__device__ __forceinline__ GemmParams select_problem(const GemmParams &P0) {
+// The parameters of problem b of a batched launch.
+__device__ __forceinline__ GemmParams select_problem(const GemmParams &P0, int64_t b = blockIdx.y) {
   GemmParams P = P0;
-  const int64_t b = (int64_t)blockIdx.y;
   if (b != 0) {
     P.A = (const char *)P.A + b * P.stride_a;
     P.B = (const char *)P.B + b * P.stride_b;
