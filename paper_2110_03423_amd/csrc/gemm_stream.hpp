@@ -5,14 +5,16 @@
 // and nothing waits at a barrier: a wavefront has 64 rows of C, D steps of four k in flight in registers, and the four wavefronts of a
 // workgroup read 1024 (fp64: 2048) bytes of every row side by side.  gemm_kernel's tiles of 64 rows, dealt over the XCDs one by one, fetched A 1.9 times
 // where its rows are no multiple of 128 bytes (256 x (2000 x 500) fp32, FETCH_SIZE; this kernel 1.2 times), and its 1000 workgroups write and read partial
-// sums of four times as many k ranges.  Calls of rsvd_stage_gemm_atn, gemm_kernel or gemm_pipe_kernel -> this, us:
-//   fp32  65536 x 16384, l = 16  737 -> 686 (6.3 TB/s)   20928 x 16320, l = 25  382 -> 269   49438 x 870, l = 24   58 -> 37
-//         98824 x 525, l = 20     67 -> 45               63168 x 2064, l = 12   101 -> 95    5680 x 21124, l = 16  91 -> 88
-//   fp64  5680 x 21120, l = 20   197 -> 160              58048 x 496, l = 22     50 -> 42    4128 x 1904, l = 48   30 -> 26
-// and of the batches 256 x (2000 x 500) fp32, l = 32, 278 -> 229 a product, 32 x (4000 x 1000) fp64, l = 48, 240 -> 207.
+// sums of four times as many k ranges.  Calls of rsvd_stage_gemm_atn, gemm_kernel or gemm_pipe_kernel -> this, us (reductions included):
+//   fp32  9599 x 12017, l = 23  147 -> 93   78704 x 3920, l = 19  403 -> 270   8118 x 4499, l = 30  51 -> 34   14645 x 1013, l = 29  31 -> 21
+//   fp64  9599 x 12017, l = 31  294 -> 183  78704 x 3920, l = 25  661 -> 471   5923 x 1303, l = 20  31 -> 21   36637 x 411, l = 27   43 -> 29
+// 70 shapes of 2e5 to 5e8 entries each: 1.14 (fp32; 0.93 at 1360 x 18352, l = 12, 25 us) and 1.08 times as fast, below 20 us the same.  Of the
+// batches 256 x (2000 x 500) fp32, l = 32, 281 -> 220 a product, 32 x (4000 x 1000) fp64, l = 48, 254 -> 221.  Whole calls: these batches 1511 -> 1394
+// and 2219 -> 2099, 65536 x 16384 fp32, l = 16, 3133 -> 3071.
 // Tried: twice the steps in flight (the batches 10 % slower, 32 columns of long products 10 % faster), the wavefronts of a workgroup on ranges of
-// their own instead of taking turns (rows of A in pieces of 256 bytes: 15 % slower).  A X, whose sixteen rows a matrix instruction takes at the same
-// k, has pieces of 64 bytes a row when read like this (0.75 times as fast as gemm_kernel); through a ring of whole lines in LDS it was 0.95 times.
+// their own instead of taking turns (rows of A in pieces of 256 bytes: 15 % slower), the problems of a batch in the opposite order to that of the
+// product before, for what the last-level cache still holds (no change).  A X, whose sixteen rows a matrix instruction takes at the same k, has pieces
+// of 64 bytes a row when read like this (0.75 times as fast as gemm_kernel); through a ring of whole lines in LDS it was 0.95 times.
 #pragma once
 
 #include "gemm_impl.hpp"
