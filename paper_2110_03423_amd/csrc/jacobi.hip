@@ -165,11 +165,11 @@ __device__ __forceinline__ void store_column(T *col, int lg, const jac_unit<T> (
 
 // Rotate the pair (kept column x of M with its column u of J, in registers; column q in
 // LDS).  Returns the relative size |x.y| / (|x| |y|) of the inner product it rotated away,
-// 0 when it left the pair alone.
+// 0 when it left the pair alone; turned: sum of s^2.
 template <typename T, int RPL, int G>
 __device__ __forceinline__ float rotate_moving(jac_unit<T> (&x)[RPL / (8 / (int)sizeof(T))],
                                                jac_unit<T> (&u)[RPL / (8 / (int)sizeof(T))], T *Mc, T *Jc, int ldm,
-                                               int q, int lg, T tol, T floor2) {
+                                               int q, int lg, T tol, T floor2, float &turned) {
   constexpr int V = 8 / sizeof(T);          // elements per LDS access
   constexpr int NV = RPL / V;               // accesses per column per lane
   jac_unit<T> y[NV];
@@ -194,6 +194,7 @@ __device__ __forceinline__ float rotate_moving(jac_unit<T> (&x)[RPL / (8 / (int)
   load_column<T, RPL, G>(Jc + q * ldm, lg, v);
   T c, s;
   rotation_params(alpha, beta, gamma, c, s);
+  turned += (float)(s * s);
 #pragma unroll
   for (int r = 0; r < NV; ++r) {
     const jac_unit<T> xo = x[r];
@@ -222,6 +223,313 @@ __host__ __device__ inline int jacobi_ldm(int l, int G, int elem_size) {
   return jacobi_rows_padded(l, G, elem_size) + 2;
 }
 
+// ---- corrections of the whole matrix inside one workgroup ----
+//
+// What polish_kernel (further down, with the method) does with all CUs: once a sweep has left the columns close to orthogonal, all Jacobi
+// angles are taken from one Gram matrix in fp64 and applied together, M <- M exp(X), J <- J exp(X).  For M and J in LDS it is a handful of
+// l x l products of one CU where a sweep is l rounds that wait for each other (50 us at l = 80, a correction 15 to 25).  Last sweeps -> corrections, the whole
+// decomposition, us: factors behind a power iteration l = 80 fp32 240 -> 180, 61 fp32 159 -> 114, 48 fp64 (32 of them) 250 -> 168, 20 fp64 50 -> 38, 16 fp32
+// 43 -> 33; factors of Gaussian matrices l = 80 fp32 436 -> 374, 48 fp32 179 -> 139, 61 fp64 458 -> 369, 24 fp64 107 -> 93; values over six decades
+// on unordered columns, where sweeps converge slowly throughout, -9 to +13 %; half of the values within 1e-5 -14 to +18 %.  X and W end
+// closer to orthogonal (|X^T X - I| / sqrt(l), fp32, l = 80: 18 -> 0.9 eps).
+// What bounds a product: 20 dependent matrix instructions a block at l = 80 and the barrier behind them; blocks of a whole matrix are read row by row
+// from LDS, those below the diagonal of symmetric ones are copies.  (As first written, 30 KB of code with registers kept in scratch memory, a correction
+// took 55 us at l = 80.)
+constexpr int kPolishSteps = 10;
+
+// Largest x for a series cut behind X^2 / 2 (1), X^3 (2), X^5 (3) and X^9 (4).  The 2-norm of X is x / 1.41 if all of it is one rotation and
+// about x / 2 as met behind a sweep; off orthogonality by that much: fp64 1e-15 (4: 1e-16), fp32 1e-8.  Beyond the last, X is
+// halved until it is below, and E doubled as often: E <- 2 E + E E.
+template <typename T> __host__ __device__ constexpr float polish_limit(int order) {
+  if (sizeof(T) == 4) return order == 1 ? 2e-3f : order == 2 ? 0.02f : order == 3 ? 0.15f : 0.75f;
+  return order == 1 ? 1e-5f : order == 2 ? 4e-4f : order == 3 ? 0.01f : 0.15f;
+}
+// Sweeps end when the angles of the last one came to this (Frobenius norm again); it is also the largest x of a correction.  A sweep
+// that turned by 14 leaves 9 on triangular factors of every kind, one of 10 leaves 2 ... 6, one of 2 leaves 0.1 ... 0.35; from 9 it takes 6
+// corrections, from 2 three or four.  A large x costs corrections of 80 to 100 us each (9 to 12 products), a sweep 110 us at l = 110, 170 at
+// 210 and 450 at 450.
+__host__ __device__ constexpr float polish_start(int l) { return l < 160 ? 4.f : l < 256 ? 7.f : 12.f; }
+constexpr double kPolishFree = 0.01;        // angles up to this are taken whatever the inner product
+constexpr float kPolishRate = 0.75f;        // x of a correction in units of that before; above that they do not converge
+
+// Corrections are tried behind a sweep whose rotations came to kCorrTurned (Frobenius norm of the angles; one of 3 leaves 0.5, one of 5 leaves 1 to 2), and
+// go on if what is left is at most kCorrStart: from 3 they take as long as the sweep that would bring it to 0.1.
+constexpr float kCorrTurned = 5.f, kCorrStart = 2.f, kCorrTurnedScale = 65536.f;
+constexpr int kCorrWaves = 16;             // wavefronts that share the 16 x 16 blocks of a product
+template <typename T, int RPL> struct CorrCfg {
+  static constexpr bool kFits = sizeof(T) == 4 ? RPL <= 6 : RPL <= 4;      // (M, J and two more matrices in LDS)
+  static constexpr int NB = RPL <= 4 ? 1 : 2;                              // blocks of a whole matrix that a wavefront has
+};
+constexpr int corr_max_order(bool f32) { return f32 ? 80 : 64; }           // a wavefront has one block on or above the diagonal
+// Row stride of the two matrices: four rows that are read side by side meet different banks.
+__host__ __device__ inline int corr_ld(int l) {
+  const int lp = (l + 15) / 16 * 16;
+  return lp % 32 == 16 ? lp : lp + 16;
+}
+
+// acc[t] = sum_k p[k][0] q[k][16 t], k = 0, 4, ... steps of the matrix instruction, n4 groups of four; the operands of a group are in flight
+// together.
+template <typename T, int W>
+__device__ __forceinline__ void corr_product(typename Mfma<T>::vec (&acc)[W], const T *p, int ldp, const T *q, int ldq, int n4) {
+#pragma unroll
+  for (int t = 0; t < W; ++t) acc[t] = (typename Mfma<T>::vec)(T)0;
+#pragma unroll 1
+  for (int n = 0; n < n4; ++n) {
+    T a[4], b[4][W];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      a[u] = p[4 * u * ldp];
+#pragma unroll
+      for (int t = 0; t < W; ++t) b[u][t] = q[4 * u * ldq + 16 * t];
+    }
+    __builtin_amdgcn_sched_barrier(0);       // (all loads in flight before the first is waited for)
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int t = 0; t < W; ++t) acc[t] = Mfma<T>::run(a[u], b[u][t], acc[t]);
+    p += 16 * ldp;
+    q += 16 * ldq;
+  }
+}
+
+// Tangent of the Jacobi angle, from zeta = (d_j - d_i) / (2 g): the hardware's estimates, refined once in fp64.
+__device__ __forceinline__ float corr_tan(double dj, double di, double g) {
+  const float z = (float)(dj - di) * fast_rcp(2.f * (float)g), az = fabsf(z);
+  const float t = az > 1e7f ? 0.5f * fast_rcp(az) : fast_rcp(az + fast_sqrt(1.f + z * z));
+  return z < 0.f ? -t : t;
+}
+__device__ __forceinline__ double once_rcp(double x) {
+  const double y = __builtin_amdgcn_rcp(x);
+  return y * (2.0 - x * y);
+}
+__device__ __forceinline__ double corr_tan64(double dj, double di, double g) {
+  const double z = (dj - di) * once_rcp(2.0 * g), az = fabs(z), w = 1.0 + z * z;
+  double r = __builtin_amdgcn_rsq(w);
+  r = r * (1.5 - 0.5 * w * r * r);
+  const double t = az > 1e7 ? 0.5 * once_rcp(az) : once_rcp(az + w * r);
+  return z < 0.0 ? -t : t;
+}
+
+// Returns whether the columns of M are orthogonal now; `applied` counts the corrections.  B0, B1: ceil16(l) rows of corr_ld(l).
+// The Gram matrix, X and the parts of its exponential are symmetric or antisymmetric: of those a wavefront has one block on or above the
+// diagonal, whose elements stay in its registers from step to step; of whole matrices it has one or two neighbouring blocks of a row.
+template <typename T, int RPL>
+__device__ __forceinline__ bool lds_corrections(T *Mc, T *Jc, int ldm, T *B0, T *B1, int l, T tol, T floor2, double *nd, float (*red)[3],
+                                                int &applied) {
+  typedef typename Mfma<T>::vec acc_t;
+  constexpr int NB = CorrCfg<T, RPL>::NB, V = 8 / (int)sizeof(T);
+  const int nb = (l + 15) >> 4, ld = corr_ld(l);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  // (addresses are worked out where they are used: kept in registers from step to step and through the sweeps they do not fit)
+  auto lane_now = []() {
+    int lane = (int)threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    return lane;
+  };
+  const bool has = wave < nb * (nb + 1) / 2;
+  int ui = 0, uj = has ? wave : 0;
+  while (uj >= nb - ui) { uj -= nb - ui; ++ui; }
+  uj += ui;
+  const int strips = kCorrWaves / nb < nb ? kCorrWaves / nb : nb, width = (nb + strips - 1) / strips;
+  const int fi = wave % nb;
+  const bool full = wave / nb < strips;
+  // (the last strip of a row may be narrower: it begins further left, and its neighbour's block is computed twice)
+  const int fj = (wave / nb) * width + width <= nb ? (wave / nb) * width : nb - width;
+  // block (ui, uj) of sum_k P[k][i] Q[k][j]
+  auto upper = [&](acc_t &m, const T *P, const T *Q) {
+    const int lane = lane_now(), at = (lane >> 4) * ld + (lane & 15);
+    acc_t a[1];
+    if (has) corr_product<T, 1>(a, P + at + 16 * ui, ld, Q + at + 16 * uj, ld, nb);
+    m = a[0];
+  };
+  auto each = [&](auto f) {                      // f(v, i, j)
+    const int lane = lane_now();
+    if (has) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) f(v, 16 * ui + Mfma<T>::row(lane, v), 16 * uj + (lane & 15));
+    }
+  };
+  auto put = [&](T *B, const acc_t &m, T mirror) {       // and mirror times it on the other side of the diagonal
+    each([&](int v, int i, int j) {
+      B[i * ld + j] = m[v];
+      if (ui != uj) B[j * ld + i] = mirror * m[v];
+    });
+  };
+  auto strip = [&](acc_t (&m)[NB], const T *P, const T *Q, int ldq) {
+    if (!full) return;
+    const int lane = lane_now(), kq = lane >> 4, r16 = lane & 15;
+    const T *p = P + kq * ld + r16 + 16 * fi, *q = Q + kq * ldq + r16 + 16 * fj;
+    if (NB == 2 && width == 2) {
+      corr_product<T, NB>(m, p, ld, q, ldq, nb);
+    } else {
+      acc_t a[1];
+      corr_product<T, 1>(a, p, ld, q, ldq, nb);
+      m[0] = a[0];
+    }
+  };
+  auto each_full = [&](auto f) {                 // f(t, v, i, j)
+    if (!full) return;
+    const int lane = lane_now();
+#pragma unroll
+    for (int t = 0; t < NB; ++t)
+      if (t < width) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) f(t, v, 16 * fi + Mfma<T>::row(lane, v), 16 * (fj + t) + (lane & 15));
+      }
+  };
+  float x_before = 1e30f;
+#pragma unroll 1
+  for (int step = 0; step < kPolishSteps; ++step) {
+    // ---- G = M^T M in fp64, its diagonal, the angles
+    f64x4 g = (f64x4)0.0;
+    const int lane = lane_now(), r16 = lane & 15;
+    if (has) {
+      const T *p = Mc + (16 * ui + r16) * ldm + V * (lane >> 4), *q = Mc + (16 * uj + r16) * ldm + V * (lane >> 4);
+#pragma unroll 1
+      for (int n = 0; n < nb; ++n) {
+        jac_unit<T> x[4 / V], y[4 / V];
+#pragma unroll
+        for (int u = 0; u < 4 / V; ++u) {
+          x[u] = *reinterpret_cast<const jac_unit<T> *>(p + 4 * V * u);
+          y[u] = *reinterpret_cast<const jac_unit<T> *>(q + 4 * V * u);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 4 / V; ++u)
+#pragma unroll
+          for (int e = 0; e < V; ++e) g = Mfma<double>::run((double)x[u][e], (double)y[u][e], g);
+        p += 16;
+        q += 16;
+      }
+      if (ui == uj) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (Mfma<double>::row(lane, v) == r16) nd[16 * ui + r16] = g[v];
+      }
+    }
+    __syncthreads();
+    float rho = 0.f, x2 = 0.f, open = 0.f;
+    if (has) {
+      const int j = 16 * uj + r16;
+      const double dj = j < l ? nd[j] : 0.0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = 16 * ui + Mfma<double>::row(lane, v);
+        const double di = i < l ? nd[i] : 0.0, gv = g[v];
+        T angle = (T)0;
+        if (i < j && di > (double)floor2 && dj > (double)floor2 && gv != 0.0) {
+          const float rel = (float)(fabs(gv) * __builtin_amdgcn_rsq(di * dj));
+          // tan of the angle as in rotation_params, then the angle itself (to the fifth order: it only has to be a good one)
+          const T tn = sizeof(T) == 4 ? (T)corr_tan(dj, di, gv) : (T)corr_tan64(dj, di, gv);
+          // below the threshold only where it is a small one: inside a cluster it would be large, and noise
+          if (rel > (float)tol || fabs(tn) <= (T)kPolishFree) angle = tn - tn * tn * tn * ((T)(1.0 / 3.0) - (T)0.2 * tn * tn);
+          const float a2 = (float)(angle * angle);
+          if (rel > (float)tol) {
+            rho = fmaxf(rho, rel);
+            open += a2;
+          }
+          x2 += a2;
+        }
+        if (i <= j) {
+          B0[i * ld + j] = angle;
+          if (i != j) B0[j * ld + i] = -angle;
+        }
+        __builtin_amdgcn_sched_barrier(0);             // (one angle at a time: side by side they take more registers than there are)
+      }
+    }
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+      rho = fmaxf(rho, __shfl_xor(rho, m, 64));
+      x2 += __shfl_xor(x2, m, 64);
+      open += __shfl_xor(open, m, 64);
+    }
+    if (lane == 0) { red[wave][0] = rho; red[wave][1] = x2; red[wave][2] = open; }
+    __syncthreads();
+    rho = x2 = open = 0.f;
+    for (int w = 0; w < kCorrWaves; ++w) {
+      rho = fmaxf(rho, red[w][0]);
+      x2 += red[w][1];
+      open += red[w][2];
+    }
+    const float x_all = sqrtf(2.f * x2), x_now = sqrtf(2.f * open);
+    if (rho <= (float)tol) return true;
+    if (!(x_now <= kCorrStart) || !(x_now <= kPolishRate * x_before)) return false;
+    x_before = x_now;
+    const int order = x_all <= polish_limit<T>(1) ? 1 : x_all <= polish_limit<T>(2) ? 2 : x_all <= polish_limit<T>(3) ? 3 : 4;
+    int doublings = 0;
+    for (float x = x_all; x > polish_limit<T>(4) && doublings < 7; x *= 0.5f) ++doublings;
+    const T half = (T)__builtin_ldexp(1.0, -doublings);
+    // ---- E = exp(half X) - I into B1 (X[i][k] = -X[k][i]; c: the symmetric part of E)
+    acc_t x, c, sn, w;
+    each([&](int v, int i, int j) { x[v] = B0[i * ld + j]; });
+    upper(w, B0, B0);
+    w *= -half * half;
+    c = w * (T)0.5;
+    sn = w * (T)(1.0 / 6.0);
+    if (order >= 3) {
+      put(B1, w, (T)1);
+      __syncthreads();
+      upper(w, B1, B1);
+      c += w * (T)(1.0 / 24.0);
+      sn += w * (T)(1.0 / 120.0);
+      if (order == 4) {
+        put(B0, w, (T)1);                        // (X waits in registers)
+        __syncthreads();
+        upper(w, B1, B0);
+        c += w * (T)(1.0 / 720.0);
+        sn += w * (T)(1.0 / 5040.0);
+        upper(w, B0, B0);
+        c += w * (T)(1.0 / 40320.0);
+        sn += w * (T)(1.0 / 362880.0);
+      }
+      __syncthreads();
+      if (order == 4) put(B0, x, (T)-1);
+    }
+    x *= half;
+    if (order >= 2) {
+      put(B1, sn, (T)1);
+      __syncthreads();
+      upper(w, B0, B1);
+      x -= half * w;
+      __syncthreads();
+    }
+    each([&](int v, int i, int j) {
+      B1[i * ld + j] = c[v] + x[v];
+      if (ui != uj) B1[j * ld + i] = c[v] - x[v];
+    });
+    __syncthreads();
+#pragma unroll 1
+    for (int d = 0; d < doublings; ++d) {              // exp(2 X) - I = 2 E + E E, the first operand read from the transpose
+      acc_t e[NB];
+      each_full([&](int t, int v, int i, int j) { B0[j * ld + i] = B1[i * ld + j]; });
+      __syncthreads();
+      strip(e, B0, B1, ld);
+      each_full([&](int t, int v, int i, int j) { e[t][v] += (T)2 * B1[i * ld + j]; });
+      __syncthreads();
+      each_full([&](int t, int v, int i, int j) { B1[i * ld + j] = e[t][v]; });
+      __syncthreads();
+    }
+    // ---- column i of the new M and J = that of the old one + sum_k E[k][i] column k (E is zero in the rows beyond the last column)
+    {
+      acc_t am[NB], aj[NB];
+      strip(am, B1, Mc, ldm);
+      strip(aj, B1, Jc, ldm);
+      __syncthreads();
+      each_full([&](int t, int v, int i, int j) {
+        // (a block that two wavefronts have is stored by the one whose strip it begins in)
+        if (i < l && (fj + t) / width == wave / nb) {
+          Mc[i * ldm + j] += am[t][v];
+          Jc[i * ldm + j] += aj[t][v];
+        }
+      });
+      __syncthreads();
+    }
+    ++applied;
+    if (rho * x_all <= (float)tol) return true;             // the next one would find about that
+  }
+  return false;
+}
+
 // JG: the columns of J (the accumulated rotations) live in global memory (Jglobal, l columns of ldm elements, one
 // such array per problem of a batch, `stride` bytes apart) instead of LDS, for orders whose two matrices do not fit
 // there together (fp64 beyond 96).  Its columns travel through the cache of the CU: a round takes longer, but
@@ -229,7 +537,7 @@ __host__ __device__ inline int jacobi_ldm(int l, int G, int elem_size) {
 template <typename T, typename TIn, int RPL, int G, bool JG = false>
 __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restrict__ M, int l, SigmaOut sig,
                                                          T *__restrict__ X, T *__restrict__ W, DevInfo *info,
-                                                         int64_t stride, int rows, T *__restrict__ Jglobal) {
+                                                         int64_t stride, int rows, T *__restrict__ Jglobal, int corrections) {
   extern __shared__ __attribute__((aligned(16))) double lds_raw[];
   if (blockIdx.x != 0) {              // batched launch: one problem per workgroup, `stride` bytes apart
     const int64_t off = (int64_t)blockIdx.x * stride;
@@ -241,11 +549,16 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
   const int ldm = jacobi_ldm(l, G, (int)sizeof(T));
   T *Mc = reinterpret_cast<T *>(lds_raw);
   T *Jc = JG ? Jglobal : Mc + (size_t)l * ldm;
-  T *nrm = Mc + (size_t)(JG ? 1 : 2) * l * ldm;
+  T *B0 = Mc + (size_t)(JG ? 1 : 2) * l * ldm, *B1 = B0 + (corrections ? (l + 15) / 16 * 16 * corr_ld(l) : 0);      // (work of the corrections)
+  T *nrm = B1 + (B1 - B0);
   int *rnk = reinterpret_cast<int *>(nrm + l);
   __shared__ int rotations;
-  __shared__ T wave_sum[16];
+  __shared__ unsigned turned_sum;
+  __shared__ T wave_sum[16], unit[128];
   __shared__ JacLevel lev[kJacLevels][kJacGroups];
+  constexpr bool CORR = !JG && CorrCfg<T, RPL>::kFits;
+  __shared__ double corr_norms[CORR ? 16 * RPL : 1];
+  __shared__ float corr_sums[CORR ? kCorrWaves : 1][3];
 
   const int tid = threadIdx.x, nt = blockDim.x;
   // pair order: every column finds, level by level, the set it belongs to; the columns of
@@ -278,6 +591,8 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
       Mc[c * ldm + r] = (T)0;
       Jc[c * ldm + r] = (T)0;
     }
+    // (what lies between the rows of the corrections' matrices is read as columns of J beyond the last one, against zeros: it has to be finite)
+    for (T *w = B0 + tid; w < nrm; w += nt) *w = (T)0;
     for (int idx = tid; idx < l * l; idx += nt) {
       const int r = idx / l, c = idx - r * l;
       const T v = (T)M[idx];
@@ -290,7 +605,7 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) fro2 += __shfl_xor(fro2, off, 64);
   if ((tid & 63) == 0) wave_sum[tid >> 6] = fro2;
-  if (tid == 0) rotations = 0;
+  if (tid == 0) { rotations = 0; turned_sum = 0; }
   __syncthreads();
   fro2 = 0;
   for (int w = 0; w < (nt >> 6); ++w) fro2 += wave_sum[w];
@@ -316,7 +631,7 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
   constexpr int NV = RPL / (8 / (int)sizeof(T));
   while (!converged && sweeps < kJacobiMaxSweeps) {
     ++sweeps;
-    float rho = 0.f;
+    float rho = 0.f, turned = 0.f;
     int d = 0;
     for (int ms = l; ms > 1; ms = (ms + 1) >> 1, ++d) {      // ms: largest set of this level
       JacLevel e;
@@ -333,7 +648,7 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
         if (act && r < e.bsize) {
           int j = e.idx + r;
           if (j >= e.bsize) j -= e.bsize;
-          rho = fmaxf(rho, rotate_moving<T, RPL, G>(x, u, Mc, Jc, ldm, e.bstart + j, lg, tol, floor2));
+          rho = fmaxf(rho, rotate_moving<T, RPL, G>(x, u, Mc, Jc, ldm, e.bstart + j, lg, tol, floor2, turned));
         }
         __syncthreads();
       }
@@ -343,19 +658,46 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
       }
       __syncthreads();
     }
-    if (rho > 0.f) atomicMax(&rotations, __float_as_int(rho));   // positive floats order like their bit patterns
+    if (rho > 0.f) {
+      atomicMax(&rotations, __float_as_int(rho));      // positive floats order like their bit patterns
+      // (whole numbers: their sum does not depend on the order)
+      if (CORR && lg == 0) atomicAdd(&turned_sum, (unsigned)(turned * kCorrTurnedScale));
+    }
     __syncthreads();
     converged = jacobi_done(__int_as_float(rotations), rho_prev, (float)tol);
     rho_prev = __int_as_float(rotations);
+    const bool ready = CORR && 2.f * (float)turned_sum <= kCorrTurned * kCorrTurned * kCorrTurnedScale;
     __syncthreads();
-    if (tid == 0) rotations = 0;
+    if (tid == 0) { rotations = 0; turned_sum = 0; }
     __syncthreads();
+    if constexpr (CORR) {
+      if (!converged && corrections && ready) {
+        int applied = 0;
+        converged = lds_corrections<T, RPL>(Mc, Jc, ldm, B0, B1, l, tol, floor2, corr_norms, corr_sums, applied);
+        // Corrections that did not get there have met a cluster, whose angles stay large however small the inner products: the rest is left to
+        // sweeps, about whose rate the ones before say nothing.
+        if (applied > 0) { rho_prev = -1.f; corrections = 0; }
+      }
+    }
   }
 
-  for (int j = tid; j < l; j += nt) {
-    T s2 = 0;
-    for (int i = 0; i < l; ++i) { const T x = Mc[j * ldm + i]; s2 += x * x; }
-    nrm[j] = sqrt(s2);
+  // Norms of the columns of M, sixteen lanes each.  Those of J are not quite one: the rounding errors of c and s err to one side where the
+  // angles are large and, less, to the other where they are small (fp64, l = 61: J^T J - I -31 eps on the diagonal behind five sweeps, -5 behind
+  // eight), and M has the same factors.  They are taken out of both (largest error of a value, factor of a
+  // Gaussian matrix, fp64 l = 61 6.8 -> 3.6 eps, over six decades 40 -> 4.0; fp32 l = 80 7.8 -> 2.1).
+  for (int j = tid >> 4; j < l; j += nt >> 4) {
+    double sm = 0.0, sj = 0.0;
+    for (int r = tid & 15; r < l; r += 16) {
+      const double x = (double)Mc[j * ldm + r], u = (double)Jc[j * ldm + r];
+      sm += x * x;
+      sj += u * u;
+    }
+    sm = group_sum<16>(sm);
+    sj = group_sum<16>(sj);
+    if ((tid & 15) == 0) {
+      unit[j] = (T)(1.5 - 0.5 * sj);
+      nrm[j] = (T)(sqrt(sm) * (1.5 - 0.5 * sj));
+    }
   }
   __syncthreads();
   for (int j = tid; j < l; j += nt) {
@@ -373,8 +715,8 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
     const int r = idx / l, c = idx - r * l;
     const int dst = r * l + rnk[c];
     const T s = nrm[c];
-    X[dst] = (s * s > floor2) ? Mc[c * ldm + r] / s : (T)0;
-    W[dst] = Jc[c * ldm + r];
+    X[dst] = (s * s > floor2) ? Mc[c * ldm + r] * unit[c] / s : (T)0;
+    W[dst] = Jc[c * ldm + r] * unit[c];
   }
   if (tid == 0 && info != nullptr) {
     atomicMax(&info->jacobi_sweeps, sweeps);
@@ -522,7 +864,7 @@ struct JbRun {
   int used;                          // sweeps done when it stopped
   int pad;
 };
-constexpr int kPolishSteps = 10, kPolishPhases = 13;
+constexpr int kPolishPhases = 13;
 // The corrections of the whole matrix behind the first run, and the run behind those.
 struct JbSync {
   JbRun run[2];
@@ -1011,20 +1353,6 @@ __device__ __forceinline__ float jg_pair_params(const T *G, int p, int q, T tol,
 // Everything is decided from the counters of JbSync, which are sums of whole numbers and maxima: no order of arrival shows in the result.
 constexpr float kPolishScale = 140737488355328.f;            // 2^47; a tile adds at most 128, more than any correction may
 
-// Largest x for a series cut behind X^2 / 2 (1), X^3 (2), X^5 (3) and X^9 (4).  The 2-norm of X is x / 1.41 if all of it is one rotation and
-// about x / 2 as met behind a sweep; off orthogonality by that much: fp64 1e-15 (4: 1e-16), fp32 1e-8.  Beyond the last, X is
-// halved until it is below, and E doubled as often: E <- 2 E + E E.
-template <typename T> __host__ __device__ constexpr float polish_limit(int order) {
-  if (sizeof(T) == 4) return order == 1 ? 2e-3f : order == 2 ? 0.02f : order == 3 ? 0.15f : 0.75f;
-  return order == 1 ? 1e-5f : order == 2 ? 4e-4f : order == 3 ? 0.01f : 0.15f;
-}
-// Sweeps end when the angles of the last one came to this (Frobenius norm again); it is also the largest x of a correction.  A sweep
-// that turned by 14 leaves 9 on triangular factors of every kind, one of 10 leaves 2 ... 6, one of 2 leaves 0.1 ... 0.35; from 9 it takes 6
-// corrections, from 2 three or four.  A large x costs corrections of 80 to 100 us each (9 to 12 products), a sweep 110 us at l = 110, 170 at
-// 210 and 450 at 450.
-__host__ __device__ constexpr float polish_start(int l) { return l < 160 ? 4.f : l < 256 ? 7.f : 12.f; }
-constexpr double kPolishFree = 0.01;        // angles up to this are taken whatever the inner product
-constexpr float kPolishRate = 0.75f;        // x of a correction in units of that before; above that they do not converge
 // (Large angles at tiny inner products are a cluster, which sweeps turn faster.)
 __device__ __forceinline__ bool sweeps_ready(unsigned long long sumsq, float rho, int l) {
   const float x2 = (float)sumsq * (2.f / kJbSumScale);
@@ -2018,9 +2346,9 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
 
 template <typename T, typename TIn, int RPL, int G>
 static hipError_t launch_lds(hipStream_t s, int nt, size_t lds, const void *M, int l, const SigmaOut &sig, void *X, void *W,
-                             DevInfo *info, int batch, int64_t stride, int rows) {
+                             DevInfo *info, int batch, int64_t stride, int rows, int corrections) {
   hipLaunchKernelGGL((jacobi_lds_kernel<T, TIn, RPL, G>), dim3(batch), dim3(nt), lds, s, (const TIn *)M, l,
-                     sig, (T *)X, (T *)W, info, stride, rows, (T *)nullptr);
+                     sig, (T *)X, (T *)W, info, stride, rows, (T *)nullptr, corrections);
   return hipGetLastError();
 }
 // fp64 orders 97 .. 128: M in LDS, J in global memory
@@ -2029,29 +2357,29 @@ static hipError_t launch_lds_jg(hipStream_t s, int nt, size_t lds, const void *M
                                 DevInfo *info, int batch, int64_t stride, int rows, void *Jglobal) {
   hipLaunchKernelGGL((jacobi_lds_kernel<double, double, RPL, 16, true>), dim3(batch), dim3(nt), lds, s,
                      (const double *)M, l, sig, (double *)X, (double *)W, info, stride, rows,
-                     (double *)Jglobal);
+                     (double *)Jglobal, 0);
   return hipGetLastError();
 }
 
 // rows per lane = padded rows / G
 template <typename T, typename TIn>
 static hipError_t launch_lds_g(hipStream_t s, int nt, int G, int rpl, size_t lds, const void *M, int l, const SigmaOut &sig,
-                               void *X, void *W, DevInfo *info, int batch, int64_t stride, int rows) {
+                               void *X, void *W, DevInfo *info, int batch, int64_t stride, int rows, int corrections) {
   if (G == 16) {
     // fp32 rows come in pairs (8-byte units), fp64 rows singly
     if constexpr (sizeof(T) == 8) {
       switch (rpl) {
-        case 1: return launch_lds<T, TIn, 1, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
-        case 3: return launch_lds<T, TIn, 3, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
-        case 5: return launch_lds<T, TIn, 5, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
+        case 1: return launch_lds<T, TIn, 1, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows, corrections);
+        case 3: return launch_lds<T, TIn, 3, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows, corrections);
+        case 5: return launch_lds<T, TIn, 5, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows, corrections);
         default: break;
       }
     }
     switch (rpl) {
-      case 2: return launch_lds<T, TIn, 2, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
-      case 4: return launch_lds<T, TIn, 4, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
-      case 6: return launch_lds<T, TIn, 6, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
-      case 8: return launch_lds<T, TIn, 8, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows);
+      case 2: return launch_lds<T, TIn, 2, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows, corrections);
+      case 4: return launch_lds<T, TIn, 4, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows, corrections);
+      case 6: return launch_lds<T, TIn, 6, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows, corrections);
+      case 8: return launch_lds<T, TIn, 8, 16>(s, nt, lds, M, l, sig, X, W, info, batch, stride, rows, corrections);
       default: return hipErrorNotSupported;
     }
   }
@@ -2108,6 +2436,17 @@ hipError_t jacobi_init_device(rsvd_ctx *ctx) {
   return e;
 }
 
+// The two matrices that the corrections work in.
+static size_t corr_lds_bytes(rsvd_dtype dtype, int64_t l) {
+  return 2 * (size_t)(ceil_div(l, 16) * 16) * (size_t)corr_ld((int)l) * dtype_size(dtype);
+}
+// From 16 columns on (12: 44 -> 49 us), and where no CU has two problems of a batch: with 16 wavefronts and twice the LDS a problem they no longer run side
+// by side (1500 x (l = 24), fp32: 116 -> 242 us; 64 x (l = 16) 42 -> 33), which from 65 columns on they hardly did (300 x (l = 80) 625 -> 504).
+static bool lds_takes_corrections(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t l, int batch) {
+  return l >= 16 && l <= corr_max_order(dtype == RSVD_F32) && (batch <= ctx->cu_count || l > 64) &&
+         jacobi_lds_bytes(dtype, l) + corr_lds_bytes(dtype, l) + 4096 <= ctx->lds_per_block;
+}
+
 hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t l, const void *M,
                          int m_is_f64, const SigmaOut &sig, void *X, void *W, DevInfo *info, void *scratch,
                          size_t scratch_bytes, int batch, int64_t stride, int rows, const JacobiSlots *slots) {
@@ -2143,13 +2482,18 @@ hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t
   int nt = (int)align_up((size_t)npairs * G, 64);
   if (nt > 64 * G) nt = 64 * G;
   const int g = jacobi_rows_padded((int)l, G, (int)dtype_size(dtype)) / G;          // rows per lane
-  const size_t lds = jacobi_lds_bytes(dtype, l);
+  size_t lds = jacobi_lds_bytes(dtype, l);
+  const int corrections = lds_takes_corrections(ctx, dtype, l, batch) ? 1 : 0;
+  if (corrections) {
+    lds += corr_lds_bytes(dtype, l);
+    nt = 64 * kCorrWaves;
+  }
   ProfScope ps(ctx, s, PK_JACOBI);
   if (dtype == RSVD_F32) {
-    if (m_is_f64) return launch_lds_g<float, double>(s, nt, G, g, lds, M, (int)l, sig, X, W, info, batch, stride, rows);
-    return launch_lds_g<float, float>(s, nt, G, g, lds, M, (int)l, sig, X, W, info, batch, stride, rows);
+    if (m_is_f64) return launch_lds_g<float, double>(s, nt, G, g, lds, M, (int)l, sig, X, W, info, batch, stride, rows, corrections);
+    return launch_lds_g<float, float>(s, nt, G, g, lds, M, (int)l, sig, X, W, info, batch, stride, rows, corrections);
   }
-  return launch_lds_g<double, double>(s, nt, G, g, lds, M, (int)l, sig, X, W, info, batch, stride, rows);
+  return launch_lds_g<double, double>(s, nt, G, g, lds, M, (int)l, sig, X, W, info, batch, stride, rows, corrections);
 }
 
 }  // namespace rsvd
