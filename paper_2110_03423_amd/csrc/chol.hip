@@ -16,22 +16,6 @@ namespace rsvd {
 
 hipError_t gemm_launch_f64(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d);
 
-// 1 / sqrt(d) for d > 0: hardware estimate refined by two Newton steps (error below
-// 2 ulp); the pivot chain is the serial bottleneck, so it must be short.
-__device__ __forceinline__ double fast_rsqrt(double d) {
-  double y = __builtin_amdgcn_rsq(d);
-  y = y * (1.5 - 0.5 * d * y * y);
-  y = y * (1.5 - 0.5 * d * y * y);
-  return y;
-}
-
-// 64-bit lane read (the lane index is a compile-time constant where this is used).
-__device__ __forceinline__ double readlane_f64(double v, int lane) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-  return __hiloint2double(hi, lo);
-}
-
 // One workgroup of NB wavefronts factors an nb x nb block (nb <= 16 NB) and inverts the
 // factor.  The block is the sum of n_parts matrices spaced part_stride elements apart
 // (split-K partial Gram matrices are added here, in a fixed order).
@@ -50,9 +34,13 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
 //     diagonal block, updates that block with it and hands it over through LDS;        -- barrier
 //   * wavefront 0 factors block kb + 1 and publishes R, T and the flags, while the
 //     wavefronts r > kb take  block(r, J) -= R[kb][r]^T block(kb, J)  for their (other) slots,
-//     wavefront kb + 1 then leaves its row in LDS; behind that every wavefront but the factoring
-//     one writes its share of block row kb of R and block column kb of R^-1 (the transpose
-//     of Z).                                                                           -- barrier
+//     wavefront kb + 1 then leaves its row in LDS; block row kb of R and block column kb of R^-1 (the
+//     transpose of Z) are written by the wavefronts whose own rows are complete, or behind their updates
+//     by all but the factoring one while those are fewer than two.                     -- barrier
+// What bounds it, in cycles of one factorisation (l = 77, 109): a step takes the factoring wavefront 4200 for its block and about 2000
+// beside it, and the others about as long; 3400 to 4200 are the loads at the start and 1700 the stores at the end.  48100 -> 38900, 70000 -> 56400
+// by a shorter elimination of the blocks (5800 -> 4200), stores that take few instructions (3500 -> 2200 of a step in each wavefront)
+// and slots without work left out.  Whole calls: 10000 x 2000 fp32, l = 80, q = 2 794 -> 772 us; 2000 x 1000 fp64, l = 110, q = 2 1371 -> 1344.
 //   g0    : original squared column norms for the pivot test, or NULL to use the diagonal
 //   Rinv  : nb x nb block of R^-1 (ld ldri, type TOut, zeros below the diagonal)
 //   R     : same for R in fp64 (ld ldr), or NULL
@@ -63,24 +51,91 @@ template <int NB> struct CholLds {
   static constexpr size_t bytes = ((size_t)LP * LD + (size_t)NB * 16 * TLD + LP + 256) * sizeof(double);
 };
 
-// Factor and invert one 16 x 16 symmetric block held in the accumulator layout
-// (register v of lane L: row 4 v + L / 16, column L % 16).  One wavefront runs this
-// alone and a lone wavefront issues about one instruction every five cycles, so the cost
-// is the number of instructions per column; everything is arranged to keep that small.
-// Square-root-free elimination: column j is eliminated by ONE matrix-core instruction per
-// block, a rank-one update whose operands are row j itself (it already sits in the lanes
-// that feed k-slot j % 4), once for the block and once for the identity next to it.  The
-// update is not masked: rows that are already finished are copied out first (sd, sz) and
-// what the update leaves in their place is never read.  Rows are scaled by 1 / sqrt(d_j)
-// at the end.
-//   dblk : in  S_kk, out R_kk (valid on and above the diagonal)
-//   z    : out Z_kk = R_kk^-T (lower triangular)
+// Lane J of each group of sixteen to all of them.
+template <int J> __device__ __forceinline__ double row_bcast(double x) {
+  long v = __builtin_bit_cast(long, x);
+  v = __builtin_amdgcn_update_dpp(0L, v, 0x150 + J, 0xf, 0xf, true);       // row_newbcast
+  return __builtin_bit_cast(double, v);
+}
+
+// s[i] -= (t of lane i) * m for the rows I .. E - 1: one instruction a row (left to itself the compiler copies t first and adds up late,
+// with every copy kept until then).  An instruction that reads other lanes needs two more between it and the one that
+// wrote its operand: diag_eliminate sees to that.
+template <int I, int E>
+__device__ __forceinline__ void diag_rows(double (&s)[16], double t, double m) {
+  if constexpr (I < E && I < 16) {
+    asm volatile("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(s[I]) : "v"(t), "v"(m), "n"(I));
+    diag_rows<I + 1, E>(s, t, m);
+  }
+}
+
+// CHECK: pivots at or below their thresholds are dropped or set aside (the masks tell which).
+template <int J, bool CHECK>
+__device__ __forceinline__ void diag_eliminate(double (&s)[16], double t0, double m0, double thr, unsigned pos, int c, bool raise, int cols,
+                                               unsigned &dmask, unsigned &wmask) {
+  if constexpr (J < 16) {
+    if (J % 4 == 0 && J >= cols) return;
+    double d = row_bcast<J>(s[J]);                              // pivot S[J][J]
+    if constexpr (CHECK) {
+      const unsigned gt = (unsigned)__ballot(s[J] > thr);       // bit J: it exceeds the threshold of its column
+      if ((((gt & pos) >> J) & 1u) == 0u) {
+        if (raise && ((pos >> J) & 1u)) {                       // set aside: nothing of R but the raised diagonal element
+          wmask |= 1u << J;
+          d = row_bcast<J>(thr);
+          s[J] = c == J ? d : c > J ? 0.0 : s[J];
+        } else {
+          dmask |= 1u << J;                                     // dependent column: a row of zeros
+          d = 1.0;
+          s[J] = 0.0;
+        }
+      }
+    }
+    // The row over sqrt(d): the hardware's 1 / sqrt(d) is good to ~1e-7, the series that corrects it goes to the second power of its error.
+    // What is left to do with the row before, t0 and m0, stands between the steps of this chain.
+    constexpr int N = J > 0 ? (15 - J + 4) / 5 : 0, R0 = J + 1;
+    const double r0 = __builtin_amdgcn_rsq(d);
+    diag_rows<R0, R0 + N>(s, t0, m0);
+    __builtin_amdgcn_sched_barrier(0);
+    const double u = s[J] * r0, w = d * r0;
+    diag_rows<R0 + N, R0 + 2 * N>(s, t0, m0);
+    __builtin_amdgcn_sched_barrier(0);
+    const double e = fma(-w, r0, 1.0);
+    diag_rows<R0 + 2 * N, R0 + 3 * N>(s, t0, m0);
+    __builtin_amdgcn_sched_barrier(0);
+    const double g = fma(0.375, e, 0.5), ue = u * e;
+    diag_rows<R0 + 3 * N, R0 + 4 * N>(s, t0, m0);
+    __builtin_amdgcn_sched_barrier(0);
+    const double t = fma(ue, g, u);
+    diag_rows<R0 + 4 * N, R0 + 5 * N>(s, t0, m0);
+    __builtin_amdgcn_sched_barrier(0);
+    const double m = c == J ? 0.0 : t;
+    s[J] = t;
+    if constexpr (J < 15)
+      asm volatile("s_nop 1\n\tv_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf\n\ts_nop 1"
+                   : "+v"(s[J + 1]) : "v"(t), "v"(m), "n"(J + 1));
+    diag_eliminate<J + 1, CHECK>(s, t, m, thr, pos, c, raise, cols, dmask, wmask);
+  }
+}
+
+// Factor and invert one 16 x 16 symmetric block.  One wavefront runs this alone, and every step of the elimination
+// waits for the one before: the cost is the chain  pivot, one over its root, the row, the next pivot.
+// Elimination on [S | I] without the second half: lane c (the four groups of sixteen lanes do the same)
+// holds column c, register i row i.  With pivot j, row j is divided by sqrt(d_j) and the rows i > j take
+// S[i][c] -= R[j][i] R[j][c],  those of Z = R_kk^-T the same with Z[j][c] in the place of R[j][c].  Column c of Z begins with pivot c, when
+// column c of S is done with, and its entries are then -S[i][c] / d_c: kept without that factor, Z takes the place of S as it
+// stands, and one fused multiply-add a row, with an element that all lanes get from lane i, does both.  The products commute, so S stays
+// symmetric to the bit: Z is the inverse of this R, to the rounding of its elements, however small a pivot is (with rows scaled
+// by 1 / d_j instead, of which one factor of each product has it, the two triangles drift apart by the rounding of the large elements).
+// A block takes 4200 cycles (16 pivots of about 200, and its way from and to LDS); as rank-one updates by matrix instructions, 64 cycles for
+// S and as many for Z, 5800.  Errors of R and R^-1 against 80-bit arithmetic, orders 16 to 128, columns over none to six decades: R^T R - G
+// 0.76 to 0.99 of what they were, R^-1 R - 1 0.43 to 0.68 (with one correction of 1 / r below: 0.97 to 1.3).
+//   blk  : 16 x 16 doubles in LDS, row-major: S_kk; what it holds afterwards is of no use
+//   dblk, z : out, in the accumulator layout (register v of lane L: row 4 v + L / 16, column L % 16):
+//          R_kk (valid on and above the diagonal), Z_kk = R_kk^-T (lower triangular)
 //   thr  : lane c holds tau * (reference squared norm of column c); pos: bit c set when that norm is > 0
 //          (and not below the caller's absolute floor)
 //   piv  : 16 doubles of LDS scratch
-//   cols : pivots from here on are padding, which is the identity, and are left out four at a time (0.2 us each; asked for
-//          one by one, the branches cost the chain 0.1 us a pivot).  16 in the kernel for larger orders: no gain was
-//          seen there.
+//   cols : rows and columns from here on are padding, of which this makes the identity; pivots are left out four at a time.
 //   raise: a pivot at or below its threshold (with a usable reference norm) does not drop its column but SETS IT
 //          ASIDE: the pivot takes the value of the threshold, the row is not used to eliminate anything (its
 //          part of R is the diagonal element alone), so the column comes out of Q = Y R^-1 as what is left of it
@@ -88,63 +143,79 @@ template <int NB> struct CholLds {
 //          still carries magnified to where the next round can resolve it, and with no large entries in R^-1
 //          (eliminating with a raised pivot instead couples the weak rows by ratios far above one, and their
 //          inverse overflowed on a sketch with ~100 such rows)
+//   look : look at each pivot when it is due, 45 cycles a pivot more.  Otherwise they are looked at when all are done, and the
+//          elimination is done again if one was too small: the caller asks for a look once there was such a pivot in its call.
 //   returns the 16-bit mask of dropped (dependent) columns, and in bits 16..31 that of the columns set aside
-__device__ __forceinline__ unsigned diag_factor(f64x4 &dblk, f64x4 &z, double thr, unsigned pos, int lane,
-                                                double *piv, bool raise, int cols) {
+__device__ __forceinline__ unsigned diag_factor(double *blk, f64x4 &dblk, f64x4 &z, double thr, unsigned pos, int lane,
+                                                double *piv, bool raise, int cols, bool look) {
   const int lr = lane >> 4, lc = lane & 15;
-  double mrow[4];
+  double s[16];
+  auto load = [&]() {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) mrow[q] = (lr == q) ? 1.0 : 0.0;
+    for (int i = 0; i < 16; ++i) s[i] = blk[i <= lc ? i * 16 + lc : lc * 16 + i];       // (the upper triangle counts)
+    if (cols < 16) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) z[v] = (4 * v + lr == lc) ? 1.0 : 0.0;
-  f64x4 sd, sz;                             // (rows of the padding: those of the identity, as they come in)
-#pragma unroll
-  for (int v = 0; v < 4; ++v) sd[v] = sz[v] = (4 * v + lr == lc && 4 * v >= cols) ? 1.0 : 0.0;
-  unsigned dmask = 0, wmask = 0;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    if (j % 4 == 0 && j >= cols) break;
-    const int q = j & 3, v4 = j >> 2;
-    double rowv = dblk[v4];
-    const double d = readlane_f64(rowv, 16 * q + j);            // pivot S[j][j]
-    const unsigned gt = (unsigned)__ballot(d > thr);            // bit c: d exceeds the threshold of column c
-    double y = __builtin_amdgcn_rcp(d);
-    y = fma(fma(-d, y, 1.0), y, y);        // the hardware estimate is good to ~1e-8: one step squares that
-    if (!(((gt & pos) >> j) & 1u)) {                            // pivot at the rounding level of the Gram matrix (rare)
-      y = 0.0;                                                  // no elimination with this row
-      if (raise && ((pos >> j) & 1u)) {
-        const double dr = readlane_f64(thr, j);                 // lane j holds the threshold of column j
-        wmask |= 1u << j;
-        if (lane == 16 * q + j) rowv = dr;                      // the diagonal element of the row takes the raised value
-      } else {
-        dmask |= 1u << j;                                       // dependent column
-      }
+      for (int i = 0; i < 16; ++i)
+        if (i == lc && i >= cols) s[i] = 1.0;
     }
-    const double b_d = rowv * mrow[q];
-    const double b_z = z[v4] * mrow[q];
-    const double a_op = b_d * -y;
-    sd[v4] += b_d;
-    sz[v4] += b_z;
-    dblk = Mfma<double>::run(a_op, b_d, dblk);
-    z = Mfma<double>::run(a_op, b_z, z);
-  }
-  // pivot of row i = diagonal element of the saved row: pass it along the lane row through LDS
+  };
+  auto store = [&]() {
+    if (lane < 16) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v)
-    if (lc == 4 * v + lr) piv[lc] = sd[v];
+      for (int i = 0; i < 16; ++i) blk[i * 16 + lc] = s[i];
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+  unsigned dmask = 0, wmask = 0;
+  double r;                                      // R[c][c] in lane c
+  auto diagonal = [&]() {
+    r = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) r = i == lc ? s[i] : r;
+  };
+  bool done = false;
+  if (!look) {
+    load();
+    diag_eliminate<0, false>(s, 0.0, 0.0, thr, pos, lc, raise, cols, dmask, wmask);
+    diagonal();                                  // (a pivot below zero leaves NaN)
+    const unsigned need = cols < 16 ? (1u << cols) - 1u : 0xffffu;
+    done = ((unsigned)__ballot(r * r > thr) & pos & need) == need;
+  }
+  if (!done) {
+    load();
+    diag_eliminate<0, true>(s, 0.0, 0.0, thr, pos, lc, raise, cols, dmask, wmask);
+    diagonal();
+  }
+  double rv = __builtin_amdgcn_rcp(r);
+  rv = fma(fma(-r, rv, 1.0), rv, rv);
+  rv = fma(fma(-r, rv, 1.0), rv, rv);
+  rv = ((dmask >> lc) & 1u) ? 0.0 : rv;
+  const double ny = ((wmask >> lc) & 1u) ? 0.0 : -rv * rv;
+  store();
+  if (lane < 16) piv[lc] = rv;
   __builtin_amdgcn_wave_barrier();
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    const double x = piv[4 * v + lr];
-    double rv = __builtin_amdgcn_rsq(x);
-    rv = rv * (1.5 - 0.5 * x * rv * rv);
-    rv = rv * (1.5 - 0.5 * x * rv * rv);
-    if ((dmask >> (4 * v + lr)) & 1u) rv = 0.0;
-    dblk[v] = sd[v] * rv;
-    if (((wmask >> (4 * v + lr)) & 1u) && lc != 4 * v + lr) dblk[v] = 0.0;      // set aside: the diagonal alone
-    z[v] = sz[v] * rv;
+    const int row = 4 * v + lr;
+    const double x = blk[row * 16 + lc];
+    dblk[v] = x;
+    z[v] = lc < row ? x * ny : lc == row ? piv[row] : 0.0;
   }
   return dmask | (wmask << 16);
+}
+
+// Stores through a buffer descriptor: p plus `lane_bytes` plus `bytes` (the same for all lanes), and none for lane_bytes = kNoStore, which is
+// out of the range that the descriptor states whatever `bytes` is.  The matrices here are a few MB at most.
+constexpr unsigned kNoStore = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t store_buffer(void *p) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7fffffff, 0x00027000);
+}
+__device__ __forceinline__ void store_at(__amdgpu_buffer_rsrc_t buf, unsigned lane_bytes, unsigned bytes, double x) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), buf, lane_bytes, bytes, 0);
+}
+__device__ __forceinline__ void store_at(__amdgpu_buffer_rsrc_t buf, unsigned lane_bytes, unsigned bytes, float x) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), buf, lane_bytes, bytes, 0);
 }
 
 template <typename TOut, int NB>
@@ -188,7 +259,7 @@ __global__ __launch_bounds__(NB * 64) void chol_mfma_kernel(const double *__rest
   double *Sm = smem;                       // LP x LD: rows of [R | Z]
   double *Td = Sm + LP * LD;               // NB x 16 x TLD: R_kk^-1
   double *d0 = Td + NB * 16 * TLD;         // LP: reference squared norms for the pivot test
-  double *Dg = d0 + LP;                    // 4 x 64: the diagonal block in hand, accumulator layout
+  double *Dg = d0 + LP;                    // 16 x 16: the diagonal block in hand
   __shared__ double piv[16];
   __shared__ int n_dead, n_weak, bad;
   __shared__ unsigned wmask_sh;            // rows of the current pivot block that were set aside
@@ -196,9 +267,10 @@ __global__ __launch_bounds__(NB * 64) void chol_mfma_kernel(const double *__rest
   const int tid = threadIdx.x, lane = tid & 63;
   // Block row of this wavefront; the wavefront of row 0 also factors the diagonal blocks.  Wavefronts w and w + 4
   // share a SIMD unit and its matrix pipe: the one next to the factoring wavefront takes row 1, which is complete
-  // after the first step, so that the factorisations that follow have the pipe to themselves.
-  const int wv = tid >> 6;
-  const int wr = NB > 4 ? (wv == 4 ? 1 : (wv == 1 ? 4 : wv)) : wv;
+  // after the first step, so that the factorisations that follow have the pipe to themselves; of two others that
+  // share one, one has a low row and is done early.
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = NB > 4 ? (wv == 4 ? 1 : wv > 0 && wv < 4 ? wv + 1 : wv) : wv;
   const int lr = lane >> 4, lc = lane & 15;
   // register slot t of wavefront wr holds column block (wr + t) mod NB: slot 0 is the
   // diagonal block, slots 1 .. NB-1-wr the S blocks to its right, the rest the Z blocks
@@ -237,17 +309,19 @@ __global__ __launch_bounds__(NB * 64) void chol_mfma_kernel(const double *__rest
     }
   }
 
+  // Too small pivots are expected where the call has met some (a panel that lacks directions lacks them in every round).  The
+  // counts may be those of another problem of a batch, or be changing: the result is the same with a look and without.
+  bool look = info != nullptr && (info->refilled | info->raised) != 0;
   // Wavefront 0: factor the block in Dg as diagonal block kb, publish R_kk, T = R_kk^-1 and the flags.
   auto factor_block = [&](int kb) {
     const int k0 = kb * 16;
     f64x4 dblk, z;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) dblk[v] = Dg[v * 64 + lane];
     const double d0c = d0[k0 + lc];
     const unsigned pos = (unsigned)__ballot(d0c > 0.0 && d0c >= floor_abs) & 0xffffu;
     // pivot threshold: tau times the column's reference norm, or the same for every column (abs_thr > 0:
     // rounds that work on a panel whose resolved columns have unit length)
-    const unsigned masks = diag_factor(dblk, z, abs_thr > 0.0 ? abs_thr : tau * d0c, pos, lane, piv, raise != 0, 16);
+    const unsigned masks = diag_factor(Dg, dblk, z, abs_thr > 0.0 ? abs_thr : tau * d0c, pos, lane, piv, raise != 0, 16, look);
+    look |= masks != 0u;
     const unsigned dmask = masks & 0xffffu, wmask = masks >> 16;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -278,16 +352,15 @@ __global__ __launch_bounds__(NB * 64) void chol_mfma_kernel(const double *__rest
     }
   };
 
+  const __amdgpu_buffer_rsrc_t R_buf = store_buffer(R), X_buf = store_buffer(Rinv), E_buf = store_buffer(Rinv_elim);
   if (wr == 0) { put_diag(); put_row(); }
-  __syncthreads();
-  if (wr == 0) factor_block(0);
   __syncthreads();
 
 #pragma unroll 1
-  for (int kb = 0; kb < NB; ++kb) {
+  for (int kb = -1; kb < NB; ++kb) {                // (-1: the first diagonal block is factored)
     const int k0 = kb * 16;
     // ---- row kb times T^T, in place: wavefront J takes column block J (R to the right of the diagonal, Z to the left)
-    if (wr != kb) {
+    if (kb >= 0 && wr != kb) {
       double ta[4], bo[4];
       double *blk = Sm + (k0 + lr) * LD + 16 * wr + lc;
 #pragma unroll
@@ -313,68 +386,90 @@ __global__ __launch_bounds__(NB * 64) void chol_mfma_kernel(const double *__rest
         put_diag();
       }
     }
-    __syncthreads();
-    if (wr > kb) {
+    if (kb >= 0) __syncthreads();
+    if (kb >= 0 && wr > kb) {
       // ---- trailing rows: block(wr, J) -= R[kb][wr]^T block(kb, J)
+      // (slots in use: the S blocks and the Z blocks up to kb, which are the first NB - wr + kb + 1; two at a time, whose
+      // matrix-core instructions do not wait for each other)
       double na[4], b[NB][4];
 #pragma unroll
       for (int s = 0; s < 4; ++s) na[s] = -Sm[(k0 + 4 * s + lr) * LD + 16 * wr + lc];
 #pragma unroll
       for (int t = 0; t < NB; ++t) {
         const int J = col_block(t);
-        const bool on = !(J > kb && J < wr);       // an S slot (J >= wr) or a touched Z slot (J <= kb)
         const double *src = (J == kb) ? Td + (k0 + lc) * TLD + lr                   // Z_kk = T_kk^T
                                       : Sm + (k0 + lr) * LD + 16 * J + lc;
         const int step = (J == kb) ? 4 : 4 * LD;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) b[t][s] = on ? src[s * step] : 0.0;      // untouched slots take a zero update
+        for (int s = 0; s < 4; ++s) b[t][s] = src[s * step];
       }
-      // (slot loop innermost: consecutive matrix-core instructions are independent)
-      if (wr == kb + 1) {
+      const int used = NB - wr + kb + 1, first = wr == kb + 1 ? 1 : 0;           // (the diagonal block of row kb + 1 is up to date)
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+      for (int t = 0; t < NB; t += 2) {
+        if (t >= used) break;
 #pragma unroll
-          for (int t = 1; t < NB; ++t) acc[t] = Mfma<double>::run(na[s], b[t][s], acc[t]);
-        put_row();
-      } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-          for (int t = 0; t < NB; ++t) acc[t] = Mfma<double>::run(na[s], b[t][s], acc[t]);
+        for (int s = 0; s < 4; ++s) {
+          if (t > 0 || first == 0) acc[t] = Mfma<double>::run(na[s], b[t][s], acc[t]);
+          if (t + 1 < NB) acc[t + 1] = Mfma<double>::run(na[s], t + 1 < used ? b[t + 1][s] : 0.0, acc[t + 1]);
+        }
       }
+      if (first) put_row();
     } else if (wr == 0 && kb + 1 < NB) {
       factor_block(kb + 1);
     }
     // ---- block row kb of R and block column kb of R^-1 are written out (R^-1 = Z^T: column k0 + c of R^-1 is
-    // row k0 + c of Z) by every wavefront but the one that factors, each behind its update: off the critical path
-    const bool last = kb + 1 == NB;
-    if (wr != 0 || last) {
-      const int parts = NB - 1 + (last ? 1 : 0), me = wr == 0 ? NB - 1 : wr - 1;
-      const int ldr_i = (int)ldr, ldri_i = (int)ldri;      // orders here are at most a few hundred
+    // row k0 + c of Z), off the critical path: by the wavefronts whose rows are complete once there are two of them, before by
+    // every one but the one that factors, behind its update, and in the end by all
+    const bool last = kb + 1 == NB, few = kb >= 2 && !last;
+    if (kb >= 0 && (last || (wr != 0 && (!few || wr <= kb)))) {
+      const int parts = last ? NB : few ? kb : NB - 1, me = last ? wr : wr - 1;
+      // A wavefront takes whole rows of R, and four rows of sixteen columns of R^-1 at a time: what differs from one to the next
+      // is the same for all lanes.  Instructions and branches are what this costs, so there are none for the edges: rows beyond the last
+      // are the last once more, and lanes beyond it store out of the range of the buffer, where nothing happens.
+      const int lds_c = min(lane, LP - 1), lds_c2 = min(64 + lane, LP - 1);
       if (R != nullptr) {
         const int rows = min(16, nb - k0);
-        for (int c = lane; c < nb; c += 64) {
-#pragma unroll 4
-          for (int i = me; i < rows; i += parts) {
-            const int r = k0 + i;
-            R[r * ldr_i + c] = (c >= r) ? Sm[r * LD + c] : 0.0;
+        const unsigned off = lane < nb ? 8u * lane : kNoStore, off2 = 64 + lane < nb ? 8u * (64 + lane) : kNoStore;
+        for (int i0 = me; i0 < rows; i0 += 4 * parts) {
+          double v[4], v2[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int r = k0 + min(i0 + parts * u, rows - 1);
+            v[u] = Sm[r * LD + lds_c];
+            if (LP > 64) v2[u] = Sm[r * LD + lds_c2];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int r = k0 + min(i0 + parts * u, rows - 1);
+            store_at(R_buf, off, 8u * (unsigned)(r * (int)ldr), lane >= r ? v[u] : 0.0);
+            if (LP > 64) store_at(R_buf, off2, 8u * (unsigned)(r * (int)ldr), 64 + lane >= r ? v2[u] : 0.0);
           }
         }
       }
-      const int c = k0 + lc;
-      if (c < nb) {
-#pragma unroll 4
-        for (int r = lr + 4 * me; r < nb; r += 4 * parts) {
-          double v = 0.0;
-          if (r <= c) v = (r >= k0) ? Td[r * TLD + lc] : Sm[c * LD + r];
-          Rinv[r * ldri_i + c] = (TOut)v;
-          if (Rinv_elim != nullptr) Rinv_elim[r * (int)ldre + c] = aside[c] ? 0.0 : v;
+      const int c = k0 + lc, groups = (nb + 3) / 4;
+      const bool cleared = Rinv_elim != nullptr && aside[c];
+      const unsigned off = (unsigned)sizeof(TOut) * (unsigned)(lr * (int)ldri + c), off_e = 8u * (unsigned)(lr * (int)ldre + c);
+      for (int g0 = me; g0 < groups; g0 += 4 * parts) {
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int r0 = 4 * min(g0 + parts * u, groups - 1);
+          const double *src = r0 >= k0 ? Td + r0 * TLD + lr * TLD + lc : Sm + c * LD + r0 + lr;
+          v[u] = *src;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int r0 = 4 * min(g0 + parts * u, groups - 1);
+          const bool in = r0 + lr < nb && c < nb;
+          const double x = r0 + lr <= c ? v[u] : 0.0;
+          store_at(X_buf, in ? off : kNoStore, (unsigned)sizeof(TOut) * (unsigned)(r0 * (int)ldri), (TOut)x);
+          if (Rinv_elim != nullptr) store_at(E_buf, in ? off_e : kNoStore, 8u * (unsigned)(r0 * (int)ldre), cleared ? 0.0 : x);
         }
       }
     }
-    __syncthreads();
+    if (!last) __syncthreads();
   }
-  if (tid == 0) {
+  if (tid == 0) {                          // (the counts are this wavefront's own)
     if (info != nullptr) {
       if (n_dead > 0) atomicAdd(&info->refilled, n_dead);
       if (n_weak > 0) atomicAdd(&info->raised, n_weak);
@@ -495,6 +590,7 @@ __global__ __launch_bounds__(kPanelThreads) void panel_qr_kernel(const PanelPara
     }
   }
   int refilled = 0, bad = 0;
+  bool look = P.info != nullptr && P.info->refilled != 0;
   for (int round = 0; round < P.rounds; ++round) {
     __syncthreads();
     // ---- Gram matrix: the wavefronts share the rows
@@ -525,15 +621,10 @@ __global__ __launch_bounds__(kPanelThreads) void panel_qr_kernel(const PanelPara
     // ---- factor and inverse (wavefront 0); the padding of the Gram matrix is the identity
     if (wave == 0) {
       f64x4 d, z;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        d[v] = Gt[(4 * v + lr) * 16 + lc];
-        if (4 * v + lr == lc && lc >= l) d[v] = 1.0;
-      }
       const double d0 = lc < l ? Gt[lc * 17] : 1.0;
       if (__ballot(!(fabs(d0) <= 1.79e308))) bad = 1;
       const unsigned pos = (unsigned)__ballot(d0 > 0.0) & 0xffffu;
-      const unsigned dead = diag_factor(d, z, P.tau * d0, pos, lane, piv, false, l) & ((1u << l) - 1u);
+      const unsigned dead = diag_factor(Gt, d, z, P.tau * d0, pos, lane, piv, false, l, look) & ((1u << l) - 1u);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int row = 4 * v + lr;
@@ -541,6 +632,7 @@ __global__ __launch_bounds__(kPanelThreads) void panel_qr_kernel(const PanelPara
         Xl[lc * LD + row] = lc <= row ? (float)z[v] : 0.f;       // R^-1 = Z^T
       }
       refilled += __popc(dead);
+      look |= dead != 0u;
       if (lane == 0) dead_sh = dead;
     }
     __syncthreads();
