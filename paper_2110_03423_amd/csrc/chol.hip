@@ -847,12 +847,12 @@ static hipError_t launch_block(hipStream_t s, const double *G, int64_t ldg, int 
   return hipGetLastError();
 }
 
-// The kernels of this file that need more LDS than the default limit of a launch: raised once per context.
+// The kernels of this file that need more LDS than the default limit of a launch (64 KB): raised once per context.
 template <typename TOut>
 static hipError_t chol_raise_lds_limits() {
   hipError_t e = hipSuccess;
 #define RSVD_CHOL_ATTR(NBV)                                                                              \
-  if (e == hipSuccess)                                                                                   \
+  if (e == hipSuccess && CholLds<NBV>::bytes > 60 * 1024)                                                \
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(&chol_mfma_kernel<TOut, NBV>),                \
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)CholLds<NBV>::bytes)
   RSVD_CHOL_ATTR(1); RSVD_CHOL_ATTR(2); RSVD_CHOL_ATTR(3); RSVD_CHOL_ATTR(4);
