@@ -14,8 +14,8 @@ hipError_t gemm_split_init_device(rsvd_ctx *ctx) {
   return e == hipSuccess ? split_init_t() : e;
 }
 
-// Which products are split, by their shape (times in us, fp32 kernel against split one).  Up to 32 columns both kernels wait for
-// memory and the fp32 one needs no conversion (65536 x 16384, l = 16: 5.8 TB/s), and below 2^29 multiply-adds (2000 x 500, l = 33:
+// Which products are split, by their shape (times in us, fp32 kernel against split one).  Up to 32 columns (of A^T X: what is left of
+// them by gemm_stream_kernel) both kernels wait for memory and the fp32 one needs no conversion (65536 x 16384, l = 16: 5.8 TB/s), and below 2^29 multiply-adds (2000 x 500, l = 33:
 // 22, 25) the longer prologue of the large tiles costs more than the faster instruction brings.  Where both operands are aligned for
 // 16-byte loads the fp32 kernel also wins on
 //  - a k range of a few k-tiles, unless one column tile of 96 to 144 shares the traffic of A: 1000000 x 64, l = 64: 131, 217; 69568 x

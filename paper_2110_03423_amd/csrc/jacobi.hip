@@ -2234,7 +2234,8 @@ static int jb_block_width(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t l) {
 //         96 1064, 571, 583 against 582, 303, 365
 // In fp32 the line lies where all three are faster (at 96 one is not).  In fp64 the blocks win at 64 already, and lose at 56; the orders between
 // are not measured, and the line is the first order behind them.  Factors with many equal values, which the corrections leave to sweeps, gain
-// less: l = 98 with 90 of them, 45 matrices, fp64 1318 -> 1306, fp32 514 -> 629.
+// less: l = 98 with 90 of them, 45 matrices, fp64 1318 -> 1306, fp32 514 -> 629.  (The one workgroup of these figures had no corrections; up to l = 80
+// and 64 it has them by now and takes less, see lds_takes_corrections.)
 bool jacobi_prefers_blocks(rsvd_dtype dtype, int64_t l) { return l >= (dtype == RSVD_F32 ? 97 : 65); }
 
 // Scratch of the block path: header, Mt, Jt, norms, ranks.
