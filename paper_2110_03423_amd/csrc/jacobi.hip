@@ -233,8 +233,8 @@ __host__ __device__ inline int jacobi_ldm(int l, int G, int elem_size) {
 // on unordered columns, where sweeps converge slowly throughout, -9 to +13 %; half of the values within 1e-5 -14 to +18 %.  X and W end
 // closer to orthogonal (|X^T X - I| / sqrt(l), fp32, l = 80: 18 -> 0.9 eps).
 // What bounds a product: 20 dependent matrix instructions a block at l = 80 and the barrier behind them; blocks of a whole matrix are read row by row
-// from LDS, those below the diagonal of symmetric ones are copies.  (As first written, 30 KB of code with registers kept in scratch memory, a correction
-// took 55 us at l = 80.)
+// from LDS, those below the diagonal of symmetric ones are copies.  (As first written, 30 KB of code with registers kept in scratch memory in loops, a
+// correction took 55 us at l = 80.  fp32 has none there now, fp64 keeps 4 to 16 registers of a lane in it.)
 constexpr int kPolishSteps = 10;
 
 // Largest x for a series cut behind X^2 / 2 (1), X^3 (2), X^5 (3) and X^9 (4).  The 2-norm of X is x / 1.41 if all of it is one rotation and
@@ -534,10 +534,10 @@ __device__ __forceinline__ bool lds_corrections(T *Mc, T *Jc, int ldm, T *B0, T 
 // such array per problem of a batch, `stride` bytes apart) instead of LDS, for orders whose two matrices do not fit
 // there together (fp64 beyond 96).  Its columns travel through the cache of the CU: a round takes longer, but
 // the problems of a batch still run side by side, one workgroup each.
-template <typename T, typename TIn, int RPL, int G, bool JG = false>
+template <typename T, typename TIn, int RPL, int G, bool JG = false, bool CORR = false>
 __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restrict__ M, int l, SigmaOut sig,
                                                          T *__restrict__ X, T *__restrict__ W, DevInfo *info,
-                                                         int64_t stride, int rows, T *__restrict__ Jglobal, int corrections) {
+                                                         int64_t stride, int rows, T *__restrict__ Jglobal) {
   extern __shared__ __attribute__((aligned(16))) double lds_raw[];
   if (blockIdx.x != 0) {              // batched launch: one problem per workgroup, `stride` bytes apart
     const int64_t off = (int64_t)blockIdx.x * stride;
@@ -549,14 +549,14 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
   const int ldm = jacobi_ldm(l, G, (int)sizeof(T));
   T *Mc = reinterpret_cast<T *>(lds_raw);
   T *Jc = JG ? Jglobal : Mc + (size_t)l * ldm;
-  T *B0 = Mc + (size_t)(JG ? 1 : 2) * l * ldm, *B1 = B0 + (corrections ? (l + 15) / 16 * 16 * corr_ld(l) : 0);      // (work of the corrections)
+  T *B0 = Mc + (size_t)(JG ? 1 : 2) * l * ldm, *B1 = B0 + (CORR ? (l + 15) / 16 * 16 * corr_ld(l) : 0);      // (work of the corrections)
   T *nrm = B1 + (B1 - B0);
   int *rnk = reinterpret_cast<int *>(nrm + l);
   __shared__ int rotations;
   __shared__ unsigned turned_sum;
-  __shared__ T wave_sum[16], unit[128];
-  __shared__ JacLevel lev[kJacLevels][kJacGroups];
-  constexpr bool CORR = !JG && CorrCfg<T, RPL>::kFits;
+  __shared__ T wave_sum[16];
+  __shared__ __attribute__((aligned(16))) JacLevel lev[kJacLevels][kJacGroups];
+  static_assert(!CORR || (!JG && CorrCfg<T, RPL>::kFits), "no room for the matrices of the corrections");
   __shared__ double corr_norms[CORR ? 16 * RPL : 1];
   __shared__ float corr_sums[CORR ? kCorrWaves : 1][3];
 
@@ -592,7 +592,8 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
       Jc[c * ldm + r] = (T)0;
     }
     // (what lies between the rows of the corrections' matrices is read as columns of J beyond the last one, against zeros: it has to be finite)
-    for (T *w = B0 + tid; w < nrm; w += nt) *w = (T)0;
+    if (CORR)
+      for (T *w = B0 + tid; w < nrm; w += nt) *w = (T)0;
     for (int idx = tid; idx < l * l; idx += nt) {
       const int r = idx / l, c = idx - r * l;
       const T v = (T)M[idx];
@@ -628,6 +629,7 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
   int sweeps = 0;
   bool converged = (l < 2);
   float rho_prev = -1.f;
+  bool corrections = CORR;
   constexpr int NV = RPL / (8 / (int)sizeof(T));
   while (!converged && sweeps < kJacobiMaxSweeps) {
     ++sweeps;
@@ -676,7 +678,7 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
         converged = lds_corrections<T, RPL>(Mc, Jc, ldm, B0, B1, l, tol, floor2, corr_norms, corr_sums, applied);
         // Corrections that did not get there have met a cluster, whose angles stay large however small the inner products: the rest is left to
         // sweeps, about whose rate the ones before say nothing.
-        if (applied > 0) { rho_prev = -1.f; corrections = 0; }
+        if (applied > 0) { rho_prev = -1.f; corrections = false; }
       }
     }
   }
@@ -685,6 +687,8 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
   // angles are large and, less, to the other where they are small (fp64, l = 61: J^T J - I -31 eps on the diagonal behind five sweeps, -5 behind
   // eight), and M has the same factors.  They are taken out of both (largest error of a value, factor of a
   // Gaussian matrix, fp64 l = 61 6.8 -> 3.6 eps, over six decades 40 -> 4.0; fp32 l = 80 7.8 -> 2.1).
+  static_assert(sizeof(lev) >= 128 * sizeof(T), "one factor for each column");
+  T *unit = reinterpret_cast<T *>(&lev[0][0]);        // (the pair order is no longer needed)
   for (int j = tid >> 4; j < l; j += nt >> 4) {
     double sm = 0.0, sj = 0.0;
     for (int r = tid & 15; r < l; r += 16) {
@@ -2345,11 +2349,21 @@ static hipError_t jacobi_block_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype d
   return hipGetLastError();
 }
 
+// (The corrections have kernels of their own: with them a kernel takes 99 to 128 registers, without 32 to 72, and twice as many
+// wavefronts of it fit a CU.)
 template <typename T, typename TIn, int RPL, int G>
 static hipError_t launch_lds(hipStream_t s, int nt, size_t lds, const void *M, int l, const SigmaOut &sig, void *X, void *W,
-                             DevInfo *info, int batch, int64_t stride, int rows, int corrections) {
+                             DevInfo *info, int batch, int64_t stride, int rows, bool corrections) {
+  if constexpr (CorrCfg<T, RPL>::kFits) {
+    if (corrections) {
+      hipLaunchKernelGGL((jacobi_lds_kernel<T, TIn, RPL, G, false, true>), dim3(batch), dim3(nt), lds, s, (const TIn *)M, l,
+                         sig, (T *)X, (T *)W, info, stride, rows, (T *)nullptr);
+      return hipGetLastError();
+    }
+  }
+  if (corrections) return hipErrorInvalidValue;
   hipLaunchKernelGGL((jacobi_lds_kernel<T, TIn, RPL, G>), dim3(batch), dim3(nt), lds, s, (const TIn *)M, l,
-                     sig, (T *)X, (T *)W, info, stride, rows, (T *)nullptr, corrections);
+                     sig, (T *)X, (T *)W, info, stride, rows, (T *)nullptr);
   return hipGetLastError();
 }
 // fp64 orders 97 .. 128: M in LDS, J in global memory
@@ -2358,14 +2372,14 @@ static hipError_t launch_lds_jg(hipStream_t s, int nt, size_t lds, const void *M
                                 DevInfo *info, int batch, int64_t stride, int rows, void *Jglobal) {
   hipLaunchKernelGGL((jacobi_lds_kernel<double, double, RPL, 16, true>), dim3(batch), dim3(nt), lds, s,
                      (const double *)M, l, sig, (double *)X, (double *)W, info, stride, rows,
-                     (double *)Jglobal, 0);
+                     (double *)Jglobal);
   return hipGetLastError();
 }
 
 // rows per lane = padded rows / G
 template <typename T, typename TIn>
 static hipError_t launch_lds_g(hipStream_t s, int nt, int G, int rpl, size_t lds, const void *M, int l, const SigmaOut &sig,
-                               void *X, void *W, DevInfo *info, int batch, int64_t stride, int rows, int corrections) {
+                               void *X, void *W, DevInfo *info, int batch, int64_t stride, int rows, bool corrections) {
   if (G == 16) {
     // fp32 rows come in pairs (8-byte units), fp64 rows singly
     if constexpr (sizeof(T) == 8) {
@@ -2387,13 +2401,27 @@ static hipError_t launch_lds_g(hipStream_t s, int nt, int G, int rpl, size_t lds
   return hipErrorNotSupported;
 }
 
+// The two matrices that the corrections work in.
+static size_t corr_lds_bytes(rsvd_dtype dtype, int64_t l) {
+  return 2 * (size_t)(ceil_div(l, 16) * 16) * (size_t)corr_ld((int)l) * dtype_size(dtype);
+}
+
 // The kernels of this file are launched with up to 156 KB of dynamic LDS (jb_flow_kernel: kJgLds): the limit is raised here, once per
-// context (with its device current), for every instantiation the dispatch above can reach.
+// context (with its device current), for every instantiation the dispatch above can reach and whose largest order asks for more than
+// the default of 64 KB (each call takes 3 to 4 us of rsvd_create).
 template <typename T, typename TIn, int RPL>
 static void raise_lds_limit_lds(hipError_t &e) {
-  if (e == hipSuccess)
+  constexpr rsvd_dtype dtype = sizeof(T) == 4 ? RSVD_F32 : RSVD_F64;
+  const size_t bytes = jacobi_lds_bytes(dtype, 16 * RPL);
+  if (e == hipSuccess && bytes > 60 * 1024)
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(&jacobi_lds_kernel<T, TIn, RPL, 16>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
+  if constexpr (CorrCfg<T, RPL>::kFits) {
+    const int64_t l = 16 * RPL < corr_max_order(sizeof(T) == 4) ? 16 * RPL : corr_max_order(sizeof(T) == 4);
+    if (e == hipSuccess && jacobi_lds_bytes(dtype, l) + corr_lds_bytes(dtype, l) > 60 * 1024)
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(&jacobi_lds_kernel<T, TIn, RPL, 16, false, true>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
+  }
 }
 template <int RPL>
 static void raise_lds_limit_jg(hipError_t &e) {
@@ -2437,14 +2465,11 @@ hipError_t jacobi_init_device(rsvd_ctx *ctx) {
   return e;
 }
 
-// The two matrices that the corrections work in.
-static size_t corr_lds_bytes(rsvd_dtype dtype, int64_t l) {
-  return 2 * (size_t)(ceil_div(l, 16) * 16) * (size_t)corr_ld((int)l) * dtype_size(dtype);
-}
-// From 16 columns on (12: 44 -> 49 us), and where no CU has two problems of a batch: with 16 wavefronts and twice the LDS a problem they no longer run side
-// by side (1500 x (l = 24), fp32: 116 -> 242 us; 64 x (l = 16) 42 -> 33), which from 65 columns on they hardly did (300 x (l = 80) 625 -> 504).
+// From 16 columns on (12: 44 -> 49 us), and where no CU has two problems of a batch: with 16 wavefronts, twice the registers and twice the LDS a problem
+// they no longer run side by side (fp32, q = 2, us without and with: 1500 x (l = 24) 89, 233; 600 x 48 223, 262; 300 x 72 369, 419; 300 x 80 450, 484;
+// 256 x 48 128, 99; fp64 600 x 40 369, 402; 300 x 64 550, 492; 256 x 64 377, 274).
 static bool lds_takes_corrections(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t l, int batch) {
-  return l >= 16 && l <= corr_max_order(dtype == RSVD_F32) && (batch <= ctx->cu_count || l > 64) &&
+  return l >= 16 && l <= corr_max_order(dtype == RSVD_F32) && batch <= ctx->cu_count &&
          jacobi_lds_bytes(dtype, l) + corr_lds_bytes(dtype, l) + 4096 <= ctx->lds_per_block;
 }
 
@@ -2484,7 +2509,7 @@ hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t
   if (nt > 64 * G) nt = 64 * G;
   const int g = jacobi_rows_padded((int)l, G, (int)dtype_size(dtype)) / G;          // rows per lane
   size_t lds = jacobi_lds_bytes(dtype, l);
-  const int corrections = lds_takes_corrections(ctx, dtype, l, batch) ? 1 : 0;
+  const bool corrections = lds_takes_corrections(ctx, dtype, l, batch);
   if (corrections) {
     lds += corr_lds_bytes(dtype, l);
     nt = 64 * kCorrWaves;
