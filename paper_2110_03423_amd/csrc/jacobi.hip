@@ -626,7 +626,7 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
 
   const int group = tid / G, lg = tid % G;       // G lanes per column pair
   const T tol = Eps<T>::value * sqrt((T)l);
-  int sweeps = 0;
+  int sweeps = 0, applied = 0;                   // (applied: corrections)
   bool converged = (l < 2);
   float rho_prev = -1.f;
   bool corrections = CORR;
@@ -674,7 +674,6 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
     __syncthreads();
     if constexpr (CORR) {
       if (!converged && corrections && ready) {
-        int applied = 0;
         converged = lds_corrections<T, RPL>(Mc, Jc, ldm, B0, B1, l, tol, floor2, corr_norms, corr_sums, applied);
         // Corrections that did not get there have met a cluster, whose angles stay large however small the inner products: the rest is left to
         // sweeps, about whose rate the ones before say nothing.
@@ -723,7 +722,7 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
     W[dst] = Jc[c * ldm + r] * unit[c];
   }
   if (tid == 0 && info != nullptr) {
-    atomicMax(&info->jacobi_sweeps, sweeps);
+    atomicMax(&info->jacobi_sweeps, sweeps + applied);
     if (!converged) atomicMax(&info->status, (int)RSVD_ERR_NO_CONVERGENCE);
   }
 }

@@ -48,6 +48,18 @@ def test_small_jacobi(dt, l, kind):
 
 
 @pytest.mark.parametrize("dt", ["f32", "f64"])
+@pytest.mark.parametrize("l", [16, 33, 48, 64, 80])
+def test_corrections_are_counted(dt, l):
+    """jacobi_sweeps has the corrections in it: a sweep that turned by 1e-3 over the gap leaves what its own rotations moved, which is far above
+    the threshold, and one sweep says nothing about a rate, so a second step of either kind follows."""
+    say("corrections counted", dt, l)
+    M = np.diag(np.linspace(2.0, 1.0, l)) + 1e-3 * workloads.gaussian_matrix(l, l, l)
+    sig, X, W, info = ctx().rsvd_stage_jacobi(to_dev(M.astype(NPDT[dt])))
+    say("  steps", info.jacobi_sweeps)
+    assert info.status == 0 and 2 <= info.jacobi_sweeps <= 8
+
+
+@pytest.mark.parametrize("dt", ["f32", "f64"])
 @pytest.mark.parametrize("l", [16, 48, 64])
 def test_special_matrices(dt, l):
     """Nothing to rotate, equal columns, zero, one nonzero column, values that are not finite (as they come out: no wait, no write elsewhere)."""
