@@ -78,6 +78,21 @@ template <int G, typename T> __device__ __forceinline__ T group_sum(T v) {
   return v;
 }
 
+template <int G> __device__ __forceinline__ float group_max(float v) {
+  v = fmaxf(v, dpp_mov<0xB1>(v));
+  v = fmaxf(v, dpp_mov<0x4E>(v));
+  if (G >= 8) v = fmaxf(v, dpp_mov<0x141>(v));
+  if (G == 16) v = fmaxf(v, dpp_mov<0x140>(v));
+  return v;
+}
+// Sum or maximum over the wavefront.
+template <bool MAX> __device__ __forceinline__ float all_lanes(float v) {
+  v = MAX ? group_max<16>(v) : group_sum<16>(v);
+#pragma unroll
+  for (int m = 16; m < 64; m <<= 1) v = MAX ? fmaxf(v, __shfl_xor(v, m, 64)) : v + __shfl_xor(v, m, 64);
+  return v;
+}
+
 // Reciprocal, square root and reciprocal square root from the hardware estimates
 // (1 ulp in fp32; refined by Newton steps in fp64).  The rotation parameters sit
 // on the serial path of every pair, so their instruction count matters.
@@ -228,13 +243,12 @@ __host__ __device__ inline int jacobi_ldm(int l, int G, int elem_size) {
 // What polish_kernel (further down, with the method) does with all CUs: once a sweep has left the columns close to orthogonal, all Jacobi
 // angles are taken from one Gram matrix in fp64 and applied together, M <- M exp(X), J <- J exp(X).  For M and J in LDS it is a handful of
 // l x l products of one CU where a sweep is l rounds that wait for each other (50 us at l = 80, a correction 15 to 25).  Last sweeps -> corrections, the whole
-// decomposition, us: factors behind a power iteration l = 80 fp32 240 -> 180, 61 fp32 159 -> 114, 48 fp64 (32 of them) 250 -> 168, 20 fp64 50 -> 38, 16 fp32
-// 43 -> 33; factors of Gaussian matrices l = 80 fp32 436 -> 374, 48 fp32 179 -> 139, 61 fp64 458 -> 369, 24 fp64 107 -> 93; values over six decades
-// on unordered columns, where sweeps converge slowly throughout, -9 to +13 %; half of the values within 1e-5 -14 to +18 %.  X and W end
+// decomposition, us: nearly diagonal factors l = 80 fp32 232 -> 147, 48 fp32 83 -> 62, 64 fp64 272 -> 159, 24 fp64 64 -> 49, 16 fp64 44 -> 32;
+// triangular factors of Gaussian matrices l = 80 fp32 367 -> 315, 48 fp32 150 -> 134, 64 fp64 414 -> 318, 24 fp64 103 -> 88.  X and W end
 // closer to orthogonal (|X^T X - I| / sqrt(l), fp32, l = 80: 18 -> 0.9 eps).
 // What bounds a product: 20 dependent matrix instructions a block at l = 80 and the barrier behind them; blocks of a whole matrix are read row by row
 // from LDS, those below the diagonal of symmetric ones are copies.  (As first written, 30 KB of code with registers kept in scratch memory in loops, a
-// correction took 55 us at l = 80.  fp32 has none there now, fp64 keeps 4 to 16 registers of a lane in it.)
+// correction took 55 us at l = 80.  fp32 has none there now, fp64 keeps 3 to 24 registers of a lane in it.)
 constexpr int kPolishSteps = 10;
 
 // Largest x for a series cut behind X^2 / 2 (1), X^3 (2), X^5 (3) and X^9 (4).  The 2-norm of X is x / 1.41 if all of it is one rotation and
@@ -252,10 +266,21 @@ __host__ __device__ constexpr float polish_start(int l) { return l < 160 ? 4.f :
 constexpr double kPolishFree = 0.01;        // angles up to this are taken whatever the inner product
 constexpr float kPolishRate = 0.75f;        // x of a correction in units of that before; above that they do not converge
 
-// Corrections are tried behind a sweep whose rotations came to kCorrTurned (Frobenius norm of the angles; one of 3 leaves 0.5, one of 5 leaves 1 to 2), and
-// go on if what is left is at most kCorrStart: from 3 they take as long as the sweep that would bring it to 0.1.
-constexpr float kCorrTurned = 5.f, kCorrStart = 2.f, kCorrTurnedScale = 65536.f;
-constexpr int kCorrWaves = 16;             // wavefronts that share the 16 x 16 blocks of a product
+// Corrections are looked at behind a sweep whose rotations came to corr_turned (Frobenius norm of the angles), and made if those that are left come to
+// kCorrStart at most and those that the correction would leave to kCorrNext.  Those are estimated from the first Gram matrix: a correction
+// leaves inner products of second order, about q = x |R| / l of the lengths (x: the norm of the angles, R: the relative inner products), hence angles
+// of atan(q / gap) / 2.  Where values lie in clusters the gaps are so small that these are as large as before, however small the inner
+// products, and corrections do not converge (norms estimated and found next at l = 48: noise 1.6 -> 0.3, half of the values within 1e-5
+// 17 -> 1).  A look costs 2 to 4 us; behind one that refused, the next is when half as much was turned.  Jacobi times in units
+// of those without corrections, 24 calls of each order (8 spectra, q = 0 to 2; low rank and noise to plateaus of equal values), geometric mean and
+// largest, with a norm of 5 turned and no estimate -> now: fp32 l = 16 1.04, 1.29 -> 1.03, 1.12; 24 1.00, 1.33 -> 1.01, 1.11; 32 0.91, 1.23 -> 0.97, 1.14; 48 0.89, 1.19 -> 0.90,
+// 1.04; 64 0.93, 1.26 -> 0.92, 1.11; 80 0.90, 1.18 -> 0.92, 1.07; fp64 16 1.01, 1.30 -> 0.87, 1.07; 32 0.81, 1.15 -> 0.82, 1.10; 48 0.81, 1.13 -> 0.80, 1.01;
+// 64 0.86, 1.22 -> 0.84, 1.06.  (Refusing by the largest angle left, or by the largest one turned, which ordinary factors have as well: 0.99 to 1.01 in fp32.)
+constexpr float kCorrStart = 2.f, kCorrNext = 2.f, kCorrTurnedScale = 65536.f;
+__host__ __device__ constexpr float corr_turned(int l) { return l / 14.f; }
+constexpr int kCorrWaves = 16;             // wavefronts that share the 16 x 16 blocks of a product, at most
+// Strips into which a row of blocks of a whole matrix is cut: one for each of nb * corr_strips(nb) wavefronts.
+__host__ __device__ constexpr int corr_strips(int nb) { return kCorrWaves / nb < nb ? kCorrWaves / nb : nb; }
 template <typename T, int RPL> struct CorrCfg {
   static constexpr bool kFits = sizeof(T) == 4 ? RPL <= 6 : RPL <= 4;      // (M, J and two more matrices in LDS)
   static constexpr int NB = RPL <= 4 ? 1 : 2;                              // blocks of a whole matrix that a wavefront has
@@ -314,7 +339,7 @@ __device__ __forceinline__ double corr_tan64(double dj, double di, double g) {
 // The Gram matrix, X and the parts of its exponential are symmetric or antisymmetric: of those a wavefront has one block on or above the
 // diagonal, whose elements stay in its registers from step to step; of whole matrices it has one or two neighbouring blocks of a row.
 template <typename T, int RPL>
-__device__ __forceinline__ bool lds_corrections(T *Mc, T *Jc, int ldm, T *B0, T *B1, int l, T tol, T floor2, double *nd, float (*red)[3],
+__device__ __forceinline__ bool lds_corrections(T *Mc, T *Jc, int ldm, T *B0, T *B1, int l, T tol, T floor2, double *nd, f32x4 *red,
                                                 int &applied) {
   typedef typename Mfma<T>::vec acc_t;
   constexpr int NB = CorrCfg<T, RPL>::NB, V = 8 / (int)sizeof(T);
@@ -330,7 +355,7 @@ __device__ __forceinline__ bool lds_corrections(T *Mc, T *Jc, int ldm, T *B0, T 
   int ui = 0, uj = has ? wave : 0;
   while (uj >= nb - ui) { uj -= nb - ui; ++ui; }
   uj += ui;
-  const int strips = kCorrWaves / nb < nb ? kCorrWaves / nb : nb, width = (nb + strips - 1) / strips;
+  const int strips = corr_strips(nb), width = (nb + strips - 1) / strips;
   const int fi = wave % nb;
   const bool full = wave / nb < strips;
   // (the last strip of a row may be narrower: it begins further left, and its neighbour's block is computed twice)
@@ -408,7 +433,7 @@ __device__ __forceinline__ bool lds_corrections(T *Mc, T *Jc, int ldm, T *B0, T 
       }
     }
     __syncthreads();
-    float rho = 0.f, x2 = 0.f, open = 0.f;
+    float rho = 0.f, x2 = 0.f, open = 0.f, rel2 = 0.f;
     if (has) {
       const int j = 16 * uj + r16;
       const double dj = j < l ? nd[j] : 0.0;
@@ -427,6 +452,7 @@ __device__ __forceinline__ bool lds_corrections(T *Mc, T *Jc, int ldm, T *B0, T 
           if (rel > (float)tol) {
             rho = fmaxf(rho, rel);
             open += a2;
+            rel2 += rel * rel;
           }
           x2 += a2;
         }
@@ -437,23 +463,44 @@ __device__ __forceinline__ bool lds_corrections(T *Mc, T *Jc, int ldm, T *B0, T 
         __builtin_amdgcn_sched_barrier(0);             // (one angle at a time: side by side they take more registers than there are)
       }
     }
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-      rho = fmaxf(rho, __shfl_xor(rho, m, 64));
-      x2 += __shfl_xor(x2, m, 64);
-      open += __shfl_xor(open, m, 64);
-    }
-    if (lane == 0) { red[wave][0] = rho; red[wave][1] = x2; red[wave][2] = open; }
+    rho = all_lanes<true>(rho);
+    x2 = all_lanes<false>(x2);
+    open = all_lanes<false>(open);
+    rel2 = all_lanes<false>(rel2);
+    if (lane == 0) red[wave] = f32x4{rho, x2, open, rel2};
     __syncthreads();
-    rho = x2 = open = 0.f;
-    for (int w = 0; w < kCorrWaves; ++w) {
-      rho = fmaxf(rho, red[w][0]);
-      x2 += red[w][1];
-      open += red[w][2];
-    }
+    const f32x4 sums = red[r16];
+    rho = group_max<16>(sums[0]);
+    x2 = group_sum<16>(sums[1]);
+    open = group_sum<16>(sums[2]);
+    rel2 = group_sum<16>(sums[3]);
     const float x_all = sqrtf(2.f * x2), x_now = sqrtf(2.f * open);
     if (rho <= (float)tol) return true;
     if (!(x_now <= kCorrStart) || !(x_now <= kPolishRate * x_before)) return false;
+    if (step == 0) {
+      // what a correction would leave, atan(y) / 2 as y / sqrt(4 + 1.62 y^2)
+      const double q2 = 4.0 * (double)open * (double)rel2 / ((double)l * l);
+      float next = 0.f;
+      if (has) {
+        const int j = 16 * uj + r16;
+        const double dj = j < l ? nd[j] : 0.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int i = 16 * ui + Mfma<double>::row(lane, v);
+          const double di = i < l ? nd[i] : 0.0;
+          if (i < j && di > (double)floor2 && dj > (double)floor2) {
+            const double t = q2 * di * dj;
+            next += (float)(t * __builtin_amdgcn_rcp((dj - di) * (dj - di) + 1.62 * t));
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      next = all_lanes<false>(next);
+      __syncthreads();
+      if (lane == 0) red[wave][0] = next;
+      __syncthreads();
+      if (!(2.f * group_sum<16>(red[r16][0]) <= kCorrNext * kCorrNext)) return false;
+    }
     x_before = x_now;
     const int order = x_all <= polish_limit<T>(1) ? 1 : x_all <= polish_limit<T>(2) ? 2 : x_all <= polish_limit<T>(3) ? 3 : 4;
     int doublings = 0;
@@ -558,7 +605,7 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
   __shared__ __attribute__((aligned(16))) JacLevel lev[kJacLevels][kJacGroups];
   static_assert(!CORR || (!JG && CorrCfg<T, RPL>::kFits), "no room for the matrices of the corrections");
   __shared__ double corr_norms[CORR ? 16 * RPL : 1];
-  __shared__ float corr_sums[CORR ? kCorrWaves : 1][3];
+  __shared__ f32x4 corr_sums[CORR ? kCorrWaves : 1];
 
   const int tid = threadIdx.x, nt = blockDim.x;
   // pair order: every column finds, level by level, the set it belongs to; the columns of
@@ -592,8 +639,10 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
       Jc[c * ldm + r] = (T)0;
     }
     // (what lies between the rows of the corrections' matrices is read as columns of J beyond the last one, against zeros: it has to be finite)
-    if (CORR)
+    if (CORR) {
       for (T *w = B0 + tid; w < nrm; w += nt) *w = (T)0;
+      if (tid < kCorrWaves) corr_sums[tid] = f32x4{0.f, 0.f, 0.f, 0.f};       // (as many are added up, with fewer wavefronts as well)
+    }
     for (int idx = tid; idx < l * l; idx += nt) {
       const int r = idx / l, c = idx - r * l;
       const T v = (T)M[idx];
@@ -630,6 +679,7 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
   bool converged = (l < 2);
   float rho_prev = -1.f;
   bool corrections = CORR;
+  float turned_limit = corr_turned(l);           // (of the angles' Frobenius norm in a sweep, for a look at corrections)
   constexpr int NV = RPL / (8 / (int)sizeof(T));
   while (!converged && sweeps < kJacobiMaxSweeps) {
     ++sweeps;
@@ -668,16 +718,17 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
     __syncthreads();
     converged = jacobi_done(__int_as_float(rotations), rho_prev, (float)tol);
     rho_prev = __int_as_float(rotations);
-    const bool ready = CORR && 2.f * (float)turned_sum <= kCorrTurned * kCorrTurned * kCorrTurnedScale;
+    const float turned_all = CORR ? sqrtf(2.f / kCorrTurnedScale * (float)turned_sum) : 0.f;
     __syncthreads();
     if (tid == 0) { rotations = 0; turned_sum = 0; }
     __syncthreads();
     if constexpr (CORR) {
-      if (!converged && corrections && ready) {
+      if (!converged && corrections && turned_all <= turned_limit) {
         converged = lds_corrections<T, RPL>(Mc, Jc, ldm, B0, B1, l, tol, floor2, corr_norms, corr_sums, applied);
         // Corrections that did not get there have met a cluster, whose angles stay large however small the inner products: the rest is left to
         // sweeps, about whose rate the ones before say nothing.
         if (applied > 0) { rho_prev = -1.f; corrections = false; }
+        else turned_limit = 0.5f * turned_all;
       }
     }
   }
@@ -2464,9 +2515,10 @@ hipError_t jacobi_init_device(rsvd_ctx *ctx) {
   return e;
 }
 
-// From 16 columns on (12: 44 -> 49 us), and where no CU has two problems of a batch: with 16 wavefronts, twice the registers and twice the LDS a problem
-// they no longer run side by side (fp32, q = 2, us without and with: 1500 x (l = 24) 89, 233; 600 x 48 223, 262; 300 x 72 369, 419; 300 x 80 450, 484;
-// 256 x 48 128, 99; fp64 600 x 40 369, 402; 300 x 64 550, 492; 256 x 64 377, 274).
+// From 16 columns on (12: 44 -> 49 us; in fp32 up to 31 it depends on the values whether the corrections bring more than a sweep of this kernel takes longer:
+// 300 x 200, l = 16, values that fall by e^-0.25 each 40 -> 36, low rank and noise 41 -> 43), and where no CU has two problems of a batch: with up to 16
+// wavefronts, twice the registers and twice the LDS a problem they no longer run side by side (fp32, q = 2, us without and with: 1500 x (l = 24)
+// 89, 233; 600 x 48 223, 262; 300 x 72 369, 419; 300 x 80 450, 484; 256 x 48 128, 99; fp64 600 x 40 369, 402; 300 x 64 550, 492; 256 x 64 377, 274).
 static bool lds_takes_corrections(const rsvd_ctx *ctx, rsvd_dtype dtype, int64_t l, int batch) {
   return l >= 16 && l <= corr_max_order(dtype == RSVD_F32) && batch <= ctx->cu_count &&
          jacobi_lds_bytes(dtype, l) + corr_lds_bytes(dtype, l) + 4096 <= ctx->lds_per_block;
@@ -2511,7 +2563,8 @@ hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t
   const bool corrections = lds_takes_corrections(ctx, dtype, l, batch);
   if (corrections) {
     lds += corr_lds_bytes(dtype, l);
-    nt = 64 * kCorrWaves;
+    const int nb = (int)ceil_div(l, 16), waves = nb * corr_strips(nb);
+    if (nt < 64 * waves) nt = 64 * waves;
   }
   ProfScope ps(ctx, s, PK_JACOBI);
   if (dtype == RSVD_F32) {

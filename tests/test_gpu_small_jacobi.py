@@ -14,7 +14,8 @@ NPDT = {"f32": np.float32, "f64": np.float64}
 def _matrix(l, kind, dt):
     i, rng = np.arange(l), np.random.default_rng(l)
     s = {"fast": np.exp(-3.0 * i / l), "slow": (1.0 + i) ** -0.1, "steep": 10.0 ** (-i / 8.0), "gauss": None, "tiny": 1e-15 / (1.0 + i),
-         "clusters": np.where(i < l // 2, 1.0, 0.5) * (1 + 1e-6 * rng.random(l)), "rank": np.where(i < l - 5, 1.0 / (1 + i), 0.0)}[kind]
+         "clusters": np.where(i < l // 2, 1.0, 0.5) * (1 + 1e-6 * rng.random(l)),
+         "half": np.where(i < l // 2, 1.0 + 1e-5 * rng.random(l), 0.9 ** (i - l // 2.0)), "rank": np.where(i < l - 5, 1.0 / (1 + i), 0.0)}[kind]
     if s is None:
         return np.linalg.qr(rng.standard_normal((l + 9, l)))[1].T.astype(NPDT[dt])
     near = np.linalg.qr(np.eye(l) + 0.05 * rng.standard_normal((l, l)))[0]      # nearly aligned, as a power iteration leaves them
@@ -57,6 +58,21 @@ def test_corrections_are_counted(dt, l):
     sig, X, W, info = ctx().rsvd_stage_jacobi(to_dev(M.astype(NPDT[dt])))
     say("  steps", info.jacobi_sweeps)
     assert info.status == 0 and 2 <= info.jacobi_sweeps <= 8
+
+
+# (order, sweeps that the kernel without corrections takes)
+CLUSTERED = [("f32", "half", {32: 5, 33: 5, 48: 5, 64: 5, 80: 4}), ("f32", "clusters", {32: 3, 33: 3, 48: 3, 64: 3, 80: 3}),
+             ("f64", "half", {16: 6, 17: 7, 33: 7, 48: 8, 64: 8}), ("f64", "clusters", {16: 6, 17: 5, 33: 7, 48: 8, 64: 8})]
+
+
+@pytest.mark.parametrize("dt,kind,l,sweeps", [(d, k, l, n) for d, k, c in CLUSTERED for l, n in c.items()])
+def test_clusters_are_left_to_sweeps(dt, kind, l, sweeps):
+    """Half of the values or more in clusters, where corrections of the whole matrix do not converge: they are not tried before they do, so there are
+    no more steps than sweeps alone and the first correction behind a sweep that had nearly finished."""
+    say("clusters", dt, kind, l)
+    sig, X, W, info = ctx().rsvd_stage_jacobi(to_dev(_matrix(l, kind, dt)))
+    say("  steps", info.jacobi_sweeps, "sweeps alone", sweeps)
+    assert info.status == 0 and info.jacobi_sweeps <= sweeps + 1
 
 
 @pytest.mark.parametrize("dt", ["f32", "f64"])
