@@ -10,6 +10,7 @@
 // orthonormal basis that contains range(Y).
 #include "common.hpp"
 #include "mfma.hpp"
+#include "pivot.hpp"
 #include "philox_dev.hpp"
 
 namespace rsvd {
@@ -179,7 +180,7 @@ __device__ __forceinline__ unsigned diag_factor(double *blk, f64x4 &dblk, f64x4 
     diag_eliminate<0, false>(s, 0.0, 0.0, thr, pos, lc, raise, cols, dmask, wmask);
     diagonal();                                  // (a pivot below zero leaves NaN)
     const unsigned need = cols < 16 ? (1u << cols) - 1u : 0xffffu;
-    done = ((unsigned)__ballot(r * r > thr) & pos & need) == need;
+    done = ((unsigned)__ballot(pivot_surely_above(r, thr)) & pos & need) == need;
   }
   if (!done) {
     load();
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(NB * 64) void chol_mfma_kernel(const double *__rest
   }
 
   // Too small pivots are expected where the call has met some (a panel that lacks directions lacks them in every round).  The
-  // counts may be those of another problem of a batch, or be changing: the result is the same with a look and without.
+  // counts may be those of another problem of a batch, or be changing: the result is the same with a look and without (pivot_surely_above).
   bool look = info != nullptr && (info->refilled | info->raised) != 0;
   // Wavefront 0: factor the block in Dg as diagonal block kb, publish R_kk, T = R_kk^-1 and the flags.
   auto factor_block = [&](int kb) {
