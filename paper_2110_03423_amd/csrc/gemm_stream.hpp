@@ -235,20 +235,24 @@ template <typename T> inline bool stream_takes(const GemmDesc &d) {
 // workgroup of the queue, and the partial sums with their launch.  Over 92 products with up to 24 choices each (l = 6 to 48, 10^6 to 10^9 entries) the one
 // taken is 0.5 % (fp32) and 1.5 % (fp64) slower than the best (geometric means; 8 % at most, 39 % at one of 19 us).  20 x 13 workgroups take 1.5 times as
 // long as 20 x 12 (25536 x 4928, l = 18: 151 us; 39 x 13 of two wavefronts a tile: 104).  The ranges are never more than gemm_kernel's, for which the
-// workspace has room, and no accumulator sums up more terms than there.
+// workspace has room, and no accumulator sums up more terms than there.  So wavefronts that take turns may have fewer ranges, in short products a single one, without
+// a launch for the sums: gemm_kernel or gemm_pipe_kernel, with the ranges of a single wavefront, now, us: fp64 304 x 6528, l = 24 11.8, 14.0, 11.1; 240 x 4784, l = 38
+// 11.9, 13.9, 10.9; 225 x 7308, l = 8 10.9, 13.7, 10.8; fp32 464 x 7280, l = 31 14.8, 13.8, 10.9.  (Beyond 12 tiles of k one range in fp64, whose matrix
+// instructions take twice as long, is too long a chain: 464 x 4192, l = 36 14.5 -> 15.8, 513 x 2712, l = 47 14.6 -> 17.2.)
 template <typename T>
 inline int stream_ranges(const rsvd_ctx *ctx, const GemmDesc &d, SplitChoice &c) {
   const int64_t cus = ctx->cu_count, ktiles = ceil_div(d.K, 32), most = c.splits;
   const double unit = 64.0 * sizeof(T) / 23000.0;               // us for one k of 64 rows of C
   const double each = sizeof(T) == 4 ? 1.0 : 6.0;
   static const double turns[5] = {0.0, 1.0, 1.03, 0.0, 1.08};
+  const bool short_k = sizeof(T) == 4 || ktiles <= 12;
   double best = -1.0;
   int best_kw = 1;
   int64_t best_s = most;
   for (int kw = 1; kw <= 4; kw *= 2) {
     const int64_t tiles = ceil_div(d.M, kStreamRows * (4 / kw)) * d.batch, least = ceil_div(most, kw);
-    for (int64_t q = 0; q <= 4; ++q) {                    // q > 0: as many ranges as make queues of q
-      int64_t s = q == 0 ? most : cus * q / tiles;
+    for (int64_t q = short_k ? -1 : 0; q <= 4; ++q) {     // q > 0: as many ranges as make queues of q; -1: as few as may be
+      int64_t s = q < 0 ? least : q == 0 ? most : cus * q / tiles;
       s = s < least ? least : s > most ? most : s;
       const int64_t per = ceil_div(ktiles, s), ranges = ceil_div(ktiles, per), queue = ceil_div(tiles * ranges, cus);
       const double sums = (double)ranges * (double)d.M * (double)d.N * d.batch * sizeof(T) * 1e-6;

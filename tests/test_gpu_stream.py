@@ -33,7 +33,7 @@ def _check(dt, got, A, Q):
 # of a CU with one, two and more workgroups; results with fewer rows than a lane reads
 SHAPES = [(262147, 4, 4), (200003, 5, 3), (110003, 65, 16), (16001, 66, 17), (17003, 67, 31), (4003, 257, 32), (30011, 191, 1),
           (1021, 1024, 16), (33, 40001, 32), (31, 33000, 18), (5001, 2003, 30), (2500, 5000, 15), (1200, 22000, 20), (9001, 4099, 9),
-          (3003, 1001, 33), (7001, 515, 47), (2002, 3001, 48), (61, 20483, 40), (40960, 256, 32), (25536, 1232, 18)]
+          (3003, 1001, 33), (7001, 515, 47), (2002, 3001, 48), (61, 20483, 40), (40960, 256, 32), (25536, 1232, 18), (304, 6528, 24), (241, 4783, 38)]
 
 
 @pytest.mark.parametrize("dt", ["f32", "f64"])
