@@ -28,6 +28,9 @@ constexpr int kStreamK = 4;                // k of a step
 // Steps whose loads are in flight: 8 KB and more of A for each of four to eight wavefronts on a CU.
 template <typename T> __host__ __device__ constexpr int stream_depth() { return sizeof(T) == 4 ? 8 : 4; }
 template <typename T> constexpr int stream_max_cols() { return sizeof(T) == 4 ? 32 : 48; }
+// Neighbouring columns of a lane: never more than there are.
+constexpr int stream_col_blocks(int64_t N) { return (int)((N + 15) / 16); }
+static_assert(stream_col_blocks(1) == 1 && stream_col_blocks(17) == 2 && stream_col_blocks(33) == 3, "N >= NB, which the kernel takes for granted");
 
 // A lane's NB neighbouring columns of B and C (three as a structure: a vector of three takes the place of four in memory).
 template <typename T, int NB> struct StreamVec { typedef T type __attribute__((ext_vector_type(NB), aligned(sizeof(T)))); };
@@ -225,7 +228,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void gemm_stream_kerne
 template <typename T> inline bool stream_takes(const GemmDesc &d) {
   constexpr int V = 16 / (int)sizeof(T);
   const double entries = (double)d.M * (double)d.K * (double)d.batch;
-  return d.trans_a != 0 && d.N <= stream_max_cols<T>() && d.N >= ceil_div(d.N, 16) && d.M >= V && entries >= 1e6 && d.alpha == 1.0 && d.beta == 0.0 &&
+  return d.trans_a != 0 && d.N >= 1 && d.N <= stream_max_cols<T>() && d.M >= V && entries >= 1e6 && d.alpha == 1.0 && d.beta == 0.0 &&
          !d.upper_only && !d.b_upper && !d.trans_c && d.dead == nullptr && d.a_shift == nullptr && d.lda < ((int64_t)1 << 22) &&
          d.ldb < ((int64_t)1 << 22) && d.batch >= 1 && d.batch <= 65535;
 }
@@ -293,9 +296,10 @@ inline hipError_t stream_launch(rsvd_ctx *ctx, hipStream_t s, const GemmDesc &d)
   hipError_t e;
   {
     ProfScope ps(ctx, s, d.prof_kind);
-    if (d.N <= 16) e = stream_by_waves<T, 1>(s, P, kw, d.batch);
-    else if (d.N <= 32) e = stream_by_waves<T, 2>(s, P, kw, d.batch);
-    else if constexpr (stream_max_cols<T>() > 32) e = stream_by_waves<T, 3>(s, P, kw, d.batch);
+    const int nb = stream_col_blocks(d.N);
+    if (nb == 1) e = stream_by_waves<T, 1>(s, P, kw, d.batch);
+    else if (nb == 2) e = stream_by_waves<T, 2>(s, P, kw, d.batch);
+    else if constexpr (stream_col_blocks(stream_max_cols<T>()) > 2) e = stream_by_waves<T, 3>(s, P, kw, d.batch);
     else e = hipErrorInvalidValue;
   }
   if (e != hipSuccess) return e;
