@@ -59,18 +59,13 @@ template <int CTRL> __device__ __forceinline__ double dpp_mov(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned int)lo);
 }
-// Sum over the 8 lanes of a half row: neighbours (quad_perm 1,0,3,2), pairs
-// (quad_perm 2,3,0,1), then the other quad (row_half_mirror).  Every lane adds
-// the same two partial sums at each step, so all 8 end with identical bits.
-template <typename T> __device__ __forceinline__ T half_row_sum(T v) {
-  v += dpp_mov<0xB1>(v);
-  v += dpp_mov<0x4E>(v);
-  v += dpp_mov<0x141>(v);
-  return v;
-}
-
-// Sum over the G = 4, 8 or 16 lanes that share a column pair (16, the one in use: a whole DPP row).
+// Sum over the G = 4, 8 or 16 lanes that share a column pair (16, the one in use: a whole DPP row): neighbours (quad_perm 1,0,3,2), pairs
+// (quad_perm 2,3,0,1), the other quad (row_half_mirror), the other half (row_mirror).  Every lane adds the same two partial sums at each step, so all end
+// with identical bits, which their rotation needs.  So the additions are kept from being fused with a product that a lane adds up (one
+// alone, in fp64 up to 16 rows): each lane would add its own product unrounded and its neighbour's rounded, and turn its rows by an angle of its
+// own (columns of lengths 1e-6 apart: the decomposition off by 1e-8, now by 1e-15).
 template <int G, typename T> __device__ __forceinline__ T group_sum(T v) {
+#pragma clang fp contract(off)
   v += dpp_mov<0xB1>(v);
   v += dpp_mov<0x4E>(v);
   if (G >= 8) v += dpp_mov<0x141>(v);
@@ -87,6 +82,7 @@ template <int G> __device__ __forceinline__ float group_max(float v) {
 }
 // Sum or maximum over the wavefront.
 template <bool MAX> __device__ __forceinline__ float all_lanes(float v) {
+#pragma clang fp contract(off)
   v = MAX ? group_max<16>(v) : group_sum<16>(v);
 #pragma unroll
   for (int m = 16; m < 64; m <<= 1) v = MAX ? fmaxf(v, __shfl_xor(v, m, 64)) : v + __shfl_xor(v, m, 64);
@@ -796,6 +792,7 @@ __global__ __launch_bounds__(64 * G) void jacobi_lds_kernel(const TIn *__restric
 // Sum over the 32 lanes of a pair group: the 16-lane row by DPP (neighbours, pairs,
 // half-row mirror, row mirror), then one exchange with the partner row.
 template <typename T> __device__ __forceinline__ T group32_sum(T v) {
+#pragma clang fp contract(off)
   v += dpp_mov<0xB1>(v);
   v += dpp_mov<0x4E>(v);
   v += dpp_mov<0x141>(v);

@@ -28,14 +28,13 @@ def _matrix(l, kind, dt):
 @pytest.mark.parametrize("kind", ["fast", "slow", "steep", "gauss", "tiny", "clusters", "rank"])
 def test_small_jacobi(dt, l, kind):
     say("small jacobi", dt, l, kind)
-    if kind == "clusters" and dt == "f64":
-        pytest.skip("the rule that ends the sweeps leaves values of a cluster off by up to 1e-11, without corrections as well")
     M = _matrix(l, kind, dt)
     sig, X, W, info = ctx().rsvd_stage_jacobi(to_dev(M))
     assert info.status == 0 and info.jacobi_sweeps <= 20
     sig, X, W = (to_np(t).astype(np.float64) for t in (sig, X, W))
     M64, eps, tol = M.astype(np.float64), np.finfo(NPDT[dt]).eps, parity.jacobi_tol(l, dt)
     want = np.linalg.svd(M64, compute_uv=False)
+    say("  values", np.abs(sig - want).max() / want[0] / eps, "residual", np.linalg.norm(X * sig @ W.T - M64) / want[0] / tol)
     assert (np.diff(sig) <= 0).all() and np.abs(sig - want).max() <= 20 * eps * np.sqrt(l) * want[0]
     assert np.linalg.norm(X * sig @ W.T - M64) <= tol * want[0]
     # each column of W goes through ~l rotations a sweep: a random walk of ~20 l roundings; its length is set to one at the end: l / 16 + 4
@@ -45,7 +44,10 @@ def test_small_jacobi(dt, l, kind):
     if dt == "f32" or l <= 64:                     # (65 and more in fp64: the block kernels)
         assert np.abs(length - 1).max() <= 2 * eps + (l / 16 + 4) / 2 * 2.0 ** -52
     nz = sig > 100 * l * eps * want[0]
-    assert np.linalg.norm((X.T @ X)[np.ix_(nz, nz)] - np.eye(nz.sum())) <= tol
+    # The rule that ends the sweeps takes the next one for granted where the last two converged by an order of 1.5: in an fp64 cluster of relative
+    # width 1e-6 that one would still have found inner products of 1e-13 to 1e-12, with corrections or without.
+    known = 1e-11 if kind == "clusters" and dt == "f64" else 0.0
+    assert np.linalg.norm((X.T @ X)[np.ix_(nz, nz)] - np.eye(nz.sum())) <= tol + known
 
 
 @pytest.mark.parametrize("dt", ["f32", "f64"])
