@@ -1,9 +1,13 @@
 """Small SVD in one workgroup: sweeps, and the corrections of the whole matrix that take the place of the last ones."""
+import ctypes as C
+
 import numpy as np
 import pytest
+import torch
 
 import parity
 import workloads
+from paper_2110_03423_amd import binding
 from gpu_util import ctx, say, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
@@ -80,7 +84,7 @@ def test_clusters_are_left_to_sweeps(dt, kind, l, sweeps):
 @pytest.mark.parametrize("dt", ["f32", "f64"])
 @pytest.mark.parametrize("l", [16, 48, 64])
 def test_special_matrices(dt, l):
-    """Nothing to rotate, equal columns, zero, one nonzero column, values that are not finite (as they come out: no wait, no write elsewhere)."""
+    """Nothing to rotate, equal columns, zero, values that are not finite (as they come out: no wait, no write elsewhere)."""
     c, T = ctx(), NPDT[dt]
     eps = np.finfo(T).eps
     d = np.linspace(2.0, 1.0, l).astype(T)
@@ -94,5 +98,14 @@ def test_special_matrices(dt, l):
     assert info.status == 0 and abs(sig[0] - l) <= 20 * eps * l and sig[1] <= 20 * eps * l
     assert np.linalg.norm(W.T @ W - np.eye(l)) <= parity.jacobi_tol(l, dt)
     one[0, 0] = np.nan
-    sig, X, W, info = c.rsvd_stage_jacobi(to_dev(one))
-    assert info.jacobi_sweeps <= 60
+    M, guard = to_dev(one), 512
+    out = [torch.full((n + 2 * guard,), 7.0, dtype=M.dtype, device=M.device) for n in (l, l * l, l * l)]
+    dtype, need, info = binding.F32 if dt == "f32" else binding.F64, C.c_size_t(), binding._Info()
+    c._check(c.lib.rsvd_stage_workspace_bytes(c.h, dtype, l, l, C.byref(need)))
+    ws = torch.full((need.value + 2 * 4096,), 7, dtype=torch.uint8, device=M.device)
+    at = [C.c_void_p(t.data_ptr() + guard * t.element_size()) for t in out]
+    c._check(c.lib.rsvd_stage_jacobi(c.h, c._stream(), dtype, l, C.c_void_p(M.data_ptr()), *at, C.c_void_p(ws.data_ptr() + 4096), need.value, C.byref(info)))
+    for t in out:
+        assert bool((t[:guard] == 7).all()) and bool((t[-guard:] == 7).all())
+    assert bool((ws[:4096] == 7).all()) and bool((ws[-4096:] == 7).all())
+    assert info.jacobi_sweeps <= 4                 # (the column with the NaN is left alone, the others are equal)
