@@ -22,11 +22,12 @@ def _randn(dt, shape, seed, pad=0):
 
 def _check(dt, got, A, Q):
     """Each of K additions rounds a partial sum s_k by at most eps / 2 of it: a random walk of errors eps / sqrt(12) |s_k|, and s_k is one of sqrt(k)
-    products, so that the standard deviation is 0.2 eps K products' root mean square.  Allowed is ten times that (in fp64, whose reference has as
-    much, twenty): no element of a million is off by it, but a single term of any is far above it."""
+    products, so that the standard deviation is 0.2 eps K products' root mean square.  Allowed is twenty times that (the
+    walk of a sum that is large throughout is five times the usual one, and an fp64 reference has as much): no element of a million is off by it,
+    but a single term is far above it."""
     A, Q = A.double().T.contiguous(), Q.double().contiguous()
     K, want = A.shape[1], A @ Q
-    bound = (2 if dt == "f32" else 4) * EPS[dt] * K ** 0.5 * ((A * A) @ (Q * Q)).sqrt()
+    bound = 4 * EPS[dt] * K ** 0.5 * ((A * A) @ (Q * Q)).sqrt()
     worst = float(((got.double() - want).abs() / bound).max())
     say("  worst", worst)
     assert worst <= 1
