@@ -8,7 +8,7 @@
 // sums of four times as many k ranges.  Calls of rsvd_stage_gemm_atn, gemm_kernel or gemm_pipe_kernel -> this, us (reductions included):
 //   fp32  9599 x 12017, l = 23  147 -> 93   78704 x 3920, l = 19  403 -> 270   8118 x 4499, l = 30  51 -> 34   14645 x 1013, l = 29  31 -> 21
 //   fp64  9599 x 12017, l = 31  294 -> 183  78704 x 3920, l = 25  661 -> 471   5923 x 1303, l = 20  31 -> 21   36637 x 411, l = 27   43 -> 29
-// 70 shapes of 2e5 to 5e8 entries each: 1.14 (fp32; 0.93 at 1360 x 18352, l = 12, 25 us) and 1.08 times as fast, below 20 us the same.  Of the
+// 70 shapes of 2e5 to 5e8 entries each: 1.14 (fp32; 0.95 at 1360 x 18352, l = 12, 23 us) and 1.08 times as fast, below 20 us the same.  Of the
 // batches 256 x (2000 x 500) fp32, l = 32, 281 -> 220 a product, 32 x (4000 x 1000) fp64, l = 48, 254 -> 221.  Whole calls: these batches 1511 -> 1394
 // and 2219 -> 2099, 65536 x 16384 fp32, l = 16, 3133 -> 3071.
 // Tried: twice the steps in flight (the batches 10 % slower, 32 columns of long products 10 % faster), the wavefronts of a workgroup on ranges of

@@ -10,7 +10,8 @@
 //
 // Stopping rule (the paper gives none): a sweep in which every pair satisfies
 // |a_p . a_q| <= tol * ||a_p|| * ||a_q||, tol = eps * sqrt(l); at most 60 sweeps (24 beyond the orders of the one-launch
-// block kernel, where every sweep is launched in advance).
+// block kernel, where every sweep is launched in advance).  Corrections of the whole matrix, which take the place of the last sweeps,
+// end by the same rule or where the one just made leaves about tol (the largest inner product before it times its angles).
 // The sweep that would only confirm this is saved when the rate of the last two sweeps says what it would find
 // (jacobi_done below): with rho the largest relative inner product a sweep rotated away, the next sweep meets about
 // rho^2 where the method converges quadratically (the paper: "3-4 iterations ... converges quadratically"; taken for
