@@ -270,13 +270,14 @@ constexpr float kPolishRate = 0.75f;        // x of a correction in units of tha
 // products, and corrections do not converge (norms estimated and found next at l = 48: noise 1.6 -> 0.3, half of the values within 1e-5
 // 17 -> 1).  A look costs 2 to 4 us; behind one that refused, the next is when half as much was turned.  Jacobi times in units
 // of those without corrections, 24 calls of each order (8 spectra, q = 0 to 2; low rank and noise to plateaus of equal values), geometric mean and
-// largest, with a norm of 5 turned and no estimate -> now: fp32 l = 16 1.04, 1.29 -> 1.03, 1.12; 24 1.00, 1.33 -> 1.01, 1.11; 32 0.91, 1.23 -> 0.97, 1.14; 48 0.89, 1.19 -> 0.90,
-// 1.04; 64 0.93, 1.26 -> 0.92, 1.11; 80 0.90, 1.18 -> 0.92, 1.07; fp64 16 1.01, 1.30 -> 0.87, 1.07; 32 0.81, 1.15 -> 0.82, 1.10; 48 0.81, 1.13 -> 0.80, 1.01;
-// 64 0.86, 1.22 -> 0.84, 1.06.  (Refusing by the largest angle left, or by the largest one turned, which ordinary factors have as well: 0.99 to 1.01 in fp32.)
+// largest, with a norm of 5 turned, 16 wavefronts and no estimate -> now: fp32 l = 16 1.05, 1.30 -> 1.03, 1.12; 24 1.00, 1.31 -> 0.99, 1.10; 32 0.91, 1.22 ->
+// 0.94, 1.11; 48 0.89, 1.20 -> 0.89, 1.03; 64 0.94, 1.26 -> 0.92, 1.11; 80 0.90, 1.19 -> 0.91, 1.07; fp64 16 1.01, 1.29 -> 0.85, 1.05; 24 0.92, 1.17 -> 0.87, 1.08;
+// 32 0.81, 1.13 -> 0.80, 1.00; 48 0.81, 1.12 -> 0.79, 1.02; 64 0.86, 1.22 -> 0.83, 1.07.  (Refusing by the largest angle left, or by the largest one turned, which
+// ordinary factors have as well: 0.99 to 1.01 in fp32.)
 constexpr float kCorrStart = 2.f, kCorrNext = 2.f, kCorrTurnedScale = 65536.f;
 __host__ __device__ constexpr float corr_turned(int l) { return l / 14.f; }
 constexpr int kCorrWaves = 16;             // wavefronts that share the 16 x 16 blocks of a product, at most
-// Strips into which a row of blocks of a whole matrix is cut: one for each of nb * corr_strips(nb) wavefronts.
+// Strips into which a row of blocks of a whole matrix is cut: one for each of nb * corr_strips(nb) wavefronts, 4 nb at most.
 __host__ __device__ constexpr int corr_strips(int nb) { return kCorrWaves / nb < nb ? kCorrWaves / nb : nb; }
 template <typename T, int RPL> struct CorrCfg {
   static constexpr bool kFits = sizeof(T) == 4 ? RPL <= 6 : RPL <= 4;      // (M, J and two more matrices in LDS)
@@ -2513,7 +2514,7 @@ hipError_t jacobi_init_device(rsvd_ctx *ctx) {
   return e;
 }
 
-// From 16 columns on (12: 44 -> 49 us; in fp32 up to 31 it depends on the values whether the corrections bring more than a sweep of this kernel takes longer:
+// From 16 columns on (12: 44 -> 49 us; in fp32 below 24 it depends on the values whether the corrections bring more than a sweep of this kernel takes longer:
 // 300 x 200, l = 16, values that fall by e^-0.25 each 40 -> 36, low rank and noise 41 -> 43), and where no CU has two problems of a batch: with up to 16
 // wavefronts, twice the registers and twice the LDS a problem they no longer run side by side (fp32, q = 2, us without and with: 1500 x (l = 24)
 // 89, 233; 600 x 48 223, 262; 300 x 72 369, 419; 300 x 80 450, 484; 256 x 48 128, 99; fp64 600 x 40 369, 402; 300 x 64 550, 492; 256 x 64 377, 274).
@@ -2561,8 +2562,10 @@ hipError_t jacobi_launch(rsvd_ctx *ctx, hipStream_t s, rsvd_dtype dtype, int64_t
   const bool corrections = lds_takes_corrections(ctx, dtype, l, batch);
   if (corrections) {
     lds += corr_lds_bytes(dtype, l);
-    const int nb = (int)ceil_div(l, 16), waves = nb * corr_strips(nb);
-    if (nt < 64 * waves) nt = 64 * waves;
+    // Four wavefronts for each 16 rows: the products have work for nb * corr_strips(nb) of them, loads and stores for more, and every one
+    // waits at the barriers of a sweep (fp32 l = 32, one sweep of equal values and all of a Gaussian factor, us: 4 wavefronts 18.6, 66.6; 8 17.2, 65.4; 16 17.7, 66.7).
+    const int waves = 4 * (int)ceil_div(l, 16);
+    nt = 64 * (waves < kCorrWaves ? waves : kCorrWaves);
   }
   ProfScope ps(ctx, s, PK_JACOBI);
   if (dtype == RSVD_F32) {
